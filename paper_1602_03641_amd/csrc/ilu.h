@@ -34,6 +34,16 @@ struct IluArgs {
     double *fval;           // factor values: L below the diagonal (unit diagonal implied), U from it
 };
 
+// LDS of the solve that stages a block's factor and schedules there: the same
+// layout for every block, sized for the largest counts of any block.
+struct IluLds {
+    int32_t rows = 0, ents = 0, levs = 0;  // rows, factor entries and levels (of either sweep) of a block
+    size_t slots_f() const { return 8 * (size_t)(2 * rows + ents); }  // after y, 1 / diag and the values
+    size_t bytes() const { return slots_f() + 16 * (size_t)rows + 2 * (2 * (size_t)(levs + 3) + ents); }
+    // entry and slot indices inside a block are 16-bit there
+    bool fits() const { return rows > 0 && ents <= 65535 && bytes() <= 160 * 1024; }
+};
+
 class Ilu {
 public:
     // Host symbolic phase from the device matrix's pattern (once per handle
@@ -54,6 +64,7 @@ private:
     int B_ = 0, nlev_ = 0;
     int64_t nent_ = 0;
     IluArgs a_{};
+    IluLds lds_;
     DBuf<int32_t> fptr_, fsrc_, fdiag_, rdev_, lvb_f_, lptr_f_, rows_f_, lvb_b_, lptr_b_, rows_b_;
     DBuf<int4> slot_f_, slot_b_;
     DBuf<uint16_t> fcol_;
