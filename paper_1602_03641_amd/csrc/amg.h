@@ -104,18 +104,25 @@ void cl_launch_interp_fill(hipStream_t s, Sell<double> A, const uint8_t *sf, con
 void cl_launch_transpose(hipStream_t s, Sell<double> A, int32_t nc, const int32_t *cfine, const int8_t *st,
                          const int32_t *pptr, const int32_t *pcol, const double *pval, int32_t *rlen,
                          const int32_t *rptr, int32_t *rcol, double *rval);
-void cl_launch_ap_cap(hipStream_t s, Sell<double> A, const int32_t *pptr, int32_t *cap);
+// rows of X Y (X: AX in sliced ELL, output in CSR; else X = xptr/xcol/xval in
+// CSR, output in sliced ELL): count into rowlen, marking in big[] (and
+// counting in *nbig) the rows that do not fit in LDS, or fill the others
+void cl_launch_product_rows(hipStream_t s, int32_t n, const Sell<double> *AX, const int32_t *xptr,
+                            const int32_t *xcol, const double *xval, const int32_t *yptr, const int32_t *ycol,
+                            const double *yval, int32_t *big, int *nbig, bool fill, int32_t *rowlen,
+                            const int64_t *optr, int32_t *ocol, double *oval);
+// the big rows: table sizes (0 for the other rows), their sums per chunk
+void cl_launch_ap_cap(hipStream_t s, Sell<double> A, const int32_t *pptr, const int32_t *big, int32_t *cap);
 void cl_launch_rap_cap(hipStream_t s, int32_t nc, const int32_t *rptr, const int32_t *rcol, const int32_t *apptr,
-                       int32_t *cap);
+                       const int32_t *big, int32_t *cap);
 void cl_launch_chunk_sums(hipStream_t s, int32_t n, const int32_t *cap, int64_t *sums);
-// rows [r0, r1) of X Y (X: AX in sliced ELL, or CSR xptr/xcol/xval); tables at
-// hoff[i - r0]; count (rowlen) or fill (CSR optr, or sliced ELL when sell_out)
+// big rows of [r0, r1) of X Y; tables at hoff[i - r0]; count (rowlen) or fill
+// (CSR optr, or sliced ELL when sell_out)
 void cl_launch_product(hipStream_t s, int32_t r0, int32_t r1, const Sell<double> *AX, const int32_t *xptr,
                        const int32_t *xcol, const double *xval, const int32_t *yptr, const int32_t *ycol,
                        const double *yval, const int32_t *cap, const int32_t *hoff, int32_t *hkey, double *hval,
-                       bool fill, int32_t *rowlen, const int64_t *optr, bool sell_out, int32_t *ocol, double *oval,
-                       int *overflow);
-void cl_launch_widen(hipStream_t s, int32_t n, const int32_t *in, int64_t *out);
+                       const int32_t *big, bool fill, int32_t *rowlen, const int64_t *optr, bool sell_out,
+                       int32_t *ocol, double *oval, int *overflow);
 template <class X>
 void cl_launch_restrict(hipStream_t s, int32_t nc, const int32_t *rptr, const int32_t *rcol, const double *rval,
                         const X *r, X *bc, const X *dinv_c, X *xc, const PcgState *st);
@@ -211,15 +218,26 @@ class Amg {
     DBuf<uint64_t> ckey_;
     DBuf<int8_t> cst_, cst2_;
     DBuf<int32_t> cplen_, cflag_, ccidx_, ccfine_, crlen_, ccap_, choff_, chkey_, captr_, capcol_;
-    DBuf<int64_t> captr64_, csums_;
+    DBuf<int64_t> captr64_, csums_, ctmp64_;
     void setup_classical(hipStream_t s, Tracker &tr, int64_t stored0);
     // vectors, K-cycle work and the coarsest inverse once level l is the coarsest
     void finish_setup(hipStream_t s, Tracker &tr, int l, int64_t stored_total, int64_t stored0);
-    // sparse product X Y in chunks (count: rowlen; fill: into optr/ocol/oval); false on table overflow
-    bool product(hipStream_t s, Tracker &tr, int32_t n, const Sell<double> *AX, const int32_t *xptr,
-                 const int32_t *xcol, const double *xval, const int32_t *yptr, const int32_t *ycol,
-                 const double *yval, bool fill, int32_t *rowlen, const int64_t *optr, bool sell_out, int32_t *ocol,
-                 double *oval);
+    // sparse product X Y: the row lengths of the rows that fit in LDS, and the
+    // number of the others into h_[8] (read back by the caller's next synchronisation)
+    struct Product {
+        const Sell<double> *AX;  // X in sliced ELL and the output in CSR, or null:
+        const int32_t *xptr, *xcol;  // X in CSR and the output in sliced ELL
+        const double *xval;
+        const int32_t *yptr, *ycol;
+        const double *yval;
+    };
+    void product_count(hipStream_t s, Tracker &tr, int32_t n, const Product &p, int32_t *rowlen);
+    // the other rows' lengths; false when one of them is too wide for a table
+    bool product_count_big(hipStream_t s, Tracker &tr, int32_t n, const Product &p, int32_t *rowlen);
+    void product_fill(hipStream_t s, int32_t n, const Product &p, bool big, const int64_t *optr, int32_t *ocol,
+                      double *oval);
+    void product_tables(hipStream_t s, int32_t n, const Product &p, bool fill, int32_t *rowlen, const int64_t *optr,
+                        int32_t *ocol, double *oval);
     template <class V, class X>
     void cycle(hipStream_t s, int l, const X *b, X *out, const PcgState *st, bool x_ready, double *rz);
     template <class V, class X>

@@ -135,32 +135,52 @@ void Amg::finish_setup(hipStream_t s, Tracker &tr, int l, int64_t stored_total, 
     }
 }
 
-bool Amg::product(hipStream_t s, Tracker &tr, int32_t n, const Sell<double> *AX, const int32_t *xptr,
-                  const int32_t *xcol, const double *xval, const int32_t *yptr, const int32_t *ycol,
-                  const double *yval, bool fill, int32_t *rowlen, const int64_t *optr, bool sell_out, int32_t *ocol,
-                  double *oval) {
+void Amg::product_count(hipStream_t s, Tracker &tr, int32_t n, const Product &p, int32_t *rowlen) {
+    ensure(big_, (size_t)n + 1, tr);
+    VAG_HIP(hipMemsetAsync(counters_.p + 61, 0, 2 * sizeof(int), s));
+    cl_launch_product_rows(s, n, p.AX, p.xptr, p.xcol, p.xval, p.yptr, p.ycol, p.yval, big_.p, counters_.p + 62, false,
+                           rowlen, nullptr, nullptr, nullptr);
+    VAG_HIP(hipMemcpyAsync(h_ + 8, counters_.p + 62, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+}
+
+bool Amg::product_count_big(hipStream_t s, Tracker &tr, int32_t n, const Product &p, int32_t *rowlen) {
     // table sizes are in ccap_; each chunk of rows gets its tables side by side
     const int32_t nch = (n + kClChunk - 1) / kClChunk;
-    if (nch == 0) return true;
+    ensure(ccap_, (size_t)n + 1, tr);
+    if (p.AX)
+        cl_launch_ap_cap(s, *p.AX, p.yptr, big_.p, ccap_.p);
+    else
+        cl_launch_rap_cap(s, n, p.xptr, p.xcol, p.yptr, big_.p, ccap_.p);
     ensure(csums_, (size_t)nch, tr);
     cl_launch_chunk_sums(s, n, ccap_.p, csums_.p);
     std::vector<int64_t> sums((size_t)nch);
     VAG_HIP(hipMemcpyAsync(sums.data(), csums_.p, (size_t)nch * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    VAG_HIP(hipMemsetAsync(counters_.p + 61, 0, sizeof(int), s));
     VAG_HIP(hipStreamSynchronize(s));
     const int64_t mx = *std::max_element(sums.begin(), sums.end());
     ensure(chkey_, (size_t)mx, tr);
     ensure(chval_, (size_t)mx, tr);
     ensure(choff_, (size_t)kClChunk + 1, tr);
-    for (int32_t q = 0; q < nch; ++q) {
-        const int32_t r0 = q * kClChunk, r1 = std::min(n, r0 + kClChunk);
-        amg_launch_scan(s, r1 - r0, ccap_.p + r0, choff_.p, stmp_.p);
-        cl_launch_product(s, r0, r1, AX, xptr, xcol, xval, yptr, ycol, yval, ccap_.p, choff_.p, chkey_.p, chval_.p,
-                          fill, rowlen, optr, sell_out, ocol, oval, counters_.p + 61);
-    }
-    VAG_HIP(hipMemcpyAsync(h_ + 8, counters_.p + 61, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    product_tables(s, n, p, false, rowlen, nullptr, nullptr, nullptr);
+    VAG_HIP(hipMemcpyAsync(h_ + 9, counters_.p + 61, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     VAG_HIP(hipStreamSynchronize(s));
-    return h_[8] == 0;
+    return h_[9] == 0;
+}
+
+void Amg::product_tables(hipStream_t s, int32_t n, const Product &p, bool fill, int32_t *rowlen, const int64_t *optr,
+                         int32_t *ocol, double *oval) {
+    for (int32_t r0 = 0; r0 < n; r0 += kClChunk) {
+        const int32_t r1 = std::min(n, r0 + kClChunk);
+        amg_launch_scan(s, r1 - r0, ccap_.p + r0, choff_.p, stmp_.p);
+        cl_launch_product(s, r0, r1, p.AX, p.xptr, p.xcol, p.xval, p.yptr, p.ycol, p.yval, ccap_.p, choff_.p,
+                          chkey_.p, chval_.p, big_.p, fill, rowlen, optr, !p.AX, ocol, oval, counters_.p + 61);
+    }
+}
+
+void Amg::product_fill(hipStream_t s, int32_t n, const Product &p, bool big, const int64_t *optr, int32_t *ocol,
+                       double *oval) {
+    cl_launch_product_rows(s, n, p.AX, p.xptr, p.xcol, p.xval, p.yptr, p.ycol, p.yval, big_.p, counters_.p + 62, true,
+                           nullptr, optr, ocol, oval);
+    if (big) product_tables(s, n, p, true, nullptr, optr, ocol, oval);
 }
 
 // Classical hierarchy: strength, PMIS splitting, direct interpolation, R = P^T
@@ -234,50 +254,52 @@ void Amg::setup_classical(hipStream_t s, Tracker &tr, int64_t stored0) {
         cl_launch_transpose(s, lv.A, nc, ccfine_.p, cst_.p, lv.pptr.p, lv.pcol.p, lv.pval.p, nullptr, lv.rptr.p,
                             lv.rcol.p, lv.rval.p);
         // A P (CSR)
-        ensure(ccap_, (size_t)std::max(n, nc) + 1, tr);
-        cl_launch_ap_cap(s, lv.A, lv.pptr.p, ccap_.p);
-        if (!product(s, tr, n, &lv.A, nullptr, nullptr, nullptr, lv.pptr.p, lv.pcol.p, lv.pval.p, false, cplen_.p,
-                     nullptr, false, nullptr, nullptr))
-            break;  // a row of A P is too wide for its table: stop coarsening here
-        cl_launch_chunk_sums(s, n, cplen_.p, csums_.p);
-        {
-            const int32_t nch = (n + kClChunk - 1) / kClChunk;
-            std::vector<int64_t> sums((size_t)nch);
-            VAG_HIP(hipMemcpyAsync(sums.data(), csums_.p, (size_t)nch * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            VAG_HIP(hipStreamSynchronize(s));
-            int64_t tot = 0;
-            for (auto v : sums) tot += v;
-            if (tot >= INT32_MAX) break;  // A P would need 64-bit row pointers: stop coarsening here
-        }
+        const Product ap{&lv.A, nullptr, nullptr, nullptr, lv.pptr.p, lv.pcol.p, lv.pval.p};
         ensure(captr_, (size_t)n + 1, tr);
         ensure(captr64_, (size_t)n + 1, tr);
-        amg_launch_scan(s, n, cplen_.p, captr_.p, stmp_.p);
-        read32(captr_.p + n, 0);
-        VAG_HIP(hipStreamSynchronize(s));
-        const int32_t apnnz = h_[0];
-        cl_launch_widen(s, n, captr_.p, captr64_.p);
-        ensure(capcol_, (size_t)std::max(apnnz, 1), tr);
-        ensure(capval_, (size_t)std::max(apnnz, 1), tr);
-        product(s, tr, n, &lv.A, nullptr, nullptr, nullptr, lv.pptr.p, lv.pcol.p, lv.pval.p, true, nullptr,
-                captr64_.p, false, capcol_.p, capval_.p);
+        ensure(ctmp64_, (size_t)n / 1024 + 4, tr);
+        int64_t apnnz = 0;
+        auto ap_offsets = [&] {
+            launch_scan64(s, n, cplen_.p, captr64_.p, ctmp64_.p);
+            amg_launch_scan(s, n, cplen_.p, captr_.p, stmp_.p);
+            VAG_HIP(hipMemcpyAsync(&apnnz, captr64_.p + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+            VAG_HIP(hipStreamSynchronize(s));
+        };
+        product_count(s, tr, n, ap, cplen_.p);
+        ap_offsets();
+        const bool ap_big = h_[8] != 0;
+        if (ap_big) {
+            if (!product_count_big(s, tr, n, ap, cplen_.p))
+                break;  // a row of A P is too wide for its table: stop coarsening here
+            ap_offsets();
+        }
+        if (apnnz >= INT32_MAX) break;  // A P would need 64-bit row pointers: stop coarsening here
+        ensure(capcol_, (size_t)std::max<int64_t>(apnnz, 1), tr);
+        ensure(capval_, (size_t)std::max<int64_t>(apnnz, 1), tr);
+        product_fill(s, n, ap, ap_big, captr64_.p, capcol_.p, capval_.p);
         // R (A P): the coarse level in sliced ELL
         if ((int)L.size() <= l + 1) L.emplace_back(new AmgLevel());
         AmgLevel &cv = *L[l + 1];
+        const Product rap{nullptr, lv.rptr.p, lv.rcol.p, lv.rval.p, captr_.p, capcol_.p, capval_.p};
         const int32_t ns = (nc + 63) / 64;
         ensure(cv.ptr, (size_t)ns + 1, tr);
-        cl_launch_rap_cap(s, nc, lv.rptr.p, lv.rcol.p, captr_.p, ccap_.p);
-        if (!product(s, tr, nc, nullptr, lv.rptr.p, lv.rcol.p, lv.rval.p, captr_.p, capcol_.p, capval_.p, false,
-                     crlen_.p, nullptr, true, nullptr, nullptr))
-            break;
-        amg_launch_slices(s, nc, crlen_.p, width_.p, scnt_.p, cv.ptr.p, level_nnz.p + l + 1);
         int64_t stored = 0;
-        VAG_HIP(hipMemcpyAsync(&stored, cv.ptr.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        VAG_HIP(hipStreamSynchronize(s));
+        auto slices = [&] {
+            amg_launch_slices(s, nc, crlen_.p, width_.p, scnt_.p, cv.ptr.p, level_nnz.p + l + 1);
+            VAG_HIP(hipMemcpyAsync(&stored, cv.ptr.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+            VAG_HIP(hipStreamSynchronize(s));
+        };
+        product_count(s, tr, nc, rap, crlen_.p);
+        slices();
+        const bool rap_big = h_[8] != 0;
+        if (rap_big) {
+            if (!product_count_big(s, tr, nc, rap, crlen_.p)) break;
+            slices();
+        }
         if (stored >= INT32_MAX) break;
         ensure(cv.col, (size_t)stored, tr);
         ensure(cv.val, (size_t)stored, tr);
-        product(s, tr, nc, nullptr, lv.rptr.p, lv.rcol.p, lv.rval.p, captr_.p, capcol_.p, capval_.p, true, nullptr,
-                cv.ptr.p, true, cv.col.p, cv.val.p);
+        product_fill(s, nc, rap, rap_big, cv.ptr.p, cv.col.p, cv.val.p);
         amg_launch_slice_tail(s, nc, cv.ptr.p, cv.col.p, cv.val.p);
         cv.n = nc;
         cv.stored = stored;

@@ -35,3 +35,50 @@ def test_ilu_substitutions(dims, B):
     z, zr = h.apply_preconditioner(r), ilu.bj_ilu0_apply(rows, r)
     assert np.abs(z - zr).max() <= 1e-11 * np.abs(zr).max()
     h.close()
+
+
+def _fan(sectors, layers):
+    """Wedges around an axis: its nodes couple to every node of three layers."""
+    k, i = np.meshgrid(np.arange(layers), np.arange(sectors), indexing="ij")
+    k, i = k.ravel(), i.ravel()
+    at = lambda k, i: k * (sectors + 1) + 1 + i % sectors  # noqa: E731
+    axis = k * (sectors + 1)
+    up = sectors + 1
+    cells = np.stack([axis, at(k, i), at(k, i + 1), axis + up, at(k, i) + up, at(k, i + 1) + up], 1)
+    a = 2 * np.pi * np.arange(sectors) / sectors
+    ring = np.concatenate([[[0.0, 0.0]], np.stack([np.cos(a), np.sin(a)], 1)])
+    xyz = np.concatenate([np.c_[ring, np.full(sectors + 1, 0.3 * z)] for z in range(layers + 1)])
+    cfp, cf, fnp, fn, _ = synth.faces_of_cells(cells)
+    z = np.repeat(np.arange(layers + 1), sectors + 1)
+    nc = len(cells)
+    perm = np.zeros((nc, 6))
+    perm[:, :3] = np.random.default_rng(3).uniform(0.5, 2.0, (nc, 1))
+    return synth.GeneralProblem(
+        name="fan", xyz=xyz, cells=cells, cell_face_ptr=cfp, cell_faces=cf, face_node_ptr=fnp, face_nodes=fn,
+        frac_face_ids=np.zeros(0, np.int32), frac_width=np.zeros(0), frac_perm=np.zeros(0), frac_poro=np.zeros(0),
+        perm=perm, poro=np.ones(nc), mu=1.0, dirichlet=((z == 0) | (z == layers)).astype(np.uint8),
+        p_bar=1.0 - z / layers, c_bar=(z == 0).astype(float))
+
+
+@pytest.mark.parametrize("mesh,coarse", [((5, 4, 4), 8), ((14, 12, 11), 6), ((26, 24, 22), 12), ("fan", 12)])
+def test_classical_products(mesh, coarse):
+    """Classical hierarchies coarsened far down; on the fan, rows of A P and
+    R A P with more columns than a wavefront holds in LDS: every coarse operator
+    is P^T A P of the level above.  An entry sums at most ~10^4 products, each
+    rounded relative to max |A|: 1e-12 max |A|."""
+    from paper_1602_03641_amd import vag
+    import scipy.sparse as sp
+    p = _fan(120, 14) if mesh == "fan" else synth.random_problem(mesh, 23, n_patches=5, n_steps=0, ratios=(1e2, 1e4))
+    h, info = _handle(p, rtol=1e-8, precond=vag.VAG_PC_AMG, amg_kind=1, amg_coarse_size=coarse)
+    mats = []
+    for d in (h.amg_level(l) for l in range(info["amg_levels"])):
+        n = len(d["A"][0]) - 1
+        A = sp.csr_matrix((d["A"][2], d["A"][1], d["A"][0]), shape=(n, n))
+        P = sp.csr_matrix((d["P"][2], d["P"][1], d["P"][0]), shape=(n, d["n_coarse"])) if d["P"] is not None else None
+        mats.append((A, P))
+    wide = []
+    for (A, P), (Ac, _) in zip(mats, mats[1:]):
+        assert abs(P.T @ A @ P - Ac).max() <= 1e-12 * abs(A).max()
+        wide.append((int((abs(A).sign() @ P.getnnz(axis=1)).max()), int(Ac.getnnz(axis=1).max())))
+    print("most contributions to a row of A P, most columns of R A P, per level:", wide)
+    h.close()
