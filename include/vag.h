@@ -306,9 +306,11 @@ vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const d
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * transport of vag_transport (time step dt = cfl * CFL bound, then n_steps
- * explicit upwind steps, or t_final as there) without the upwind operator that
- * vag_transport builds in memory it allocates.  Each step gathers the upwind
- * fluxes of every control volume from the handle's resident Darcy fluxes.
+ * explicit upwind steps, or t_final as there) without memory of its own.  A
+ * call of a few steps gathers the upwind fluxes of every control volume from
+ * the handle's resident Darcy fluxes in each step; a longer one first builds
+ * the upwind operator of vag_transport in the handle's array of local matrices
+ * (which the next solve computes again).
  * The call allocates nothing: the CFL reduction's partial minima and the time
  * step live in a static device array of the library (3 * 512 + 8 doubles,
  * about 12 KB, one copy per device, held until the process ends), the

@@ -667,8 +667,8 @@ __global__ __launch_bounds__(64) void xcd_split_kernel(int32_t nslice, int32_t s
     xlo[t] = x == 8 ? b1 : lo;
 }
 
-// One explicit step without the upwind operator (the entry point for callers
-// that cannot allocate): every control volume gathers the upwind fluxes
+// One explicit step without the upwind operator (calls of a few steps through
+// the entry point for callers that cannot allocate): every control volume gathers the upwind fluxes
 // H = c_up F of eq darcyfluxH from the resident Darcy fluxes, one thread per
 // control volume.  Cells read their 8 node fluxes and fracture faces; a
 // fracture face its 4 node fluxes, its (at most 2) cells and its well; a node

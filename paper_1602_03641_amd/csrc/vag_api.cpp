@@ -1610,6 +1610,60 @@ vag_status vag_serving_transport_end(vag_handle *h, vag_transport_info *info) {
     });
 }
 
+namespace {
+// The upwind operator of vag_transport_noalloc, laid out in the handle's array
+// of local matrices: the next solve (or vag_set_fluxes) computes those again,
+// and nothing reads them in between.  Every flux pair gives one entry and a
+// well's injection one more, so the bounds of the sizes need no device read.
+// Building the operator pays from this many steps on.  Measured with wells,
+// gather / operator, whole call: 64^3 134 / 215 us for 1 step, 304 / 238 for 4,
+// 3158 / 742 for 64; 160^3 3162 / 2116 for 4; below 2^18 control volumes a
+// step is a launch either way (7 / 4 us): 16^3 130 / 148 us for 4 steps,
+// 209 / 191 for 16.
+int64_t noalloc_op_steps(int64_t nrow) { return nrow >= (1 << 18) ? 4 : 12; }
+struct NoallocOp {
+    int32_t *width, *nnz, *col, *base;
+    int64_t *ptr, *scan;
+    uint16_t *meta, *col16;
+    double *val, *diag;
+    UpwindOp T;
+    int32_t nslice;
+    bool fits;
+};
+NoallocOp noalloc_operator(vag_handle *h) {
+    const Symbolic &S = h->S;
+    const int64_t nrow = (int64_t)S.nc + S.nf + S.nn, nent = 8 * (int64_t)S.nc + 6 * (int64_t)S.nf + h->nw;
+    NoallocOp o{};
+    o.nslice = (int32_t)((nrow + kSliceRows - 1) / kSliceRows);
+    char *p = reinterpret_cast<char *>(h->aK.p);
+    size_t used = 0;
+    auto take = [&](auto *&q, int64_t n) {
+        q = reinterpret_cast<std::remove_reference_t<decltype(q)>>(p + used);
+        used += ((size_t)n * sizeof(*q) + 255) / 256 * 256;
+    };
+    take(o.val, nent);
+    take(o.diag, nrow);
+    take(o.ptr, o.nslice + 1);
+    take(o.scan, o.nslice / 1024 + 4);
+    take(o.col, nent);
+    take(o.width, o.nslice);
+    take(o.nnz, o.nslice);
+    take(o.base, o.nslice);
+    take(o.col16, nent);
+    take(o.meta, (int64_t)o.nslice * kSliceRows);
+    o.fits = used <= h->aK.n * sizeof(double);
+    o.T = UpwindOp{(int32_t)nrow, o.ptr, o.meta, o.col, o.col16, o.base, o.val, o.diag, {}, {}};
+    // equal runs of slices per XCD: the cost split of vag_transport is read
+    // back from the device, and hexahedra's rows are alike (4 entries on
+    // average in cells and nodes)
+    for (int x = 0; x < 9; ++x) {
+        o.T.xlo[x] = (int32_t)((int64_t)o.nslice * x / 8);
+        o.T.ylo[x] = o.nslice;
+    }
+    return o;
+}
+}  // namespace
+
 vag_status vag_transport_noalloc(vag_handle *h, int64_t n_steps, double t_final, const double *c0_cell,
                                  const double *c0_frac, const double *c0_node, double *c_cell, double *c_frac,
                                  double *c_node, vag_transport_info *info) {
@@ -1669,14 +1723,33 @@ vag_status vag_transport_noalloc(vag_handle *h, int64_t n_steps, double t_final,
             last_dt = t_final - (double)(N - 1) * dt;
             theta_last = last_dt / dt;
         }
+        const NoallocOp o = noalloc_operator(h);
+        const bool op = o.fits && N >= noalloc_op_steps(nrow);
+        if (op) {
+            launch_upwind_count(s, S.nc, S.nf, S.nn, h->fmask.p, h->cell_frac.p, h->frac_cell.p, h->dirichlet.p,
+                                h->node_cell_ptr.p, h->node_cell.p, h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p,
+                                h->F_cell_frac.p, h->F_frac.p, h->well_src(), o.width, o.meta, o.nnz);
+            launch_scan64(s, o.nslice, o.nnz, o.ptr, o.scan);
+            launch_upwind_fill(s, S.nc, S.nf, S.nn, h->hex8.p, h->fmask.p, h->cell_frac.p, h->frac_cell.p,
+                               h->frac_nodes.p, h->dirichlet.p, h->node_cell_ptr.p, h->node_cell.p,
+                               h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p, h->F_cell_frac.p, h->F_frac.p,
+                               h->well_src(), h->well_out(), h->phi_cell.p, h->phi_frac.p, h->phi_node.p, dt4, o.ptr,
+                               o.meta, o.col, o.val, o.diag);
+            launch_upwind_pack(s, o.T, o.col16, o.base);
+            launch_fill(s, 1, 1.0, h->cbuf0.p + nrow);  // the constant control volume of well injection
+            launch_fill(s, 1, 1.0, h->cbuf1.p + nrow);
+        }
         VAG_HIP(hipEventRecord(h->ev[6], s));
         for (int64_t k = 0; k < N; ++k) {
             const double th = (k == N - 1) ? theta_last : 1.0;
-            launch_transport_gather(s, S.nc, S.nf, S.nn, h->hex8.p, h->fmask.p, h->cell_frac.p, h->frac_cell.p,
-                                    h->frac_nodes.p, h->dirichlet.p, h->node_cell_ptr.p, h->node_cell.p,
-                                    h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p, h->F_cell_frac.p, h->F_frac.p,
-                                    h->well_src(), h->well_out(), h->phi_cell.p, h->phi_frac.p, h->phi_node.p, dt4,
-                                    th, h->c_cur(), h->c_next());
+            if (op)
+                launch_transport_step(s, o.T, h->c_cur(), h->c_next(), th, (k & 1) != 0);
+            else
+                launch_transport_gather(s, S.nc, S.nf, S.nn, h->hex8.p, h->fmask.p, h->cell_frac.p, h->frac_cell.p,
+                                        h->frac_nodes.p, h->dirichlet.p, h->node_cell_ptr.p, h->node_cell.p,
+                                        h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p, h->F_cell_frac.p,
+                                        h->F_frac.p, h->well_src(), h->well_out(), h->phi_cell.p, h->phi_frac.p,
+                                        h->phi_node.p, dt4, th, h->c_cur(), h->c_next());
             h->cur ^= 1;
         }
         const double *c = h->c_cur();

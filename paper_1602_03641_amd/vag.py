@@ -335,8 +335,8 @@ class Handle:
         return d
 
     def transport_noalloc(self, n_steps=0, t_final=0.0, c0=None, info=True):
-        """vag_transport_noalloc: the steps gathered from the fluxes, with the
-        library's static scratch; returns (concentrations as device tensors,
+        """vag_transport_noalloc: the steps with the library's static scratch and
+        the handle's own arrays; returns (concentrations as device tensors,
         info dict or None)."""
         args = (None, None, None)
         if c0 is not None:

@@ -82,3 +82,28 @@ def test_classical_products(mesh, coarse):
         wide.append((int((abs(A).sign() @ P.getnnz(axis=1)).max()), int(Ac.getnnz(axis=1).max())))
     print("most contributions to a row of A P, most columns of R A P, per level:", wide)
     h.close()
+
+
+@pytest.mark.parametrize("dims", [(6, 5, 4), (17, 16, 15), (66, 50, 48)])
+def test_noalloc_step_counts(dims):
+    """Step counts on both sides of where vag_transport_noalloc builds the
+    operator, wells included, on meshes below and above 2^18 control volumes:
+    the state of vag_transport within the 1e-12 of the order of additions."""
+    p = synth.random_problem(dims, 25, n_patches=5, n_steps=0, ratios=(1e2, 1e4))
+    synth.add_wells(p, 4, n_inj=1, n_prod=1)
+    h, _ = _handle(p, rtol=1e-8, precond=1)
+    rng = np.random.default_rng(26)
+    c0 = {k: rng.uniform(0, 1, n) for k, n in (("c_cell", p.n_cells), ("c_frac", p.n_frac), ("c_node", p.n_nodes))}
+    from paper_1602_03641_amd import vag
+    for n in (0, 1, 3, 4, 11, 12, 13):
+        h.transport(n_steps=n, c0=c0)
+        ref = vag.to_numpy(h.concentration())
+        got = vag.to_numpy(h.transport_noalloc(n_steps=n, c0=c0)[0])
+        for k in ref:
+            assert np.abs(got[k] - ref[k]).max(initial=0.0) <= 1e-12, (n, k)
+        # the operator lives in the local matrices: the next solve is unharmed
+    u = vag.to_numpy(h.pressure())
+    h.solve_pressure()
+    for k, v in vag.to_numpy(h.pressure()).items():
+        assert np.array_equal(v, u[k]), k
+    h.close()
