@@ -10,7 +10,7 @@ namespace vag {
 
 // levels of at most this many rows run their V-cycle kernels with several
 // lanes per row
-constexpr int32_t kSmallRows = 131072;
+constexpr int32_t kSmallRows = (int32_t)kSplitMaxRows;
 
 // kernel launchers (amg.hip)
 void amg_launch_diag(hipStream_t s, Sell<double> A, double *diag, double *dinv);
@@ -55,19 +55,34 @@ template <class V, class X>
 void amg_launch_post(hipStream_t s, Sell<V> A, const X *dinv, const X *b, const X *x, const int32_t *agg,
                      const X *e, X *y, X *out, double *rz, const PcgState *st, double *zq = nullptr,
                      const X *qv = nullptr);
-// K-cycle kernels (see amg.hip); parts: 5 * kc_grid(n) doubles
+// K-cycle kernels (see amg.hip); parts: 5 * kc_grid(n) doubles for a level of n rows
 int kc_grid(int32_t n);
 template <class V, class X>
 void amg_launch_kc_av(hipStream_t s, Sell<V> A, const X *c, const X *b, X *v, double *parts, const PcgState *st);
 template <class X>
-void amg_launch_kc_rt(hipStream_t s, int32_t n, const X *b, const X *v, const X *dinv, const double *parts, X *rt,
-                      X *xa, const PcgState *st);
+void amg_launch_kc_rt(hipStream_t s, int32_t n, const X *b, const X *v, const X *dinv, double *parts, X *rt, X *xa,
+                      const PcgState *st);
+// kc_rt and the next V-cycle's residual r = rt - A D^-1 rt in one launch (xa not written)
 template <class V, class X>
-void amg_launch_kc_aw(hipStream_t s, Sell<V> A, const X *d, const X *v, const X *rt, X *w, double *parts,
+void amg_launch_kc_rt_resid(hipStream_t s, Sell<V> A, const X *b, const X *v, const X *dinv, double *parts, X *rt,
+                            X *r, const PcgState *st);
+template <class V, class X>
+void amg_launch_kc_aw(hipStream_t s, Sell<V> A, const X *d, const X *v, const X *rt, double *parts,
                       const PcgState *st);
 template <class X>
-void amg_launch_kc_combine(hipStream_t s, int32_t n, const X *c, const X *d, const double *parts, X *e,
+void amg_launch_kc_combine(hipStream_t s, int32_t n, const X *c, const X *d, double *parts, X *e,
                            const PcgState *st);
+// CG's update with the first residual of the V-cycle, and the prolongation
+// with the V-cycle's last sweep (d: the correction is the K-cycle's
+// combination of e and d, with the partials of its level of nc rows)
+template <class V>
+void amg_launch_update_resid(hipStream_t s, Sell<V> A, int k, double *x, const double *r_in, double *r_out,
+                             const double *p, const double *q, const double *dinv, double *x0, double *res, PcgParts P,
+                             PcgState *st);
+template <class V, class X>
+void amg_launch_post_rz(hipStream_t s, Sell<V> A, const X *dinv, const X *b, const X *x, const int32_t *agg, const X *e,
+                        const X *d, double *parts, int32_t nc, X *out, double *rz, double *zq, const X *qv,
+                        const PcgState *st);
 // the same with x = D^-1 b and y formed on the fly (one kernel)
 template <class V, class X>
 void amg_launch_post_fused(hipStream_t s, Sell<V> A, const X *dinv, const X *b, const int32_t *agg, const X *e,
@@ -150,7 +165,7 @@ struct AmgLevel {
     DBuf<double> b, xa, xb, r;      // cycle vectors
     DBuf<float> val32, dinv32, b32, xa32, xb32, r32;
     DBuf<double> dg32;  // FP64 diagonal of the FP32 copy (row sums kept)
-    DBuf<double> kc_c, kc_v, kc_rt, kc_d, kc_w, kc_parts;  // K-cycle work of this level
+    DBuf<double> kc_c, kc_v, kc_rt, kc_d, kc_parts;  // K-cycle work of this level
     Sell<float> A32;
 };
 
@@ -196,6 +211,11 @@ class Amg {
     // FP32 matrices, FP64 vectors
     void apply_mixed(hipStream_t s, const double *r, double *z, const PcgState *st, bool x_ready = false,
                      double *rz = nullptr, double *zq = nullptr, const double *qv = nullptr);
+    // CG's update fused with the first residual of the next application, which
+    // then takes x_ready = r_ready = true (FP32 matrices with mixed)
+    void update_resid(hipStream_t s, bool mixed, int k, double *x, const double *r_in, double *r_out, const double *p,
+                      const double *q, PcgParts P, PcgState *st);
+    bool r_ready = false;  // the next apply finds the residual of x_ready's iterate in L[0]->r
     // true when applying the hierarchy runs K-cycles (a nonlinear preconditioner)
     bool nonlinear() const { return o_.kcycle > 0 && nlev >= 3; }
     bool classical() const { return o_.kind == 1; }
@@ -239,12 +259,15 @@ class Amg {
     void product_tables(hipStream_t s, int32_t n, const Product &p, bool fill, int32_t *rowlen, const int64_t *optr,
                         int32_t *ocol, double *oval);
     template <class V, class X>
-    void cycle(hipStream_t s, int l, const X *b, X *out, const PcgState *st, bool x_ready, double *rz);
+    void cycle(hipStream_t s, int l, const X *b, X *out, const PcgState *st, bool x_ready, double *rz,
+               bool r_ready = false);
     template <class V, class X>
     void cycle_classical(hipStream_t s, int l, const X *b, X *out, const PcgState *st, bool x_ready);
-    // coarse-grid correction of level m: a V-cycle, or a K-cycle (two flexible CG steps)
+    // coarse-grid correction of level m: a V-cycle, or a K-cycle (two flexible
+    // CG steps); with split a K-cycle leaves its two directions in kc_c and
+    // kc_d for the caller to combine, and returns true
     template <class V, class X>
-    void coarse(hipStream_t s, int m, const X *b, X *e, const PcgState *st, bool x_ready);
+    bool coarse(hipStream_t s, int m, const X *b, X *e, const PcgState *st, bool x_ready, bool split = false);
 
   public:
     ~Amg();

@@ -30,7 +30,6 @@
 namespace vag {
 
 constexpr int kAT = 256;
-constexpr int kRzThreads = kKrylovThreads;  // the r.z sweep writes Krylov partials
 constexpr int kCap = 8192;  // candidate entries per coarse row held in LDS
 
 #define GS(i, n) \
@@ -1148,26 +1147,32 @@ __global__ __launch_bounds__(kAT) void vc_prolong_kernel(int32_t n, const X *__r
 // With zq also the partials of qv . out (flexible CG: the new preconditioned
 // residual against the last A p).
 template <class V, class X>
-__global__ __launch_bounds__(kRzThreads) void vc_sweep_kernel(Sell<V> A, const X *__restrict__ dinv, const X *__restrict__ b,
+__global__ __launch_bounds__(kAT) void vc_sweep_kernel(Sell<V> A, const X *__restrict__ dinv, const X *__restrict__ b,
                                                        const X *__restrict__ y, X *__restrict__ out,
-                                                       double *__restrict__ rz, double *__restrict__ zq,
-                                                       const X *__restrict__ qv, const PcgState *st) {
+                                                       const PcgState *st) {
     if (st && st->done) return;
-    double v[2] = {0.0, 0.0};
     GS(i, A.n) {
         const X s = sell_row_apply<V, X>(A, (int32_t)i, [&](int32_t j) { return y[j]; });
-        const X o = y[i] + dinv[i] * (b[i] - s);
-        out[i] = o;
-        v[0] += (double)b[i] * (double)o;
-        if (zq) v[1] += (double)qv[i] * (double)o;
+        out[i] = y[i] + dinv[i] * (b[i] - s);
     }
-    if (rz) {
-        block_reduce<OpSum, 2, kRzThreads>(v);
-        if (threadIdx.x == 0) {
-            rz[blockIdx.x] = v[0];
-            if (zq) zq[blockIdx.x] = v[1];
-        }
-    }
+}
+// (levels of more than kSmallRows rows)
+template <class V, class X>
+__global__ __launch_bounds__(kKrylovThreads) void vc_sweep_rz_kernel(Sell<V> A, const X *__restrict__ dinv,
+                                                                     const X *__restrict__ b, const X *__restrict__ y,
+                                                                     X *__restrict__ out, double *__restrict__ rz,
+                                                                     double *__restrict__ zq,
+                                                                     const X *__restrict__ qv, const PcgState *st) {
+    if (st && st->done) return;
+    krylov_rows<kKrylovThreads, 2, true, V, X>(
+        A, false, 0, [&](int32_t j) { return y[j]; },
+        [&](int32_t i, X s, double *v) {
+            const X o = y[i] + dinv[i] * (b[i] - s);
+            out[i] = o;
+            v[0] += (double)b[i] * (double)o;
+            if (zq) v[1] += (double)qv[i] * (double)o;
+        },
+        [&](int k) { return k ? zq : rz; });
 }
 // prolongation and sweep in one pass (small levels): y = x + P e with
 // x = D^-1 b formed on the fly, out = y + D^-1 (b - A y)
@@ -1208,21 +1213,8 @@ __global__ __launch_bounds__(kAT) void vc_small_kernel(Sell<V> A, const X *__res
     };
     for (int64_t w = ((int64_t)xcd_block() * blockDim.x + threadIdx.x) >> 6; w * kRowsPerWave < A.n; w += nw) {
         const int32_t i = (int32_t)(w * kRowsPerWave) + rr;
-        X s0 = 0, s1 = 0;
-        if (i < A.n) {
-            const int64_t b1 = A.ptr[(i >> 6) + 1];
-            int64_t q = A.ptr[i >> 6] + (i & 63) + (int64_t)g * 64;
-            for (; q + kG * 64 < b1; q += 2 * kG * 64) {
-                s0 += (X)A.val[q] * f(A.col[q]);
-                s1 += (X)A.val[q + kG * 64] * f(A.col[q + kG * 64]);
-            }
-            if (q < b1) s0 += (X)A.val[q] * f(A.col[q]);
-        }
-        X sum = s0 + s1;
-#pragma unroll
-        for (int o = kRowsPerWave; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+        const X sum = lane_row(A, i, f).template sum<X, 2>([](X t) { return t; });
         if (g == 0 && i < A.n) {
-            if (A.dg) sum += (X)A.dg[i] * f(i);
             if constexpr (MODE == 0) {
                 out[i] = b[i] - sum;
             } else {
@@ -1250,89 +1242,242 @@ static inline unsigned grid_small(int32_t n) {
 // Scalars are formed by each consuming kernel from per-block partials, in a
 // fixed order.  parts: [c.v | c.b | d.w | d.v | d.rt] x G.
 // ---------------------------------------------------------------------------
+// Up to kSmallRows rows the partials are sums of 64-row slices (4 per 256 rows,
+// zeros past the last), from kernels with 4 lanes per row; above, one per block
+// of 256 threads that strides over the rows (kReduceBlocks of them).  Summed
+// here in the order of the latter, whichever kernels wrote them.
+template <int NT, int NV, class P>
+__device__ inline void kc_sums(bool slices, P p, int G, double (&v)[NV]) {
+    static_assert(NT >= 256, "one thread per group of partials");
+    __shared__ double lds[NV][4];
+    const int t = threadIdx.x;
+    if (t < 256) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double *q = p(k);
+            double s = 0.0;
+            if (slices) {
+                for (int g = 4 * t; g < G; g += 1024) s += ((q[g] + q[g + 1]) + q[g + 2]) + q[g + 3];
+            } else {
+                for (int g = t; g < G; g += 256) s += q[g];
+            }
+            s = wave_reduce<OpSum>(s);
+            if ((t & 63) == 0) lds[k][t >> 6] = s;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        v[k] = lds[k][0];
+        for (int w = 1; w < 4; ++w) v[k] += lds[k][w];
+    }
+    __syncthreads();
+}
+struct KcParts {
+    double *base;
+    int G;
+    bool slices;
+    __device__ double *at(int k) const { return base + (size_t)k * G; }
+};
+template <int NT>
+__device__ inline double kc_alpha1(const KcParts &P) {
+    double t[2];
+    kc_sums<NT>(P.slices, [&](int k) { return P.at(k); }, P.G, t);
+    return t[0] > 0.0 ? t[1] / t[0] : 0.0;
+}
+// the correction a level takes from the one below: e, or with d the K-cycle's
+// combination ac e + ad d
 template <class X>
-__device__ inline void kc_scalars(const double *parts, int G, double &rho, double &a1, double &g, double &a2) {
-    rho = sum_parts<OpSum, kAT>(parts, G);
-    const double cb = sum_parts<OpSum, kAT>(parts + G, G);
-    a1 = rho > 0.0 ? cb / rho : 0.0;
-    g = 0.0;
-    a2 = 0.0;
+struct KcE {
+    const X *e, *d;
+    KcParts P;
+};
+template <int NT, class X>
+__device__ inline void kc_weights(const KcE<X> &E, X &ac, X &ad) {
+    ac = 1;
+    ad = 0;
+    if (!E.d) return;  // uniform
+    double t[5];
+    kc_sums<NT>(E.P.slices, [&](int k) { return E.P.at(k); }, E.P.G, t);
+    const double rho = t[0];
+    double a1 = 0.0, g = 0.0, a2 = 0.0;
+    if (rho > 0.0) {
+        a1 = t[1] / rho;
+        g = t[3];
+        const double beta = t[2] - g * g / rho;
+        a2 = beta > 0.0 ? t[4] / beta : 0.0;
+    }
+    ac = (X)(rho > 0.0 ? a1 - g * a2 / rho : 0.0);
+    ad = (X)a2;
+}
+template <class X>
+__device__ inline X kc_e(X ac, X ad, X e, X d) {
+    return fma(ac, e, ad * d);
 }
 // v = A c; partials c.v and c.b
-template <class V, class X>
+template <bool SPLIT, class V, class X>
 __global__ __launch_bounds__(kAT) void kc_av_kernel(Sell<V> A, const X *__restrict__ c, const X *__restrict__ b,
-                                                    X *__restrict__ v, double *__restrict__ parts,
-                                                    const PcgState *st) {
+                                                    X *__restrict__ v, KcParts P, const PcgState *st) {
     if (st && st->done) return;
-    double p[2] = {0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < A.n; i += (int64_t)gridDim.x * blockDim.x) {
-        const X vi = sell_row_apply<V, X>(A, (int32_t)i, [&](int32_t j) { return c[j]; });
+    auto f = [&](int32_t j) { return c[j]; };
+    auto row = [&](int32_t i, X vi, double *p) {
         v[i] = vi;
         p[0] += (double)c[i] * (double)vi;
         p[1] += (double)c[i] * (double)b[i];
-    }
-    block_reduce<OpSum, 2, kAT>(p);
-    if (threadIdx.x == 0) {
-        parts[blockIdx.x] = p[0];
-        parts[gridDim.x + blockIdx.x] = p[1];
+    };
+    auto put = [&](int k) { return P.at(k); };
+    if constexpr (SPLIT) {
+        const int32_t i = split_row<kAT, false>();
+        const X s = lane_row(A, i, f).template sum<X, 1>([](X t) { return t; });
+        split_rows<kAT, 2, false>(A.n, P.G, i, s, row, put);
+    } else {
+        krylov_rows<kAT, 2, false, V, X>(A, false, P.G, f, row, put);
     }
 }
 // rt = b - alpha1 v, and the next V-cycle's first iterate xa = D^-1 rt
 template <class X>
 __global__ __launch_bounds__(kAT) void kc_rt_kernel(int32_t n, const X *__restrict__ b, const X *__restrict__ v,
-                                                    const X *__restrict__ dinv, const double *__restrict__ parts,
-                                                    X *__restrict__ rt, X *__restrict__ xa, const PcgState *st) {
+                                                    const X *__restrict__ dinv, KcParts P, X *__restrict__ rt,
+                                                    X *__restrict__ xa, const PcgState *st) {
     if (st && st->done) return;
-    double rho, a1, g, a2;
-    kc_scalars<X>(parts, gridDim.x, rho, a1, g, a2);
-    const X a = (X)a1;
+    const X a = (X)kc_alpha1<kAT>(P);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const X r = b[i] - a * v[i];
         rt[i] = r;
         xa[i] = dinv[i] * r;
     }
 }
-// w = A d; partials d.w, d.v, d.rt
+// The same (xa is not needed) with the next V-cycle's residual r = rt - A D^-1 rt,
+// in one launch: levels of at most kSmallRows rows, where a launch (~3 us of the
+// host's time) costs more than forming rt again at every gathered entry.
 template <class V, class X>
-__global__ __launch_bounds__(kAT) void kc_aw_kernel(Sell<V> A, const X *__restrict__ d, const X *__restrict__ v,
-                                                    const X *__restrict__ rt, X *__restrict__ w,
-                                                    double *__restrict__ parts, const PcgState *st) {
+__global__ __launch_bounds__(kAT) void kc_rt_resid_kernel(Sell<V> A, const X *__restrict__ b, const X *__restrict__ v,
+                                                          const X *__restrict__ dinv, KcParts P, X *__restrict__ rt,
+                                                          X *__restrict__ r, const PcgState *st) {
     if (st && st->done) return;
-    double p[3] = {0.0, 0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < A.n; i += (int64_t)gridDim.x * blockDim.x) {
-        const X wi = sell_row_apply<V, X>(A, (int32_t)i, [&](int32_t j) { return d[j]; });
-        w[i] = wi;
+    const int lane = threadIdx.x & 63;
+    const int32_t i = (int32_t)(((int64_t)xcd_block() * kAT + threadIdx.x) >> 6) * kSplitRows + lane % kSplitRows;
+    struct Raw {
+        X b, v, d;
+    };
+    auto R = lane_row(A, i, [&](int32_t j) { return Raw{b[j], v[j], dinv[j]}; });
+    const X a = (X)kc_alpha1<kAT>(P);
+    const X s = R.template sum<X, 2>([&](const Raw &w) {
+        const X t = w.b - a * w.v;
+        return w.d * t;
+    });
+    if (lane < kSplitRows && i < A.n) {
+        const X t = b[i] - a * v[i];
+        rt[i] = t;
+        r[i] = t - s;
+    }
+}
+// partials d.w (w = A d), d.v, d.rt
+template <bool SPLIT, class V, class X>
+__global__ __launch_bounds__(kAT) void kc_aw_kernel(Sell<V> A, const X *__restrict__ d, const X *__restrict__ v,
+                                                    const X *__restrict__ rt, KcParts P, const PcgState *st) {
+    if (st && st->done) return;
+    auto f = [&](int32_t j) { return d[j]; };
+    auto row = [&](int32_t i, X wi, double *p) {
         p[0] += (double)d[i] * (double)wi;
         p[1] += (double)d[i] * (double)v[i];
         p[2] += (double)d[i] * (double)rt[i];
-    }
-    block_reduce<OpSum, 3, kAT>(p);
-    if (threadIdx.x == 0) {
-        const int G = gridDim.x;
-        parts[2 * G + blockIdx.x] = p[0];
-        parts[3 * G + blockIdx.x] = p[1];
-        parts[4 * G + blockIdx.x] = p[2];
+    };
+    auto put = [&](int k) { return P.at(2 + k); };
+    if constexpr (SPLIT) {
+        const int32_t i = split_row<kAT, false>();
+        const X s = lane_row(A, i, f).template sum<X, 1>([](X t) { return t; });
+        split_rows<kAT, 3, false>(A.n, P.G, i, s, row, put);
+    } else {
+        krylov_rows<kAT, 3, false, V, X>(A, false, P.G, f, row, put);
     }
 }
 // e = (alpha1 - gamma alpha2 / rho) c + alpha2 d
 template <class X>
-__global__ __launch_bounds__(kAT) void kc_combine_kernel(int32_t n, const X *__restrict__ c, const X *__restrict__ d,
-                                                         const double *__restrict__ parts, X *__restrict__ e,
-                                                         const PcgState *st) {
+__global__ __launch_bounds__(kAT) void kc_combine_kernel(int32_t n, KcE<X> E, X *__restrict__ e, const PcgState *st) {
     if (st && st->done) return;
-    const int G = gridDim.x;
-    double rho, a1, g, a2;
-    kc_scalars<X>(parts, G, rho, a1, g, a2);
-    if (rho > 0.0) {
-        const double dw = sum_parts<OpSum, kAT>(parts + 2 * G, G);
-        g = sum_parts<OpSum, kAT>(parts + 3 * G, G);
-        const double drt = sum_parts<OpSum, kAT>(parts + 4 * G, G);
-        const double beta = dw - g * g / rho;
-        a2 = beta > 0.0 ? drt / beta : 0.0;
-    }
-    const X ac = (X)(rho > 0.0 ? a1 - g * a2 / rho : 0.0), ad = (X)a2;
+    X ac, ad;
+    kc_weights<kAT>(E, ac, ad);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        e[i] = ac * c[i] + ad * d[i];
+        e[i] = kc_e(ac, ad, E.e[i], E.d[i]);
+}
+
+// ---------------------------------------------------------------------------
+// CG around a finest level of at most kSmallRows rows: fewer launches.
+// There an iteration is bound by its launches and by each kernel's one chain of
+// loads.  Five kernels and 26 us of them per two-level iteration at 1089 rows
+// (product, residual and sweep alone were 10 us each); a time step on 10^3
+// cells with its set-up 441 -> 330 launches, 2540 -> 1980 us; on 33x37x35 cells
+// 5040 -> 4380 us
+// ---------------------------------------------------------------------------
+// CG's update and the V-cycle's first residual: x += alpha p, r_out = r_in -
+// alpha q, x0 = D^-1 r_out, res = r_out - A x0 (x0 formed again at every
+// gathered entry), partials of r_out . r_out
+template <class V>
+__global__ __launch_bounds__(kSplitThreads) void pcg_update_resid_kernel(
+    Sell<V> A, int k, double *__restrict__ x, const double *__restrict__ r_in, double *__restrict__ r_out,
+    const double *__restrict__ p, const double *__restrict__ q, const double *__restrict__ dinv,
+    double *__restrict__ x0, double *__restrict__ res, PcgParts P, PcgState *st) {
+    if (st->done) return;
+    const int32_t i = split_row<kSplitThreads, false>();
+    struct Raw {
+        double r, q, d;
+    };
+    auto R = lane_row(A, i, [&](int32_t j) { return Raw{r_in[j], q[j], dinv[j]}; });
+    double t[2];
+    krylov_sums<kSplitThreads>(true, [&](int m) { return m ? P.pq(k) : P.rz(k - 1); }, P.G, t);
+    const double a = t[0] / t[1];
+    const double s = R.template sum<double, 2>([&](const Raw &w) {
+        const double rj = w.r - a * w.q;
+        return w.d * rj;
+    });
+    split_rows<kSplitThreads, 1, false>(
+        A.n, P.G, i, s,
+        [&](int32_t m, double sm, double *v) {
+            x[m] += a * p[m];
+            const double ri = r_in[m] - a * q[m];
+            r_out[m] = ri;
+            x0[m] = dinv[m] * ri;
+            res[m] = ri - sm;
+            v[0] += ri * ri;
+        },
+        [&](int) { return P.rr(k); });
+    if (threadIdx.x == 0 && blockIdx.x == 0) st->iter = k + 1;
+}
+// the prolongation and the last sweep: out = y + D^-1 (b - A y) with y = x + P e,
+// partials of b . out and (with zq) qv . out
+template <class V, class X>
+__global__ __launch_bounds__(kSplitThreads) void vc_post_rz_kernel(
+    Sell<V> A, int G, const X *__restrict__ dinv, const X *__restrict__ b, const X *__restrict__ x,
+    const int32_t *__restrict__ agg, KcE<X> E, X *__restrict__ out, double *__restrict__ rz, double *__restrict__ zq,
+    const X *__restrict__ qv, const PcgState *st) {
+    if (st && st->done) return;
+    const int32_t i = split_row<kSplitThreads, true>();
+    const bool two = E.d != nullptr;
+    struct Raw {
+        X x, c, d;
+    };
+    auto R = lane_row(A, i, [&](int32_t j) {
+        const int32_t J = agg[j];
+        return Raw{x[j], E.e[J], two ? E.d[J] : (X)0};
+    });
+    X ac, ad;
+    kc_weights<kSplitThreads>(E, ac, ad);
+    auto use = [&](const Raw &w) -> X {
+        const X e = two ? kc_e(ac, ad, w.c, w.d) : w.c;
+        return w.x + e;
+    };
+    const X s = R.template sum<X, 1>(use);
+    split_rows<kSplitThreads, 2, true>(
+        A.n, G, i, s,
+        [&](int32_t m, X sm, double *v) {
+            const X y = use(R.gather(m));
+            const X o = y + dinv[m] * (b[m] - sm);
+            out[m] = o;
+            v[0] += (double)b[m] * (double)o;
+            if (zq) v[1] += (double)qv[m] * (double)o;
+        },
+        [&](int k) { return k ? zq : rz; });
 }
 
 // dense coarse solve x = Ainv b: one wavefront per row, lanes along the
@@ -1484,38 +1629,75 @@ void amg_launch_dense_inverse(hipStream_t s, Sell<double> A, double *D, double *
         }
     }
 }
-int kc_grid(int32_t n) { return (int)reduce_grid(n, kAT); }
+int kc_grid(int32_t n) {
+    const int b = (int)reduce_grid(n, kAT);
+    return n <= kSmallRows ? 4 * b : b;
+}
+static inline KcParts kc_parts(double *base, int32_t n) { return KcParts{base, kc_grid(n), n <= kSmallRows}; }
 template <class V, class X>
 void amg_launch_kc_av(hipStream_t s, Sell<V> A, const X *c, const X *b, X *v, double *parts, const PcgState *st) {
-    ALAUNCH((kc_av_kernel<V, X>), kc_grid(A.n), kAT, A, c, b, v, parts, st);
+    if (A.n <= kSmallRows)
+        ALAUNCH((kc_av_kernel<true, V, X>), kc_grid(A.n), kAT, A, c, b, v, kc_parts(parts, A.n), st);
+    else
+        ALAUNCH((kc_av_kernel<false, V, X>), kc_grid(A.n), kAT, A, c, b, v, kc_parts(parts, A.n), st);
 }
 template <class X>
-void amg_launch_kc_rt(hipStream_t s, int32_t n, const X *b, const X *v, const X *dinv, const double *parts, X *rt,
-                      X *xa, const PcgState *st) {
-    ALAUNCH(kc_rt_kernel<X>, kc_grid(n), kAT, n, b, v, dinv, parts, rt, xa, st);
+void amg_launch_kc_rt(hipStream_t s, int32_t n, const X *b, const X *v, const X *dinv, double *parts, X *rt, X *xa,
+                      const PcgState *st) {
+    ALAUNCH(kc_rt_kernel<X>, reduce_grid(n, kAT), kAT, n, b, v, dinv, kc_parts(parts, n), rt, xa, st);
 }
 template <class V, class X>
-void amg_launch_kc_aw(hipStream_t s, Sell<V> A, const X *d, const X *v, const X *rt, X *w, double *parts,
+void amg_launch_kc_rt_resid(hipStream_t s, Sell<V> A, const X *b, const X *v, const X *dinv, double *parts, X *rt,
+                            X *r, const PcgState *st) {
+    ALAUNCH((kc_rt_resid_kernel<V, X>), grid_small(A.n), kAT, A, b, v, dinv, kc_parts(parts, A.n), rt, r, st);
+}
+template <class V, class X>
+void amg_launch_kc_aw(hipStream_t s, Sell<V> A, const X *d, const X *v, const X *rt, double *parts,
                       const PcgState *st) {
-    ALAUNCH((kc_aw_kernel<V, X>), kc_grid(A.n), kAT, A, d, v, rt, w, parts, st);
+    if (A.n <= kSmallRows)
+        ALAUNCH((kc_aw_kernel<true, V, X>), kc_grid(A.n), kAT, A, d, v, rt, kc_parts(parts, A.n), st);
+    else
+        ALAUNCH((kc_aw_kernel<false, V, X>), kc_grid(A.n), kAT, A, d, v, rt, kc_parts(parts, A.n), st);
 }
 template <class X>
-void amg_launch_kc_combine(hipStream_t s, int32_t n, const X *c, const X *d, const double *parts, X *e,
+void amg_launch_kc_combine(hipStream_t s, int32_t n, const X *c, const X *d, double *parts, X *e,
                            const PcgState *st) {
-    ALAUNCH(kc_combine_kernel<X>, kc_grid(n), kAT, n, c, d, parts, e, st);
+    ALAUNCH(kc_combine_kernel<X>, reduce_grid(n, kAT), kAT, n, (KcE<X>{c, d, kc_parts(parts, n)}), e, st);
 }
-template void amg_launch_kc_av<double, double>(hipStream_t, Sell<double>, const double *, const double *, double *,
-                                               double *, const PcgState *);
-template void amg_launch_kc_av<float, double>(hipStream_t, Sell<float>, const double *, const double *, double *,
-                                              double *, const PcgState *);
-template void amg_launch_kc_aw<double, double>(hipStream_t, Sell<double>, const double *, const double *,
-                                               const double *, double *, double *, const PcgState *);
-template void amg_launch_kc_aw<float, double>(hipStream_t, Sell<float>, const double *, const double *,
-                                              const double *, double *, double *, const PcgState *);
-template void amg_launch_kc_rt<double>(hipStream_t, int32_t, const double *, const double *, const double *,
-                                       const double *, double *, double *, const PcgState *);
-template void amg_launch_kc_combine<double>(hipStream_t, int32_t, const double *, const double *, const double *,
-                                            double *, const PcgState *);
+template <class V>
+void amg_launch_update_resid(hipStream_t s, Sell<V> A, int k, double *x, const double *r_in, double *r_out,
+                             const double *p, const double *q, const double *dinv, double *x0, double *res, PcgParts P,
+                             PcgState *st) {
+    ALAUNCH(pcg_update_resid_kernel<V>, krylov_shape(A.n).row_blocks, kSplitThreads, A, k, x, r_in, r_out, p, q, dinv, x0,
+            res, P, st);
+}
+template <class V, class X>
+void amg_launch_post_rz(hipStream_t s, Sell<V> A, const X *dinv, const X *b, const X *x, const int32_t *agg, const X *e,
+                        const X *d, double *parts, int32_t nc, X *out, double *rz, double *zq, const X *qv,
+                        const PcgState *st) {
+    const KrylovShape ks = krylov_shape(A.n);
+    ALAUNCH((vc_post_rz_kernel<V, X>), ks.row_blocks, kSplitThreads, A, ks.G, dinv, b, x, agg,
+            (KcE<X>{e, d, kc_parts(parts, nc)}), out, rz, zq, qv, st);
+}
+#define KC_INST(V)                                                                                                    \
+    template void amg_launch_kc_av<V, double>(hipStream_t, Sell<V>, const double *, const double *, double *, double *, \
+                                              const PcgState *);                                                      \
+    template void amg_launch_kc_rt_resid<V, double>(hipStream_t, Sell<V>, const double *, const double *,             \
+                                                    const double *, double *, double *, double *, const PcgState *);  \
+    template void amg_launch_kc_aw<V, double>(hipStream_t, Sell<V>, const double *, const double *, const double *,   \
+                                              double *, const PcgState *);                                            \
+    template void amg_launch_update_resid<V>(hipStream_t, Sell<V>, int, double *, const double *, double *,           \
+                                             const double *, const double *, const double *, double *, double *,      \
+                                             PcgParts, PcgState *);                                                   \
+    template void amg_launch_post_rz<V, double>(hipStream_t, Sell<V>, const double *, const double *, const double *, \
+                                                const int32_t *, const double *, const double *, double *, int32_t,   \
+                                                double *, double *, double *, const double *, const PcgState *);
+KC_INST(double)
+KC_INST(float)
+template void amg_launch_kc_rt<double>(hipStream_t, int32_t, const double *, const double *, const double *, double *,
+                                       double *, double *, const PcgState *);
+template void amg_launch_kc_combine<double>(hipStream_t, int32_t, const double *, const double *, double *, double *,
+                                            const PcgState *);
 template <class V, class X>
 void amg_launch_pre(hipStream_t s, Sell<V> A, const X *dinv, const X *b, X *x, X *r, const PcgState *st) {
     ALAUNCH(vc_scale_kernel<X>, gridv(A.n), kAT, A.n, dinv, b, x, st);
@@ -1553,9 +1735,10 @@ void amg_launch_post(hipStream_t s, Sell<V> A, const X *dinv, const X *b, const 
     ALAUNCH(vc_prolong_kernel<X>, gridv(A.n), kAT, A.n, x, agg, e, y, st);
     // with rz the partials must match the Krylov kernels' grid and block size
     if (rz)
-        ALAUNCH((vc_sweep_kernel<V, X>), reduce_grid(A.n, kRzThreads), kRzThreads, A, dinv, b, y, out, rz, zq, qv, st);
+        ALAUNCH((vc_sweep_rz_kernel<V, X>), krylov_shape(A.n).row_blocks, kKrylovThreads, A, dinv, b, y, out, rz, zq, qv,
+                st);
     else
-        ALAUNCH((vc_sweep_kernel<V, X>), gridv(A.n), kAT, A, dinv, b, y, out, nullptr, nullptr, nullptr, st);
+        ALAUNCH((vc_sweep_kernel<V, X>), gridv(A.n), kAT, A, dinv, b, y, out, st);
 }
 template <class X>
 void amg_launch_dense(hipStream_t s, int32_t n, const X *Ainv, const X *b, X *x, const PcgState *st) {
@@ -1567,7 +1750,7 @@ void amg_launch_sweep(hipStream_t s, Sell<V> A, const X *dinv, const X *b, const
         ALAUNCH((vc_small_kernel<1, V, X>), grid_small(A.n), kAT, A, dinv, b, x, (const int32_t *)nullptr,
                 (const X *)nullptr, out, st);
     else
-        ALAUNCH((vc_sweep_kernel<V, X>), gridv(A.n), kAT, A, dinv, b, x, out, nullptr, nullptr, nullptr, st);
+        ALAUNCH((vc_sweep_kernel<V, X>), gridv(A.n), kAT, A, dinv, b, x, out, st);
 }
 void launch_to_float(hipStream_t s, int64_t n, const double *a, float *b) {
     if (n > 0) ALAUNCH(to_float_kernel, gridv(n), kAT, n, a, b);

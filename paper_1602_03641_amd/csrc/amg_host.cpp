@@ -2,6 +2,7 @@
 #include "amg.h"
 
 #include <algorithm>
+#include <utility>
 
 namespace vag {
 
@@ -124,7 +125,7 @@ void Amg::finish_setup(hipStream_t s, Tracker &tr, int l, int64_t stored_total, 
     // K-cycle work on levels 1 .. kcycle that are not the coarsest
     for (int m = 1; m < nlev - 1 && m <= o_.kcycle; ++m) {
         AmgLevel &kv = *L[m];
-        for (auto *v : {&kv.kc_c, &kv.kc_v, &kv.kc_rt, &kv.kc_d, &kv.kc_w}) ensure(*v, kv.n, tr);
+        for (auto *v : {&kv.kc_c, &kv.kc_v, &kv.kc_rt, &kv.kc_d}) ensure(*v, kv.n, tr);
         ensure(kv.kc_parts, (size_t)5 * kc_grid(kv.n), tr);
     }
     if (cl.n <= o_.dense_max && cl.n > 0) {
@@ -333,7 +334,8 @@ void Amg::make_fp32(hipStream_t s, Tracker &tr, const int32_t *) {
 // V-cycle on level l: out = M_l^-1 b.  x_ready: xa already holds D^-1 b (the
 // first smoothing iterate), written by the kernel that produced b.
 template <class V, class X>
-void Amg::cycle(hipStream_t s, int l, const X *b, X *out, const PcgState *st, bool x_ready, double *rz) {
+void Amg::cycle(hipStream_t s, int l, const X *b, X *out, const PcgState *st, bool x_ready, double *rz,
+                bool r_ready) {
     if (o_.kind == 1 && l < nlev - 1) {
         if (rz) throw Error(VAG_ERR_ARG, "internal: the classical hierarchy does not fuse r.z");
         cycle_classical<V, X>(s, l, b, out, st, x_ready);
@@ -389,12 +391,22 @@ void Amg::cycle(hipStream_t s, int l, const X *b, X *out, const PcgState *st, bo
     // (the same number before and after the coarse correction: symmetric)
     const int nu = l == 0 ? 1 : std::max(1, o_.sweeps);
     if (nu == 1) {
-        if (x_ready)
+        if (r_ready)
+            ;  // r = b - A D^-1 b came with b
+        else if (x_ready)
             amg_launch_resid<V, X>(s, A, b, xa, r, st);
         else
             amg_launch_pre<V, X>(s, A, dinv, b, xa, r, st);
         amg_launch_restrict<X>(s, cv.n, lv.mptr.p, lv.mrows.p, r, bc, coarse_x ? dinv_c : nullptr,
                                coarse_x ? xc : nullptr, st);
+        if constexpr (sizeof(X) == 8) {
+            if (rz && lv.n <= kSmallRows) {
+                const bool two = coarse<V, X>(s, l + 1, bc, ec, st, coarse_x, true);
+                amg_launch_post_rz<V, X>(s, A, dinv, b, xa, lv.agg.p, two ? cv.kc_c.p : ec, two ? cv.kc_d.p : nullptr,
+                                         cv.kc_parts.p, cv.n, out, rz, zq_, zq_ ? qv_ : nullptr, st);
+                return;
+            }
+        }
         coarse<V, X>(s, l + 1, bc, ec, st, coarse_x);
         if (lv.n <= kFusedPostRows && !rz) {
             amg_launch_post_fused<V, X>(s, A, dinv, b, lv.agg.p, ec, out, st);
@@ -487,30 +499,46 @@ void Amg::cycle_classical(hipStream_t s, int l, const X *b, X *out, const PcgSta
 }
 
 template <class V, class X>
-void Amg::coarse(hipStream_t s, int m, const X *b, X *e, const PcgState *st, bool x_ready) {
+bool Amg::coarse(hipStream_t s, int m, const X *b, X *e, const PcgState *st, bool x_ready, bool split) {
     if constexpr (sizeof(X) == 8) {
         if (m <= o_.kcycle && m < nlev - 1 && x_ready) {
             // two flexible CG steps on A_m e = b, each preconditioned by a V-cycle from level m
             AmgLevel &lv = *L[m];
             Sell<V> A;
             if constexpr (sizeof(V) == 4) A = lv.A32; else A = lv.A;
+            const bool one = lv.n <= kSmallRows && o_.sweeps <= 1;  // fewer launches
             cycle<V, X>(s, m, b, lv.kc_c.p, st, true, nullptr);                  // c = B b (xa = D^-1 b given)
             amg_launch_kc_av<V, X>(s, A, lv.kc_c.p, b, lv.kc_v.p, lv.kc_parts.p, st);
-            amg_launch_kc_rt<X>(s, lv.n, b, lv.kc_v.p, lv.dinv.p, lv.kc_parts.p, lv.kc_rt.p, lv.xa.p, st);
-            cycle<V, X>(s, m, lv.kc_rt.p, lv.kc_d.p, st, true, nullptr);          // d = B rt
-            amg_launch_kc_aw<V, X>(s, A, lv.kc_d.p, lv.kc_v.p, lv.kc_rt.p, lv.kc_w.p, lv.kc_parts.p, st);
+            if (one)
+                amg_launch_kc_rt_resid<V, X>(s, A, b, lv.kc_v.p, lv.dinv.p, lv.kc_parts.p, lv.kc_rt.p, lv.r.p, st);
+            else
+                amg_launch_kc_rt<X>(s, lv.n, b, lv.kc_v.p, lv.dinv.p, lv.kc_parts.p, lv.kc_rt.p, lv.xa.p, st);
+            cycle<V, X>(s, m, lv.kc_rt.p, lv.kc_d.p, st, true, nullptr, one);    // d = B rt
+            amg_launch_kc_aw<V, X>(s, A, lv.kc_d.p, lv.kc_v.p, lv.kc_rt.p, lv.kc_parts.p, st);
+            if (split) return true;
             amg_launch_kc_combine<X>(s, lv.n, lv.kc_c.p, lv.kc_d.p, lv.kc_parts.p, e, st);
-            return;
+            return false;
         }
     }
     cycle<V, X>(s, m, b, e, st, x_ready, nullptr);
+    return false;
+}
+
+void Amg::update_resid(hipStream_t s, bool mixed, int k, double *x, const double *r_in, double *r_out, const double *p,
+                       const double *q, PcgParts P, PcgState *st) {
+    AmgLevel &lv = *L[0];
+    if (mixed)
+        amg_launch_update_resid<float>(s, lv.A32, k, x, r_in, r_out, p, q, lv.dinv.p, lv.xa.p, lv.r.p, P, st);
+    else
+        amg_launch_update_resid<double>(s, lv.A, k, x, r_in, r_out, p, q, lv.dinv.p, lv.xa.p, lv.r.p, P, st);
+    r_ready = true;
 }
 
 void Amg::apply(hipStream_t s, const double *r, double *z, const PcgState *st, bool x_ready, double *rz, double *zq,
                 const double *qv) {
     zq_ = zq;
     qv_ = qv;
-    cycle<double, double>(s, 0, r, z, st, x_ready, rz);
+    cycle<double, double>(s, 0, r, z, st, x_ready, rz, std::exchange(r_ready, false));
     zq_ = nullptr;
     qv_ = nullptr;
 }
@@ -523,7 +551,7 @@ void Amg::apply_mixed(hipStream_t s, const double *r, double *z, const PcgState 
                       double *zq, const double *qv) {
     zq_ = zq;
     qv_ = qv;
-    cycle<float, double>(s, 0, r, z, st, x_ready, rz);
+    cycle<float, double>(s, 0, r, z, st, x_ready, rz, std::exchange(r_ready, false));
     zq_ = nullptr;
     qv_ = nullptr;
 }

@@ -30,6 +30,7 @@ constexpr int kT = kKrylovThreads;
 struct BcgParts {
     double *base;
     int G;
+    bool slices;
     __device__ double *rho(int k) const { return base + (size_t)(k & 1) * G; }
     __device__ double *rv() const { return base + (size_t)2 * G; }
     __device__ double *ts() const { return base + (size_t)3 * G; }
@@ -38,42 +39,56 @@ struct BcgParts {
     __device__ double *ss() const { return base + (size_t)7 * G; }
 };
 
-__device__ inline double total(const double *p, int G) { return sum_parts<OpSum, kT>(p, G); }
+__device__ inline double total(const BcgParts &P, const double *p) {
+    double v[1];
+    krylov_sums<kT>(P.slices, [&](int) { return p; }, P.G, v);
+    return v[0];
+}
+__device__ inline int my_slice() { return (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6); }
 
-// x0 given: r = b - A x (or r = b when x is zero: A == null), rhat = r;
+// x0 given: r = b - A x, rhat = r;
 // partials r.r and rhat.r for iteration k0 - 1
-__global__ __launch_bounds__(kT) void bcg_init_kernel(Sell<double> A, int zero_x, int k0, const double *__restrict__ b,
-                                                      double *__restrict__ x, double *__restrict__ r,
+__global__ __launch_bounds__(kT) void bcg_init_kernel(Sell<double> A, int k0, const double *__restrict__ b,
+                                                      const double *__restrict__ x, double *__restrict__ r,
                                                       double *__restrict__ rhat, BcgParts P) {
-    double v[1] = {0.0};
-    GSB(i, A.n) {
-        double ri;
-        if (zero_x) {
-            x[i] = 0.0;
-            ri = b[i];
-        } else {
-            ri = b[i] - sell_row_apply<double, double>(A, (int32_t)i, [&](int32_t j) { return x[j]; });
-        }
+    krylov_rows<kT, 2, false, double, double>(
+        A, P.slices, P.G, [&](int32_t j) { return x[j]; },
+        [&](int32_t i, double s, double *v) {
+            const double ri = b[i] - s;
+            r[i] = ri;
+            rhat[i] = ri;
+            v[0] += ri * ri;
+            v[1] += ri * ri;
+        },
+        [&](int i) { return i ? P.rho(k0 - 1) : P.rr(k0 - 1); });
+}
+// the same for x = 0
+__global__ __launch_bounds__(kT) void bcg_init_zero_kernel(int32_t n, int k0, const double *__restrict__ b,
+                                                           double *__restrict__ x, double *__restrict__ r,
+                                                           double *__restrict__ rhat, BcgParts P) {
+    double v[2] = {0.0, 0.0};
+    GSB(i, n) {
+        const double ri = b[i];
+        x[i] = 0.0;
         r[i] = ri;
         rhat[i] = ri;
         v[0] += ri * ri;
+        v[1] += ri * ri;
     }
-    block_reduce<OpSum, 1, kT>(v);
-    if (threadIdx.x == 0) {
-        P.rr(k0 - 1)[blockIdx.x] = v[0];
-        P.rho(k0 - 1)[blockIdx.x] = v[0];
-    }
+    krylov_put<kT, 2>(P.slices, [&](int i) { return i ? P.rho(k0 - 1) : P.rr(k0 - 1); }, my_slice(), v);
 }
 
-__global__ __launch_bounds__(kT) void bcg_start_kernel(BcgParts P, PcgState *st, double rtol, int k0) {
-    const double rr = total(P.rr(k0 - 1), P.G);
+__global__ __launch_bounds__(kT) void bcg_start_kernel(BcgParts P, PcgState *st, double rtol, int k0,
+                                                       int *host_done) {
+    const double rr = total(P, P.rr(k0 - 1));
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         if (k0 == 0) st->bnorm2 = rr;
         st->tol2 = rtol * rtol * rr;
         st->rr = rr;
         st->iter = k0;
-        st->done = (rr == 0.0);
-        st->converged = (rr == 0.0);
+        st->host_done = host_done;
+        st->done = st->converged = 0;
+        if (rr == 0.0) krylov_done(st, 1, rr);
     }
 }
 
@@ -82,15 +97,11 @@ __global__ __launch_bounds__(kT) void bcg_direction_kernel(int32_t n, int k, int
                                                            double *__restrict__ p, const double *__restrict__ v,
                                                            BcgParts P, PcgState *st, int update) {
     if (st->done) return;
-    const double rr = total(P.rr(k - 1), P.G);
-    const double rho = total(P.rho(k - 1), P.G);
+    const double rr = total(P, P.rr(k - 1));
+    const double rho = total(P, P.rho(k - 1));
     const bool conv = rr <= st->tol2;
     if (conv || rho == 0.0 || !(rr == rr)) {  // converged, breakdown (rhat orthogonal to r) or NaN
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            st->done = 1;
-            st->converged = conv ? 1 : 0;
-            st->rr = rr;
-        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) krylov_done(st, conv ? 1 : 0, rr);
         return;
     }
     if (!update) {
@@ -101,30 +112,33 @@ __global__ __launch_bounds__(kT) void bcg_direction_kernel(int32_t n, int k, int
         GSB(i, n) p[i] = r[i];
         return;
     }
-    const double rho_prev = total(P.rho(k - 2), P.G);
-    const double alpha = rho_prev / total(P.rv(), P.G);
-    const double omega = total(P.ts(), P.G) / total(P.tt(), P.G);
+    const double rho_prev = total(P, P.rho(k - 2));
+    const double alpha = rho_prev / total(P, P.rv());
+    const double omega = total(P, P.ts()) / total(P, P.tt());
     const double beta = (rho / rho_prev) * (alpha / omega);
     GSB(i, n) p[i] = r[i] + beta * (p[i] - omega * v[i]);
 }
 
 // y = A x with the partials of w . y into parts (and of y . y into parts2)
-__global__ __launch_bounds__(kT) void bcg_spmv_dot_kernel(Sell<double> A, const double *__restrict__ x,
+template <bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? kSplitThreads : kT) void bcg_spmv_dot_kernel(Sell<double> A, const double *__restrict__ x,
                                                           double *__restrict__ y, const double *__restrict__ w,
-                                                          double *__restrict__ parts, double *__restrict__ parts2,
-                                                          const PcgState *st) {
+                                                          BcgParts P, double *__restrict__ parts,
+                                                          double *__restrict__ parts2, const PcgState *st) {
     if (st->done) return;
-    double v[2] = {0.0, 0.0};
-    GSB(i, A.n) {
-        const double yi = sell_row_apply<double, double>(A, (int32_t)i, [&](int32_t j) { return x[j]; });
+    auto f = [&](int32_t j) { return x[j]; };
+    auto row = [&](int32_t i, double yi, double *v) {
         y[i] = yi;
         v[0] += w[i] * yi;
         v[1] += yi * yi;
-    }
-    block_reduce<OpSum, 2, kT>(v);
-    if (threadIdx.x == 0) {
-        parts[blockIdx.x] = v[0];
-        if (parts2) parts2[blockIdx.x] = v[1];
+    };
+    auto put = [&](int i) { return i ? parts2 : parts; };
+    if constexpr (SPLIT) {
+        const int32_t i = split_row<kSplitThreads, false>();
+        const double s = lane_row(A, i, f).template sum<double, 1>([](double t) { return t; });
+        split_rows<kSplitThreads, 2, false>(A.n, P.G, i, s, row, put);
+    } else {
+        krylov_rows<kT, 2, false, double, double>(A, false, P.G, f, row, put);
     }
 }
 
@@ -133,30 +147,27 @@ __global__ __launch_bounds__(kT) void bcg_s_kernel(int32_t n, int k, const doubl
                                                    const double *__restrict__ v, double *__restrict__ s, BcgParts P,
                                                    const PcgState *st) {
     if (st->done) return;
-    const double alpha = total(P.rho(k - 1), P.G) / total(P.rv(), P.G);
+    const double alpha = total(P, P.rho(k - 1)) / total(P, P.rv());
     double w[1] = {0.0};
     GSB(i, n) {
         const double si = r[i] - alpha * v[i];
         s[i] = si;
         w[0] += si * si;
     }
-    block_reduce<OpSum, 1, kT>(w);
-    if (threadIdx.x == 0) P.ss()[blockIdx.x] = w[0];
+    krylov_put<kT, 1>(P.slices, [&](int) { return P.ss(); }, my_slice(), w);
 }
 
 // the half step: when |s|^2 <= tol2, x += alpha phat and the solve is done
 __global__ __launch_bounds__(kT) void bcg_half_kernel(int32_t n, int k, const double *__restrict__ phat,
                                                       double *__restrict__ x, BcgParts P, PcgState *st) {
     if (st->done) return;
-    const double ss = total(P.ss(), P.G);
+    const double ss = total(P, P.ss());
     if (!(ss <= st->tol2)) return;
-    const double alpha = total(P.rho(k - 1), P.G) / total(P.rv(), P.G);
+    const double alpha = total(P, P.rho(k - 1)) / total(P, P.rv());
     GSB(i, n) x[i] += alpha * phat[i];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->done = 1;
-        st->converged = 1;
-        st->rr = ss;
         st->iter = k + 1;
+        krylov_done(st, 1, ss);
     }
 }
 
@@ -167,9 +178,9 @@ __global__ __launch_bounds__(kT) void bcg_update_kernel(int32_t n, int k, const 
                                                         const double *__restrict__ rhat, double *__restrict__ x,
                                                         double *__restrict__ r, BcgParts P, PcgState *st) {
     if (st->done) return;
-    const double alpha = total(P.rho(k - 1), P.G) / total(P.rv(), P.G);
-    const double tt = total(P.tt(), P.G);
-    const double omega = tt > 0.0 ? total(P.ts(), P.G) / tt : 0.0;
+    const double alpha = total(P, P.rho(k - 1)) / total(P, P.rv());
+    const double tt = total(P, P.tt());
+    const double omega = tt > 0.0 ? total(P, P.ts()) / tt : 0.0;
     double v[2] = {0.0, 0.0};
     GSB(i, n) {
         x[i] += alpha * phat[i] + omega * shat[i];
@@ -178,57 +189,62 @@ __global__ __launch_bounds__(kT) void bcg_update_kernel(int32_t n, int k, const 
         v[0] += ri * ri;
         v[1] += rhat[i] * ri;
     }
-    block_reduce<OpSum, 2, kT>(v);
-    if (threadIdx.x == 0) {
-        P.rr(k)[blockIdx.x] = v[0];
-        P.rho(k)[blockIdx.x] = v[1];
-        if (blockIdx.x == 0) st->iter = k + 1;
-    }
+    krylov_put<kT, 2>(P.slices, [&](int i) { return i ? P.rho(k) : P.rr(k); }, my_slice(), v);
+    if (threadIdx.x == 0 && blockIdx.x == 0) st->iter = k + 1;
 }
 
 }  // namespace
 
-int bcg_grid(int64_t n) { return (int)reduce_grid(n, kT); }
+int bcg_grid(int64_t n) { return krylov_shape(n).G; }
+static BcgParts bcg_parts(double *base, int64_t n) {
+    const KrylovShape k = krylov_shape(n);
+    return BcgParts{base, k.G, k.split};
+}
 
-#define BLAUNCH(kern, G, ...)                                                      \
-    do {                                                                           \
-        hipLaunchKernelGGL(kern, dim3(G), dim3(kT), 0, s, __VA_ARGS__);            \
-        VAG_HIP(hipGetLastError());                                                \
+#define BLAUNCH(n, kern, ...)                                                                                \
+    do {                                                                                                     \
+        hipLaunchKernelGGL(kern, dim3(krylov_shape(n).vec_blocks), dim3(kT), 0, s, __VA_ARGS__);             \
+        VAG_HIP(hipGetLastError());                                                                          \
     } while (0)
+#define BROWS(n, kern, ...) \
+    VAG_ROWS_LAUNCH(n, hipLaunchKernelGGL(kern<SPLIT>, dim3(ks.row_blocks), dim3(threads), 0, s, __VA_ARGS__))
 
 void launch_bcg_init(hipStream_t s, Sell<double> A, bool zero_x, int k0, const double *b, double *x, double *r,
                      double *rhat, double *parts) {
-    const int G = bcg_grid(A.n);
-    BLAUNCH(bcg_init_kernel, G, A, zero_x ? 1 : 0, k0, b, x, r, rhat, BcgParts{parts, G});
+    const BcgParts P = bcg_parts(parts, A.n);
+    if (zero_x)
+        BLAUNCH(A.n, bcg_init_zero_kernel, A.n, k0, b, x, r, rhat, P);
+    else
+        BLAUNCH(A.n, bcg_init_kernel, A, k0, b, x, r, rhat, P);
 }
-void launch_bcg_start(hipStream_t s, int32_t n, double *parts, PcgState *st, double rtol, int k0) {
-    BLAUNCH(bcg_start_kernel, 1, BcgParts{parts, bcg_grid(n)}, st, rtol, k0);
+void launch_bcg_start(hipStream_t s, int32_t n, double *parts, PcgState *st, double rtol, int k0, int *host_done) {
+    BLAUNCH(1, bcg_start_kernel, bcg_parts(parts, n), st, rtol, k0, host_done);
 }
 void launch_bcg_direction(hipStream_t s, int32_t n, int k, int k0, const double *r, double *p, const double *v,
                           double *parts, PcgState *st, bool update) {
-    const int G = bcg_grid(n);
-    BLAUNCH(bcg_direction_kernel, G, n, k, k0, r, p, v, BcgParts{parts, G}, st, update ? 1 : 0);
+    const BcgParts P = bcg_parts(parts, n);
+    BLAUNCH(n, bcg_direction_kernel, n, k, k0, r, p, v, P, st, update ? 1 : 0);
 }
 void launch_bcg_spmv_v(hipStream_t s, Sell<double> A, const double *phat, double *v, const double *rhat,
                        double *parts, const PcgState *st) {
-    const int G = bcg_grid(A.n);
-    BLAUNCH(bcg_spmv_dot_kernel, G, A, phat, v, rhat, parts + (size_t)2 * G, (double *)nullptr, st);
+    const BcgParts P = bcg_parts(parts, A.n);
+    BROWS(A.n, bcg_spmv_dot_kernel, A, phat, v, rhat, P, parts + (size_t)2 * P.G, (double *)nullptr, st);
 }
 void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, const double *phat, double *sv,
                   double *x, double *parts, PcgState *st) {
-    const int G = bcg_grid(n);
-    BLAUNCH(bcg_s_kernel, G, n, k, r, v, sv, BcgParts{parts, G}, st);
-    BLAUNCH(bcg_half_kernel, G, n, k, phat, x, BcgParts{parts, G}, st);
+    const BcgParts P = bcg_parts(parts, n);
+    BLAUNCH(n, bcg_s_kernel, n, k, r, v, sv, P, st);
+    BLAUNCH(n, bcg_half_kernel, n, k, phat, x, P, st);
 }
 void launch_bcg_spmv_t(hipStream_t s, Sell<double> A, const double *shat, double *t, const double *sv, double *parts,
                        const PcgState *st) {
-    const int G = bcg_grid(A.n);
-    BLAUNCH(bcg_spmv_dot_kernel, G, A, shat, t, sv, parts + (size_t)3 * G, parts + (size_t)4 * G, st);
+    const BcgParts P = bcg_parts(parts, A.n);
+    BROWS(A.n, bcg_spmv_dot_kernel, A, shat, t, sv, P, parts + (size_t)3 * P.G, parts + (size_t)4 * P.G, st);
 }
 void launch_bcg_update(hipStream_t s, int32_t n, int k, const double *phat, const double *shat, const double *sv,
                        const double *t, const double *rhat, double *x, double *r, double *parts, PcgState *st) {
-    const int G = bcg_grid(n);
-    BLAUNCH(bcg_update_kernel, G, n, k, phat, shat, sv, t, rhat, x, r, BcgParts{parts, G}, st);
+    const BcgParts P = bcg_parts(parts, n);
+    BLAUNCH(n, bcg_update_kernel, n, k, phat, shat, sv, t, rhat, x, r, P, st);
 }
 
 }  // namespace vag

@@ -32,10 +32,30 @@ struct OpMin {
     __device__ static double op(double a, double b) { return a < b ? a : b; }
 };
 
+// The value of lane i + O for the lanes a reduction tree asks for it (O = 32:
+// i < 32; O = 16: even rows of 16 lanes; O = 8, 4, 2, 1: inside a row of 16, 0
+// past its end), by lane swaps and row shifts of the vector unit: a shuffle
+// through LDS takes about three times as long.
+template <int O>
+__device__ inline int lane_down(int v) {
+    if constexpr (O == 32) return (int)__builtin_amdgcn_permlane32_swap(v, v, false, false)[1];
+    else if constexpr (O == 16) return (int)__builtin_amdgcn_permlane16_swap(v, v, false, false)[1];
+    else return __builtin_amdgcn_update_dpp(0, v, 0x100 | O, 0xf, 0xf, true);  // row_shl
+}
+template <int O>
+__device__ inline double lane_down(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)lane_down<O>((int)(uint32_t)u), hi = (uint32_t)lane_down<O>((int)(uint32_t)(u >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
 template <class Op>
 __device__ inline double wave_reduce(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = Op::op(v, __shfl_down(v, o, 64));
+    v = Op::op(v, lane_down<32>(v));
+    v = Op::op(v, lane_down<16>(v));
+    v = Op::op(v, lane_down<8>(v));
+    v = Op::op(v, lane_down<4>(v));
+    v = Op::op(v, lane_down<2>(v));
+    v = Op::op(v, lane_down<1>(v));
     return v;  // valid in lane 0
 }
 
@@ -79,6 +99,101 @@ __device__ inline double sum_parts(const double *parts, int nparts) {
     for (int i = threadIdx.x; i < nparts; i += NT) v[0] = Op::op(v[0], parts[i]);
     block_reduce<Op, 1, NT>(v);
     return v[0];
+}
+
+// Totals of NV arrays of nparts partials (p(k) names the k-th): one pass, one
+// block reduction.
+template <class Op, int NT, int NV, class P>
+__device__ inline void sum_parts_of(P p, int nparts, double (&v)[NV]) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = Op::id();
+    for (int i = threadIdx.x; i < nparts; i += NT)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) v[k] = Op::op(v[k], p(k)[i]);
+    block_reduce<Op, NV, NT>(v);
+}
+
+// The place of logical block b of xcd_block()'s numbering: the inverse map.
+__device__ inline unsigned xcd_unblock(unsigned b, unsigned nb) {
+    const unsigned q = nb >> 3, r = nb & 7, big = r * (q + 1);
+    const unsigned x = b < big ? b / (q + 1) : r + (b - big) / max(q, 1u);
+    return (b - (x * q + (x < r ? x : r))) * 8 + x;
+}
+
+// Totals of NV arrays of G slice sums (see KrylovShape), in every thread: the
+// 16 slices of 1024 rows one after the other, then the shuffle tree and the
+// wavefront totals as block_reduce and sum_parts combine blocks of 1024 rows.
+template <int NT, int NV, class P>
+__device__ inline void slice_sums(P p, int G, double (&v)[NV]) {
+    __shared__ double lds[NV][(kSplitMaxRows / kSliceRows + 1023) / 1024];
+    const int lane = threadIdx.x & 63, nc = (G + 1023) / 1024;
+    for (int c = threadIdx.x >> 6; c < nc; c += NT / 64) {
+        const int at = (c * 64 + lane) * 16;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            double t = 0.0;
+            if (at < G) {
+                const double2 *q = reinterpret_cast<const double2 *>(p(k) + at);
+                double2 w[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) w[j] = q[j];
+                t = w[0].x + w[0].y;
+#pragma unroll
+                for (int j = 1; j < 8; ++j) {
+                    t += w[j].x;
+                    t += w[j].y;
+                }
+            }
+            t = wave_reduce<OpSum>(t);
+            if (lane == 0) lds[k][c] = t;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        v[k] = lds[k][0];
+        for (int c = 1; c < nc; ++c) v[k] += lds[k][c];
+    }
+    __syncthreads();
+}
+
+// Totals of NV Krylov reductions, either form of their partials
+template <int NT, int NV, class P>
+__device__ inline void krylov_sums(bool slices, P p, int G, double (&v)[NV]) {
+    if (slices)
+        slice_sums<NT>(p, G, v);
+    else
+        sum_parts_of<OpSum, NT>(p, G, v);
+}
+
+// A thread's share v[k] of NV reductions as partials in p(k): the sum of the
+// wavefront's 64 consecutive rows as slice `slice`, or the block's sum (null:
+// not wanted).
+template <int NT, int NV, class P>
+__device__ inline void krylov_put(bool slices, P p, int slice, double (&v)[NV]) {
+    if (slices) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double t = wave_reduce<OpSum>(v[k]);
+            if ((threadIdx.x & 63) == 0 && p(k)) p(k)[slice] = t;
+        }
+    } else {
+        block_reduce<OpSum, NV, NT>(v);
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int k = 0; k < NV; ++k)
+                if (p(k)) p(k)[blockIdx.x] = v[k];
+    }
+}
+
+// Ends a Krylov solve (one thread calls it): the later kernels return at
+// once, and the host, which looks at its flag before it queues an iteration,
+// queues no more of them.
+__device__ inline void krylov_done(PcgState *st, int converged, double rr) {
+    st->done = 1;
+    st->converged = converged;
+    st->rr = rr;
+    if (st->host_done) __hip_atomic_store(st->host_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 inline unsigned reduce_grid(int64_t n_items, int threads) {

@@ -1,7 +1,9 @@
 // Row kernels on sliced ELL (64-row slices, column-major inside a slice).
 #pragma once
 
-#include "vag_internal.h"
+#include <utility>
+
+#include "reduce.h"
 
 namespace vag {
 
@@ -67,5 +69,151 @@ __device__ inline Acc sell_row_apply(const Sell<V> &A, int32_t row, F f) {
     if (A.dg) s[0] += (Acc)A.dg[row] * f(row);
     return s[0];
 }
+
+// A row with kChains lanes, for matrices too small to fill the device with one
+// lane per row: a wavefront holds 64 / kChains consecutive rows, lane group g
+// taking the entries g, g + kChains, ... in turn.  load() reads a lane's
+// columns and values of a batch (a row of up to 32 entries), then what
+// gather(j) returns for each column, so that the row waits for one chain of
+// loads, and that while the kernel forms the scalars it needs; sum() then
+// combines each value with use(gathered).  A lane past the row's end repeats
+// its first entry and adds nothing.  Called by whole wavefronts.
+constexpr int kSplitRows = 64 / kChains;  // rows per wavefront
+template <class V, class Gather>
+struct LaneRow {
+    static constexpr int B = 8;
+    using Raw = decltype(std::declval<Gather>()(0));
+    const Sell<V> &A;
+    const int32_t row;
+    Gather gather;
+    int64_t q, b1;
+    V v[B];
+    Raw x[B];
+    __device__ inline LaneRow(const Sell<V> &A_, int32_t row_, Gather g) : A(A_), row(row_), gather(g) {
+        const bool in = row < A.n;
+        const int32_t r = in ? row : 0;
+        b1 = A.ptr[(r >> 6) + 1];
+        q = A.ptr[r >> 6] + (r & 63) + (int64_t)((threadIdx.x & 63) / kSplitRows) * 64;
+        if (!in) b1 = q;  // no entries
+        load();
+    }
+    __device__ inline void load() {
+        if (q >= b1) return;
+        int32_t c[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int64_t p = q + b * kChains * 64;
+            c[b] = A.col[p < b1 ? p : q];
+            v[b] = A.val[p < b1 ? p : q];
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) x[b] = gather(c[b]);
+    }
+    // ACC accumulators a lane: 1, the chains of sell_row_apply, combined in its
+    // order (the same bits); 2, the order of the V-cycle kernels on small
+    // levels.  Valid in the wavefront's first kSplitRows lanes.
+    template <class Acc, int ACC, class Use>
+    __device__ inline Acc sum(Use use) {
+        Acc s[ACC];
+#pragma unroll
+        for (int k = 0; k < ACC; ++k) s[k] = 0;
+        while (q < b1) {
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const Acc t = s[b % ACC] + (Acc)v[b] * use(x[b]);
+                s[b % ACC] = q + b * kChains * 64 < b1 ? t : s[b % ACC];
+            }
+            q += B * kChains * 64;
+            load();
+        }
+        Acc t = s[0];
+        if constexpr (ACC == 2) {
+            t += s[1];
+            t += down<16>(t);
+            t += down<32>(t);
+        } else {
+            t += down<32>(t);
+            t += down<16>(t);
+        }
+        if (A.dg && row < A.n) t += (Acc)A.dg[row] * use(gather(row));
+        return t;
+    }
+    template <int O>
+    __device__ static inline double down(double t) {
+        return lane_down<O>(t);
+    }
+    template <int O>
+    __device__ static inline float down(float t) {
+        return __int_as_float(lane_down<O>(__float_as_int(t)));
+    }
+};
+template <class V, class Gather>
+__device__ inline LaneRow<V, Gather> lane_row(const Sell<V> &A, int32_t row, Gather g) {
+    return LaneRow<V, Gather>(A, row, g);
+}
+
+// The rows of a Krylov kernel of NT threads, one lane per row: row(i, (A f)_i,
+// v) adds the row's share of NV reductions to v, whose partials go to p(k).
+// slices: one pass (the grid covers the partials' rows); else a grid-stride
+// loop.  XCD: blocks numbered by xcd_block(); the partials are then those of a
+// launch over 1024-row blocks so numbered.
+template <bool XCD>
+__device__ inline int slice_place(int slice, int G) {
+    return XCD ? (int)(xcd_unblock((unsigned)slice >> 4, (unsigned)G >> 4) * 16 + (slice & 15)) : slice;
+}
+template <int NT, int NV, bool XCD, class V, class Acc, class F, class Row, class P>
+__device__ inline void krylov_rows(const Sell<V> &A, bool slices, int G, F f, Row row, P p) {
+    const int64_t blk = XCD ? xcd_block() : blockIdx.x;
+    double v[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = 0.0;
+    for (int64_t i = blk * NT + threadIdx.x; i < A.n; i += (int64_t)gridDim.x * NT)
+        row((int32_t)i, sell_row_apply<V, Acc>(A, (int32_t)i, f), v);
+    krylov_put<NT, NV>(slices, p, slice_place<XCD>((int)((blk * NT + threadIdx.x) >> 6), G), v);
+}
+// The same with kChains lanes per row and slices: the kernel has read its row
+// into r (lane_row of split_row) and gives the sum s to row.
+template <int NT, bool XCD>
+__device__ inline int32_t split_row() {
+    const int64_t blk = XCD ? xcd_block() : blockIdx.x;
+    return (int32_t)(blk * (NT / kChains) + (threadIdx.x >> 6) * kSplitRows + (threadIdx.x & 63) % kSplitRows);
+}
+template <int NT, int NV, bool XCD, class Acc, class Row, class P>
+__device__ inline void split_rows(int32_t n, int G, int32_t i, Acc s, Row row, P p) {
+    __shared__ double share[NV][NT / kChains];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double v[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = 0.0;
+    if (lane < kSplitRows) {
+        if (i < n) row(i, s, v);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) share[k][wave * kSplitRows + lane] = v[k];
+    }
+    __syncthreads();
+    if (wave < NT / kChains / 64) {  // whole wavefronts: one slice each
+#pragma unroll
+        for (int k = 0; k < NV; ++k) v[k] = share[k][threadIdx.x];
+        const int64_t blk = XCD ? xcd_block() : blockIdx.x;
+        krylov_put<NT, NV>(true, p, slice_place<XCD>((int)(blk * (NT / kChains / 64) + wave), G), v);
+    }
+}
+
+// Evaluates call (a launch of some kern<SPLIT, ...> over matrix rows, blocks of
+// `threads`) in the shape ks of n rows
+#define VAG_ROWS_LAUNCH(n, call)                \
+    do {                                        \
+        const KrylovShape ks = krylov_shape(n); \
+        if (ks.split) {                         \
+            constexpr bool SPLIT = true;        \
+            constexpr int threads = kSplitThreads; \
+            call;                               \
+        } else {                                \
+            constexpr bool SPLIT = false;       \
+            constexpr int threads = kKrylovThreads; \
+            call;                               \
+        }                                       \
+        VAG_HIP(hipGetLastError());             \
+    } while (0)
 
 }  // namespace vag

@@ -171,6 +171,7 @@ struct vag_handle {
     DBuf<int> coef_bad;  // [2]: first cell / fracture face with invalid coefficients
     // Krylov
     DBuf<double> x, r, z, p, q, parts, rparts, scal;
+    DBuf<double> r2, p2;  // second copies of r and p for the fused CG kernels (small systems)
     DBuf<PcgState> pcg;  // [0] the solve, [1] kernel timing (never done)
     // results
     DBuf<double> u_node, u_cell, u_frac, F_cell, F_cell_frac, F_frac, phi_cell, phi_frac, phi_node;
@@ -233,7 +234,13 @@ struct vag_handle {
     double *h_gm = nullptr;
     int h_gm_m = 0;
     int last_outer = 1, last_inner = 0;
+    // pinned: the state read back, and the flag a solve sets when it ends
+    static constexpr size_t kPcgBytes = 256;
     PcgState *h_pcg = nullptr;
+    int *h_done() { return reinterpret_cast<int *>(reinterpret_cast<char *>(h_pcg) + kPcgBytes / 2); }
+    // the host looks at the flag before it queues an iteration; where the host's
+    // launches are what a small system waits for, no iteration is queued past the end
+    bool krylov_ended() { return *static_cast<volatile int *>(h_done()) != 0; }
     double *h_scal = nullptr;
     hipEvent_t ev[8] = {};
 
@@ -258,7 +265,7 @@ struct vag_handle {
     double *c_next() { return cur ? cbuf0.p : cbuf1.p; }
 
     ~vag_handle() {
-        pinned_put(h_pcg, sizeof(PcgState));
+        pinned_put(h_pcg, kPcgBytes);
         pinned_put(h_scal, 16 * sizeof(double));
         pinned_put(h_cnt, kCntWords * sizeof(unsigned long long));
         pinned_put(h_gm, (3 * (size_t)(h_gm_m + 1) + 1) * sizeof(double));
@@ -456,7 +463,7 @@ AmgOptions amg_options(const vag_options &o) {
 void run_pcg(vag_handle *h) {
     hipStream_t s = h->stream;
     const int32_t n = h->S.nunk;
-    const PcgParts P{h->parts.p, pcg_grid(n)};
+    const PcgParts P = pcg_parts(h->parts.p, n);
     PcgState *st = h->pcg.p;
     const bool jacobi = h->opt.precond == VAG_PC_JACOBI;
     // the aggregation V-cycle takes D^-1 r from the update kernel and returns
@@ -464,43 +471,67 @@ void run_pcg(vag_handle *h) {
     const bool fused = !jacobi && h->amg.nlev > 1 && !h->amg.classical();
     const bool flexible = fused && h->amg.nonlinear();
     const Sell<double> A = h->Asell();
+    // several lanes per row: the kernels with the direction in the product and
+    // the update in the V-cycle's residual, which read the vectors of the last
+    // iteration while they write the next
+    const bool small = krylov_shape(n).split;
+    double *p = h->p.p, *p2 = nullptr, *r = h->r.p, *r2 = nullptr;
+    if (small) {
+        ensure(h->p2, (size_t)std::max(n, 1), h->tr);
+        ensure(h->r2, (size_t)std::max(n, 1), h->tr);
+        p2 = h->p2.p;
+        r2 = h->r2.p;
+    }
     const int max_iter = h->opt.max_iter;
     int k = 0, k0 = 0;
     double rtol = h->opt.rtol, bb = -1.0;
     for (int restart = 0;; ++restart) {
         if (restart == 0) {
-            launch_pcg_init(s, n, h->b.p, jacobi ? h->dinv.p : nullptr, h->x.p, h->r.p, h->z.p, P);
+            launch_pcg_init(s, n, h->b.p, jacobi ? h->dinv.p : nullptr, h->x.p, r, h->z.p, P);
         } else {
-            launch_pcg_init_warm(s, A, k0, h->b.p, h->x.p, h->r.p, jacobi ? h->dinv.p : nullptr, h->z.p, P);
+            launch_pcg_init_warm(s, A, k0, h->b.p, h->x.p, r, jacobi ? h->dinv.p : nullptr, h->z.p, P);
         }
         if (!jacobi) {
-            precond_apply(h, h->r.p, h->z.p, nullptr);
-            launch_pcg_dot_rz<double>(s, n, k0 - 1, h->r.p, h->z.p, P, nullptr);
+            precond_apply(h, r, h->z.p, nullptr);
+            launch_pcg_dot_rz<double>(s, n, k0 - 1, r, h->z.p, P, nullptr);
         }
-        launch_pcg_start(s, P, st, rtol, k0);
+        *h->h_done() = 0;
+        launch_pcg_start(s, P, st, rtol, k0, h->h_done());
         for (;;) {
             const int kend = std::min(k + h->opt.check_every, max_iter);
-            for (; k < kend; ++k) {
-                launch_pcg_direction<double>(s, n, k, k0, h->z.p, h->p.p, P, st, true, flexible);
-                launch_pcg_spmv<double, double>(s, A, h->p.p, h->q.p, P, st);
+            for (; k < kend && !h->krylov_ended(); ++k) {
+                if (small) {
+                    launch_pcg_direction_spmv(s, A, k, k0, h->z.p, p, p2, h->q.p, P, st, flexible);
+                    std::swap(p, p2);
+                    if (fused) {
+                        h->amg.update_resid(s, h->opt.precision == VAG_MIXED, k, h->x.p, r, r2, p, h->q.p, P, st);
+                        std::swap(r, r2);
+                        precond_apply(h, r, h->z.p, st, true, P.rz(k), flexible ? P.zq() : nullptr,
+                                      flexible ? h->q.p : nullptr);
+                        continue;
+                    }
+                } else {
+                    launch_pcg_direction<double>(s, n, k, k0, h->z.p, p, P, st, true, flexible);
+                    launch_pcg_spmv<double, double>(s, A, k, p, h->q.p, P, st);
+                }
                 if (jacobi) {
-                    launch_pcg_update(s, n, k, h->x.p, h->r.p, h->z.p, h->p.p, h->q.p, h->dinv.p, P, st);
+                    launch_pcg_update(s, n, k, h->x.p, r, h->z.p, p, h->q.p, h->dinv.p, P, st);
                 } else {
                     if (fused) {
                         // the update also writes the V-cycle's first iterate D^-1 r, and
                         // the V-cycle's last sweep the partials of r.z
-                        launch_pcg_update_xr<double>(s, n, k, h->x.p, h->r.p, h->p.p, h->q.p, P, st,
+                        launch_pcg_update_xr<double>(s, n, k, h->x.p, r, p, h->q.p, P, st,
                                                      h->amg.L[0]->dinv.p, h->amg.L[0]->xa.p);
-                        precond_apply(h, h->r.p, h->z.p, st, true, P.rz(k), flexible ? P.zq() : nullptr,
+                        precond_apply(h, r, h->z.p, st, true, P.rz(k), flexible ? P.zq() : nullptr,
                                       flexible ? h->q.p : nullptr);
                     } else {
-                        launch_pcg_update_xr<double>(s, n, k, h->x.p, h->r.p, h->p.p, h->q.p, P, st);
-                        precond_apply(h, h->r.p, h->z.p, st);
-                        launch_pcg_dot_rz<double>(s, n, k, h->r.p, h->z.p, P, st);
+                        launch_pcg_update_xr<double>(s, n, k, h->x.p, r, p, h->q.p, P, st);
+                        precond_apply(h, r, h->z.p, st);
+                        launch_pcg_dot_rz<double>(s, n, k, r, h->z.p, P, st);
                     }
                 }
             }
-            if (k >= max_iter) launch_pcg_direction<double>(s, n, k, k0, h->z.p, h->p.p, P, st, false);
+            if (k >= max_iter) launch_pcg_direction<double>(s, n, k, k0, h->z.p, p, P, st, false);
             VAG_HIP(hipMemcpyAsync(h->h_pcg, st, sizeof(PcgState), hipMemcpyDeviceToHost, s));
             VAG_HIP(hipStreamSynchronize(s));
             if (h->h_pcg->done || k >= max_iter) break;
@@ -533,7 +564,7 @@ void run_bicgstab(vag_handle *h) {
     const int32_t n = h->S.nunk;
     const size_t nv = (size_t)std::max(n, 1);
     for (auto *v : {&h->bcg_rhat, &h->bcg_s, &h->bcg_shat, &h->bcg_t}) ensure(*v, nv, h->tr);
-    ensure(h->bcg_parts, 8 * (size_t)kReduceBlocks, h->tr);
+    ensure(h->bcg_parts, 8 * (size_t)bcg_grid(n), h->tr);
     double *parts = h->bcg_parts.p;
     PcgState *st = h->pcg.p;
     const Sell<double> A = h->Asell();
@@ -542,10 +573,11 @@ void run_bicgstab(vag_handle *h) {
     double rtol = h->opt.rtol, bb = -1.0;
     for (int restart = 0;; ++restart) {
         launch_bcg_init(s, A, restart == 0, k0, h->b.p, h->x.p, h->r.p, h->bcg_rhat.p, parts);
-        launch_bcg_start(s, n, parts, st, rtol, k0);
+        *h->h_done() = 0;
+        launch_bcg_start(s, n, parts, st, rtol, k0, h->h_done());
         for (;;) {
             const int kend = std::min(k + h->opt.check_every, max_iter);
-            for (; k < kend; ++k) {
+            for (; k < kend && !h->krylov_ended(); ++k) {
                 launch_bcg_direction(s, n, k, k0, h->r.p, h->p.p, h->q.p, parts, st, true);
                 precond_apply(h, h->p.p, h->z.p, st);
                 launch_bcg_spmv_v(s, A, h->z.p, h->q.p, h->bcg_rhat.p, parts, st);
@@ -640,7 +672,7 @@ void run_gmres(vag_handle *h) {
 void run_mixed(vag_handle *h) {
     hipStream_t s = h->stream;
     const int32_t n = h->S.nunk;
-    const PcgParts P{h->parts.p, pcg_grid(n)};
+    const PcgParts P = pcg_parts(h->parts.p, n);
     PcgState *st = h->pcg.p;
     Tracker &tr = h->tr;
     for (auto *v : {&h->b32, &h->x32, &h->r32, &h->z32, &h->p32, &h->q32}) ensure(*v, (size_t)std::max(n, 1), tr);
@@ -684,14 +716,15 @@ void run_mixed(vag_handle *h) {
         launch_pcg_init_plain<float>(s, n, h->b32.p, h->x32.p, h->r32.p, P);
         h->amg.apply32(s, h->r32.p, h->z32.p, nullptr);
         launch_pcg_dot_rz<float>(s, n, -1, h->r32.p, h->z32.p, P, nullptr);
-        launch_pcg_start(s, P, st, h->opt.inner_rtol, 0);
+        *h->h_done() = 0;
+        launch_pcg_start(s, P, st, h->opt.inner_rtol, 0, h->h_done());
         const int budget = h->opt.max_iter - inner_total;
         int k = 0;
         for (;;) {
             const int kend = std::min(k + h->opt.check_every, budget);
-            for (; k < kend; ++k) {
+            for (; k < kend && !h->krylov_ended(); ++k) {
                 launch_pcg_direction<float>(s, n, k, 0, h->z32.p, h->p32.p, P, st, true);
-                launch_pcg_spmv<float, float>(s, A32, h->p32.p, h->q32.p, P, st);
+                launch_pcg_spmv<float, float>(s, A32, k, h->p32.p, h->q32.p, P, st);
                 launch_pcg_update_xr<float>(s, n, k, h->x32.p, h->r32.p, h->p32.p, h->q32.p, P, st);
                 h->amg.apply32(s, h->r32.p, h->z32.p, st);
                 launch_pcg_dot_rz<float>(s, n, k, h->r32.p, h->z32.p, P, st);
@@ -1082,7 +1115,7 @@ vag_status vag_create(const vag_mesh *mesh, const vag_fractures *frac, const vag
         h->bad.alloc(1, h->tr);
         h->coef_bad.alloc(2, h->tr);
         for (auto *v : {&h->x, &h->r, &h->z, &h->p, &h->q}) v->alloc(n, h->tr);
-        h->parts.alloc(6 * (size_t)kReduceBlocks, h->tr);
+        h->parts.alloc(PcgParts::kSlots * (size_t)pcg_grid(S.nunk), h->tr);
         h->rparts.alloc(4 * (size_t)kReduceBlocks, h->tr);
         h->scal.alloc(8, h->tr);
         h->pcg.alloc(2, h->tr);
@@ -1113,7 +1146,7 @@ vag_status vag_create(const vag_mesh *mesh, const vag_fractures *frac, const vag
         h->dt4.alloc(4, h->tr);
         h->tscan.alloc((size_t)nslice / 1024 + 2, h->tr);
         h->h_cnt = static_cast<unsigned long long *>(pinned_get(vag_handle::kCntWords * sizeof(unsigned long long)));
-        h->h_pcg = static_cast<PcgState *>(pinned_get(sizeof(PcgState)));
+        h->h_pcg = static_cast<PcgState *>(pinned_get(vag_handle::kPcgBytes));
         h->h_scal = static_cast<double *>(pinned_get(16 * sizeof(double)));
         for (auto &e : h->ev) VAG_HIP(hipEventCreate(&e));
         inputs.finish();
@@ -1894,11 +1927,11 @@ vag_status vag_benchmark_kernel(vag_handle *h, int kernel, int reps, double *ms)
             switch (kernel) {
                 case VAG_KERNEL_SPMV:  // the Krylov loop's SpMV (with its dot-product partials)
                     if (h->opt.precision == VAG_MIXED_IR && h->amg.have32)
-                        launch_pcg_spmv<float, float>(s, h->amg.L[0]->A32, h->x32.p, h->q32.p,
-                                                      PcgParts{h->parts.p, pcg_grid(S.nunk)}, h->pcg.p + 1);
+                        launch_pcg_spmv<float, float>(s, h->amg.L[0]->A32, 0, h->x32.p, h->q32.p,
+                                                      pcg_parts(h->parts.p, S.nunk), h->pcg.p + 1);
                     else
-                        launch_pcg_spmv<double, double>(s, h->Asell(), h->x.p, h->q.p,
-                                                        PcgParts{h->parts.p, pcg_grid(S.nunk)}, h->pcg.p + 1);
+                        launch_pcg_spmv<double, double>(s, h->Asell(), 0, h->x.p, h->q.p,
+                                                        pcg_parts(h->parts.p, S.nunk), h->pcg.p + 1);
                     break;
                 case VAG_KERNEL_TRANSPORT_STEP:  // reads the current state, writes the spare buffer;
                     // the sweep direction alternates as in vag_transport
@@ -2100,7 +2133,7 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
     b += 3000.0 * Nf;                                               // fracture-face groups
     b += 56 * Nc + 24 * Nf + 16 * Nn;                               // rock, fracture, boundary data
     b += 376 * Nc + 304 * Nf + 8 * S + 16 * Nx;                     // local matrices, system
-    b += 40 * Nx + 64.0 * 1024;                                     // Krylov vectors and partials
+    b += 42 * Nx + 16 * std::min(Nx, 131072.0) + 64.0 * 1024;       // Krylov vectors and partials
     b += 88 * Nc + 56 * Nf + 16 * Nn;                               // pressures, fluxes, porous volumes
     if (o.alpha_rule == 1) b += 8 * Nn;                             // largest permeability per node
     const double nrow = Nn + Nc + Nf, tst = 2.0 * (8 * Nc + 6 * Nf) + 64.0 * 16;

@@ -92,7 +92,26 @@ __host__ __device__ constexpr int sym5(int i, int j) {
 constexpr int kSliceRows = 64;      // SELL slice height = one wavefront
 constexpr int kReduceBlocks = 512;  // fixed grid of the deterministic reductions
 constexpr int kReduceThreads = 256;
-constexpr int kKrylovThreads = 1024;  // block size of the Krylov kernels (and of their partials' producers)
+constexpr int kKrylovThreads = 1024;
+// Launch shape of the Krylov kernels on n rows, and of the partials of their
+// reductions.  Up to kSplitMaxRows the kernels over matrix rows take 4 lanes
+// per row, 64 rows a block of kSplitThreads, and a partial is the sum over one
+// 64-row slice: G of them (16 per 1024 rows, zeros past the last), summed by
+// the consumer in the order of a reduction over blocks of 1024 rows.  Above, at
+// most kReduceBlocks blocks of 1024 rows stride over the rows and write a
+// partial each.  So a sum has the same bits whichever kernels ran.
+// The line: below it one lane per row leaves most of the 256 CUs without a
+// block and every kernel waits for one row's chain of loads (product 10 us at
+// 1089 and at 45 k rows; 6.3 and 10.3 us with 4 lanes, the direction included);
+// from 262 k rows the product runs at the last-level cache's 5 TB/s either way,
+// and fusing would gather two vectors instead of one.
+struct KrylovShape {
+    int G;           // partials
+    bool split;      // slice partials, 4 lanes per row
+    int row_blocks;  // in the kernels over matrix rows
+    int vec_blocks;  // of kKrylovThreads, in the kernels over vectors
+};
+KrylovShape krylov_shape(int64_t n);
 
 // ---------------------------------------------------------------------------
 // device buffer
@@ -300,20 +319,23 @@ void launch_sell_pack(hipStream_t s, int32_t n, const int64_t *ptr, const int32_
                       uint16_t *col16, int32_t *cbase);
 
 struct PcgState {       // device-resident scalars of a Krylov solve
-    double tol2, bnorm2, rr, pad;
+    double tol2, bnorm2, rr;
+    int *host_done;     // pinned host flag set with `done`, or null
     int iter, done, converged, pad2;
 };
 
-// Partials of the CG scalars, double-buffered by iteration parity:
-// pq at [0, G), rz[p] at [(1+p) G, (2+p) G), rr[p] at [(3+p) G, (4+p) G).
+// The block partials of the CG scalars, G each, pq, rz and rr double-buffered
+// by iteration parity.
 struct PcgParts {
     double *base;
     int G;
-    __host__ __device__ double *pq() const { return base; }
-    __host__ __device__ double *rz(int k) const { return base + (size_t)(1 + (k & 1)) * G; }
-    __host__ __device__ double *rr(int k) const { return base + (size_t)(3 + (k & 1)) * G; }
+    bool slices;  // partials of slices (KrylovShape::split)
+    __host__ __device__ double *pq(int k) const { return base + (size_t)(k & 1) * G; }
+    __host__ __device__ double *rz(int k) const { return base + (size_t)(2 + (k & 1)) * G; }
+    __host__ __device__ double *rr(int k) const { return base + (size_t)(4 + (k & 1)) * G; }
     // flexible CG: z_{k+1} . q_k (written by the preconditioner's last sweep)
-    __host__ __device__ double *zq() const { return base + (size_t)5 * G; }
+    __host__ __device__ double *zq() const { return base + (size_t)6 * G; }
+    static constexpr int kSlots = 7;
 };
 
 // assembly
@@ -391,7 +413,7 @@ void launch_diag_inv(hipStream_t s, int32_t n, const int32_t *diag_pos, const do
 int bcg_grid(int64_t n);
 void launch_bcg_init(hipStream_t s, Sell<double> A, bool zero_x, int k0, const double *b, double *x, double *r,
                      double *rhat, double *parts);
-void launch_bcg_start(hipStream_t s, int32_t n, double *parts, PcgState *st, double rtol, int k0);
+void launch_bcg_start(hipStream_t s, int32_t n, double *parts, PcgState *st, double rtol, int k0, int *host_done);
 void launch_bcg_direction(hipStream_t s, int32_t n, int k, int k0, const double *r, double *p, const double *v,
                           double *parts, PcgState *st, bool update);
 void launch_bcg_spmv_v(hipStream_t s, Sell<double> A, const double *phat, double *v, const double *rhat,
@@ -405,17 +427,17 @@ void launch_bcg_update(hipStream_t s, int32_t n, int k, const double *phat, cons
 
 // Krylov
 int pcg_grid(int64_t n);
+PcgParts pcg_parts(double *base, int64_t n);
 void launch_fill(hipStream_t s, int64_t n, double v, double *x);
 void launch_copy(hipStream_t s, int64_t n, const double *src, double *dst);
 void launch_jacobi(hipStream_t s, int64_t n, const double *dinv, const double *r, double *z);
-void launch_spmv(hipStream_t s, Sell<double> A, const double *x, double *y);
 void launch_residual_norm(hipStream_t s, Sell<double> A, const double *x, const double *b, double *r,
                           double *parts, double *out2 /* [2]: ||b-Ax||^2, ||b||^2 */);
 // x = 0, r = b, parts rr(-1) = b.b; with dinv also z = D^-1 b, p = z and parts rz(-1)
 void launch_pcg_init(hipStream_t s, int32_t n, const double *b, const double *dinv, double *x, double *r,
                      double *z, PcgParts P);
 // one block: tolerance rtol^2 rr(k0-1), state reset to iteration k0
-void launch_pcg_start(hipStream_t s, PcgParts P, PcgState *st, double rtol, int k0);
+void launch_pcg_start(hipStream_t s, PcgParts P, PcgState *st, double rtol, int k0, int *host_done);
 // warm start at iteration k0 from the current x (see krylov.hip)
 void launch_pcg_init_warm(hipStream_t s, Sell<double> A, int k0, const double *b, const double *x, double *r,
                           const double *dinv, double *z, PcgParts P);
@@ -425,9 +447,14 @@ void launch_pcg_init_warm(hipStream_t s, Sell<double> A, int k0, const double *b
 template <class T>
 void launch_pcg_direction(hipStream_t s, int32_t n, int k, int k0, const T *z, T *p, PcgParts P, PcgState *st,
                           bool update, bool flexible = false);
+// direction and product in one kernel, for the shapes with several lanes per
+// row: p_out = z + beta p_in (formed again at every gathered entry), q = A
+// p_out, partials of p.q
+void launch_pcg_direction_spmv(hipStream_t s, Sell<double> A, int k, int k0, const double *z, const double *p_in,
+                               double *p_out, double *q, PcgParts P, PcgState *st, bool flexible);
 // q = A p, partials of p.q
 template <class V, class T>
-void launch_pcg_spmv(hipStream_t s, Sell<V> A, const T *p, T *q, PcgParts P, const PcgState *st);
+void launch_pcg_spmv(hipStream_t s, Sell<V> A, int k, const T *p, T *q, PcgParts P, const PcgState *st);
 // alpha = rz(k-1) / p.q; x += alpha p; r -= alpha q; Jacobi: z = D^-1 r and partials rz(k), rr(k)
 void launch_pcg_update(hipStream_t s, int32_t n, int k, double *x, double *r, double *z, const double *p,
                        const double *q, const double *dinv, PcgParts P, PcgState *st);

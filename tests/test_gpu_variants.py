@@ -107,3 +107,30 @@ def test_noalloc_step_counts(dims):
     for k, v in vag.to_numpy(h.pressure()).items():
         assert np.array_equal(v, u[k]), k
     h.close()
+
+
+@pytest.mark.parametrize("dims", [(3, 3, 3), (8, 4, 2), (16, 15, 3), (51, 48, 50), (53, 49, 50)])
+@pytest.mark.parametrize("opt", ["cg", "cg mixed", "cg V", "jacobi", "bicgstab"])
+def test_krylov_rows_per_block(dims, opt):
+    """Fewer unknowns than a wavefront's rows, ragged last slices, and both
+    sides of 131072 unknowns, where rows go from four lanes to one; hierarchies
+    of several levels, K-cycles and V-cycles.  The systems' condition numbers
+    are below 50^2 times the contrast of 10^3: rtol 1e-12 leaves 1e-6 of max
+    |u|.  A second solve gives the same bits."""
+    from paper_1602_03641_amd import vag
+    kw = {"cg": dict(precond=vag.VAG_PC_AMG, amg_coarse_size=12),
+          "cg mixed": dict(precond=vag.VAG_PC_AMG, amg_coarse_size=12, precision=vag.VAG_MIXED),
+          "cg V": dict(precond=vag.VAG_PC_AMG, amg_coarse_size=12, amg_kcycle=0),
+          "jacobi": dict(precond=vag.VAG_PC_JACOBI),
+          "bicgstab": dict(precond=vag.VAG_PC_AMG, amg_coarse_size=12, krylov=vag.VAG_BICGSTAB)}[opt]
+    p = synth.random_problem(dims, 27, n_patches=5, n_steps=0, ratios=(1e2, 1e3))
+    od = oracle.solve_darcy(p, rtol=1e-13)
+    h, info = _handle(p, rtol=1e-12, eliminate_frac_faces=0, **kw)
+    assert info["status"] == 0 and info["n_unknowns"] == oracle.system(p)[0].shape[0]
+    u = vag.to_numpy(h.pressure())
+    for k in ("u_node", "u_frac"):
+        assert np.abs(u[k] - od[k]).max(initial=0.0) <= 1e-6 * np.abs(od["u_node"]).max(), k
+    h.solve_pressure()
+    for k, v in vag.to_numpy(h.pressure()).items():
+        assert np.array_equal(v, u[k]), k
+    h.close()
