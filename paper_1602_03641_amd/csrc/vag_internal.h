@@ -105,6 +105,9 @@ constexpr int kKrylovThreads = 1024;
 // 1089 and at 45 k rows; 6.3 and 10.3 us with 4 lanes, the direction included);
 // from 262 k rows the product runs at the last-level cache's 5 TB/s either way,
 // and fusing would gather two vectors instead of one.
+constexpr int64_t kSplitMaxRows = 131072;
+constexpr int kSplitThreads = 256;
+
 struct KrylovShape {
     int G;           // partials
     bool split;      // slice partials, 4 lanes per row
