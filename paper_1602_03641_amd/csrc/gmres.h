@@ -18,16 +18,16 @@ namespace vag {
 int gmres_grid(int64_t n);
 template <class V, class T>
 void launch_gm_spmv(hipStream_t s, Sell<V> A, const T *x, T *y);
-// w -= V h with h = V^T w (k basis vectors), then partials of ||w||^2 in nparts
+// CGS2 against k basis vectors: w -= V h1 with h1 = V^T w, w -= V h2 with h2 =
+// V^T w, then partials of ||w||^2 in nparts
 template <class T>
 void launch_gm_orthogonalize(hipStream_t s, int32_t n, int k, const T *V, int64_t ld, T *w, double *parts,
-                             double *h, double *nparts);
+                             double *h1, double *h2, double *nparts);
 template <class T>
 void launch_gm_normalize(hipStream_t s, int32_t n, const double *nparts, const T *w, T *out, double *hn);
+// x += V y
 template <class T>
-void launch_gm_combine(hipStream_t s, int32_t n, int k, const T *V, int64_t ld, const double *y, T *t);
-template <class T>
-void launch_gm_add(hipStream_t s, int32_t n, const T *z, T *x);
+void launch_gm_combine(hipStream_t s, int32_t n, int k, const T *V, int64_t ld, const double *y, T *x);
 template <class V, class T>
 void launch_gm_residual(hipStream_t s, Sell<V> A, const T *b, const T *x, T *r, double *nparts);
 
@@ -36,7 +36,7 @@ template <class T>
 struct GmresWork {
     T *V = nullptr;          // (m+1) * n basis
     T *Z = nullptr;          // m * n preconditioned basis vectors
-    T *w = nullptr, *t = nullptr;
+    T *w = nullptr;
     double *parts = nullptr;  // (m+1) * gmres_grid(n)
     double *nparts = nullptr; // gmres_grid(n)
     double *hd = nullptr;     // device: h1[m+1], h2[m+1], hn, y[m+1]
@@ -82,8 +82,7 @@ GmresResult gmres_solve(hipStream_t s, Sell<V> A, const T *b, T *x, double tol, 
             T *zj = W.Z + (int64_t)j * ld;
             prec(vj, zj);
             launch_gm_spmv<V, T>(s, A, zj, W.w);
-            launch_gm_orthogonalize<T>(s, n, j + 1, W.V, ld, W.w, W.parts, h1, W.nparts);
-            launch_gm_orthogonalize<T>(s, n, j + 1, W.V, ld, W.w, W.parts, h2, W.nparts);
+            launch_gm_orthogonalize<T>(s, n, j + 1, W.V, ld, W.w, W.parts, h1, h2, W.nparts);
             launch_gm_normalize<T>(s, n, W.nparts, W.w, W.V + (int64_t)(j + 1) * ld, hn);
             VAG_HIP(hipMemcpyAsync(W.hh, W.hd, (2 * (m + 1) + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
             VAG_HIP(hipStreamSynchronize(s));
@@ -116,8 +115,7 @@ GmresResult gmres_solve(hipStream_t s, Sell<V> A, const T *b, T *x, double tol, 
             Y[i] = v / R[(size_t)i * (m + 1) + i];
         }
         VAG_HIP(hipMemcpyAsync(yd, Y, j * sizeof(double), hipMemcpyHostToDevice, s));
-        launch_gm_combine<T>(s, n, j, W.Z, ld, yd, W.t);
-        launch_gm_add<T>(s, n, W.t, x);
+        launch_gm_combine<T>(s, n, j, W.Z, ld, yd, x);
         // true residual; restart from it
         launch_gm_residual<V, T>(s, A, b, x, W.w, W.nparts);
         launch_gm_normalize<T>(s, n, W.nparts, W.w, W.V, hn);

@@ -227,8 +227,8 @@ struct vag_handle {
     DBuf<int> ilu_bad;       // 1 + natural row of a zero pivot, else 0
     DBuf<float> b32, x32, r32, z32, p32, q32;  // inner single-precision solve (VAG_MIXED)
     // GMRES(m) work: FP64 basis (VAG_FP64 / VAG_MIXED) or FP32 basis (inner solves of VAG_MIXED_IR)
-    DBuf<double> gmV, gmZ, gmw, gmt, gmparts, gmnparts, gmhd;
-    DBuf<float> gmV32, gmZ32, gmw32, gmt32;
+    DBuf<double> gmV, gmZ, gmw, gmparts, gmnparts, gmhd;
+    DBuf<float> gmV32, gmZ32, gmw32;
     // BiCGStab work (p, phat, v are p, z, q)
     DBuf<double> bcg_rhat, bcg_s, bcg_shat, bcg_t, bcg_parts;
     double *h_gm = nullptr;
@@ -614,13 +614,12 @@ void run_bicgstab(vag_handle *h) {
 
 // Scratch of GMRES(m) on n unknowns with vectors of type T.
 template <class T>
-GmresWork<T> gmres_work(vag_handle *h, int32_t n, DBuf<T> &V, DBuf<T> &Z, DBuf<T> &w, DBuf<T> &t) {
+GmresWork<T> gmres_work(vag_handle *h, int32_t n, DBuf<T> &V, DBuf<T> &Z, DBuf<T> &w) {
     const int m = h->opt.gmres_restart;
     Tracker &tr = h->tr;
     ensure(V, (size_t)(m + 1) * (size_t)std::max(n, 1), tr);
     ensure(Z, (size_t)m * (size_t)std::max(n, 1), tr);
     ensure(w, (size_t)std::max(n, 1), tr);
-    ensure(t, (size_t)std::max(n, 1), tr);
     ensure(h->gmparts, (size_t)(m + 1) * gmres_grid(n), tr);
     ensure(h->gmnparts, (size_t)gmres_grid(n), tr);
     ensure(h->gmhd, (size_t)3 * (m + 1) + 1, tr);
@@ -634,7 +633,6 @@ GmresWork<T> gmres_work(vag_handle *h, int32_t n, DBuf<T> &V, DBuf<T> &Z, DBuf<T
     W.V = V.p;
     W.Z = Z.p;
     W.w = w.p;
-    W.t = t.p;
     W.parts = h->gmparts.p;
     W.nparts = h->gmnparts.p;
     W.hd = h->gmhd.p;
@@ -647,7 +645,7 @@ GmresWork<T> gmres_work(vag_handle *h, int32_t n, DBuf<T> &V, DBuf<T> &Z, DBuf<T
 void run_gmres(vag_handle *h) {
     hipStream_t s = h->stream;
     const int32_t n = h->S.nunk;
-    const GmresWork<double> W = gmres_work<double>(h, n, h->gmV, h->gmZ, h->gmw, h->gmt);
+    const GmresWork<double> W = gmres_work<double>(h, n, h->gmV, h->gmZ, h->gmw);
     launch_fill(s, n, 0.0, h->x.p);
     launch_residual_norm(s, h->Asell(), h->x.p, h->b.p, h->r.p, h->rparts.p, h->scal.p);
     VAG_HIP(hipMemcpyAsync(h->h_scal, h->scal.p, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -698,7 +696,7 @@ void run_mixed(vag_handle *h) {
             // The true FP32 residual of an FP32 iterate cannot fall much below
             // ||A|| ||x|| eps_32 / ||b|| (about 1e-2 at contrast 1e6), so restarts
             // from it would stall; the FP64 refinement takes over instead.
-            const GmresWork<float> W = gmres_work<float>(h, n, h->gmV32, h->gmZ32, h->gmw32, h->gmt32);
+            const GmresWork<float> W = gmres_work<float>(h, n, h->gmV32, h->gmZ32, h->gmw32);
             VAG_HIP(hipMemsetAsync(h->x32.p, 0, (size_t)n * sizeof(float), s));
             const int cycle = std::min(h->opt.gmres_restart, h->opt.max_iter - inner_total);
             const GmresResult R = gmres_solve<float, float>(
@@ -2151,9 +2149,9 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
         b += 1.125 * amg + 12.0 * d * d + 1024.0 * d + 0.5 * 1024 * 1024;
     }
     if (o.precond == VAG_PC_BJILU0) b += 14 * nnz + 28 * Nx;        // factor entries, rows, schedules
-    if (o.krylov == VAG_GMRES) {  // flexible GMRES: m + 1 basis vectors, m preconditioned ones, two work vectors
+    if (o.krylov == VAG_GMRES) {  // flexible GMRES: m + 1 basis vectors, m preconditioned ones, a work vector
         const double m = o.gmres_restart > 0 ? o.gmres_restart : 100;
-        b += (2 * m + 3) * Nx * (o.precision == VAG_MIXED_IR ? 4.0 : 8.0) + 8 * (m + 1) * Nx / 256;
+        b += (2 * m + 2) * Nx * (o.precision == VAG_MIXED_IR ? 4.0 : 8.0) + 8 * (m + 1) * Nx / 256;
     }
     return (size_t)(1.15 * b) + ((size_t)1 << 20);
 }

@@ -134,3 +134,24 @@ def test_krylov_rows_per_block(dims, opt):
     for k, v in vag.to_numpy(h.pressure()).items():
         assert np.array_equal(v, u[k]), k
     h.close()
+
+
+@pytest.mark.parametrize("restart", [5, 8, 9, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("dims,opt", [((16, 15, 3), "jacobi"), ((53, 49, 50), "mixed"), ((16, 15, 3), "mixed_ir")])
+def test_gmres_basis_sizes(dims, opt, restart):
+    """Cycle lengths on both sides of 8, 16 and 32 basis vectors, which the
+    orthogonalisation holds at once, and of two such sets: the pressures of the
+    oracle.  Condition numbers below 50^2 times the contrast of 10: rtol 1e-11
+    leaves 1e-6 of max |u|."""
+    from paper_1602_03641_amd import vag
+    kw = {"jacobi": dict(precond=vag.VAG_PC_JACOBI), "mixed": dict(precond=vag.VAG_PC_AMG, precision=vag.VAG_MIXED),
+          "mixed_ir": dict(precond=vag.VAG_PC_AMG, precision=vag.VAG_MIXED_IR, inner_rtol=1e-6)}[opt]
+    p = synth.random_problem(dims, 29, n_patches=3, n_steps=0, ratios=(1e1, 1e1))
+    od = oracle.solve_darcy(p, rtol=1e-13)
+    h, info = _handle(p, rtol=1e-11, krylov=vag.VAG_GMRES, gmres_restart=restart, **kw)
+    assert info["status"] == 0
+    print("iterations", info["iterations"])
+    u = vag.to_numpy(h.pressure())
+    for k in ("u_node", "u_frac"):
+        assert np.abs(u[k] - od[k]).max(initial=0.0) <= 1e-6 * np.abs(od["u_node"]).max(), k
+    h.close()
