@@ -1164,15 +1164,21 @@ __global__ __launch_bounds__(kKrylovThreads) void vc_sweep_rz_kernel(Sell<V> A, 
                                                                      double *__restrict__ zq,
                                                                      const X *__restrict__ qv, const PcgState *st) {
     if (st && st->done) return;
-    krylov_rows<kKrylovThreads, 2, true, V, X>(
-        A, false, 0, [&](int32_t j) { return y[j]; },
-        [&](int32_t i, X s, double *v) {
-            const X o = y[i] + dinv[i] * (b[i] - s);
-            out[i] = o;
-            v[0] += (double)b[i] * (double)o;
-            if (zq) v[1] += (double)qv[i] * (double)o;
-        },
-        [&](int k) { return k ? zq : rz; });
+    double v[2] = {0.0, 0.0};
+    for (int64_t i = (int64_t)xcd_block() * kKrylovThreads + threadIdx.x; i < A.n;
+         i += (int64_t)gridDim.x * kKrylovThreads) {
+        const X yi = y[i], di = dinv[i], bi = b[i];  // ahead of the row, not a second wait after it
+        const X s = sell_row_apply<V, X>(A, (int32_t)i, [&](int32_t j) { return y[j]; });
+        const X o = yi + di * (bi - s);
+        out[i] = o;
+        v[0] += (double)bi * (double)o;
+        if (zq) v[1] += (double)qv[i] * (double)o;
+    }
+    block_reduce<OpSum, 2, kKrylovThreads>(v);
+    if (threadIdx.x == 0) {
+        rz[blockIdx.x] = v[0];
+        if (zq) zq[blockIdx.x] = v[1];
+    }
 }
 // prolongation and sweep in one pass (small levels): y = x + P e with
 // x = D^-1 b formed on the fly, out = y + D^-1 (b - A y)

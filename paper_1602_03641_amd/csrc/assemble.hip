@@ -24,7 +24,7 @@
 //   A5[nf][25]  fracture 5x5 over (sigma, input nodes 0..3)
 #include <climits>
 
-#include "vag_internal.h"
+#include "reduce.h"
 
 namespace vag {
 
@@ -232,18 +232,6 @@ __device__ inline int64_t sell_find(const AsmArgs &g, int32_t r, int32_t c) {
     return -1;
 }
 
-// Adds v to (r, column unknown c) of the system; c < 0: Dirichlet column of
-// node `node`, to the right-hand side; c >= nsys: an eliminated face, held
-// by its group block instead (nothing to do).
-__device__ inline void add_sys(const AsmArgs &g, int32_t r, int32_t c, int32_t node, double v, double &rhs) {
-    if (c < 0) {
-        rhs -= v * g.p_bar[node];
-    } else if (c < g.nsys) {
-        const int64_t q = sell_find(g, r, c);
-        if (q >= 0) g.A[q] += v; else atomicMin(g.bad, INT_MIN);
-    }
-}
-
 // The coefficients the scheme takes (§2: Lambda_m symmetric positive
 // definite; d_f and Lambda_f positive): a cell's packed tensor passes when
 // its leading principal minors are positive and every entry is finite, a
@@ -319,17 +307,43 @@ __global__ __launch_bounds__(128) void node_pos_kernel(AsmArgs g, uint16_t *__re
     }
 }
 
+// Slots of a fracture block's columns (the face, then its nodes 0..3) in the
+// row of each node_frac entry, likewise: frac_pos[8 q + k], 0xffff for a
+// Dirichlet node and for an eliminated face.
+__global__ __launch_bounds__(128) void frac_pos_kernel(AsmArgs g, int64_t n, uint16_t *__restrict__ frac_pos) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const int32_t q = (int32_t)(t >> 3), k = (int32_t)(t & 7), e = g.node_frac[q], sig = e >> 2;
+    const int32_t r = g.node_unk[g.frac_nodes[4 * (int64_t)sig + (e & 3)]];
+    uint16_t slot = 0xffff;
+    if (k < 5 && r >= 0) {
+        const int32_t c = k ? g.node_unk[g.frac_nodes[4 * (int64_t)sig + k - 1]] : g.frac_unk[sig];
+        if (c >= 0 && c < g.nsys) {
+            const int64_t p = sell_find(g, r, c), sl = (p - (g.sell_ptr[r >> 6] + (r & 63))) >> 6;
+            if (p < 0 || sl >= 0xffff) atomicMin(g.bad, INT_MIN);
+            else slot = (uint16_t)sl;
+        }
+    }
+    frac_pos[t] = slot;
+}
+
 // One thread per node row.  The row's first kAccSlots slots accumulate in
 // LDS (the thread's own column of acc) and are stored once at the end: a
 // read-modify-write of the row in global memory would make every addition
 // wait for the previous one, since the compiler cannot tell the slots apart.
 // Slots beyond kAccSlots (rows next to eliminated fracture groups) are added
-// in global memory, which the caller has zeroed.
-constexpr int kAccSlots = 32;
+// in global memory, which the caller has zeroed.  The wavefronts are few (32 KB
+// of LDS per block: 10 on a CU), so the time is each one's chain of loads; what
+// the chain held beyond the cells' data (searches of the fracture columns, the
+// Dirichlet columns' p_bar one by one, lists' lines fetched again) is gone:
+// 64^3 cells 309 -> 94 us, 128^3 1134 -> 581, 192^3 4700 -> 1960 (its bytes at
+// 5 TB/s: 35, 270 and 900).
+constexpr int kAccSlots = 31;
+constexpr int kAsmCells = 2;  // cells whose loads are in flight together
 __global__ __launch_bounds__(128) void asm_node_rows_kernel(AsmArgs g) {
-    __shared__ double acc[kAccSlots][128];
+    __shared__ double acc[kAccSlots + 1][128];
     const int tid = threadIdx.x;
-    const int32_t r = blockIdx.x * blockDim.x + tid;
+    const int32_t r = (int32_t)xcd_block() * 128 + tid;
     if (r >= g.nfree) return;
     const int32_t s = g.unk_node[r];
     const int64_t base = g.sell_ptr[r >> 6] + (r & 63);
@@ -340,146 +354,248 @@ __global__ __launch_bounds__(128) void asm_node_rows_kernel(AsmArgs g) {
         if (k < kAccSlots) acc[k][tid] += v;
         else g.A[base + 64 * (int64_t)k] += v;
     };
-    // column unknown c (node `node` or a face; c < 0: Dirichlet node; c >= nsys:
-    // an eliminated face, held by its group block)
-    auto put_col = [&](int32_t c, int32_t node, double v) {
-        if (c < 0) {
-            rhs -= v * g.p_bar[node];
-        } else if (c < g.nsys) {
-            const int64_t p = sell_find(g, r, c);
-            if (p >= 0) put((int)((p - base) >> 6), v);
-            else atomicMin(g.bad, INT_MIN);
-        }
+    const bool kept = g.nsys > g.nfree;  // some faces have rows and columns
+    auto put_face = [&](int32_t c, double v) {
+        const int64_t p = sell_find(g, r, c);
+        if (p >= 0) put((int)((p - base) >> 6), v);
+        else atomicMin(g.bad, INT_MIN);
     };
     // cells of the node: row a of M_K
-    for (int32_t q = g.node_cell_ptr[s]; q < g.node_cell_ptr[s + 1]; ++q) {
-        const int32_t K = g.node_cell[q] >> 3;
-        const int a = g.node_cell[q] & 7;
-        const double inv = 1.0 / g.AKK[K];
-        const double ra = g.rK[(int64_t)a * g.nc + K];
-        // the cell's loads first, all in flight together: an addition to a
-        // slot beyond kAccSlots stores to the row in global memory, which the
-        // compiler would not move a later load past
-        double v[8];
+    const int32_t q1 = g.node_cell_ptr[s + 1];
+    for (int32_t qb = g.node_cell_ptr[s]; qb < q1; qb += 8) {
+        // eight entries of the node's lists at once: neighbouring lanes read 128
+        // bytes apart, and a line would have left the L1 before its next entry
+        int32_t e8[8];
+        uint4 p8[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = g.aK[(int64_t)sym8(a, c) * g.nc + K] - ra * g.rK[(int64_t)c * g.nc + K] * inv;
-        const uint4 pos = *reinterpret_cast<const uint4 *>(g.node_pos + 8 * (int64_t)q);  // 8 slots, 16 bytes
-        const uint32_t pw[4] = {pos.x, pos.y, pos.z, pos.w};
+        for (int j = 0; j < 8; ++j) e8[j] = g.node_cell[min(qb + j, q1 - 1)];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const uint16_t k = (uint16_t)(pw[c >> 1] >> (16 * (c & 1)));
-            if (k != 0xffff) put(k, v[c]);
-            else rhs -= v[c] * g.p_bar[g.hex8[8 * (int64_t)K + c]];  // Dirichlet column
-        }
-        const unsigned mask = g.fmask[K];
-        for (int f = 0; f < 6; ++f) {
-            if (!((mask >> f) & 1u)) continue;
-            const int32_t sig = g.cell_frac[6 * (int64_t)K + f];
-            const int sd = g.frac_cell[2 * (int64_t)sig] == K ? 0 : 1;
-            const double *o = g.fside + (2 * (int64_t)sig + sd) * 6;
-            const int i = face_vertex(f, a);
-            const double v = (i >= 0 ? o[1 + i] : 0.0) - ra * o[5] * inv;
-            put_col(g.frac_unk[sig], -1, v);
+        for (int j = 0; j < 8; ++j)  // 8 slots each
+            p8[j] = *reinterpret_cast<const uint4 *>(g.node_pos + 8 * (int64_t)min(qb + j, q1 - 1));
+#pragma unroll
+        for (int jb = 0; jb < 8; jb += kAsmCells) {
+            const int32_t q0 = qb + jb;
+            if (q0 >= q1) break;
+            // the loads of kAsmCells cells first, all in flight together (past the
+            // node's last cell that one's again): an addition to a slot beyond
+            // kAccSlots stores to the row in global memory, which the compiler
+            // would not move a later load past
+            int32_t K[kAsmCells];
+            int a[kAsmCells];
+            double inv[kAsmCells], ra[kAsmCells], v[kAsmCells][8];
+            uint4 pos[kAsmCells];
+            unsigned mask[kAsmCells];
+#pragma unroll
+            for (int j = 0; j < kAsmCells; ++j) {
+                K[j] = e8[jb + j] >> 3;
+                a[j] = e8[jb + j] & 7;
+                pos[j] = p8[jb + j];
+            }
+#pragma unroll
+            for (int j = 0; j < kAsmCells; ++j) {
+                mask[j] = g.fmask[K[j]];
+                inv[j] = 1.0 / g.AKK[K[j]];
+                ra[j] = g.rK[(int64_t)a[j] * g.nc + K[j]];
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    v[j][c] =
+                        g.aK[(int64_t)sym8(a[j], c) * g.nc + K[j]] - ra[j] * g.rK[(int64_t)c * g.nc + K[j]] * inv[j];
+            }
+            // p_bar of the Dirichlet columns, likewise before the additions: rows of
+            // a mesh with two Dirichlet sides have them in nearly every wavefront,
+            // and a load and its address at each column made the kernel's time
+            double pb[kAsmCells][8];
+#pragma unroll
+            for (int j = 0; j < kAsmCells; ++j) {
+                const uint32_t pw[4] = {pos[j].x, pos[j].y, pos[j].z, pos[j].w};
+                bool dir = false;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    pb[j][c] = 0.0;
+                    dir |= (uint16_t)(pw[c >> 1] >> (16 * (c & 1))) == 0xffff;
+                }
+                if (dir) {
+                    int32_t node[8];
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) node[c] = g.hex8[8 * (int64_t)K[j] + c];
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) pb[j][c] = g.p_bar[node[c]];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kAsmCells; ++j) {
+                if (q0 + j >= q1) break;
+                const uint32_t pw[4] = {pos[j].x, pos[j].y, pos[j].z, pos[j].w};
+                // the cell's columns differ, so its slots in LDS are read, added to and
+                // written together; slot kAccSlots takes what belongs elsewhere
+                bool beyond = false;
+                int k[8];
+                double t[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    k[c] = (int)((pw[c >> 1] >> (16 * (c & 1))) & 0xffffu);
+                    beyond |= k[c] >= kAccSlots && k[c] != 0xffff;
+                    t[c] = acc[min(k[c], kAccSlots)][tid];
+                }
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc[min(k[c], kAccSlots)][tid] = t[c] + v[j][c];
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    if (k[c] == 0xffff) rhs -= v[j][c] * pb[j][c];  // Dirichlet column
+                if (beyond)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+                        if (k[c] >= kAccSlots && k[c] != 0xffff) g.A[base + 64 * (int64_t)k[c]] += v[j][c];
+                for (int f = 0; kept && f < 6; ++f) {
+                    if (!((mask[j] >> f) & 1u)) continue;
+                    const int32_t sig = g.cell_frac[6 * (int64_t)K[j] + f];
+                    if (g.frac_unk[sig] >= g.nsys) continue;  // eliminated: held by its group block
+                    const int sd = g.frac_cell[2 * (int64_t)sig] == K[j] ? 0 : 1;
+                    const double *o = g.fside + (2 * (int64_t)sig + sd) * 6;
+                    const int i = face_vertex(f, a[j]);
+                    const double t = (i >= 0 ? o[1 + i] : 0.0) - ra[j] * o[5] * inv[j];
+                    put_face(g.frac_unk[sig], t);
+                }
+            }
         }
     }
-    // fracture blocks of the faces the node is a vertex of: row 1+i of the 5x5 block
-    for (int32_t q = g.node_frac_ptr[s]; q < g.node_frac_ptr[s + 1]; ++q) {
-        const int32_t sig = g.node_frac[q] >> 2;
-        const int i = g.node_frac[q] & 3;
-        const double *M = g.A5 + 25 * (int64_t)sig + 5 * (1 + i);
-        put_col(g.frac_unk[sig], -1, M[0]);
-        for (int k = 0; k < 4; ++k) {
-            const int32_t node = g.frac_nodes[4 * (int64_t)sig + k];
-            put_col(g.node_unk[node], node, M[1 + k]);
+    // fracture blocks of the faces the node is a vertex of: row 1+i of the 5x5
+    // block, its slots (face, nodes 0..3) found once per handle as well: a
+    // search is five dependent loads for each of the up to 20 entries, and the
+    // wavefronts next to fractures decided the kernel's time
+    const int32_t f1 = g.node_frac_ptr[s + 1];
+    for (int32_t q0 = g.node_frac_ptr[s]; q0 < f1; q0 += 2) {
+        int32_t sig[2];
+        uint4 pos[2];
+        double M[2][5];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int32_t q = min(q0 + j, f1 - 1), e = g.node_frac[q];
+            sig[j] = e >> 2;
+            pos[j] = *reinterpret_cast<const uint4 *>(g.frac_pos + 8 * (int64_t)q);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) M[j][k] = g.A5[25 * (int64_t)sig[j] + 5 * (1 + (e & 3)) + k];
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (q0 + j >= f1) break;
+            const uint32_t pw[3] = {pos[j].x, pos[j].y, pos[j].z};
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                const uint16_t c = (uint16_t)(pw[k >> 1] >> (16 * (k & 1)));
+                if (c != 0xffff) put(c, M[j][k]);
+                else if (k) rhs -= M[j][k] * g.p_bar[g.frac_nodes[4 * (int64_t)sig[j] + k - 1]];  // Dirichlet column
+            }
         }
     }
     for (int k = 0; k < w; ++k) g.A[base + 64 * (int64_t)k] = acc[k][tid];
     g.b[r] += rhs;
 }
 
-// Row of fracture face sig (kept: system row r; eliminated: row of its group
-// block).  blk = null for a kept face.
-__device__ inline void asm_face_row(const AsmArgs &g, int32_t sig, int32_t r, double *blk, int32_t G, double &rhs) {
-    int gsize = 0, W = 0;
+// Row of fracture face sig (kept: system row r; eliminated: row blk of its
+// group's block), kFaceLanes lanes per row, whole blocks calling (sig < 0: no
+// row): lane c takes node c and face c of a cell, so that the searches of a
+// cell's columns run side by side (one lane per row took 50 us at 64^3, 310 us
+// at 192^3; now 18 and 167).  The columns of a cell differ, and the barriers keep the first
+// cell's additions before the second's and those before the fracture block's:
+// every entry is summed in that order.  Returns the right-hand side's share.
+constexpr int kFaceLanes = 8;
+__device__ inline double asm_face_row(const AsmArgs &g, int32_t sig, int32_t r, double *blk, int32_t G) {
+    const int c = threadIdx.x & (kFaceLanes - 1);
+    int gsize = 0, m = 0;
     const int32_t *B = nullptr;
-    int m = 0;
     if (blk) {
         gsize = g.grp_ptr[G + 1] - g.grp_ptr[G];
         m = g.grp_nptr[G + 1] - g.grp_nptr[G];
-        W = gsize + m;
         B = g.grp_node + g.grp_nptr[G];
     }
-    // adds v to column unknown c (node `node` or face sig2)
-    auto put = [&](int32_t c, int32_t node, int32_t sig2, double v) {
+    double rhs = 0.0;  // in every lane of the row
+    // adds v to node u's column (u < 0: Dirichlet, to the right-hand side, the
+    // lanes in turn); called by all lanes, those without an entry with on = false
+    auto put_node = [&](bool on, int32_t node, double v) {
+        const int32_t u = on ? g.node_unk[node] : 0;
+        const double pb = on && u < 0 ? g.p_bar[node] : 0.0;
+        const int dir = on && u < 0;
+#pragma unroll
+        for (int l = 0; l < kFaceLanes; ++l) {
+            const double vl = __shfl(v, l, kFaceLanes), pl = __shfl(pb, l, kFaceLanes);
+            if (__shfl(dir, l, kFaceLanes)) rhs -= vl * pl;
+        }
+        if (!on || u < 0) return;
         if (!blk) {
-            add_sys(g, r, c, node, v, rhs);
-        } else if (c < 0) {
-            rhs -= v * g.p_bar[node];
-        } else if (c >= g.nsys) {
-            blk[g.face_loc[sig2]] += v;
+            const int64_t q = sell_find(g, r, u);
+            if (q >= 0) g.A[q] += v; else atomicMin(g.bad, INT_MIN);
         } else {
-            int lo = 0, hi = m;  // free node: its index in the group's sorted node list
+            int lo = 0, hi = m;  // its index in the group's sorted node list
             while (lo < hi) {
                 const int mid = (lo + hi) >> 1;
-                if (B[mid] < c) lo = mid + 1; else hi = mid;
+                if (B[mid] < u) lo = mid + 1; else hi = mid;
             }
-            if (lo < m && B[lo] == c) blk[gsize + lo] += v; else atomicMin(g.bad, INT_MIN);
+            if (lo < m && B[lo] == u) blk[gsize + lo] += v; else atomicMin(g.bad, INT_MIN);
         }
     };
-    (void)W;
+    auto put_face = [&](int32_t sig2, double v) {
+        const int32_t u = g.frac_unk[sig2];
+        if (blk) {
+            if (u >= g.nsys) {
+                blk[g.face_loc[sig2]] += v;
+                return;
+            }
+            atomicMin(g.bad, INT_MIN);  // a group holds all faces of its cells
+        } else if (u < g.nsys) {
+            const int64_t q = sell_find(g, r, u);
+            if (q >= 0) g.A[q] += v; else atomicMin(g.bad, INT_MIN);
+        }
+    };
     for (int side = 0; side < 2; ++side) {
-        const int32_t K = g.frac_cell[2 * (int64_t)sig + side];
-        if (K < 0) continue;
-        int f = 0;
-        while (f < 6 && g.cell_frac[6 * (int64_t)K + f] != sig) ++f;
-        const unsigned mask = g.fmask[K];
-        const double inv = 1.0 / g.AKK[K];
-        const double *o = g.fside + (2 * (int64_t)sig + side) * 6;
-        const double rs = o[5];
-        for (int c = 0; c < 8; ++c) {
-            const int32_t node = g.hex8[8 * (int64_t)K + c];
-            const int i = face_vertex(f, c);
-            const double v = (i >= 0 ? o[1 + i] : 0.0) - rs * g.rK[(int64_t)c * g.nc + K] * inv;
-            put(g.node_unk[node], node, -1, v);
-        }
-        for (int f2 = 0; f2 < 6; ++f2) {
-            if (!((mask >> f2) & 1u)) continue;
-            const int32_t sig2 = g.cell_frac[6 * (int64_t)K + f2];
+        const int32_t K = sig >= 0 ? g.frac_cell[2 * (int64_t)sig + side] : -1;
+        const bool on = K >= 0;
+        const int32_t sig2 = on && c < 6 ? g.cell_frac[6 * (int64_t)K + c] : -1;
+        const unsigned mask = on ? g.fmask[K] : 0u;
+        const int32_t node = on ? g.hex8[8 * (int64_t)K + c] : 0;
+        const double inv = on ? 1.0 / g.AKK[K] : 0.0;
+        const double *o = g.fside + (2 * (int64_t)(on ? sig : 0) + side) * 6;
+        const double rs = on ? o[5] : 0.0;
+        const unsigned hit = (unsigned)(__ballot(on && c < 6 && sig2 == sig) >> (threadIdx.x & 56)) & 63u;
+        const int f = hit ? __ffs(hit) - 1 : 0;  // sig's place in the cell
+        const int i = face_vertex(f, c);
+        double v = 0.0;
+        if (on) v = (i >= 0 ? o[1 + i] : 0.0) - rs * g.rK[(int64_t)c * g.nc + K] * inv;
+        put_node(on, node, v);
+        if (c < 6 && ((mask >> c) & 1u)) {
             const int sd2 = g.frac_cell[2 * (int64_t)sig2] == K ? 0 : 1;
-            const double v = (f2 == f ? o[0] : 0.0) - rs * g.fside[(2 * (int64_t)sig2 + sd2) * 6 + 5] * inv;
-            put(g.frac_unk[sig2], -1, sig2, v);
+            put_face(sig2, (c == f ? o[0] : 0.0) - rs * g.fside[(2 * (int64_t)sig2 + sd2) * 6 + 5] * inv);
         }
+        __syncthreads();
     }
     // fracture block: row 0 of the 5x5 block
-    const double *M = g.A5 + 25 * (int64_t)sig;
-    put(g.frac_unk[sig], -1, sig, M[0]);
-    for (int k = 0; k < 4; ++k) {
-        const int32_t node = g.frac_nodes[4 * (int64_t)sig + k];
-        put(g.node_unk[node], node, -1, M[1 + k]);
-    }
+    const bool on = sig >= 0 && c < 5;
+    const double v = on ? g.A5[25 * (int64_t)sig + c] : 0.0;
+    // lanes 1..4 hold nodes 0..3, in their order
+    put_node(on && c > 0, on && c > 0 ? g.frac_nodes[4 * (int64_t)sig + c - 1] : 0, v);
+    if (on && c == 0) put_face(sig, v);
+    return rhs;
 }
 
 __global__ __launch_bounds__(128) void asm_face_rows_kernel(AsmArgs g, int32_t nkept) {
-    const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nkept) return;
-    const int32_t r = g.nfree + t;
-    double rhs = 0.0;
-    asm_face_row(g, g.unk_face[t], r, nullptr, -1, rhs);
-    g.b[r] += rhs;
+    const int32_t t = (int32_t)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kFaceLanes);
+    const bool in = t < nkept;
+    const int32_t r = g.nfree + (in ? t : 0);
+    const double rhs = asm_face_row(g, in ? g.unk_face[t] : -1, r, nullptr, -1);
+    if (in && threadIdx.x % kFaceLanes == 0) g.b[r] += rhs;
 }
 
 // rows of eliminated faces into the dense group blocks [A_GG | A_GB], b_G
 __global__ __launch_bounds__(128) void asm_elim_rows_kernel(AsmArgs g, int32_t nelim) {
-    const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nelim) return;
-    const int32_t sig = g.grp_face[t];
+    const int32_t t = (int32_t)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kFaceLanes);
+    const bool in = t < nelim;
+    const int32_t sig = g.grp_face[in ? t : 0];
     const int32_t G = g.face_grp[sig];
     const int gsize = g.grp_ptr[G + 1] - g.grp_ptr[G];
     const int W = gsize + g.grp_nptr[G + 1] - g.grp_nptr[G];
     double *blk = g.Gb + g.grp_off[G] + (int64_t)g.face_loc[sig] * W;
-    double rhs = 0.0;
-    asm_face_row(g, sig, -1, blk, G, rhs);
-    g.b[g.frac_unk[sig]] += rhs;
+    const double rhs = asm_face_row(g, in ? sig : -1, -1, blk, G);
+    if (in && threadIdx.x % kFaceLanes == 0) g.b[g.frac_unk[sig]] += rhs;
 }
 
 // Fills the sliced-ELL columns from the CSR pattern (one thread per slice
@@ -564,28 +680,23 @@ __global__ __launch_bounds__(64) void grp_pos_kernel(AsmArgs g, const int64_t *_
     }
 }
 
-// Exact elimination of fracture-face groups of one colour, one wavefront per
-// group.  The group block [A_GG | A_GB] (g x (g+m), row-major) and its
-// right-hand side b_G are factored in LDS: A_GG = L L^T, Y = L^-1 A_GB,
-// y = L^-1 b_G; then A_BB -= Y^T Y and b_B -= Y^T y are subtracted from the
-// node rows.  L, Y and y are written back for the recovery of u_G.
-// Groups of one colour share no free node, so the updates do not collide;
-// every sum runs in a fixed order (deterministic).
-__global__ __launch_bounds__(64) void vag_group_elim_kernel(
-    int32_t first, int32_t ngroup, const int32_t *__restrict__ grp_ptr, const int32_t *__restrict__ grp_face,
-    const int32_t *__restrict__ grp_nptr, const int32_t *__restrict__ grp_node, const int64_t *__restrict__ grp_off,
-    const int64_t *__restrict__ grp_poff, const int32_t *__restrict__ grp_pos, const int32_t *__restrict__ frac_unk,
-    double *__restrict__ Gb, double *__restrict__ A, double *__restrict__ b, int *__restrict__ bad) {
+// Exact elimination of fracture-face groups, one wavefront per group.  The
+// group block [A_GG | A_GB] (g x (g+m), row-major) and its right-hand side b_G
+// are factored in LDS, all groups in one launch: A_GG = L L^T, Y = L^-1 A_GB,
+// y = L^-1 b_G, written back for vag_group_schur_kernel and the recovery of
+// u_G.
+__global__ __launch_bounds__(64) void vag_group_factor_kernel(
+    const int32_t *__restrict__ grp_ptr, const int32_t *__restrict__ grp_face, const int32_t *__restrict__ grp_nptr,
+    const int64_t *__restrict__ grp_off, const int32_t *__restrict__ frac_unk, double *__restrict__ Gb,
+    double *__restrict__ b, int *__restrict__ bad) {
     extern __shared__ double lds[];
-    const int32_t G = first + blockIdx.x;
-    if (blockIdx.x >= ngroup) return;
+    const int32_t G = blockIdx.x;
     const int tid = threadIdx.x;
     const int g = grp_ptr[G + 1] - grp_ptr[G];
     const int m = grp_nptr[G + 1] - grp_nptr[G];
     const int W = g + m + 1;                       // LDS row: [A_GG | A_GB | b_G]
     double *blk = Gb + grp_off[G];
     const int32_t *faces = grp_face + grp_ptr[G];
-    const int32_t *B = grp_node + grp_nptr[G];
     for (int e = tid; e < g * W; e += 64) {
         const int i = e / W, c = e - i * W;
         lds[e] = c < g + m ? blk[(int64_t)i * (g + m) + c] : b[frac_unk[faces[i]]];
@@ -624,17 +735,38 @@ __global__ __launch_bounds__(64) void vag_group_elim_kernel(
         if (c < g + m) blk[(int64_t)i * (g + m) + c] = lds[e];
         else b[frac_unk[faces[i]]] = lds[e];
     }
-    // Schur complement on the node rows
+}
+
+// A_BB -= Y^T Y and b_B -= Y^T y on the node rows, for the groups of one
+// colour: they share no free node, so the updates do not collide, and every
+// sum runs in a fixed order.  Apart from the factorisation, whose chain of
+// loads, roots and divisions the colours do not have to wait for in turn, and
+// with four wavefronts per group: 8 colours at 64^3 took 147 us and take 89 and
+// the factorisation's 19, 10 at 192^3 809 and take 773 and 77.  A group that
+// failed (`bad`) leaves numbers that nothing reads.
+constexpr int kSchurThreads = 256;
+__global__ __launch_bounds__(kSchurThreads) void vag_group_schur_kernel(
+    int32_t first, const int32_t *__restrict__ grp_ptr, const int32_t *__restrict__ grp_face,
+    const int32_t *__restrict__ grp_nptr, const int32_t *__restrict__ grp_node, const int64_t *__restrict__ grp_off,
+    const int64_t *__restrict__ grp_poff, const int32_t *__restrict__ grp_pos, const int32_t *__restrict__ frac_unk,
+    const double *__restrict__ Gb, double *__restrict__ A, double *__restrict__ b) {
+    const int32_t G = first + blockIdx.x;
+    const int tid = threadIdx.x;
+    const int g = grp_ptr[G + 1] - grp_ptr[G];
+    const int m = grp_nptr[G + 1] - grp_nptr[G];
+    const double *Y = Gb + grp_off[G] + g;  // rows g + m apart
+    const int32_t *faces = grp_face + grp_ptr[G];
+    const int32_t *B = grp_node + grp_nptr[G];
     const int32_t *pos = grp_pos + grp_poff[G];
-    for (int e = tid; e < m * m; e += 64) {
+    for (int e = tid; e < m * m; e += kSchurThreads) {
         const int p = e / m, q = e - p * m;
         double sum = 0.0;
-        for (int k = 0; k < g; ++k) sum += lds[k * W + g + p] * lds[k * W + g + q];
+        for (int k = 0; k < g; ++k) sum += Y[k * (g + m) + p] * Y[k * (g + m) + q];
         A[pos[e]] -= sum;
     }
-    for (int p = tid; p < m; p += 64) {
+    for (int p = tid; p < m; p += kSchurThreads) {
         double sum = 0.0;
-        for (int k = 0; k < g; ++k) sum += lds[k * W + g + p] * lds[k * W + g + m];
+        for (int k = 0; k < g; ++k) sum += Y[k * (g + m) + p] * b[frac_unk[faces[k]]];
         b[B[p]] -= sum;
     }
 }
@@ -645,26 +777,32 @@ __global__ __launch_bounds__(64) void vag_group_back_kernel(
     const int32_t *__restrict__ grp_nptr, const int32_t *__restrict__ grp_node, const int64_t *__restrict__ grp_off,
     const int32_t *__restrict__ frac_unk, const double *__restrict__ Gb, const double *__restrict__ b,
     double *__restrict__ x) {
-    __shared__ double z[kGroupMaxFaces];
+    __shared__ double z[kGroupMaxFaces], xb[kGroupMaxNodes];
+    extern __shared__ double lds[];  // the group's rows [L | Y]
     const int32_t G = blockIdx.x;
     if (G >= ngroup) return;
     const int tid = threadIdx.x;
     const int g = grp_ptr[G + 1] - grp_ptr[G];
-    const int m = grp_nptr[G + 1] - grp_nptr[G];
+    const int m = grp_nptr[G + 1] - grp_nptr[G], W = g + m;
     const double *blk = Gb + grp_off[G];
     const int32_t *faces = grp_face + grp_ptr[G];
     const int32_t *B = grp_node + grp_nptr[G];
+    // the operands first, by all lanes: the substitutions below are chains
+    if (tid < m) xb[tid] = x[B[tid]];
+    if (tid < g) z[tid] = b[frac_unk[faces[tid]]];
+    for (int e = tid; e < g * W; e += 64) lds[e] = blk[e];
+    __syncthreads();
     if (tid < g) {
-        double v = b[frac_unk[faces[tid]]];
-        for (int p = 0; p < m; ++p) v -= blk[(int64_t)tid * (g + m) + g + p] * x[B[p]];
+        double v = z[tid];
+        for (int p = 0; p < m; ++p) v -= lds[tid * W + g + p] * xb[p];
         z[tid] = v;
     }
     __syncthreads();
     if (tid == 0) {
         for (int i = g - 1; i >= 0; --i) {
             double v = z[i];
-            for (int k = i + 1; k < g; ++k) v -= blk[(int64_t)k * (g + m) + i] * z[k];
-            z[i] = v / blk[(int64_t)i * (g + m) + i];
+            for (int k = i + 1; k < g; ++k) v -= lds[k * W + i] * z[k];
+            z[i] = v / lds[i * W + i];
         }
     }
     __syncthreads();
@@ -710,12 +848,19 @@ void launch_node_pos(hipStream_t s, const AsmArgs &g, uint16_t *node_pos) {
     VAG_HIP(hipGetLastError());
 }
 
+void launch_frac_pos(hipStream_t s, const AsmArgs &g, int32_t nf, uint16_t *frac_pos) {
+    const int64_t n = 32 * (int64_t)nf;  // 4 node_frac entries a face, 8 slots each
+    if (n > 0) hipLaunchKernelGGL(frac_pos_kernel, dim3(nblk(n, 128)), dim3(128), 0, s, g, n, frac_pos);
+    VAG_HIP(hipGetLastError());
+}
+
 void launch_assemble(hipStream_t s, const AsmArgs &g, int32_t nkept, int32_t nelim) {
     if (g.nfree > 0) hipLaunchKernelGGL(asm_node_rows_kernel, dim3(nblk(g.nfree, 128)), dim3(128), 0, s, g);
     VAG_HIP(hipGetLastError());
-    if (nkept > 0) hipLaunchKernelGGL(asm_face_rows_kernel, dim3(nblk(nkept, 128)), dim3(128), 0, s, g, nkept);
+    const auto lanes = [](int64_t rows) { return dim3(nblk(rows * kFaceLanes, 128)); };
+    if (nkept > 0) hipLaunchKernelGGL(asm_face_rows_kernel, lanes(nkept), dim3(128), 0, s, g, nkept);
     VAG_HIP(hipGetLastError());
-    if (nelim > 0) hipLaunchKernelGGL(asm_elim_rows_kernel, dim3(nblk(nelim, 128)), dim3(128), 0, s, g, nelim);
+    if (nelim > 0) hipLaunchKernelGGL(asm_elim_rows_kernel, lanes(nelim), dim3(128), 0, s, g, nelim);
     VAG_HIP(hipGetLastError());
 }
 
@@ -741,23 +886,32 @@ void launch_grp_pos(hipStream_t s, const AsmArgs &g, int32_t ngroup, const int64
     VAG_HIP(hipGetLastError());
 }
 
-void launch_group_elim(hipStream_t s, int32_t first, int32_t ngroup, int max_g, int max_m, const int32_t *grp_ptr,
-                       const int32_t *grp_face, const int32_t *grp_nptr, const int32_t *grp_node,
-                       const int64_t *grp_off, const int64_t *grp_poff, const int32_t *grp_pos,
-                       const int32_t *frac_unk, double *Gb, double *A, double *b, int *bad) {
+void launch_group_elim(hipStream_t s, int32_t ngroup, const std::vector<int32_t> &color_ptr, int max_g, int max_m,
+                       const int32_t *grp_ptr, const int32_t *grp_face, const int32_t *grp_nptr,
+                       const int32_t *grp_node, const int64_t *grp_off, const int64_t *grp_poff,
+                       const int32_t *grp_pos, const int32_t *frac_unk, double *Gb, double *A, double *b, int *bad) {
     if (ngroup <= 0) return;
     if (max_g > kGroupMaxFaces || max_m > kGroupMaxNodes) throw Error(VAG_ERR_ARG, "internal: group too large");
     const size_t lds = (size_t)max_g * (max_g + max_m + 1) * sizeof(double);
-    hipLaunchKernelGGL(vag_group_elim_kernel, dim3(ngroup), dim3(64), lds, s, first, ngroup, grp_ptr, grp_face,
-                       grp_nptr, grp_node, grp_off, grp_poff, grp_pos, frac_unk, Gb, A, b, bad);
+    hipLaunchKernelGGL(vag_group_factor_kernel, dim3(ngroup), dim3(64), lds, s, grp_ptr, grp_face, grp_nptr, grp_off,
+                       frac_unk, Gb, b, bad);
     VAG_HIP(hipGetLastError());
+    for (size_t c = 0; c + 1 < color_ptr.size(); ++c) {
+        const int32_t n = color_ptr[c + 1] - color_ptr[c];
+        if (n <= 0) continue;
+        hipLaunchKernelGGL(vag_group_schur_kernel, dim3(n), dim3(kSchurThreads), 0, s, color_ptr[c], grp_ptr, grp_face,
+                           grp_nptr, grp_node, grp_off, grp_poff, grp_pos, frac_unk, Gb, A, b);
+        VAG_HIP(hipGetLastError());
+    }
 }
 
-void launch_group_back(hipStream_t s, int32_t ngroup, const int32_t *grp_ptr, const int32_t *grp_face,
-                       const int32_t *grp_nptr, const int32_t *grp_node, const int64_t *grp_off,
-                       const int32_t *frac_unk, const double *Gb, const double *b, double *x) {
+void launch_group_back(hipStream_t s, int32_t ngroup, int max_g, int max_m, const int32_t *grp_ptr,
+                       const int32_t *grp_face, const int32_t *grp_nptr, const int32_t *grp_node,
+                       const int64_t *grp_off, const int32_t *frac_unk, const double *Gb, const double *b, double *x) {
     if (ngroup <= 0) return;
-    hipLaunchKernelGGL(vag_group_back_kernel, dim3(ngroup), dim3(64), 0, s, ngroup, grp_ptr, grp_face, grp_nptr,
+    if (max_g > kGroupMaxFaces || max_m > kGroupMaxNodes) throw Error(VAG_ERR_ARG, "internal: group too large");
+    const size_t lds = (size_t)max_g * (max_g + max_m) * sizeof(double);
+    hipLaunchKernelGGL(vag_group_back_kernel, dim3(ngroup), dim3(64), lds, s, ngroup, grp_ptr, grp_face, grp_nptr,
                        grp_node, grp_off, frac_unk, Gb, b, x);
     VAG_HIP(hipGetLastError());
 }

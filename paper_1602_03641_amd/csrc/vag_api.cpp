@@ -159,6 +159,7 @@ struct vag_handle {
     DBuf<int64_t> sell_ptr;
     // eliminated fracture-face groups
     DBuf<int32_t> frac_unk, grp_ptr, grp_face, grp_nptr, grp_node, grp_pos, face_grp, face_loc;
+    DBuf<uint16_t> frac_pos;  // slots of the fracture blocks' columns in the node rows
     DBuf<uint16_t> node_pos;  // slots of the cell-matrix columns in the node rows
     DBuf<int64_t> grp_off, grp_poff;
     DBuf<double> Gb;
@@ -403,6 +404,7 @@ AsmArgs asm_args(vag_handle *h) {
     g.A5 = h->A5.p;
     g.p_bar = h->p_bar.p;
     g.node_pos = h->node_pos.p;
+    g.frac_pos = h->frac_pos.p;
     g.sell_ptr = h->sell_ptr.p;
     g.sell_col = h->sell_col.p;
     g.row_len = h->row_len.p;
@@ -1156,6 +1158,8 @@ vag_status vag_create(const vag_mesh *mesh, const vag_fractures *frac, const vag
         // slots of the cell-matrix columns in the node rows
         h->node_pos.alloc(64 * (size_t)nc, h->tr);  // 8 slots per node_cell entry
         launch_node_pos(h->stream, asm_args(h), h->node_pos.p);
+        h->frac_pos.alloc(std::max<size_t>(32 * (size_t)nf, 1), h->tr);  // 8 slots per node_frac entry
+        launch_frac_pos(h->stream, asm_args(h), S.nf, h->frac_pos.p);
         int bad = 0;
         VAG_HIP(hipMemcpyAsync(&bad, h->bad.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
         VAG_HIP(hipStreamSynchronize(h->stream));
@@ -1380,10 +1384,9 @@ vag_status vag_solve_pressure(vag_handle *h, vag_solve_info *info) {
                                  WellAsm{S.nunk, h->frac_unk.p, h->diag_pos.p, h->face_grp.p, h->face_loc.p,
                                          h->grp_ptr.p, h->grp_nptr.p, h->grp_off.p, h->A.p, h->Gb.p, h->b.p});
         // fracture-face groups onto the nodes, colour by colour
-        for (int c = 0; c < S.ngcolor; ++c)
-            launch_group_elim(s, S.gcolor_ptr[c], S.gcolor_ptr[c + 1] - S.gcolor_ptr[c], S.grp_max_g, S.grp_max_m,
-                              h->grp_ptr.p, h->grp_face.p, h->grp_nptr.p, h->grp_node.p, h->grp_off.p,
-                              h->grp_poff.p, h->grp_pos.p, h->frac_unk.p, h->Gb.p, h->A.p, h->b.p, h->bad.p);
+        launch_group_elim(s, S.ngroup, S.gcolor_ptr, S.grp_max_g, S.grp_max_m, h->grp_ptr.p, h->grp_face.p,
+                          h->grp_nptr.p, h->grp_node.p, h->grp_off.p, h->grp_poff.p, h->grp_pos.p, h->frac_unk.p,
+                          h->Gb.p, h->A.p, h->b.p, h->bad.p);
         launch_diag_inv(s, n, h->diag_pos.p, h->A.p, h->dinv.p);
         VAG_HIP(hipEventRecord(h->ev[1], s));
         ph.next("vag.preconditioner_setup");
@@ -1417,7 +1420,7 @@ vag_status vag_solve_pressure(vag_handle *h, vag_solve_info *info) {
         const PcgState pst = *h->h_pcg;
         converged = pst.converged != 0;
         // 4. recovery and fluxes
-        launch_group_back(s, S.ngroup, h->grp_ptr.p, h->grp_face.p, h->grp_nptr.p, h->grp_node.p, h->grp_off.p,
+        launch_group_back(s, S.ngroup, S.grp_max_g, S.grp_max_m, h->grp_ptr.p, h->grp_face.p, h->grp_nptr.p, h->grp_node.p, h->grp_off.p,
                           h->frac_unk.p, h->Gb.p, h->b.p, h->x.p);
         launch_node_pressure(s, S.nn, h->node_unk.p, h->x.p, h->p_bar.p, h->u_node.p);
         if (S.nf) launch_node_pressure(s, S.nf, h->frac_unk.p, h->x.p, h->p_bar.p, h->u_frac.p);  // all mapped
@@ -2127,7 +2130,7 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
     const double S = 1.4 * nnz + 4096.0;
     double b = 0.0;
     b += 24 * Nn + 97 * Nc + 72 * Nf + 14 * Nn + 12.0 * S / 64;    // topology, adjacency
-    b += 4 * S + 4 * (64 * Nc + 58 * Nf) + 8 * Nc;                 // pattern, slot maps
+    b += 4 * S + 4 * (64 * Nc + 74 * Nf) + 8 * Nc;                 // pattern, slot maps
     b += 3000.0 * Nf;                                               // fracture-face groups
     b += 56 * Nc + 24 * Nf + 16 * Nn;                               // rock, fracture, boundary data
     b += 376 * Nc + 304 * Nf + 8 * S + 16 * Nx;                     // local matrices, system

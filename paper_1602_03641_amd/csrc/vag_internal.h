@@ -364,6 +364,10 @@ struct AsmArgs {
     // slot of column c of M_K in the row of each node_cell entry q:
     // node_pos[8 q + c] (0xffff: a Dirichlet column); null before it is built
     const uint16_t *node_pos;
+    // slots of fracture block columns (face, nodes 0..3) in the row of each
+    // node_frac entry q: frac_pos[8 q + k] (0xffff: a Dirichlet node or an
+    // eliminated face)
+    const uint16_t *frac_pos;
 };
 // Node rows, kept-face rows, eliminated-face rows (into the group blocks).
 void launch_assemble(hipStream_t s, const AsmArgs &g, int32_t nkept, int32_t nelim);
@@ -398,18 +402,20 @@ void launch_check_coef(hipStream_t s, int32_t nc, const double *perm, int32_t nf
                        const double *fperm, int *bad);
 // node_pos (see AsmArgs) for the rows of the free nodes, once per handle.
 void launch_node_pos(hipStream_t s, const AsmArgs &g, uint16_t *node_pos);
+void launch_frac_pos(hipStream_t s, const AsmArgs &g, int32_t nf, uint16_t *frac_pos);
 // System positions of the node pairs of each eliminated group.
 void launch_grp_pos(hipStream_t s, const AsmArgs &g, int32_t ngroup, const int64_t *grp_poff, int32_t *grp_pos);
-// Eliminates groups [first, first+ngroup) (one colour) onto the node rows.
+// Eliminates the groups onto the node rows, colour c the groups
+// [color_ptr[c], color_ptr[c + 1]).
 // bad receives -1-G for a group whose face block is not positive definite.
-void launch_group_elim(hipStream_t s, int32_t first, int32_t ngroup, int max_g, int max_m, const int32_t *grp_ptr,
-                       const int32_t *grp_face, const int32_t *grp_nptr, const int32_t *grp_node,
-                       const int64_t *grp_off, const int64_t *grp_poff, const int32_t *grp_pos,
-                       const int32_t *frac_unk, double *Gb, double *A, double *b, int *bad);
+void launch_group_elim(hipStream_t s, int32_t ngroup, const std::vector<int32_t> &color_ptr, int max_g, int max_m,
+                       const int32_t *grp_ptr, const int32_t *grp_face, const int32_t *grp_nptr,
+                       const int32_t *grp_node, const int64_t *grp_off, const int64_t *grp_poff,
+                       const int32_t *grp_pos, const int32_t *frac_unk, double *Gb, double *A, double *b, int *bad);
 // x of the eliminated faces from the solved node unknowns.
-void launch_group_back(hipStream_t s, int32_t ngroup, const int32_t *grp_ptr, const int32_t *grp_face,
-                       const int32_t *grp_nptr, const int32_t *grp_node, const int64_t *grp_off,
-                       const int32_t *frac_unk, const double *Gb, const double *b, double *x);
+void launch_group_back(hipStream_t s, int32_t ngroup, int max_g, int max_m, const int32_t *grp_ptr,
+                       const int32_t *grp_face, const int32_t *grp_nptr, const int32_t *grp_node,
+                       const int64_t *grp_off, const int32_t *frac_unk, const double *Gb, const double *b, double *x);
 void launch_diag_inv(hipStream_t s, int32_t n, const int32_t *diag_pos, const double *A, double *dinv);
 
 // BiCGStab (bicgstab.hip): parts holds 8 * bcg_grid(n) doubles

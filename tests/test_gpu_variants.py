@@ -155,3 +155,67 @@ def test_gmres_basis_sizes(dims, opt, restart):
     for k in ("u_node", "u_frac"):
         assert np.abs(u[k] - od[k]).max(initial=0.0) <= 1e-6 * np.abs(od["u_node"]).max(), k
     h.close()
+
+
+def _star(sectors, layers, dirichlet_axis):
+    """A prism of hexahedra around an axis: an axis node has `sectors` cells in
+    each layer.  Fracture faces on vertical planes through the axis (they meet
+    there: one group of many faces per layer) and horizontal ones off it."""
+    n = 2 * sectors
+    t = np.arange(n) * (2 * np.pi / n)
+    rad = np.where(np.arange(n) % 2 == 0, 1.0, 1.35)
+    inner = np.c_[rad * np.cos(t), rad * np.sin(t)]
+    ring = np.concatenate([[[0.0, 0.0]], inner, 2.0 * inner])
+    m = len(ring)
+    xyz = np.concatenate([np.c_[ring, np.full(m, 0.4 * z)] for z in range(layers + 1)])
+    quads = [(0, 1 + 2 * i, 2 + 2 * i, 1 + (2 * i + 2) % n) for i in range(sectors)]
+    quads += [(1 + i, 1 + n + i, 1 + n + (i + 1) % n, 1 + (i + 1) % n) for i in range(n)]
+    hex8 = np.array([[a + m * z for a in q] + [a + m * (z + 1) for a in q] for z in range(layers) for q in quads],
+                    np.int32)
+    frac = [(0 + m * z, 1 + 2 * i + m * z, 1 + 2 * i + m * (z + 1), 0 + m * (z + 1))
+            for z in range(layers) for i in (0, 2, 5)]
+    frac += [tuple(a + m for a in quads[sectors + i]) for i in (1, 2, 7)]
+    z = np.repeat(np.arange(layers + 1), m)
+    d = (z == 0) | (z == layers)
+    if dirichlet_axis:
+        d |= np.tile(np.arange(m) == 0, layers + 1)
+    perm = np.zeros((len(hex8), 6))
+    perm[:, :3] = np.random.default_rng(5).uniform(0.5, 2.0, (len(hex8), 3))
+    nf = len(frac)
+    return synth.Problem(
+        name="star", dims=None, xyz=xyz, hex8=hex8, frac_nodes=np.array(frac, np.int32), frac_width=np.full(nf, 0.01),
+        frac_perm=np.geomspace(10.0, 1e3, nf), frac_poro=np.ones(nf), perm=perm, poro=np.ones(len(hex8)), mu=1.0,
+        dirichlet=d.astype(np.uint8), p_bar=1.0 - z / layers, c_bar=(z == 0).astype(float))
+
+
+@pytest.mark.parametrize("mesh", [(6, 3, False), (12, 3, False), (13, 4, False), (7, 3, True), (5, 4, 3)])
+@pytest.mark.parametrize("eliminate", [0, 1])
+def test_assembled_rows(mesh, eliminate):
+    """Nodes of 6, 12 and 13 cells a layer (lists of 8 in one, two and four
+    pieces, rows of more slots than LDS holds), Dirichlet nodes among their
+    columns, fracture faces kept and eliminated in groups of one and of many:
+    the oracle's system, and its Schur complement on what is kept.  An entry
+    sums below 10^3 terms of at most max |A|, the complement two products more:
+    1e-12 max |A|."""
+    from paper_1602_03641_amd import vag
+    import scipy.sparse as sp
+    p = (synth.random_problem(mesh, 31, n_patches=9, n_steps=0, ratios=(1e1, 1e3)) if mesh == (5, 4, 3)
+         else _star(*mesh))
+    h, info = _handle(p, rtol=1e-12, precond=vag.VAG_PC_AMG, eliminate_frac_faces=eliminate)
+    d = h.amg_level(0)
+    got = sp.csr_matrix((d["A"][2], d["A"][1], d["A"][0])).toarray()
+    A = oracle.system(p)[0].toarray()
+    n = len(got)
+    assert n < len(A) if eliminate else n == len(A)
+    nfree = len(A) - p.n_frac
+    if eliminate:
+        assert n == nfree  # every group is small enough
+        S = A[:n, :n] - A[:n, n:] @ np.linalg.solve(A[n:, n:], A[n:, :n])
+    else:
+        S = A
+    assert np.abs(got - S).max() <= 1e-12 * np.abs(A).max()
+    od = oracle.solve_darcy(p, rtol=1e-13)
+    u = vag.to_numpy(h.pressure())
+    for k in ("u_node", "u_frac"):
+        assert np.abs(u[k] - od[k]).max(initial=0.0) <= 1e-6 * np.abs(od["u_node"]).max(), k
+    h.close()
