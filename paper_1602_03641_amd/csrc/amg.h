@@ -21,18 +21,22 @@ constexpr int kCntSlots = 16, kCntStride = 32, kMisRounds = 48;
 void amg_launch_mis(hipStream_t s, Sell<double> A, const double *diag, double theta, int rounds, int hops,
                     uint32_t *T, uint32_t *T1, int *undecided, int32_t *flag, int *hcnt, int32_t *scol);
 void amg_launch_scan(hipStream_t s, int32_t n, const int32_t *in, int32_t *out, int32_t *tmp);
-void amg_launch_aggregate(hipStream_t s, Sell<double> A, const double *diag, double theta, const int32_t *root,
+// scol: the strong columns that amg_launch_mis left
+void amg_launch_aggregate(hipStream_t s, Sell<double> A, const double *diag, const int32_t *scol, const int32_t *root,
                           const int32_t *rid, int32_t *agg1, int32_t *agg, int32_t *lonely);
 void amg_launch_lonely(hipStream_t s, int32_t n, const int32_t *lonely, const int32_t *lid, const int32_t *nroot,
                        int32_t *agg);
 void amg_launch_members(hipStream_t s, int32_t n, int32_t nc, const int32_t *agg, int32_t *cnt, int32_t *ptr,
                         int32_t *cursor, int32_t *tmp, int32_t *rows, int32_t *scan_tmp);
 // row i of A P into the first apn[i] slots of (apJ, apv); nspill zeroed by the caller
-void amg_launch_collapse(hipStream_t s, Sell<double> A, const int32_t *agg, int32_t *Jcol, int32_t *apJ,
-                         double *apv, int32_t *apn, int32_t *spill, int *nspill);
+void amg_launch_collapse(hipStream_t s, Sell<double> A, const int32_t *agg, int32_t *apJ, double *apv, int32_t *apn,
+                         int32_t *spill, int *nspill);
+// biglist: scratch of nc ints, nbig zeroed by the caller; both kept from mode 0
+// to mode 1
 void amg_launch_galerkin(hipStream_t s, Sell<double> A, const int32_t *Jcol, const double *apv, const int32_t *apn,
                          const int32_t *mptr, const int32_t *mrows, int32_t nc, int mode, int32_t *big,
-                         int32_t *rowlen, const int64_t *cptr, int32_t *ccol, double *cval, int *overflow);
+                         int32_t *biglist, int *nbig, int32_t *rowlen, const int64_t *cptr, int32_t *ccol,
+                         double *cval, int *overflow);
 // slice widths and pointers from row lengths; *nnz = the number of entries
 // (cnt: one int per slice, scratch)
 void amg_launch_slices(hipStream_t s, int32_t n, const int32_t *rowlen, int32_t *width, int32_t *cnt, int64_t *ptr,

@@ -56,28 +56,39 @@ __device__ inline uint32_t perm30(uint32_t x) {
 // row's priority below
 __device__ inline int rank_of(uint32_t t) { return (int)(t >> 30); }
 
-template <class V>
-__device__ inline bool strong(const V *val, const int32_t *col, int64_t q, int32_t i, double di,
-                              const double *diag, double theta, int32_t &j, double &s) {
-    j = col[q];
-    const double a = fabs((double)val[q]);
-    if (j == i || a == 0.0) return false;
-    const double dd = sqrt(fabs(di * diag[j]));
-    s = a / dd;
-    return a >= theta * dd;
+// The slots of row i of a sliced-ELL array, kSlots at a time: load(j, q) for
+// the batch (a slot past the row repeats its first, whose lines are there
+// already), so that a row waits for one chain of loads a batch and not one a
+// slot, then use(j, q) in slot order for those that exist.
+constexpr int kSlots = 8;
+template <class Load, class Use>
+__device__ inline void row_slots(const int64_t *__restrict__ ptr, int64_t i, Load load, Use use) {
+    const int64_t b1 = ptr[(i >> 6) + 1];
+    for (int64_t q0 = ptr[i >> 6] + (i & 63); q0 < b1; q0 += 64 * kSlots) {
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) load(j, q0 + 64 * j < b1 ? q0 + 64 * j : q0);
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j)
+            if (q0 + 64 * j < b1) use(j, q0 + 64 * j);
+    }
 }
 
 // diag and l1-Jacobi inverse
 __global__ __launch_bounds__(kAT) void amg_diag_kernel(Sell<double> A, double *__restrict__ diag,
                                                        double *__restrict__ dinv) {
     GS(i, A.n) {
-        const int64_t b0 = A.ptr[i >> 6], b1 = A.ptr[(i >> 6) + 1];
-        double d = 0.0, l1 = 0.0;
-        for (int64_t q = b0 + (i & 63); q < b1; q += 64) {
-            const double v = A.val[q];
-            if (A.col[q] == i) d += v;
-            l1 += fabs(v);
-        }
+        double d = 0.0, l1 = 0.0, v[kSlots];
+        int32_t c[kSlots];
+        row_slots(
+            A.ptr, i,
+            [&](int j, int64_t q) {
+                v[j] = A.val[q];
+                c[j] = A.col[q];
+            },
+            [&](int j, int64_t) {
+                if (c[j] == i) d += v[j];
+                l1 += fabs(v[j]);
+            });
         diag[i] = d;
         dinv[i] = 1.0 / l1;
     }
@@ -89,13 +100,20 @@ __global__ __launch_bounds__(kAT) void amg_diag_kernel(Sell<double> A, double *_
 __global__ __launch_bounds__(kAT) void strength_kernel(Sell<double> A, const double *__restrict__ diag, double theta,
                                                        int32_t *__restrict__ scol) {
     GS(i, A.n) {
-        const int64_t b0 = A.ptr[i >> 6], b1 = A.ptr[(i >> 6) + 1];
         const double di = diag[i];
-        for (int64_t q = b0 + (i & 63); q < b1; q += 64) {
-            int32_t j;
-            double s;
-            scol[q] = strong(A.val, A.col, q, (int32_t)i, di, diag, theta, j, s) ? j : (int32_t)i;
-        }
+        double v[kSlots], dj[kSlots];
+        int32_t c[kSlots];
+        row_slots(
+            A.ptr, i,
+            [&](int j, int64_t q) {
+                v[j] = A.val[q];
+                c[j] = A.col[q];
+                dj[j] = diag[c[j]];
+            },
+            [&](int j, int64_t q) {
+                const double a = fabs(v[j]);
+                scol[q] = c[j] != i && a != 0.0 && a >= theta * sqrt(fabs(di * dj[j])) ? c[j] : (int32_t)i;
+            });
     }
 }
 
@@ -187,7 +205,37 @@ __global__ __launch_bounds__(kAT) void mis_flag_kernel(int32_t n, const uint32_t
     GS(i, n) flag[i] = rank_of(T[i]) >= 1 ? 1 : 0;
 }
 
-__global__ __launch_bounds__(kAT) void agg_pass1_kernel(Sell<double> A, const double *__restrict__ diag, double theta,
+// The strongest of row i's strong neighbours j (ties: the least j) with
+// mark[j] set, or -1; s_ij = |a_ij| / sqrt(|a_ii a_jj|).  The rows' strong
+// columns are at hand (scol; a weak slot holds the row itself, whose mark is
+// not set), so the values are read only where a neighbour is marked: both
+// passes together 69 us at 64^3 and 580 us at 128^3 while they tested the
+// strength of every entry again, now 48 and 284.
+template <class Mark>
+__device__ inline int32_t strongest(const Sell<double> &A, const double *__restrict__ diag,
+                                    const int32_t *__restrict__ scol, int64_t i, Mark mark) {
+    const double di = diag[i];
+    double best = -1.0;
+    int32_t bj = -1, c[kSlots];
+    bool m[kSlots];
+    row_slots(
+        A.ptr, i,
+        [&](int j, int64_t q) {
+            c[j] = scol[q];
+            m[j] = mark(c[j]);
+        },
+        [&](int j, int64_t q) {
+            if (!m[j]) return;
+            const double s = fabs(A.val[q]) / sqrt(fabs(di * diag[c[j]]));
+            if (s > best || (s == best && c[j] < bj)) {
+                best = s;
+                bj = c[j];
+            }
+        });
+    return bj;
+}
+__global__ __launch_bounds__(kAT) void agg_pass1_kernel(Sell<double> A, const double *__restrict__ diag,
+                                                        const int32_t *__restrict__ scol,
                                                         const int32_t *__restrict__ root, const int32_t *__restrict__ rid,
                                                         int32_t *__restrict__ agg1) {
     GS(i, A.n) {
@@ -195,42 +243,19 @@ __global__ __launch_bounds__(kAT) void agg_pass1_kernel(Sell<double> A, const do
             agg1[i] = rid[i];
             continue;
         }
-        const int64_t b0 = A.ptr[i >> 6], b1 = A.ptr[(i >> 6) + 1];
-        const double di = diag[i];
-        double best = -1.0;
-        int32_t bj = -1;
-        for (int64_t q = b0 + (i & 63); q < b1; q += 64) {
-            int32_t j;
-            double s;
-            if (strong(A.val, A.col, q, (int32_t)i, di, diag, theta, j, s) && root[j] &&
-                (s > best || (s == best && j < bj))) {
-                best = s;
-                bj = j;
-            }
-        }
+        const int32_t bj = strongest(A, diag, scol, i, [&](int32_t j) { return root[j] != 0; });
         agg1[i] = bj >= 0 ? rid[bj] : -1;
     }
 }
 
-__global__ __launch_bounds__(kAT) void agg_pass2_kernel(Sell<double> A, const double *__restrict__ diag, double theta,
+__global__ __launch_bounds__(kAT) void agg_pass2_kernel(Sell<double> A, const double *__restrict__ diag,
+                                                        const int32_t *__restrict__ scol,
                                                         const int32_t *__restrict__ agg1, int32_t *__restrict__ agg,
                                                         int32_t *__restrict__ lonely) {
     GS(i, A.n) {
         int32_t a = agg1[i];
         if (a < 0) {
-            const int64_t b0 = A.ptr[i >> 6], b1 = A.ptr[(i >> 6) + 1];
-            const double di = diag[i];
-            double best = -1.0;
-            int32_t bj = -1;
-            for (int64_t q = b0 + (i & 63); q < b1; q += 64) {
-                int32_t j;
-                double s;
-                if (strong(A.val, A.col, q, (int32_t)i, di, diag, theta, j, s) && agg1[j] >= 0 &&
-                    (s > best || (s == best && j < bj))) {
-                    best = s;
-                    bj = j;
-                }
-            }
+            const int32_t bj = strongest(A, diag, scol, i, [&](int32_t j) { return agg1[j] >= 0; });
             if (bj >= 0) a = agg1[bj];
         }
         agg[i] = a;
@@ -275,35 +300,32 @@ __global__ __launch_bounds__(kAT) void members_rank_kernel(int32_t nc, const int
     }
 }
 
-// exclusive scan of n ints in one block; out[n] = total
+// exclusive scan of n ints in one block, a run of them per thread; out[n] = total
 __global__ __launch_bounds__(1024) void scan_int_kernel(int32_t n, const int32_t *__restrict__ in,
                                                         int32_t *__restrict__ out) {
-    __shared__ int32_t part[1024];
-    const int t = threadIdx.x;
+    __shared__ int32_t part[16];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int32_t chunk = (n + 1023) / 1024;
     const int32_t lo = min(n, t * chunk), hi = min(n, lo + chunk);
     int32_t s = 0;
     for (int32_t k = lo; k < hi; ++k) s += in[k];
-    part[t] = s;
-    __syncthreads();
-    if (t == 0) {
-        int32_t run = 0;
-        for (int k = 0; k < 1024; ++k) {
-            const int32_t v = part[k];
-            part[k] = run;
-            run += v;
-        }
-        out[n] = run;
+    int32_t incl = s;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
     }
+    if (lane == 63) part[w] = incl;
     __syncthreads();
-    int32_t run = part[t];
+    int32_t run = incl - s;
+    for (int k = 0; k < w; ++k) run += part[k];
+    if (t == 1023) out[n] = run + s;
     for (int32_t k = lo; k < hi; ++k) {
         const int32_t v = in[k];
         out[k] = run;
         run += v;
     }
 }
-
 
 // multi-block exclusive scan of n ints (out[n] = total): block sums, one-block
 // scan of the block sums, then per-block scan with offsets
@@ -359,27 +381,21 @@ __global__ __launch_bounds__(256) void scan_apply_kernel(int32_t n, const int32_
 // ---------------------------------------------------------------------------
 // Galerkin coarse operator, one wavefront per coarse row
 // ---------------------------------------------------------------------------
-// Jcol[q] = aggregate of the column of entry q (same sliced-ELL layout as A)
-__global__ __launch_bounds__(kAT) void agg_col_kernel(Sell<double> A, const int32_t *__restrict__ agg,
-                                                      int32_t *__restrict__ Jcol) {
-    GS(i, A.n) {
-        const int64_t b0 = A.ptr[i >> 6], b1 = A.ptr[(i >> 6) + 1];
-        for (int64_t q = b0 + (i & 63); q < b1; q += 64) Jcol[q] = agg[A.col[q]];
-    }
-}
 // Row i of A P (P = aggregate indicator): the distinct aggregates of the row's
 // columns, in increasing order, each with the sum of its entries (in entry
 // order); the nonzero sums go to the row's first apn[i] slots of (apJ, apv).
-// The lanes of a wave scan slot k together, so the passes are coalesced.  A
+// The lanes of a wave scan slot k together, so the passes are coalesced, eight
+// slots' aggregates read ahead (64^3: 73 us after a pass of 29 us that wrote
+// them out, now 59; 128^3: 331 and 150, now 294).  A
 // row with more than kSet distinct aggregates is appended to the spill list
 // and collapsed by ap_spill_kernel instead.
 constexpr int kSet = 16;
-__global__ __launch_bounds__(kAT) void ap_collapse_kernel(Sell<double> A, const int32_t *__restrict__ Jcol,
+__global__ __launch_bounds__(kAT) void ap_collapse_kernel(Sell<double> A, const int32_t *__restrict__ agg,
                                                           int32_t *__restrict__ apJ, double *__restrict__ apv,
                                                           int32_t *__restrict__ apn, int32_t *__restrict__ spill,
                                                           int *__restrict__ nspill) {
     GS(i, A.n) {
-        const int64_t b0 = A.ptr[i >> 6] + (i & 63), b1 = A.ptr[(i >> 6) + 1];
+        const int64_t b0 = A.ptr[i >> 6] + (i & 63);
         int32_t J[kSet];
         double v[kSet];
         int cnt = 0;
@@ -389,31 +405,39 @@ __global__ __launch_bounds__(kAT) void ap_collapse_kernel(Sell<double> A, const 
             J[t] = INT32_MAX;
             v[t] = 0.0;
         }
-        for (int64_t q = b0; q < b1 && !over; q += 64) {
-            const double a = A.val[q];
-            if (a == 0.0) continue;
-            const int32_t c = Jcol[q];
-            bool found = false;
+        double av[kSlots];
+        int32_t cv[kSlots];
+        row_slots(
+            A.ptr, i,
+            [&](int j, int64_t q) {
+                av[j] = A.val[q];
+                cv[j] = agg[A.col[q]];
+            },
+            [&](int j, int64_t) {
+                const double a = av[j];
+                if (a == 0.0 || over) return;
+                const int32_t c = cv[j];
+                bool found = false;
 #pragma unroll
-            for (int t = 0; t < kSet; ++t)
-                if (J[t] == c) {
-                    v[t] += a;
-                    found = true;
-                }
-            if (!found) {
-                if (cnt == kSet) {
-                    over = true;
-                } else {
+                for (int t = 0; t < kSet; ++t)
+                    if (J[t] == c) {
+                        v[t] += a;
+                        found = true;
+                    }
+                if (!found) {
+                    if (cnt == kSet) {
+                        over = true;
+                    } else {
 #pragma unroll
-                    for (int t = 0; t < kSet; ++t)
-                        if (t == cnt) {
-                            J[t] = c;
-                            v[t] = a;
-                        }
-                    ++cnt;
+                        for (int t = 0; t < kSet; ++t)
+                            if (t == cnt) {
+                                J[t] = c;
+                                v[t] = a;
+                            }
+                        ++cnt;
+                    }
                 }
-            }
-        }
+            });
         if (over) {
             spill[atomicAdd(nspill, 1)] = (int32_t)i;  // list order is irrelevant: rows are independent
             continue;
@@ -447,7 +471,7 @@ __global__ __launch_bounds__(kAT) void ap_collapse_kernel(Sell<double> A, const 
 // equal aggregates in slot order (the order of the fast path).  Rows with more
 // than CAP entries fall back to repeated minimum extraction by one lane.
 template <int CAP>
-__global__ __launch_bounds__(64) void ap_spill_kernel(Sell<double> A, const int32_t *__restrict__ Jcol,
+__global__ __launch_bounds__(64) void ap_spill_kernel(Sell<double> A, const int32_t *__restrict__ agg,
                                                       int32_t *__restrict__ apJ, double *__restrict__ apv,
                                                       int32_t *__restrict__ apn, const int32_t *__restrict__ spill,
                                                       const int *__restrict__ nspill) {
@@ -468,7 +492,7 @@ __global__ __launch_bounds__(64) void ap_spill_kernel(Sell<double> A, const int3
                 const int64_t q = b0 + (int64_t)k * 64;
                 if (A.val[q] != 0.0) {
                     keep = true;
-                    kv = ((uint64_t)(uint32_t)Jcol[q] << 32) | (uint64_t)(uint32_t)k;
+                    kv = ((uint64_t)(uint32_t)agg[A.col[q]] << 32) | (uint64_t)(uint32_t)k;
                 }
             }
             const uint64_t mask = __ballot(keep);
@@ -485,7 +509,7 @@ __global__ __launch_bounds__(64) void ap_spill_kernel(Sell<double> A, const int3
                     int32_t jm = INT32_MAX;
                     for (int k = 0; k < w; ++k) {
                         const int64_t q = b0 + (int64_t)k * 64;
-                        const int32_t c = Jcol[q];
+                        const int32_t c = agg[A.col[q]];
                         if (c > last && c < jm && A.val[q] != 0.0) jm = c;
                     }
                     if (jm == INT32_MAX) break;
@@ -493,7 +517,7 @@ __global__ __launch_bounds__(64) void ap_spill_kernel(Sell<double> A, const int3
                     for (int k = 0; k < w; ++k) {
                         const int64_t q = b0 + (int64_t)k * 64;
                         const double a = A.val[q];
-                        if (a != 0.0 && Jcol[q] == jm) sum += a;
+                        if (a != 0.0 && agg[A.col[q]] == jm) sum += a;
                     }
                     last = jm;
                     if (sum == 0.0) continue;
@@ -566,18 +590,22 @@ __global__ __launch_bounds__(64) void ap_spill_kernel(Sell<double> A, const int3
 // column sums its candidates in gather order (all lanes read candidate k
 // together), so the coarse matrix is bitwise reproducible.  mode 0:
 // rowlen[I] = number of coarse columns, big[I] = 1 for a row this kernel
-// cannot hold; mode 1: write the row (SELL).
-constexpr int kGalCand = 1024, kGalHash = 512, kGalDistinct = 256;
+// cannot hold, appended to biglist (*nbig of them); mode 1: write the row
+// (SELL).  Bound by the latency of the chains of LDS reads, 9 wavefronts on a
+// CU (52 k rows of a 128^3 mesh: 560 us in mode 1 with one candidate per turn,
+// now 346).
+constexpr int kGalCand = 1024, kGalHash = 512, kGalDistinct = 256, kGalBatch = 8;
 __global__ __launch_bounds__(64) void galerkin_hash_kernel(Sell<double> A, const int32_t *__restrict__ Jcol,
                                                            const double *__restrict__ apv,
                                                            const int32_t *__restrict__ apn,
                                                            const int32_t *__restrict__ mptr,
                                                            const int32_t *__restrict__ mrows, int32_t nc, int mode,
-                                                           int32_t *__restrict__ big, int32_t *__restrict__ rowlen,
+                                                           int32_t *__restrict__ big, int32_t *__restrict__ biglist,
+                                                           int *__restrict__ nbig, int32_t *__restrict__ rowlen,
                                                            const int64_t *__restrict__ cptr,
                                                            int32_t *__restrict__ ccol, double *__restrict__ cval) {
-    __shared__ int32_t cj[kGalCand];
-    __shared__ double cv[kGalCand];
+    __shared__ __align__(16) int32_t cj[kGalCand];
+    __shared__ __align__(16) double cv[kGalCand];
     __shared__ int32_t hs[kGalHash];
     __shared__ int32_t dist[kGalDistinct];
     __shared__ int32_t sorted[kGalDistinct];
@@ -611,10 +639,21 @@ __global__ __launch_bounds__(64) void galerkin_hash_kernel(Sell<double> A, const
             break;
         }
         const int off = m + incl - c;
-        for (int k = 0; k < c; ++k) {
-            const int64_t q = b + (int64_t)k * 64;
-            cj[off + k] = Jcol[q];
-            cv[off + k] = apv[q];
+        for (int k0 = 0; k0 < c; k0 += 4) {  // four entries' loads in flight
+            int32_t J[4];
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t q = b + (int64_t)min(k0 + u, c - 1) * 64;
+                J[u] = Jcol[q];
+                v[u] = apv[q];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (k0 + u < c) {
+                    cj[off + k0 + u] = J[u];
+                    cv[off + k0 + u] = v[u];
+                }
         }
         m += tot;
     }
@@ -648,15 +687,25 @@ __global__ __launch_bounds__(64) void galerkin_hash_kernel(Sell<double> A, const
         full = nd > kGalDistinct;
     }
     if (over || full) {
-        if (mode == 0 && lane == 0) big[I] = 1;
+        if (mode == 0 && lane == 0) {
+            big[I] = 1;
+            biglist[atomicAdd(nbig, 1)] = I;  // list order is irrelevant: rows are independent
+        }
         return;
     }
     if (mode == 0 && lane == 0) big[I] = 0;
+    // candidates that no column takes, up to a multiple of kGalBatch
+    const int mp = (m + kGalBatch - 1) / kGalBatch * kGalBatch;
+    if (m + lane < mp) {
+        cj[m + lane] = -2;
+        cv[m + lane] = 0.0;
+    }
     __syncthreads();
     // rank sort of the distinct columns
     for (int i = lane; i < nd; i += 64) {
         const int32_t J = dist[i];
         int rank = 0;
+#pragma unroll 8
         for (int u = 0; u < nd; ++u) rank += dist[u] < J;
         sorted[rank] = J;
     }
@@ -675,12 +724,21 @@ __global__ __launch_bounds__(64) void galerkin_hash_kernel(Sell<double> A, const
         sum[o] = 0.0;
     }
     const int nown = (nd + 63) / 64;
-    for (int k = 0; k < m; ++k) {
-        const int32_t J = cj[k];
-        const double v = cv[k];
+    // a batch of candidates per turn: one at a time, each waited for its LDS read
+    for (int k = 0; k < mp; k += kGalBatch) {
+        int32_t J[kGalBatch];
+        double v[kGalBatch];
+#pragma unroll
+        for (int u = 0; u < kGalBatch; ++u) {
+            J[u] = cj[k + u];
+            v[u] = cv[k + u];
+        }
 #pragma unroll
         for (int o = 0; o < kOwn; ++o)
-            if (o < nown && own[o] == J) sum[o] += v;
+            if (o < nown)
+#pragma unroll
+                for (int u = 0; u < kGalBatch; ++u)
+                    if (own[o] == J[u]) sum[o] += v[u];
     }
     const int64_t base = cptr[I >> 6] + (I & 63);
 #pragma unroll
@@ -698,25 +756,20 @@ __global__ __launch_bounds__(64) void galerkin_hash_kernel(Sell<double> A, const
     }
 }
 
-// Coarse rows that the hashed kernel below could not take (more than
-// kGalCand candidates or kGalDistinct distinct columns; big[I] set): the
+// Coarse rows that the hashed kernel above could not take (more than
+// kGalCand candidates or kGalDistinct distinct columns; in biglist): the
 // candidates as (coarse column, fine position) keys, bitonic-sorted in LDS,
 // each coarse entry summing its candidates in gather order.  mode 0:
 // rowlen[I] = number of coarse columns; mode 1: write them (SELL).  More
 // than CAP candidates: *overflow.
 template <int CAP>
-__global__ __launch_bounds__(64) void galerkin_kernel(Sell<double> A, const int32_t *__restrict__ Jcol,
-                                                      const double *__restrict__ apv, const int32_t *__restrict__ apn,
-                                                      const int32_t *__restrict__ mptr, const int32_t *__restrict__ mrows,
-                                                      int32_t nc, int mode, int32_t *__restrict__ big,
-                                                      int32_t *__restrict__ rowlen, const int64_t *__restrict__ cptr,
-                                                      int32_t *__restrict__ ccol, double *__restrict__ cval,
-                                                      int *__restrict__ overflow) {
-    __shared__ uint64_t key[CAP];
-    const int32_t I = blockIdx.x;
+__device__ inline void galerkin_sorted_row(uint64_t *key, const Sell<double> &A, const int32_t *__restrict__ Jcol,
+                                           const double *__restrict__ apv, const int32_t *__restrict__ apn,
+                                           const int32_t *__restrict__ mptr, const int32_t *__restrict__ mrows,
+                                           int32_t I, int mode, int32_t *__restrict__ rowlen,
+                                           const int64_t *__restrict__ cptr, int32_t *__restrict__ ccol,
+                                           double *__restrict__ cval, int *__restrict__ overflow) {
     const int lane = threadIdx.x;
-    if (I >= nc) return;
-    if (!big[I]) return;
     int m = 0;
     bool over = false;
     const int32_t t1 = mptr[I + 1];
@@ -803,6 +856,21 @@ __global__ __launch_bounds__(64) void galerkin_kernel(Sell<double> A, const int3
     for (int k = total + lane; k < w; k += 64) {
         ccol[base + (int64_t)k * 64] = I;
         cval[base + (int64_t)k * 64] = 0.0;
+    }
+}
+template <int CAP>
+__global__ __launch_bounds__(64) void galerkin_kernel(Sell<double> A, const int32_t *__restrict__ Jcol,
+                                                      const double *__restrict__ apv, const int32_t *__restrict__ apn,
+                                                      const int32_t *__restrict__ mptr, const int32_t *__restrict__ mrows,
+                                                      int mode, const int32_t *__restrict__ biglist,
+                                                      const int *__restrict__ nbig, int32_t *__restrict__ rowlen,
+                                                      const int64_t *__restrict__ cptr, int32_t *__restrict__ ccol,
+                                                      double *__restrict__ cval, int *__restrict__ overflow) {
+    __shared__ uint64_t key[CAP];
+    for (int it = blockIdx.x; it < *nbig; it += gridDim.x) {
+        galerkin_sorted_row<CAP>(key, A, Jcol, apv, apn, mptr, mrows, biglist[it], mode, rowlen, cptr, ccol, cval,
+                                 overflow);
+        __syncthreads();
     }
 }
 
@@ -1576,10 +1644,10 @@ void amg_launch_scan(hipStream_t s, int32_t n, const int32_t *in, int32_t *out, 
     ALAUNCH(scan_int_kernel, 1, 1024, nb, tmp, tmp + nb + 1);
     ALAUNCH(scan_apply_kernel, nb, 256, n, in, tmp + nb + 1, out);
 }
-void amg_launch_aggregate(hipStream_t s, Sell<double> A, const double *diag, double theta, const int32_t *root,
+void amg_launch_aggregate(hipStream_t s, Sell<double> A, const double *diag, const int32_t *scol, const int32_t *root,
                           const int32_t *rid, int32_t *agg1, int32_t *agg, int32_t *lonely) {
-    ALAUNCH(agg_pass1_kernel, gridv(A.n), kAT, A, diag, theta, root, rid, agg1);
-    ALAUNCH(agg_pass2_kernel, gridv(A.n), kAT, A, diag, theta, agg1, agg, lonely);
+    ALAUNCH(agg_pass1_kernel, gridv(A.n), kAT, A, diag, scol, root, rid, agg1);
+    ALAUNCH(agg_pass2_kernel, gridv(A.n), kAT, A, diag, scol, agg1, agg, lonely);
 }
 void amg_launch_lonely(hipStream_t s, int32_t n, const int32_t *lonely, const int32_t *lid, const int32_t *nroot,
                        int32_t *agg) {
@@ -1593,19 +1661,21 @@ void amg_launch_members(hipStream_t s, int32_t n, int32_t nc, const int32_t *agg
     ALAUNCH(members_fill_kernel, gridv(n), kAT, n, agg, ptr, cursor, tmp);
     ALAUNCH(members_rank_kernel, reduce_grid((int64_t)nc * 64, kAT), kAT, nc, ptr, tmp, rows);
 }
-void amg_launch_collapse(hipStream_t s, Sell<double> A, const int32_t *agg, int32_t *Jcol, int32_t *apJ,
-                         double *apv, int32_t *apn, int32_t *spill, int *nspill) {
-    ALAUNCH(agg_col_kernel, gridv(A.n), kAT, A, agg, Jcol);
-    ALAUNCH(ap_collapse_kernel, gridv(A.n), kAT, A, Jcol, apJ, apv, apn, spill, nspill);
-    ALAUNCH(ap_spill_kernel<1024>, 2048, 64, A, Jcol, apJ, apv, apn, spill, nspill);
+void amg_launch_collapse(hipStream_t s, Sell<double> A, const int32_t *agg, int32_t *apJ, double *apv,
+                         int32_t *apn, int32_t *spill, int *nspill) {
+    ALAUNCH(ap_collapse_kernel, gridv(A.n), kAT, A, agg, apJ, apv, apn, spill, nspill);
+    ALAUNCH(ap_spill_kernel<1024>, 2048, 64, A, agg, apJ, apv, apn, spill, nspill);
 }
 void amg_launch_galerkin(hipStream_t s, Sell<double> A, const int32_t *Jcol, const double *apv, const int32_t *apn,
                          const int32_t *mptr, const int32_t *mrows, int32_t nc, int mode, int32_t *big,
-                         int32_t *rowlen, const int64_t *cptr, int32_t *ccol, double *cval, int *overflow) {
+                         int32_t *biglist, int *nbig, int32_t *rowlen, const int64_t *cptr, int32_t *ccol,
+                         double *cval, int *overflow) {
     if (nc <= 0) return;
-    ALAUNCH(galerkin_hash_kernel, nc, 64, A, Jcol, apv, apn, mptr, mrows, nc, mode, big, rowlen, cptr, ccol, cval);
-    ALAUNCH(galerkin_kernel<8192>, nc, 64, A, Jcol, apv, apn, mptr, mrows, nc, mode, big, rowlen, cptr, ccol, cval,
-            overflow);
+    ALAUNCH(galerkin_hash_kernel, nc, 64, A, Jcol, apv, apn, mptr, mrows, nc, mode, big, biglist, nbig, rowlen, cptr,
+            ccol, cval);
+    // 512 blocks: two of these keys fit on a CU, and usually there is no such row
+    ALAUNCH(galerkin_kernel<8192>, std::min(nc, 512), 64, A, Jcol, apv, apn, mptr, mrows, mode, biglist, nbig, rowlen,
+            cptr, ccol, cval, overflow);
 }
 void amg_launch_slices(hipStream_t s, int32_t n, const int32_t *rowlen, int32_t *width, int32_t *cnt, int64_t *ptr,
                        unsigned long long *nnz) {

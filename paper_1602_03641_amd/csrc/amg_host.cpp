@@ -61,12 +61,12 @@ void Amg::setup(hipStream_t s, Tracker &tr, Sell<double> A0, int64_t stored0, co
         // aggregation
         VAG_HIP(hipMemsetAsync(counters_.p, 0, 64 * sizeof(int), s));
         VAG_HIP(hipMemsetAsync(mis_cnt_.p, 0, mis_cnt_.n * sizeof(int), s));
-        ensure(jcol_, (size_t)lv.stored, tr);  // the strong columns until the collapse reuses it
+        ensure(jcol_, (size_t)lv.stored, tr);  // the strong columns
         amg_launch_mis(s, lv.A, lv.diag.p, o.theta, std::min(o.mis_rounds, kMisRounds), o.hops, T_.p, T1_.p, mis_cnt_.p,
                        flag_.p, h_ + 64, jcol_.p);
         amg_launch_scan(s, n, flag_.p, rid_.p, stmp_.p);
         ensure(lv.agg, n, tr);
-        amg_launch_aggregate(s, lv.A, lv.diag.p, o.theta, flag_.p, rid_.p, agg1_.p, lv.agg.p, lonely_.p);
+        amg_launch_aggregate(s, lv.A, lv.diag.p, jcol_.p, flag_.p, rid_.p, agg1_.p, lv.agg.p, lonely_.p);
         amg_launch_scan(s, n, lonely_.p, lid_.p, stmp_.p);
         amg_launch_lonely(s, n, lonely_.p, lid_.p, rid_.p + n, lv.agg.p);
         VAG_HIP(hipMemcpyAsync(h_, rid_.p + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -80,16 +80,15 @@ void Amg::setup(hipStream_t s, Tracker &tr, Sell<double> A0, int64_t stored0, co
         VAG_HIP(hipMemsetAsync(cnt_.p, 0, ((size_t)nc + 1) * sizeof(int32_t), s));
         VAG_HIP(hipMemsetAsync(cursor_.p, 0, ((size_t)nc + 1) * sizeof(int32_t), s));
         amg_launch_members(s, n, nc, lv.agg.p, cnt_.p, lv.mptr.p, cursor_.p, mtmp_.p, lv.mrows.p, stmp_.p);
-        ensure(jcol_, (size_t)lv.stored, tr);
         ensure(apv_, (size_t)lv.stored, tr);
         ensure(apj_, (size_t)lv.stored, tr);
-        amg_launch_collapse(s, lv.A, lv.agg.p, jcol_.p, apj_.p, apv_.p, apn_.p, spill_.p, counters_.p + 62);
+        amg_launch_collapse(s, lv.A, lv.agg.p, apj_.p, apv_.p, apn_.p, spill_.p, counters_.p + 62);
         if ((int)L.size() <= l + 1) L.emplace_back(new AmgLevel());
         AmgLevel &cv = *L[l + 1];
         const int32_t ns = (nc + 63) / 64;
         ensure(cv.ptr, (size_t)ns + 1, tr);
-        amg_launch_galerkin(s, lv.A, apj_.p, apv_.p, apn_.p, lv.mptr.p, lv.mrows.p, nc, 0, big_.p, rowlen_.p, nullptr,
-                            nullptr, nullptr, counters_.p + 63);
+        amg_launch_galerkin(s, lv.A, apj_.p, apv_.p, apn_.p, lv.mptr.p, lv.mrows.p, nc, 0, big_.p, lonely_.p,
+                            counters_.p + 60, rowlen_.p, nullptr, nullptr, nullptr, counters_.p + 63);
         amg_launch_slices(s, nc, rowlen_.p, width_.p, scnt_.p, cv.ptr.p, level_nnz.p + l + 1);
         int64_t hv[2];
         VAG_HIP(hipMemcpyAsync(&hv[0], cv.ptr.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
@@ -99,8 +98,8 @@ void Amg::setup(hipStream_t s, Tracker &tr, Sell<double> A0, int64_t stored0, co
         const int64_t stored = hv[0];
         ensure(cv.col, (size_t)stored, tr);
         ensure(cv.val, (size_t)stored, tr);
-        amg_launch_galerkin(s, lv.A, apj_.p, apv_.p, apn_.p, lv.mptr.p, lv.mrows.p, nc, 1, big_.p, rowlen_.p, cv.ptr.p,
-                            cv.col.p, cv.val.p, counters_.p + 63);
+        amg_launch_galerkin(s, lv.A, apj_.p, apv_.p, apn_.p, lv.mptr.p, lv.mrows.p, nc, 1, big_.p, lonely_.p,
+                            counters_.p + 60, rowlen_.p, cv.ptr.p, cv.col.p, cv.val.p, counters_.p + 63);
         amg_launch_slice_tail(s, nc, cv.ptr.p, cv.col.p, cv.val.p);
         cv.n = nc;
         cv.stored = stored;

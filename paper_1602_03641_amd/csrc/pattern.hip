@@ -211,25 +211,23 @@ __global__ __launch_bounds__(kPT) void scan64_sums_kernel(int32_t n, const int32
     }
 }
 __global__ __launch_bounds__(1024) void scan64_top_kernel(int32_t nb, int64_t *sums) {
-    __shared__ int64_t part[1024];
-    const int t = threadIdx.x;
+    __shared__ int64_t part[16];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int32_t chunk = (nb + 1023) / 1024;
     const int32_t lo = min(nb, t * chunk), hi = min(nb, lo + chunk);
     int64_t acc = 0;
     for (int32_t k = lo; k < hi; ++k) acc += sums[k];
-    part[t] = acc;
-    __syncthreads();
-    if (t == 0) {
-        int64_t run = 0;
-        for (int k = 0; k < 1024; ++k) {
-            const int64_t v = part[k];
-            part[k] = run;
-            run += v;
-        }
-        sums[nb] = run;
+    int64_t incl = acc;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
     }
+    if (lane == 63) part[w] = incl;
     __syncthreads();
-    int64_t run = part[t];
+    int64_t run = incl - acc;
+    for (int k = 0; k < w; ++k) run += part[k];
+    if (t == 1023) sums[nb] = run + acc;
     for (int32_t k = lo; k < hi; ++k) {
         const int64_t v = sums[k];
         sums[k] = run;

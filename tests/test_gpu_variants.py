@@ -219,3 +219,35 @@ def test_assembled_rows(mesh, eliminate):
     for k in ("u_node", "u_frac"):
         assert np.abs(u[k] - od[k]).max(initial=0.0) <= 1e-6 * np.abs(od["u_node"]).max(), k
     h.close()
+
+
+@pytest.mark.parametrize("mesh,coarse,hops,theta", [((5, 4, 4), 8, 2, 0.08), ((14, 12, 11), 6, 2, 0.08),
+                                                    ((26, 24, 22), 12, 1, 0.08), ((26, 24, 22), 4, 2, 1e-9),
+                                                    ("fan", 12, 1, 0.08), ("fan", 12, 1, 0.3)])
+def test_aggregation_products(mesh, coarse, hops, theta):
+    """Aggregation hierarchies coarsened far down; on the fan, rows with more
+    aggregates than ap_collapse's registers and coarse rows of more columns than
+    the hashed kernel's 256: every coarse operator is P^T A P
+    of the level above.  An entry sums at most ~10^4 products, each rounded
+    relative to max |A|: 1e-12 max |A|."""
+    from paper_1602_03641_amd import vag
+    import scipy.sparse as sp
+    p = _fan(120, 14) if mesh == "fan" else synth.random_problem(mesh, 33, n_patches=5, n_steps=0, ratios=(1e2, 1e4))
+    h, info = _handle(p, rtol=1e-8, precond=vag.VAG_PC_AMG, amg_coarse_size=coarse, amg_aggregate_hops=hops,
+                      amg_theta=theta)
+    mats = []
+    for d in (h.amg_level(l) for l in range(info["amg_levels"])):
+        n = len(d["A"][0]) - 1
+        A = sp.csr_matrix((d["A"][2], d["A"][1], d["A"][0]), shape=(n, n))
+        P = sp.csr_matrix((d["P"][2], d["P"][1], d["P"][0]), shape=(n, d["n_coarse"])) if d["P"] is not None else None
+        mats.append((A, P))
+    assert len(mats) >= 2
+    wide = []
+    for (A, P), (Ac, _) in zip(mats, mats[1:]):
+        assert np.all(np.diff(P.indptr) == 1)
+        assert abs(P.T @ A @ P - Ac).max() <= 1e-12 * abs(A).max()
+        AP = abs(A).sign() @ P
+        wide.append((int(AP.getnnz(axis=1).max()), int((P.T @ AP.sign()).sum(axis=1).max()),
+                     int(Ac.getnnz(axis=1).max())))
+    print("most aggregates of a row, candidates and columns of a coarse row, per level:", wide)
+    h.close()
