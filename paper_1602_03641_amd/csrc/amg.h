@@ -14,18 +14,29 @@ constexpr int32_t kSmallRows = (int32_t)kSplitMaxRows;
 
 // kernel launchers (amg.hip)
 void amg_launch_diag(hipStream_t s, Sell<double> A, double *diag, double *dinv);
-// roots of the coarsening (flag); scol: a stored-size scratch array;
-// undecided: rounds * kCntSlots * kCntStride zeroed counters; hcnt: pinned
-// host memory of kCntSlots * kCntStride ints
+// what the coarsening of a level starts from: the keys T and T1 (n each), and
+// what is cleared: undecided (kMisRounds * kCntSlots * kCntStride), counters
+// (64), cnt and cursor (n + 1 each)
 constexpr int kCntSlots = 16, kCntStride = 32, kMisRounds = 48;
+struct CoarsenInit {
+    uint32_t *T, *T1;
+    int *undecided, *counters;
+    int32_t *cnt, *cursor;
+    int nundecided = kMisRounds * kCntSlots * kCntStride;
+};
+// roots of the coarsening (flag); scol: a stored-size scratch array; progress:
+// pinned host memory
 void amg_launch_mis(hipStream_t s, Sell<double> A, const double *diag, double theta, int rounds, int hops,
-                    uint32_t *T, uint32_t *T1, int *undecided, int32_t *flag, int *hcnt, int32_t *scol);
-void amg_launch_scan(hipStream_t s, int32_t n, const int32_t *in, int32_t *out, int32_t *tmp);
+                    const CoarsenInit &I, int32_t *flag, int32_t *scol, int *progress);
+// out[k] = the sum of in[0..k), out[n] = *host (pinned, may be null) = the total
+void amg_launch_scan(hipStream_t s, int32_t n, const int32_t *in, int32_t *out, int32_t *tmp, int *host = nullptr);
+// nodes reached by neither pass become singleton aggregates after the nroot
+// roots; *host (pinned) = their number
+void amg_launch_lonely(hipStream_t s, int32_t n, const int32_t *lonely, const int32_t *nroot, int32_t *agg,
+                       int32_t *tmp, int *host);
 // scol: the strong columns that amg_launch_mis left
 void amg_launch_aggregate(hipStream_t s, Sell<double> A, const double *diag, const int32_t *scol, const int32_t *root,
                           const int32_t *rid, int32_t *agg1, int32_t *agg, int32_t *lonely);
-void amg_launch_lonely(hipStream_t s, int32_t n, const int32_t *lonely, const int32_t *lid, const int32_t *nroot,
-                       int32_t *agg);
 void amg_launch_members(hipStream_t s, int32_t n, int32_t nc, const int32_t *agg, int32_t *cnt, int32_t *ptr,
                         int32_t *cursor, int32_t *tmp, int32_t *rows, int32_t *scan_tmp);
 // row i of A P into the first apn[i] slots of (apJ, apv); nspill zeroed by the caller
@@ -38,9 +49,10 @@ void amg_launch_galerkin(hipStream_t s, Sell<double> A, const int32_t *Jcol, con
                          int32_t *biglist, int *nbig, int32_t *rowlen, const int64_t *cptr, int32_t *ccol,
                          double *cval, int *overflow);
 // slice widths and pointers from row lengths; *nnz = the number of entries
-// (cnt: one int per slice, scratch)
+// (cnt: one int per slice, scratch); host, flag, host_flag: as launch_slice_scan
 void amg_launch_slices(hipStream_t s, int32_t n, const int32_t *rowlen, int32_t *width, int32_t *cnt, int64_t *ptr,
-                       unsigned long long *nnz);
+                       unsigned long long *nnz, int64_t *host = nullptr, const int *flag = nullptr,
+                       int *host_flag = nullptr);
 void amg_launch_slice_tail(hipStream_t s, int32_t n, const int64_t *ptr, int32_t *col, double *val);
 // D = A^-1 (dense, row-major); work holds 128 * A.n doubles
 void amg_launch_dense_inverse(hipStream_t s, Sell<double> A, double *D, double *work);
@@ -228,7 +240,7 @@ class Amg {
 
   private:
     DBuf<uint32_t> T_, T1_;
-    DBuf<int32_t> flag_, rid_, agg1_, lonely_, lid_, cnt_, cursor_, rowlen_, width_, big_, mtmp_, stmp_, jcol_, apn_, spill_, scnt_;
+    DBuf<int32_t> flag_, rid_, agg1_, lonely_, cnt_, cursor_, rowlen_, width_, big_, mtmp_, stmp_, jcol_, apn_, spill_, scnt_;
     DBuf<double> apv_;
     DBuf<int32_t> apj_;
     DBuf<int> counters_, mis_cnt_;

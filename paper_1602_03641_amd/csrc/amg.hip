@@ -7,7 +7,7 @@
 //              found by rounds of 2-hop max propagation of (state, priority)
 //              keys, the priority a bijective hash of the row index; later
 //              rounds exit at once when nothing is left undecided (the host
-//              looks every fourth round)
+//              polls)
 //   aggregates each root starts one; other nodes join their strongest root
 //              neighbour, then the strongest already-aggregated neighbour
 //   P          piecewise-constant interpolation (one 1 per row)
@@ -96,9 +96,14 @@ __global__ __launch_bounds__(kAT) void amg_diag_kernel(Sell<double> A, double *_
 
 // scol[q] = column of entry q if it is a strong off-diagonal coupling, else
 // the row itself (so the MIS passes gather without branches: a row's own key
-// never changes a maximum that already includes it)
+// never changes a maximum that already includes it); the keys' start, and
+// every counter of the level cleared (one launch where six were: on a small
+// level a launch is its whole time)
 __global__ __launch_bounds__(kAT) void strength_kernel(Sell<double> A, const double *__restrict__ diag, double theta,
-                                                       int32_t *__restrict__ scol) {
+                                                       int32_t *__restrict__ scol, CoarsenInit I) {
+    GS(k, I.nundecided) I.undecided[k] = 0;
+    GS(k, 64) I.counters[k] = 0;
+    GS(i, (int64_t)A.n + 1) I.cnt[i] = I.cursor[i] = 0;
     GS(i, A.n) {
         const double di = diag[i];
         double v[kSlots], dj[kSlots];
@@ -114,13 +119,8 @@ __global__ __launch_bounds__(kAT) void strength_kernel(Sell<double> A, const dou
                 const double a = fabs(v[j]);
                 scol[q] = c[j] != i && a != 0.0 && a >= theta * sqrt(fabs(di * dj[j])) ? c[j] : (int32_t)i;
             });
-    }
-}
-
-__global__ __launch_bounds__(kAT) void mis_init_kernel(int32_t n, uint32_t *__restrict__ T, uint32_t *__restrict__ T1) {
-    GS(i, n) {
-        T[i] = (1u << 30) | perm30((uint32_t)i);
-        T1[i] = 1u << 30;  // rank 1: computed in the first round
+        I.T[i] = (1u << 30) | perm30((uint32_t)i);
+        I.T1[i] = 1u << 30;  // rank 1: computed in the first round
     }
 }
 
@@ -159,8 +159,11 @@ __device__ inline bool any_count(const int *__restrict__ c) {
 // rounds then touch only the rows next to the undecided ones.
 __global__ __launch_bounds__(kAT) void mis_max_kernel(int32_t n, const int64_t *__restrict__ ptr,
                                                       const int32_t *__restrict__ scol, const uint32_t *__restrict__ Tin,
-                                                      uint32_t *__restrict__ Tout, const int *__restrict__ active) {
-    if (active && !any_count(active)) return;
+                                                      uint32_t *__restrict__ Tout, const int *__restrict__ active,
+                                                      int round, int *progress) {
+    const bool over = active && !any_count(active);
+    if (blockIdx.x == 0 && threadIdx.x == 0) host_put(progress, over ? kMisRounds + 1 : round + 1);
+    if (over) return;
     GS(i, n) {
         if (rank_of(Tout[i]) != 1) continue;
         Tout[i] = strong_max(ptr, scol, (int32_t)i, Tin);
@@ -263,13 +266,6 @@ __global__ __launch_bounds__(kAT) void agg_pass2_kernel(Sell<double> A, const do
     }
 }
 
-// nodes reached by neither pass become singleton aggregates after the roots
-__global__ __launch_bounds__(kAT) void agg_lonely_kernel(int32_t n, const int32_t *__restrict__ lonely,
-                                                         const int32_t *__restrict__ lid, const int32_t *__restrict__ nroot,
-                                                         int32_t *__restrict__ agg) {
-    GS(i, n) if (lonely[i]) agg[i] = *nroot + lid[i];
-}
-
 __global__ __launch_bounds__(kAT) void count_kernel(int32_t n, const int32_t *__restrict__ agg,
                                                     int32_t *__restrict__ cnt) {
     GS(i, n) atomicAdd(&cnt[agg[i]], 1);
@@ -300,9 +296,24 @@ __global__ __launch_bounds__(kAT) void members_rank_kernel(int32_t nc, const int
     }
 }
 
-// exclusive scan of n ints in one block, a run of them per thread; out[n] = total
+// Where a scan goes: out[k] the sum before k and out[n] the total; or, for the
+// flagged k alone, agg[k] = *base + the sum before k.  host (pinned): the total.
+struct ScanTo {
+    int32_t *out, *agg;
+    const int32_t *base;
+    int *host;
+    __device__ inline void put(int64_t k, int32_t in, int32_t run) const {
+        if (out) out[k] = run;
+        else if (in) agg[k] = *base + run;
+    }
+    __device__ inline void total(int64_t n, int32_t t) const {
+        if (out) out[n] = t;
+        if (host) host_put(host, t);
+    }
+};
+// exclusive scan of n ints in one block, a run of them per thread
 __global__ __launch_bounds__(1024) void scan_int_kernel(int32_t n, const int32_t *__restrict__ in,
-                                                        int32_t *__restrict__ out) {
+                                                        ScanTo to) {
     __shared__ int32_t part[16];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int32_t chunk = (n + 1023) / 1024;
@@ -319,15 +330,15 @@ __global__ __launch_bounds__(1024) void scan_int_kernel(int32_t n, const int32_t
     __syncthreads();
     int32_t run = incl - s;
     for (int k = 0; k < w; ++k) run += part[k];
-    if (t == 1023) out[n] = run + s;
+    if (t == 1023) to.total(n, run + s);
     for (int32_t k = lo; k < hi; ++k) {
         const int32_t v = in[k];
-        out[k] = run;
+        to.put(k, v, run);
         run += v;
     }
 }
 
-// multi-block exclusive scan of n ints (out[n] = total): block sums, one-block
+// multi-block exclusive scan of n ints: block sums, one-block
 // scan of the block sums, then per-block scan with offsets
 constexpr int kScanItems = 4;
 __global__ __launch_bounds__(256) void scan_sums_kernel(int32_t n, const int32_t *__restrict__ in,
@@ -347,7 +358,7 @@ __global__ __launch_bounds__(256) void scan_sums_kernel(int32_t n, const int32_t
     if (threadIdx.x == 0) sums[blockIdx.x] = w[0] + w[1] + w[2] + w[3];
 }
 __global__ __launch_bounds__(256) void scan_apply_kernel(int32_t n, const int32_t *__restrict__ in,
-                                                         const int32_t *__restrict__ offs, int32_t *__restrict__ out) {
+                                                         const int32_t *__restrict__ offs, ScanTo to) {
     __shared__ int32_t wsum[4];
     const int64_t base = (int64_t)blockIdx.x * 256 * kScanItems + (int64_t)threadIdx.x * kScanItems;
     int32_t v[kScanItems];
@@ -372,10 +383,10 @@ __global__ __launch_bounds__(256) void scan_apply_kernel(int32_t n, const int32_
     int32_t run = off + incl - t;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < n) out[base + k] = run;
+        if (base + k < n) to.put(base + k, v[k], run);
         run += v[k];
     }
-    if (base + kScanItems >= n && base < n) out[n] = run;  // the thread holding the last element
+    if (base + kScanItems >= n && base < n) to.total(n, run);  // the thread holding the last element
 }
 
 // ---------------------------------------------------------------------------
@@ -1615,43 +1626,47 @@ void amg_launch_diag(hipStream_t s, Sell<double> A, double *diag, double *dinv) 
     if (A.n > 0) ALAUNCH(amg_diag_kernel, gridv(A.n), kAT, A, diag, dinv);
 }
 void amg_launch_mis(hipStream_t s, Sell<double> A, const double *diag, double theta, int rounds, int hops,
-                    uint32_t *T, uint32_t *T1, int *undecided, int32_t *flag, int *hcnt, int32_t *scol) {
-    ALAUNCH(strength_kernel, gridv(A.n), kAT, A, diag, theta, scol);
-    ALAUNCH(mis_init_kernel, gridv(A.n), kAT, A.n, T, T1);
+                    const CoarsenInit &I, int32_t *flag, int32_t *scol, int *progress) {
+    volatile int *started = progress;
+    *started = 0;
+    ALAUNCH(strength_kernel, gridv((int64_t)A.n + 1), kAT, A, diag, theta, scol, I);
     for (int r = 0; r < rounds; ++r) {
-        int *cur = undecided + (int64_t)r * kCntSlots * kCntStride;
+        int *cur = I.undecided + (int64_t)r * kCntSlots * kCntStride;
         const int *active = r ? cur - kCntSlots * kCntStride : nullptr;
-        ALAUNCH(mis_max_kernel, gridv(A.n), kAT, A.n, A.ptr, scol, T, T1, active);
-        ALAUNCH(mis_select_kernel, gridv(A.n), kAT, A.n, hops, A.ptr, scol, T1, T, cur, active);
-        if ((r & 3) == 3 && r + 1 < rounds) {  // stop queueing rounds once nothing is undecided
-            VAG_HIP(hipMemcpyAsync(hcnt, cur, kCntSlots * kCntStride * sizeof(int), hipMemcpyDeviceToHost, s));
-            VAG_HIP(hipStreamSynchronize(s));
-            bool any = false;
-            for (int k = 0; k < kCntSlots; ++k) any = any || hcnt[k * kCntStride] != 0;
-            if (!any) break;
-        }
+        ALAUNCH(mis_max_kernel, gridv(A.n), kAT, A.n, A.ptr, scol, I.T, I.T1, active, r, progress);
+        ALAUNCH(mis_select_kernel, gridv(A.n), kAT, A.n, hops, A.ptr, scol, I.T1, I.T, cur, active);
+        // Stop queueing rounds once nothing is undecided.  The device says in
+        // pinned memory which round it has begun; the host stays at most three
+        // rounds ahead of it, so the device never waits for the host's look as
+        // it did for a copy and a synchronisation every fourth round.
+        for (int spin = 0; *started < r - 2 && *started <= kMisRounds; ++spin)
+            if ((spin & 1023) == 1023 && hipStreamQuery(s) != hipErrorNotReady) break;  // nothing runs any more
+        if (*started > kMisRounds) break;
     }
-    ALAUNCH(mis_flag_kernel, gridv(A.n), kAT, A.n, T, flag);
+    ALAUNCH(mis_flag_kernel, gridv(A.n), kAT, A.n, I.T, flag);
 }
-void amg_launch_scan(hipStream_t s, int32_t n, const int32_t *in, int32_t *out, int32_t *tmp) {
+static void scan_to(hipStream_t s, int32_t n, const int32_t *in, const ScanTo &to, int32_t *tmp) {
     // tmp: at least 2 * (n / 1024 + 2) ints
     const int32_t nb = (n + 256 * kScanItems - 1) / (256 * kScanItems);
-    if (nb <= 1) {
-        ALAUNCH(scan_int_kernel, 1, 1024, n, in, out);
+    if (nb <= 8) {  // three launches cost more than eight items a thread
+        ALAUNCH(scan_int_kernel, 1, 1024, n, in, to);
         return;
     }
     ALAUNCH(scan_sums_kernel, nb, 256, n, in, tmp);
-    ALAUNCH(scan_int_kernel, 1, 1024, nb, tmp, tmp + nb + 1);
-    ALAUNCH(scan_apply_kernel, nb, 256, n, in, tmp + nb + 1, out);
+    ALAUNCH(scan_int_kernel, 1, 1024, nb, tmp, (ScanTo{tmp + nb + 1, nullptr, nullptr, nullptr}));
+    ALAUNCH(scan_apply_kernel, nb, 256, n, in, tmp + nb + 1, to);
+}
+void amg_launch_scan(hipStream_t s, int32_t n, const int32_t *in, int32_t *out, int32_t *tmp, int *host) {
+    scan_to(s, n, in, ScanTo{out, nullptr, nullptr, host}, tmp);
+}
+void amg_launch_lonely(hipStream_t s, int32_t n, const int32_t *lonely, const int32_t *nroot, int32_t *agg,
+                       int32_t *tmp, int *host) {
+    scan_to(s, n, lonely, ScanTo{nullptr, agg, nroot, host}, tmp);
 }
 void amg_launch_aggregate(hipStream_t s, Sell<double> A, const double *diag, const int32_t *scol, const int32_t *root,
                           const int32_t *rid, int32_t *agg1, int32_t *agg, int32_t *lonely) {
     ALAUNCH(agg_pass1_kernel, gridv(A.n), kAT, A, diag, scol, root, rid, agg1);
     ALAUNCH(agg_pass2_kernel, gridv(A.n), kAT, A, diag, scol, agg1, agg, lonely);
-}
-void amg_launch_lonely(hipStream_t s, int32_t n, const int32_t *lonely, const int32_t *lid, const int32_t *nroot,
-                       int32_t *agg) {
-    ALAUNCH(agg_lonely_kernel, gridv(n), kAT, n, lonely, lid, nroot, agg);
 }
 void amg_launch_members(hipStream_t s, int32_t n, int32_t nc, const int32_t *agg, int32_t *cnt, int32_t *ptr,
                         int32_t *cursor, int32_t *tmp, int32_t *rows, int32_t *scan_tmp) {
@@ -1678,10 +1693,10 @@ void amg_launch_galerkin(hipStream_t s, Sell<double> A, const int32_t *Jcol, con
             cptr, ccol, cval, overflow);
 }
 void amg_launch_slices(hipStream_t s, int32_t n, const int32_t *rowlen, int32_t *width, int32_t *cnt, int64_t *ptr,
-                       unsigned long long *nnz) {
+                       unsigned long long *nnz, int64_t *host, const int *flag, int *host_flag) {
     const int32_t ns = (n + 63) / 64;
     if (ns > 0) ALAUNCH(slice_width_kernel, ns, 64, n, rowlen, width, cnt);
-    launch_slice_scan(s, ns, width, kSliceRows, ptr, cnt, nnz);
+    launch_slice_scan(s, ns, width, kSliceRows, ptr, cnt, nnz, host, flag, host_flag);
 }
 void amg_launch_slice_tail(hipStream_t s, int32_t n, const int64_t *ptr, int32_t *col, double *val) {
     if (n & 63) ALAUNCH(slice_tail_kernel, 1, 64, n, ptr, col, val);

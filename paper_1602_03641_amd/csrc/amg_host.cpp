@@ -29,7 +29,7 @@ void Amg::setup(hipStream_t s, Tracker &tr, Sell<double> A0, int64_t stored0, co
     if (n0 >= (1 << 30)) throw Error(VAG_ERR_UNSUPPORTED, "AMG: more than 2^30 - 1 rows");
     ensure(T_, n0, tr);
     ensure(T1_, n0, tr);
-    for (auto *b : {&flag_, &rid_, &agg1_, &lonely_, &lid_, &cnt_, &cursor_, &rowlen_}) ensure(*b, (size_t)n0 + 1, tr);
+    for (auto *b : {&flag_, &rid_, &agg1_, &lonely_, &cnt_, &cursor_, &rowlen_}) ensure(*b, (size_t)n0 + 1, tr);
     ensure(width_, (size_t)n0 / 64 + 2, tr);
     ensure(big_, (size_t)n0 + 1, tr);
     ensure(mtmp_, (size_t)n0 + 1, tr);
@@ -59,26 +59,20 @@ void Amg::setup(hipStream_t s, Tracker &tr, Sell<double> A0, int64_t stored0, co
         amg_launch_diag(s, lv.A, lv.diag.p, lv.dinv.p);
         if (n <= o.coarse_size || l + 1 >= o.max_levels) break;
         // aggregation
-        VAG_HIP(hipMemsetAsync(counters_.p, 0, 64 * sizeof(int), s));
-        VAG_HIP(hipMemsetAsync(mis_cnt_.p, 0, mis_cnt_.n * sizeof(int), s));
         ensure(jcol_, (size_t)lv.stored, tr);  // the strong columns
-        amg_launch_mis(s, lv.A, lv.diag.p, o.theta, std::min(o.mis_rounds, kMisRounds), o.hops, T_.p, T1_.p, mis_cnt_.p,
-                       flag_.p, h_ + 64, jcol_.p);
-        amg_launch_scan(s, n, flag_.p, rid_.p, stmp_.p);
+        const CoarsenInit init{T_.p, T1_.p, mis_cnt_.p, counters_.p, cnt_.p, cursor_.p};
+        amg_launch_mis(s, lv.A, lv.diag.p, o.theta, std::min(o.mis_rounds, kMisRounds), o.hops, init, flag_.p, jcol_.p,
+                       h_ + 16);
+        amg_launch_scan(s, n, flag_.p, rid_.p, stmp_.p, h_);
         ensure(lv.agg, n, tr);
         amg_launch_aggregate(s, lv.A, lv.diag.p, jcol_.p, flag_.p, rid_.p, agg1_.p, lv.agg.p, lonely_.p);
-        amg_launch_scan(s, n, lonely_.p, lid_.p, stmp_.p);
-        amg_launch_lonely(s, n, lonely_.p, lid_.p, rid_.p + n, lv.agg.p);
-        VAG_HIP(hipMemcpyAsync(h_, rid_.p + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        VAG_HIP(hipMemcpyAsync(h_ + 1, lid_.p + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        amg_launch_lonely(s, n, lonely_.p, rid_.p + n, lv.agg.p, stmp_.p, h_ + 1);
         VAG_HIP(hipStreamSynchronize(s));
         const int32_t nc = h_[0] + h_[1];
         if (nc <= 0 || nc > (int64_t)n * 9 / 10) break;  // coarsening stalled: this level is the coarsest
         // aggregate members and the Galerkin product
         ensure(lv.mptr, (size_t)nc + 1, tr);
         ensure(lv.mrows, n, tr);
-        VAG_HIP(hipMemsetAsync(cnt_.p, 0, ((size_t)nc + 1) * sizeof(int32_t), s));
-        VAG_HIP(hipMemsetAsync(cursor_.p, 0, ((size_t)nc + 1) * sizeof(int32_t), s));
         amg_launch_members(s, n, nc, lv.agg.p, cnt_.p, lv.mptr.p, cursor_.p, mtmp_.p, lv.mrows.p, stmp_.p);
         ensure(apv_, (size_t)lv.stored, tr);
         ensure(apj_, (size_t)lv.stored, tr);
@@ -89,13 +83,12 @@ void Amg::setup(hipStream_t s, Tracker &tr, Sell<double> A0, int64_t stored0, co
         ensure(cv.ptr, (size_t)ns + 1, tr);
         amg_launch_galerkin(s, lv.A, apj_.p, apv_.p, apn_.p, lv.mptr.p, lv.mrows.p, nc, 0, big_.p, lonely_.p,
                             counters_.p + 60, rowlen_.p, nullptr, nullptr, nullptr, counters_.p + 63);
-        amg_launch_slices(s, nc, rowlen_.p, width_.p, scnt_.p, cv.ptr.p, level_nnz.p + l + 1);
-        int64_t hv[2];
-        VAG_HIP(hipMemcpyAsync(&hv[0], cv.ptr.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        VAG_HIP(hipMemcpyAsync(h_ + 2, counters_.p + 63, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        int64_t *h_stored = reinterpret_cast<int64_t *>(h_ + 4);
+        amg_launch_slices(s, nc, rowlen_.p, width_.p, scnt_.p, cv.ptr.p, level_nnz.p + l + 1, h_stored,
+                          counters_.p + 63, h_ + 2);
         VAG_HIP(hipStreamSynchronize(s));
         if (h_[2] != 0) break;  // a coarse row has too many candidates: stop coarsening here
-        const int64_t stored = hv[0];
+        const int64_t stored = *h_stored;
         ensure(cv.col, (size_t)stored, tr);
         ensure(cv.val, (size_t)stored, tr);
         amg_launch_galerkin(s, lv.A, apj_.p, apv_.p, apn_.p, lv.mptr.p, lv.mrows.p, nc, 1, big_.p, lonely_.p,

@@ -186,6 +186,10 @@ __device__ inline void krylov_put(bool slices, P p, int slice, double (&v)[NV]) 
     }
 }
 
+// A value for the host, which polls pinned memory (or reads it after the next
+// synchronisation): no copy to queue and wait for.
+__device__ inline void host_put(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+
 // Ends a Krylov solve (one thread calls it): the later kernels return at
 // once, and the host, which looks at its flag before it queues an iteration,
 // queues no more of them.
@@ -193,7 +197,7 @@ __device__ inline void krylov_done(PcgState *st, int converged, double rr) {
     st->done = 1;
     st->converged = converged;
     st->rr = rr;
-    if (st->host_done) __hip_atomic_store(st->host_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (st->host_done) host_put(st->host_done, 1);
 }
 
 inline unsigned reduce_grid(int64_t n_items, int threads) {

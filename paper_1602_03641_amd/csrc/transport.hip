@@ -357,7 +357,8 @@ __global__ __launch_bounds__(kSliceRows) void upwind_count_kernel(
 __global__ __launch_bounds__(1024) void slice_scan_kernel(int32_t nslice, const int32_t *__restrict__ w,
                                                           int per_width, int64_t *__restrict__ ptr,
                                                           const int32_t *__restrict__ cnt,
-                                                          unsigned long long *__restrict__ total) {
+                                                          unsigned long long *__restrict__ total, int64_t *host,
+                                                          const int *flag, int *host_flag) {
     __shared__ int64_t wsum[16], csum[16];
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     const int32_t chunk = (nslice + 1023) / 1024;
@@ -381,7 +382,13 @@ __global__ __launch_bounds__(1024) void slice_scan_kernel(int32_t nslice, const 
     __syncthreads();
     int64_t before = 0;
     for (int k = 0; k < wid; ++k) before += wsum[k];
-    if (t == 1023) ptr[nslice] = before + v;
+    if (t == 1023) {
+        ptr[nslice] = before + v;
+        if (host) {
+            __hip_atomic_store(host, before + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            host_put(host_flag, *flag);
+        }
+    }
     if (t == 0 && total) {
         unsigned long long tc = 0;
         for (int k = 0; k < 16; ++k) tc += (unsigned long long)csum[k];
@@ -961,9 +968,10 @@ void launch_upwind_count(hipStream_t s, int32_t nc, int32_t nf, int32_t nn, cons
     VAG_HIP(hipGetLastError());
 }
 void launch_slice_scan(hipStream_t s, int32_t nslice, const int32_t *slice_width, int per_width, int64_t *slice_ptr,
-                       const int32_t *slice_nnz, unsigned long long *total) {
+                       const int32_t *slice_nnz, unsigned long long *total, int64_t *host, const int *flag,
+                       int *host_flag) {
     hipLaunchKernelGGL(slice_scan_kernel, dim3(1), dim3(1024), 0, s, nslice, slice_width, per_width, slice_ptr,
-                       slice_nnz, total);
+                       slice_nnz, total, host, flag, host_flag);
     VAG_HIP(hipGetLastError());
 }
 void launch_upwind_fill(hipStream_t s, int32_t nc, int32_t nf, int32_t nn, const int32_t *hex8,

@@ -524,9 +524,11 @@ void launch_upwind_count(hipStream_t s, int32_t nc, int32_t nf, int32_t nn, cons
                          const double *F_cell_frac, const double *F_frac, const double *wsrc, int32_t *slice_width,
                          uint16_t *meta, int32_t *slice_nnz);
 // slice_ptr = exclusive scan of per_width * slice_width (64 for padded
-// sliced ELL, 1 for counts of packed entries); with slice_nnz, *total = its sum
+// sliced ELL, 1 for counts of packed entries); with slice_nnz, *total = its
+// sum; with host (pinned), *host = slice_ptr[nslice] and *host_flag = *flag
 void launch_slice_scan(hipStream_t s, int32_t nslice, const int32_t *slice_width, int per_width, int64_t *slice_ptr,
-                       const int32_t *slice_nnz = nullptr, unsigned long long *total = nullptr);
+                       const int32_t *slice_nnz = nullptr, unsigned long long *total = nullptr,
+                       int64_t *host = nullptr, const int *flag = nullptr, int *host_flag = nullptr);
 void launch_upwind_fill(hipStream_t s, int32_t nc, int32_t nf, int32_t nn, const int32_t *hex8,
                         const uint8_t *fmask, const int32_t *cell_frac, const int32_t *frac_cell,
                         const int32_t *frac_nodes, const uint8_t *dirichlet, const int32_t *node_cell_ptr,
