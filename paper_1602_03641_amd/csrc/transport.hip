@@ -800,12 +800,26 @@ __global__ void set_dirichlet_kernel(int32_t nn, int32_t offset, const uint8_t *
 // ---------------------------------------------------------------------------
 // general cells: the same steps on the incidence lists of the control volumes
 // ---------------------------------------------------------------------------
-// Flux F_e leaves the first control volume of edge e when positive; at the
-// far end (edge & 1) it counts with the opposite sign.
-__device__ inline double inc_flux(const GenInc &I, const double *F, int64_t q) {
-    const int32_t e = I.edge[q];
-    const double f = F[e >> 1];
-    return (e & 1) ? -f : f;
+// use(q, f) for the incidences q of control volume i in turn, f the flux out of
+// it: F_e leaves the first control volume of edge e when positive; at the far
+// end (edge & 1) it counts with the opposite sign.  kInc of them are read
+// together (a node of a tetrahedral mesh has two dozen; 1.05 M cells, one at a
+// time: time step 118 us, counts 98, operator 221; now 62, 44 and 101).
+constexpr int kInc = 6;
+template <class Use>
+__device__ inline void inc_fluxes(const GenInc &I, const double *__restrict__ F, int64_t i, Use use) {
+    const int64_t q1 = I.ptr[i + 1];
+    for (int64_t q0 = I.ptr[i]; q0 < q1; q0 += kInc) {
+        int32_t e[kInc];
+        double f[kInc];
+#pragma unroll
+        for (int j = 0; j < kInc; ++j) e[j] = I.edge[min(q0 + j, q1 - 1)];
+#pragma unroll
+        for (int j = 0; j < kInc; ++j) f[j] = F[e[j] >> 1];
+#pragma unroll
+        for (int j = 0; j < kInc; ++j)
+            if (q0 + j < q1) use(q0 + j, (e[j] & 1) ? -f[j] : f[j]);
+    }
 }
 
 __global__ __launch_bounds__(kCflT) void gen_cfl_kernel(GenInc I, const double *__restrict__ F,
@@ -820,7 +834,7 @@ __global__ __launch_bounds__(kCflT) void gen_cfl_kernel(GenInc I, const double *
         const int kind = i < off_f ? 0 : (i < off_n ? 1 : 2);
         if (kind == 2 && I.dirichlet[i - off_n]) continue;
         double o = 0.0;
-        for (int64_t q = I.ptr[i]; q < I.ptr[i + 1]; ++q) o += fmax(inc_flux(I, F, q), 0.0);
+        inc_fluxes(I, F, i, [&](int64_t, double f) { o += fmax(f, 0.0); });
         if (kind == 1 && wout) o += wout[i - off_f];
         if (o > 0.0) {
             const double phi = kind == 0 ? phi_cell[i] : (kind == 1 ? phi_frac[i - off_f] : phi_node[i - off_n]);
@@ -836,7 +850,7 @@ __device__ inline int gen_row_count(const GenInc &I, const double *F, const doub
     const int64_t off_f = I.nc, off_n = (int64_t)I.nc + I.nf;
     if (i >= off_n && I.dirichlet[i - off_n]) return 0;
     int c = 0;
-    for (int64_t q = I.ptr[i]; q < I.ptr[i + 1]; ++q) c += inc_flux(I, F, q) < 0.0;
+    inc_fluxes(I, F, i, [&](int64_t, double f) { c += f < 0.0; });
     if (wsrc && i >= off_f && i < off_n) c += wsrc[i - off_f] > 0.0;
     return c;
 }
@@ -875,8 +889,7 @@ __global__ __launch_bounds__(kSliceRows) void gen_upwind_fill_kernel(
         const double w = dtp[3] / phi;
         double out = 0.0;
         int k = 0;
-        for (int64_t q = I.ptr[i]; q < I.ptr[i + 1]; ++q) {
-            const double f = inc_flux(I, F, q);
+        inc_fluxes(I, F, i, [&](int64_t q, double f) {
             if (f > 0.0) {
                 out += f;
             } else if (f < 0.0) {
@@ -884,7 +897,7 @@ __global__ __launch_bounds__(kSliceRows) void gen_upwind_fill_kernel(
                 tval[base + level_off[k]] = -w * f;
                 ++k;
             }
-        }
+        });
         if (i >= off_f && i < off_n) {
             if (wout) out += wout[i - off_f];
             if (wsrc && wsrc[i - off_f] > 0.0) {

@@ -251,3 +251,42 @@ def test_aggregation_products(mesh, coarse, hops, theta):
                      int(Ac.getnnz(axis=1).max())))
     print("most aggregates of a row, candidates and columns of a coarse row, per level:", wide)
     h.close()
+
+
+@pytest.mark.parametrize("dims,share", [((2, 2, 1), 0.6), ((3, 3, 3), 0.0), ((5, 4, 4), 0.3), ((9, 8, 7), 0.5)])
+def test_tetrahedra_fracture_faces(dims, share):
+    """Tetrahedra with none to all four of their faces fractures (ratio 10, so
+    that pressures and fluxes are compared relative to their largest at 1e-9:
+    condition numbers below 10^4 at a residual of 1e-13), faces in any order
+    and orientation; sums of incidence lists shorter and longer than a batch."""
+    from oracle import general_cells as gc
+    from paper_1602_03641_amd import vag
+    from test_gpu_general import oracle_fluxes_flat, oracle_mesh
+    p = synth.general_problem("tet", dims, 35, aniso_sigma=0.5, n_steps=9)
+    rng = np.random.default_rng(36)
+    two = np.nonzero(np.bincount(p.cell_faces, minlength=len(p.face_node_ptr) - 1) == 2)[0]
+    p.frac_face_ids = np.sort(rng.choice(two, int(share * len(two)), replace=False)).astype(np.int32)
+    nf = len(p.frac_face_ids)
+    p.frac_width, p.frac_perm, p.frac_poro = np.full(nf, 0.01), rng.uniform(5.0, 10.0, nf), np.ones(nf)
+    per_cell = np.isin(p.cell_faces, p.frac_face_ids).reshape(-1, 4).sum(axis=1)
+    print("cells by fracture faces:", np.bincount(per_cell))
+    h, info = _handle(p, rtol=1e-13, precond=vag.VAG_PC_JACOBI)
+    m = oracle_mesh(p)
+    sol = gc.solve_darcy(m)
+    g, gf = vag.to_numpy(h.pressure()), vag.to_numpy(h.fluxes())
+    for k in ("u_node", "u_cell", "u_frac"):
+        assert np.abs(g[k] - np.asarray(sol[k])).max(initial=0.0) <= 1e-9, k
+    of = oracle_fluxes_flat(p, sol)
+    scale = max(np.abs(of["F_cell"]).max(), np.abs(of["F_frac"]).max(initial=0.0))
+    for k in ("F_cell", "F_cell_frac", "F_frac"):
+        assert np.abs(gf[k] - of[k]).max(initial=0.0) <= 1e-9 * scale, k
+    phi, gphi = gc.porous_volumes(m, sol), vag.to_numpy(h.porous_volumes())
+    for k in ("phi_cell", "phi_frac", "phi_node"):
+        np.testing.assert_allclose(gphi[k], phi[k], rtol=1e-13, atol=1e-18, err_msg=k)
+    h.set_fluxes(of)
+    t = h.transport(n_steps=p.n_steps)
+    oc = gc.transport(m, sol, phi, t["dt"], p.n_steps)
+    c = vag.to_numpy(h.concentration())
+    for k in ("c_cell", "c_frac", "c_node"):
+        assert np.abs(c[k] - oc[k]).max(initial=0.0) <= 1e-12, k
+    h.close()
