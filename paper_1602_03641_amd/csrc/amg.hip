@@ -916,31 +916,39 @@ __global__ __launch_bounds__(64) void slice_tail_kernel(int32_t n, const int64_t
 // ---------------------------------------------------------------------------
 // coarsest level: dense inverse
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kAT) void dense_from_sell_kernel(Sell<double> A, double *__restrict__ D) {
-    const int32_t n = A.n;
-    GS(t, (int64_t)n * n) D[t] = 0.0;
-}
-__global__ __launch_bounds__(kAT) void dense_scatter_kernel(Sell<double> A, double *__restrict__ D) {
-    GS(i, A.n) {
-        const int64_t b0 = A.ptr[i >> 6], b1 = A.ptr[(i >> 6) + 1];
-        for (int64_t q = b0 + (i & 63); q < b1; q += 64) D[i * A.n + A.col[q]] += A.val[q];
+// D = A, dense row-major, one wavefront per row.  A row's entries have distinct
+// columns (padding entries are zero).
+constexpr int kDenseMax = 1024;
+__global__ __launch_bounds__(64) void dense_from_sell_kernel(Sell<double> A, double *__restrict__ D) {
+    __shared__ double row[kDenseMax];
+    const int32_t n = A.n, i = blockIdx.x;
+    const int lane = threadIdx.x;
+    for (int j = lane; j < n; j += 64) row[j] = 0.0;
+    __syncthreads();
+    const int64_t b0 = A.ptr[i >> 6] + (i & 63), w = (A.ptr[(i >> 6) + 1] - A.ptr[i >> 6]) >> 6;
+    for (int64_t k = lane; k < w; k += 64) {
+        const double v = A.val[b0 + 64 * k];
+        if (v != 0.0) row[A.col[b0 + 64 * k]] = v;
     }
+    __syncthreads();
+    for (int j = lane; j < n; j += 64) D[(int64_t)i * n + j] = row[j];
 }
-// In-place blocked Gauss-Jordan inversion of an SPD matrix (no pivoting
-// needed: every pivot block is a Schur complement of an SPD matrix, hence SPD).
-// With P the next kGJ indices, R the others and B = M[P,P]^-1 the block step
-// is
+// Blocked Gauss-Jordan inversion of an SPD matrix (no pivoting needed: every
+// pivot block is a Schur complement of an SPD matrix, hence SPD).  With P the
+// next kGJ indices, R the others and B = M[P,P]^-1 the block step is
 //   V = B M[P,R],  W = M[R,P] B,
 //   M[R,R] = M[R,R] - M[R,P] V,  M[P,R] = V,  M[R,P] = -W,  M[P,P] = B,
-// done by four kernels: the kGJ x kGJ inverse in one workgroup, the two
-// panels V and W (64 x 64 tiles in LDS), the update of M[R,R] (64 x 64
-// output tiles, the operands staged in LDS), and the write-back of the
-// panels.  Only M[P,*] and M[*,P] are read before the write-back, so the
-// update needs no copy of the old panels.
+// one launch, one workgroup per 64 x 64 tile, from one copy of M to another:
+// each tile of M[R,R] forms its own tile of V, and the workgroup of the next
+// pivot block inverts it before it ends.  That inversion is the chain that the
+// steps wait for (~20 us); the products, loads and launches around it were 33
+// us of a step as four kernels (pivot, panels, update, write-back in place: 62
+// us a step, now 27; 430 rows 434 -> 218 us).
 constexpr int kGJ = 64;
+constexpr int kGJLd = kGJ + 2;  // of a tile in LDS: rows 16 bytes aligned, their banks shifted
 constexpr int kQ = 4;  // pivots eliminated together inside the diagonal block
 
-// B = M[P,P]^-1 (k <= kGJ), written back in place.  256 threads as a 16 x 16
+// The inverse of the k x k block t (padded by the identity), in place.  256 threads as a 16 x 16
 // grid, each keeping a 4 x 4 tile of the (identity-padded) 64 x 64 block in
 // registers.  The elimination takes kQ pivots per step: the owners publish
 // the kQ pivot rows and columns in LDS (double-buffered, one barrier per
@@ -962,24 +970,13 @@ __device__ inline void inv4(double b[kQ][kQ]) {
         }
     }
 }
-__global__ __launch_bounds__(256) void gj_pivot_kernel(int32_t n, int32_t p0, int32_t k, double *__restrict__ M) {
+__device__ inline void gj_invert(double (&t)[4][4], int k) {
     __shared__ double rowp[2][kQ][kGJ], colp[2][kGJ][kQ];
     const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-    double t[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int i = ty * 4 + a, j = tx * 4 + c;
-            // every lane loads (the padding from the block's first entry) so the
-            // sixteen loads are in flight together
-            const bool in = i < k && j < k;
-            const double x = M[(int64_t)(p0 + (in ? i : 0)) * n + p0 + (in ? j : 0)];
-            t[a][c] = in ? x : (i == j ? 1.0 : 0.0);
-        }
     const int nsteps = (k + kQ - 1) / kQ;
     for (int pb = 0; pb < nsteps; ++pb) {
         const int buf = pb & 1;
+        const bool ip = ty == pb, jp = tx == pb;
         if (ty == pb) {
 #pragma unroll
             for (int a = 0; a < 4; ++a)
@@ -1018,154 +1015,169 @@ __global__ __launch_bounds__(256) void gj_pivot_kernel(int32_t n, int32_t p0, in
                 for (int m = 0; m < kQ; ++m) v += C[a][m] * B[m][c];
                 CB[a][c] = v;
             }
-        const bool ip = ty == pb, jp = tx == pb;
-#pragma unroll
+        #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                double upd = t[a][c], br = 0.0;
+                // the pivot rows' block B R, or what is left of t
+                double x = ip ? 0.0 : t[a][c];
 #pragma unroll
-                for (int m = 0; m < kQ; ++m) {
-                    upd -= CB[a][m] * R[m][c];
-                    br += B[a][m] * R[m][c];
-                }
-                const double bb = a < kQ && c < kQ ? B[a & (kQ - 1)][c & (kQ - 1)] : 0.0;
-                t[a][c] = ip ? (jp ? bb : br) : (jp ? -CB[a][c & (kQ - 1)] : upd);
+                for (int m = 0; m < kQ; ++m) x = fma(ip ? B[a][m] : -CB[a][m], R[m][c], x);
+                t[a][c] = jp ? (ip ? B[a][c] : -CB[a][c]) : x;
             }
     }
+}
+// Stores the inverse (zeros past k) where the next step reads it.
+__device__ inline void gj_put(const double (&t)[4][4], int k, double *__restrict__ B) {
+    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int i = ty * 4 + a, j = tx * 4 + c;
-            if (i < k && j < k) M[(int64_t)(p0 + i) * n + p0 + j] = t[a][c];
+            B[i * kGJ + j] = i < k && j < k ? t[a][c] : 0.0;
         }
 }
+__global__ __launch_bounds__(256) void gj_first_kernel(int32_t n, const double *__restrict__ M,
+                                                       double *__restrict__ B) {
+    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15, k = min(n, kGJ);
+    double t[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int i = ty * 4 + a, j = tx * 4 + c;
+            // every lane loads (the padding from the block's first entry) so the
+            // sixteen loads are in flight together
+            const bool in = i < k && j < k;
+            const double x = M[in ? (int64_t)i * n + j : 0];
+            t[a][c] = in ? x : (i == j ? 1.0 : 0.0);
+        }
+    gj_invert(t, k);
+    gj_put(t, k, B);
+}
 
-// Panels of the step, 64 x 64 tiles: blockIdx.y == 0: V[l][t] = sum_m B[l][m]
-// M[p0+m][t] (64 x n, row-major); blockIdx.y == 1: W[t][l] = sum_m M[t][p0+m]
-// B[m][l] (n x 64, row-major).  Tiles of P itself are skipped.
-__global__ __launch_bounds__(256) void gj_panel_kernel(int32_t n, int32_t p0, int32_t k,
-                                                       const double *__restrict__ M, double *__restrict__ V,
-                                                       double *__restrict__ W) {
-    __shared__ double Bs[kGJ][kGJ + 1], Ps[kGJ][kGJ + 1];
-    const int32_t t0 = blockIdx.x * kGJ;
-    if (t0 == p0) return;
+// acc = A B over k: thread (ty, tx) the rows 4 ty + a and columns 4 tx + c,
+// every entry a chain over m in order
+__device__ inline void gj_product(const double (&A)[kGJ][kGJLd], const double (&B)[kGJ][kGJLd], int k,
+                                  double (&acc)[4][4]) {
     const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-    const bool left = blockIdx.y == 1;
-    // Bs = B (zero-padded), Ps = the panel tile: M[P, T] (V) or M[T, P] (W)
-    // a fixed trip count, unrolled, so that all the tile loads are in flight together
 #pragma unroll
-    for (int it = 0; it < kGJ * kGJ / 256; ++it) {
-        const int e = threadIdx.x + it * 256;
-        const int r = e >> 6, c = e & 63;
-        // clamped addresses and selects rather than conditional loads, so that the
-        // loads of all iterations are issued before the first wait
-        const bool ib = r < k && c < k;
-        const double bv = M[(int64_t)(p0 + (ib ? r : 0)) * n + p0 + (ib ? c : 0)];
-        Bs[r][c] = ib ? bv : 0.0;
-        const bool ip = left ? (t0 + r < n && c < k) : (r < k && t0 + c < n);
-        const int64_t row = left ? (ip ? t0 + r : p0) : p0 + (ip ? r : 0);
-        const int64_t col = left ? p0 + (ip ? c : 0) : (ip ? t0 + c : p0);
-        const double pv = M[row * n + col];
-        Ps[r][c] = ip ? pv : 0.0;
-    }
-    __syncthreads();
-    double acc[4][4] = {};
-    if (!left) {
-        // V tile: rows l (4 ty + a), columns t (4 tx + c)
-        for (int m = 0; m < k; ++m) {
-            double bv[4], pv[4];
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int a = 0; a < 4; ++a) bv[a] = Bs[ty * 4 + a][m];
+        for (int c = 0; c < 4; ++c) acc[a][c] = 0.0;
+#pragma unroll 2
+    for (int m = 0; m < k; m += 2) {  // the tiles are zero past k
+        double2 x[4], y[2][2];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) pv[c] = Ps[m][tx * 4 + c];
+        for (int a = 0; a < 4; ++a) x[a] = *reinterpret_cast<const double2 *>(&A[ty * 4 + a][m]);
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc[a][c] += bv[a] * pv[c];
-        }
+            for (int h = 0; h < 2; ++h) y[u][h] = *reinterpret_cast<const double2 *>(&B[m + u][tx * 4 + 2 * h]);
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int l = ty * 4 + a, t = t0 + tx * 4 + c;
-                if (l < k && t < n) V[(int64_t)l * n + t] = acc[a][c];
-            }
-    } else {
-        // W tile: rows t (4 ty + a), columns l (4 tx + c)
-        for (int m = 0; m < k; ++m) {
-            double pv[4], bv[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) pv[a] = Ps[ty * 4 + a][m];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) bv[c] = Bs[m][tx * 4 + c];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[a][c] += pv[a] * bv[c];
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int t = t0 + ty * 4 + a, l = tx * 4 + c;
-                if (t < n && l < k) W[(int64_t)t * kGJ + l] = acc[a][c];
+            for (int h = 0; h < 2; ++h) {
+                acc[a][2 * h] = fma(x[a].y, y[1][h].x, fma(x[a].x, y[0][h].x, acc[a][2 * h]));
+                acc[a][2 * h + 1] = fma(x[a].y, y[1][h].y, fma(x[a].x, y[0][h].y, acc[a][2 * h + 1]));
             }
     }
 }
-
-// M[i][j] -= sum_l M[i][p0+l] V[l][j] for i, j outside P, one 64 x 64 output
-// tile per workgroup
-__global__ __launch_bounds__(256) void gj_update_kernel(int32_t n, int32_t p0, int32_t k, double *__restrict__ M,
-                                                        const double *__restrict__ V) {
-    __shared__ double Ls[kGJ][kGJ + 1], Vs[kGJ][kGJ + 1];
+// One block step with pivots [p0, p0 + k): Mout from Min and B = Min[P,P]^-1;
+// next = the inverse of the following pivot block.
+__global__ __launch_bounds__(256) void gj_step_kernel(int32_t n, int32_t p0, int32_t k,
+                                                      const double *__restrict__ Min, double *__restrict__ Mout,
+                                                      const double *__restrict__ B, double *__restrict__ next) {
+    __shared__ __align__(16) double S[kGJ][kGJLd], T[kGJ][kGJLd];
     const int32_t i0 = blockIdx.y * kGJ, j0 = blockIdx.x * kGJ;
-    if (i0 == p0 || j0 == p0) return;
+    const bool ri = i0 == p0, rj = j0 == p0;
     const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
+    constexpr int kIt = kGJ * kGJ / 256;
+    // S and T: B and M[P,J], or for the column panel M[I,P] and B.  Clamped
+    // addresses and selects rather than conditional loads, so that all loads
+    // are issued before the first wait.
+    double u[kIt];  // M[I,P]: S for the column panel, the second product's S for M[R,R]
+    double v[kIt];  // M[P,J]
 #pragma unroll
-    for (int it = 0; it < kGJ * kGJ / 256; ++it) {
-        const int e = threadIdx.x + it * 256;
-        const int r = e >> 6, c = e & 63;
-        const bool il = i0 + r < n && c < k, iv = r < k && j0 + c < n;
-        const double lv = M[(int64_t)(il ? i0 + r : p0) * n + p0 + (il ? c : 0)];
-        const double vv = V[(int64_t)(iv ? r : 0) * n + (iv ? j0 + c : 0)];
-        Ls[r][c] = il ? lv : 0.0;
-        Vs[r][c] = iv ? vv : 0.0;
+    for (int it = 0; it < kIt; ++it) {
+        const int e = threadIdx.x + it * 256, r = e >> 6, c = e & 63;
+        const bool iu = i0 + r < n && c < k, iv = r < k && j0 + c < n;
+        const double b = B[e];
+        const double x = Min[(int64_t)(iu ? i0 + r : p0) * n + p0 + (iu ? c : 0)];
+        const double y = Min[(int64_t)(p0 + (iv ? r : 0)) * n + (iv ? j0 + c : p0)];
+        u[it] = iu ? x : 0.0;
+        v[it] = iv ? y : 0.0;
+        S[r][c] = rj && !ri ? u[it] : b;
+        T[r][c] = rj ? b : v[it];
     }
     __syncthreads();
-    double acc[4][4] = {};
-    for (int l = 0; l < k; ++l) {
-        double lv[4], vv[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) lv[a] = Ls[ty * 4 + a][l];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) vv[c] = Vs[l][tx * 4 + c];
+    double out[4][4];
+    if (ri && rj) {
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[a][c] += lv[a] * vv[c];
+            for (int c = 0; c < 4; ++c) out[a][c] = S[ty * 4 + a][tx * 4 + c];
+    } else {
+        double acc[4][4];
+        gj_product(S, T, k, acc);
+        if (rj) {
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) out[a][c] = -acc[a][c];
+        } else if (ri) {
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) out[a][c] = acc[a][c];
+        } else {
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int i = i0 + ty * 4 + a, j = j0 + tx * 4 + c;
+                    const bool in = i < n && j < n;
+                    out[a][c] = Min[in ? (int64_t)i * n + j : 0];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < kIt; ++it) {
+                const int e = threadIdx.x + it * 256;
+                S[e >> 6][e & 63] = u[it];
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) T[ty * 4 + a][tx * 4 + c] = acc[a][c];
+            __syncthreads();
+            gj_product(S, T, k, acc);
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) out[a][c] -= acc[a][c];
+        }
+    }
+    if (i0 == j0 && i0 == p0 + kGJ) {  // the next pivot block
+        const int kn = min(kGJ, n - i0);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int i = ty * 4 + a, j = tx * 4 + c;
+                if (i >= kn || j >= kn) out[a][c] = i == j ? 1.0 : 0.0;
+            }
+        gj_invert(out, kn);
+        gj_put(out, kn, next);
+        return;
     }
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int i = i0 + ty * 4 + a, j = j0 + tx * 4 + c;
-            if (i < n && j < n) M[(int64_t)i * n + j] -= acc[a][c];
+            if (i < n && j < n) Mout[(int64_t)i * n + j] = out[a][c];
         }
-}
-
-// M[P,t] = V[.,t] and M[t,P] = -W[t,.] for t outside P
-__global__ __launch_bounds__(256) void gj_writeback_kernel(int32_t n, int32_t p0, int32_t k, double *__restrict__ M,
-                                                           const double *__restrict__ V, const double *__restrict__ W) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < (int64_t)n * k;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int l = (int)(e / n);
-        const int64_t t = e % n;
-        if (t >= p0 && t < p0 + k) continue;
-        M[(int64_t)(p0 + l) * n + t] = V[(int64_t)l * n + t];
-        M[t * n + p0 + l] = -W[t * kGJ + l];
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1703,21 +1715,17 @@ void amg_launch_slice_tail(hipStream_t s, int32_t n, const int64_t *ptr, int32_t
 }
 void amg_launch_dense_inverse(hipStream_t s, Sell<double> A, double *D, double *work) {
     const int32_t n = A.n;
-    ALAUNCH(dense_from_sell_kernel, gridv((int64_t)n * n), kAT, A, D);
-    ALAUNCH(dense_scatter_kernel, gridv(n), kAT, A, D);
-    const unsigned nt = (unsigned)((n + kGJ - 1) / kGJ);
-    const unsigned gw = (unsigned)std::min<int64_t>(((int64_t)n * kGJ + 255) / 256, 4096);
-    double *V = work, *W = work + (int64_t)kGJ * n;
-    for (int32_t p0 = 0; p0 < n; p0 += kGJ) {
-        const int32_t k = std::min(kGJ, n - p0);
-        ALAUNCH(gj_pivot_kernel, 1, 256, n, p0, k, D);
-        if (nt > 1) {
-            hipLaunchKernelGGL(gj_panel_kernel, dim3(nt, 2), dim3(256), 0, s, n, p0, k, D, V, W);
-            VAG_HIP(hipGetLastError());
-            hipLaunchKernelGGL(gj_update_kernel, dim3(nt, nt), dim3(256), 0, s, n, p0, k, D, V);
-            VAG_HIP(hipGetLastError());
-            ALAUNCH(gj_writeback_kernel, gw, 256, n, p0, k, D, V, W);
-        }
+    if (n > kDenseMax) throw Error(VAG_ERR_ARG, "internal: dense inverse of too many rows");
+    const int nt = (n + kGJ - 1) / kGJ;
+    double *B[2] = {work, work + kGJ * kGJ};
+    double *M[2] = {D, work + 2 * kGJ * kGJ};  // the steps alternate and end in D
+    int m = nt & 1;
+    ALAUNCH(dense_from_sell_kernel, n, 64, A, M[m]);
+    ALAUNCH(gj_first_kernel, 1, 256, n, M[m], B[0]);
+    for (int p = 0; p < nt; ++p, m ^= 1) {
+        hipLaunchKernelGGL(gj_step_kernel, dim3(nt, nt), dim3(256), 0, s, n, p * kGJ, std::min(kGJ, n - p * kGJ), M[m],
+                           M[m ^ 1], B[p & 1], B[(p & 1) ^ 1]);
+        VAG_HIP(hipGetLastError());
     }
 }
 int kc_grid(int32_t n) {

@@ -2149,7 +2149,7 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
         // modes) and its elimination workspace: at most coarse_size rows
         const double cs = o.amg_coarse_size > 0 ? o.amg_coarse_size : 1000.0;
         const double d = std::min(Nx, std::min(cs, 1024.0));
-        b += 1.125 * amg + 12.0 * d * d + 1024.0 * d + 0.5 * 1024 * 1024;
+        b += 1.125 * amg + 20.0 * d * d + 65536.0 + 0.5 * 1024 * 1024;
     }
     if (o.precond == VAG_PC_BJILU0) b += 14 * nnz + 28 * Nx;        // factor entries, rows, schedules
     if (o.krylov == VAG_GMRES) {  // flexible GMRES: m + 1 basis vectors, m preconditioned ones, a work vector

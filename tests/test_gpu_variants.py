@@ -290,3 +290,22 @@ def test_tetrahedra_fracture_faces(dims, share):
     for k in ("c_cell", "c_frac", "c_node"):
         assert np.abs(c[k] - oc[k]).max(initial=0.0) <= 1e-12, k
     h.close()
+
+
+@pytest.mark.parametrize("dims,n", [((2, 1, 1), 4), ((2, 8, 6), 63), ((2, 7, 7), 64), ((2, 12, 4), 65),
+                                    ((3, 7, 7), 128), ((2, 42, 2), 129), ((2, 32, 30), 1023), ((2, 31, 31), 1024)])
+def test_dense_inverse(dims, n):
+    """Hierarchies of one level, whose V-cycle is the dense inverse: one tile,
+    last tiles of one row and of all but one, an odd and an even number of
+    steps, the most rows there are.  Condition numbers below 10^5: 1e-10 of
+    max |z|."""
+    from paper_1602_03641_amd import vag
+    p = synth.random_problem(dims, 37, n_patches=0, n_steps=0, ratios=(1e2,))
+    h, info = _handle(p, rtol=1e-10, precond=vag.VAG_PC_AMG, amg_coarse_size=1024)
+    assert info["amg_levels"] == 1 and info["n_unknowns"] == n
+    A = oracle.system(p)[0].toarray()
+    r = np.random.default_rng(38).standard_normal(n)
+    z, zr = h.apply_preconditioner(r), np.linalg.solve(A, r)
+    print("condition", np.linalg.cond(A))
+    assert np.abs(z - zr).max() <= 1e-10 * np.abs(zr).max()
+    h.close()
