@@ -64,6 +64,8 @@ void block_levels(const std::vector<int32_t> &fptr, const std::vector<uint16_t> 
 
 __global__ void ilu_solve_lds_kernel(IluArgs g, IluLds L, const double *__restrict__ r, double *__restrict__ z,
                                      const PcgState *st);
+__global__ void ilu_solve_sub_kernel(IluArgs g, IluSub L, const double *__restrict__ r, double *__restrict__ z,
+                                     const PcgState *st);
 
 void Ilu::build(hipStream_t s, Tracker &tr, const Symbolic &S, int B) {
     const int32_t n = S.nunk;
@@ -161,6 +163,26 @@ void Ilu::build(hipStream_t s, Tracker &tr, const Symbolic &S, int B) {
     if (lds_.fits())
         VAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(ilu_solve_lds_kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_.bytes()));
+    // sub-blocks, where their inverses fit in LDS too
+    sub_ = IluSub{};
+    sub_.rows = (B + kIluSub - 1) / kIluSub * kIluSub;
+    sub_.ents = lds_.ents;
+    std::vector<ushort4> sptr;
+    if (n > 0 && ilu_sub_inverses(B) && sub_.fits()) {
+        sptr.resize(n);
+        for (int32_t o = 0; o < n; ++o) {
+            const int32_t b0 = o / B * B, s0 = (o - b0) / kIluSub * kIluSub, e0 = fptr[b0];
+            const auto c0 = fcol.begin() + fptr[o], c1 = fcol.begin() + fptr[o + 1];
+            auto at = [&](int32_t c) { return (uint16_t)(std::lower_bound(c0, c1, c) - fcol.begin() - e0); };
+            sptr[o] = make_ushort4((uint16_t)(fptr[o] - e0), at(s0), at(s0 + kIluSub), (uint16_t)(fptr[o + 1] - e0));
+        }
+        put(s, tr, sptr_, sptr);
+        sinv_.alloc((size_t)nblk * ilu_sub_inverses(B), tr);
+        sub_.ptr = sptr_.p;
+        sub_.inv = sinv_.p;
+        VAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(ilu_solve_sub_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)sub_.bytes()));
+    }
     VAG_HIP(hipStreamSynchronize(s));  // the host vectors go out of scope
     nent_ = nent;
     B_ = B;
@@ -261,7 +283,8 @@ __device__ inline void ilu_sweep(int nlev, const uint16_t *__restrict__ lp, cons
     }
 }
 
-// z = (L U)^-1 r of a block, one wavefront.  The block's values, columns,
+// z = (L U)^-1 r of a block by levels, one wavefront: blocks too large for
+// their sub-blocks' inverses in LDS.  The block's values, columns,
 // schedules and vector are staged in LDS by coalesced loads, all in flight
 // together; the substitutions then touch LDS only.  (Reading slots and entries
 // from global memory level by level cost two dependent round trips per level,
@@ -298,6 +321,132 @@ __global__ __launch_bounds__(kIluThreads) void ilu_solve_lds_kernel(IluArgs g, I
     ilu_sweep<false>(nf, lpf, slf, val, col, nullptr, y);  // L y = r (unit diagonal), in place
     ilu_sweep<true>(nb, lpb, slb, val, col, dinv, y);      // U z = y, in place
     for (int i = tid; i < nr; i += kIluThreads) z[g.rdev[r0 + i]] = y[i];
+}
+
+// The inverses of the sub-blocks' triangles, one wavefront per sub-block: lane
+// j < 16 column j of L^-1, lane 16 + j column j of U^-1.  Rows past the block's
+// end count as the identity.
+__global__ __launch_bounds__(64) void ilu_inverse_kernel(IluArgs g, IluSub L) {
+    __shared__ double M[kIluSub][kIluSub + 1], X[2][kIluSub][kIluSub + 1];
+    const int nsub = L.rows / kIluSub, b = blockIdx.x / nsub, s0 = (blockIdx.x - b * nsub) * kIluSub;
+    const int32_t r0 = b * g.B, nr = min(g.n, r0 + g.B) - r0;
+    const int lane = threadIdx.x;
+    for (int e = lane; e < kIluSub * kIluSub; e += 64) M[e / kIluSub][e % kIluSub] = e / kIluSub == e % kIluSub;
+    __syncthreads();
+    if (lane < kIluSub && s0 + lane < nr) {
+        const ushort4 m = L.ptr[r0 + s0 + lane];
+        const int32_t e0 = g.fptr[r0];
+        for (int p = m.y; p < m.z; ++p) M[lane][g.fcol[e0 + p] - s0] = g.fval[e0 + p];
+    }
+    __syncthreads();
+    const int j = lane & (kIluSub - 1);
+    if (lane < kIluSub) {
+        for (int i = 0; i < kIluSub; ++i) {
+            double v = i == j;
+            for (int k = j; k < i; ++k) v -= M[i][k] * X[0][k][j];
+            X[0][i][j] = i < j ? 0.0 : v;
+        }
+    } else if (lane < 2 * kIluSub) {
+        for (int i = kIluSub - 1; i >= 0; --i) {
+            double v = i == j;
+            for (int k = i + 1; k <= j; ++k) v -= M[i][k] * X[1][k][j];
+            X[1][i][j] = i > j ? 0.0 : v / M[i][i];
+        }
+    }
+    __syncthreads();
+    double *out = L.inv + (int64_t)blockIdx.x * kIluSub * kIluSub;
+    for (int e = lane; e < kIluSub * kIluSub; e += 64) {
+        const int i = e / kIluSub, c = e % kIluSub, col = (c & 3) * 4 + (c >> 2);
+        out[e] = X[col < i ? 0 : 1][i][col];
+    }
+}
+
+// One substitution by sub-blocks, by the block's first wavefront: lane 4 i + q
+// takes every fourth of row i's entries outside the sub-block, then columns q,
+// q + 4, ... of the inverse.  Two exchanges through LDS per 16 rows; what does
+// not depend on y is read a sub-block ahead.
+template <bool BACK>
+__device__ inline void ilu_sub_sweep(int ns, const ushort4 *__restrict__ ptr, const double *__restrict__ val,
+                                     const uint16_t *__restrict__ col, const double *__restrict__ inv, double *y) {
+    const int lane = threadIdx.x, i = lane >> 2, q = lane & 3;
+    struct Ahead {
+        int p, p1;  // the lane's next entry past the two read ahead, and the end
+        double v0, v1;
+        int c0, c1;
+        double m[4];
+    };
+    auto ahead = [&](int s) {
+        Ahead a;
+        const ushort4 w = ptr[s * kIluSub + i];
+        const int p = (BACK ? w.z : w.x) + q;
+        a.p1 = BACK ? w.w : w.y;
+        a.v0 = p < a.p1 ? val[p] : 0.0;
+        a.c0 = p < a.p1 ? col[p] : s * kIluSub;
+        a.v1 = p + 4 < a.p1 ? val[p + 4] : 0.0;
+        a.c1 = p + 4 < a.p1 ? col[p + 4] : s * kIluSub;
+        a.p = p + 8;
+        const double2 *m = reinterpret_cast<const double2 *>(inv + (s * kIluSub + i) * kIluSub + 4 * q);
+        const double2 m0 = m[0], m1 = m[1];
+        const double mm[4] = {m0.x, m0.y, m1.x, m1.y};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a.m[k] = (q + 4 * k >= i) == BACK ? mm[k] : 0.0;
+        return a;
+    };
+    Ahead a = ahead(BACK ? ns - 1 : 0);
+    for (int u = 0; u < ns; ++u) {
+        const int s = BACK ? ns - 1 - u : u, n1 = BACK ? max(s - 1, 0) : min(s + 1, ns - 1);
+        const double y0 = y[s * kIluSub + i];
+        double t = a.v0 * y[a.c0] + a.v1 * y[a.c1];
+        for (int p = a.p; p < a.p1; p += 4) t += val[p] * y[col[p]];
+        const Ahead next = ahead(n1);
+        t = dpp_sum<0xB1>(t);
+        t = y0 - dpp_sum<0x4E>(t);
+        double x = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x += a.m[k] * __shfl(t, 4 * (q + 4 * k), 64);
+        x = dpp_sum<0xB1>(x);
+        x = dpp_sum<0x4E>(x);
+        if (q == 0) y[s * kIluSub + i] = BACK ? x : t + x;
+        // the stores before the next sub-block's loads (one wavefront: LDS in order)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        a = next;
+    }
+}
+
+// z = (L U)^-1 r of a block by sub-blocks, everything staged in LDS by four
+// wavefronts; the first then does the substitutions.  At 113 k unknowns in
+// blocks of 128 an application by levels (~100 of them, one exchange through
+// LDS each) takes 35 us, this 14.
+constexpr int kIluStage = 256;
+__global__ __launch_bounds__(kIluStage) void ilu_solve_sub_kernel(IluArgs g, IluSub L, const double *__restrict__ r,
+                                                                  double *__restrict__ z, const PcgState *st) {
+    if (st && st->done) return;
+    extern __shared__ double lds[];
+    double *inv = lds, *y = inv + L.rows * kIluSub, *val = y + L.rows;
+    ushort4 *ptr = reinterpret_cast<ushort4 *>(val + L.ents);
+    uint16_t *col = reinterpret_cast<uint16_t *>(ptr + L.rows);
+    const int32_t b = blockIdx.x, r0 = b * g.B, nr = min(g.n, r0 + g.B) - r0;
+    const int32_t e0 = g.fptr[r0], ne = g.fptr[r0 + nr] - e0;
+    const int ns = (nr + kIluSub - 1) / kIluSub, tid = threadIdx.x;
+    for (int i = tid; i < ns * kIluSub; i += kIluStage) {
+        y[i] = i < nr ? r[g.rdev[r0 + i]] : 0.0;
+        ptr[i] = i < nr ? L.ptr[r0 + i] : make_ushort4(0, 0, 0, 0);
+    }
+    const double2 *src = reinterpret_cast<const double2 *>(L.inv + (int64_t)b * L.rows * kIluSub);
+#pragma unroll 4
+    for (int e = tid; e < ns * kIluSub * kIluSub / 2; e += kIluStage) reinterpret_cast<double2 *>(inv)[e] = src[e];
+#pragma unroll 4
+    for (int e = tid; e < ne; e += kIluStage) {
+        val[e] = g.fval[e0 + e];
+        col[e] = g.fcol[e0 + e];
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    ilu_sub_sweep<false>(ns, ptr, val, col, inv, y);  // L y = r (unit diagonal), in place
+    ilu_sub_sweep<true>(ns, ptr, val, col, inv, y);   // U z = y, in place
+    for (int i = tid; i < nr; i += 64) z[g.rdev[r0 + i]] = y[i];
 }
 
 // The same from global memory, for blocks whose factor does not fit in LDS
@@ -340,10 +489,19 @@ void Ilu::factor(hipStream_t s, const double *A, int *bad) {
     if (a_.nblk == 0) return;
     hipLaunchKernelGGL(ilu_factor_kernel, dim3(a_.nblk), dim3(kIluThreads), 0, s, a_, A, bad);
     VAG_HIP(hipGetLastError());
+    if (sub_.inv) {
+        hipLaunchKernelGGL(ilu_inverse_kernel, dim3(a_.nblk * (sub_.rows / kIluSub)), dim3(64), 0, s, a_, sub_);
+        VAG_HIP(hipGetLastError());
+    }
 }
 
 void Ilu::apply(hipStream_t s, const double *r, double *z, const PcgState *st) const {
     if (a_.nblk == 0) return;
+    if (sub_.inv) {
+        hipLaunchKernelGGL(ilu_solve_sub_kernel, dim3(a_.nblk), dim3(kIluStage), sub_.bytes(), s, a_, sub_, r, z, st);
+        VAG_HIP(hipGetLastError());
+        return;
+    }
     if (lds_.fits()) {
         hipLaunchKernelGGL(ilu_solve_lds_kernel, dim3(a_.nblk), dim3(kIluThreads), lds_.bytes(), s, a_, lds_, r, z, st);
         VAG_HIP(hipGetLastError());

@@ -309,3 +309,23 @@ def test_dense_inverse(dims, n):
     print("condition", np.linalg.cond(A))
     assert np.abs(z - zr).max() <= 1e-10 * np.abs(zr).max()
     h.close()
+
+
+@pytest.mark.parametrize("dims,B", [((9, 7, 6), 15), ((9, 7, 6), 16), ((9, 7, 6), 17), ((3, 2, 2), 128),
+                                    ((12, 11, 9), 33), ((12, 11, 9), 128), ((12, 11, 9), 400), ((12, 11, 9), 1600)])
+def test_ilu_sub_blocks(dims, B):
+    """Blocks below, of and just past a sub-block of 16 rows, of fewer rows than
+    asked for, of ragged last sub-blocks, and on both sides of where a block's
+    inverses fit in LDS: as test_ilu_substitutions."""
+    from paper_1602_03641_amd import vag
+    from oracle import ilu
+    p = synth.random_problem(dims, 39, n_patches=4, n_steps=0, ratios=(1e2, 1e4))
+    h, info = _handle(p, rtol=1e-8, precond=vag.VAG_PC_BJILU0, krylov=vag.VAG_BICGSTAB, ilu_block_rows=B,
+                      eliminate_frac_faces=0)
+    A, _ = oracle.system(p)
+    rows = ilu.bj_ilu0(A, B)
+    r = np.random.default_rng(40).standard_normal(A.shape[0])
+    z, zr = h.apply_preconditioner(r), ilu.bj_ilu0_apply(rows, r)
+    print("distance", np.abs(z - zr).max() / np.abs(zr).max())
+    assert np.abs(z - zr).max() <= 1e-11 * np.abs(zr).max()
+    h.close()
