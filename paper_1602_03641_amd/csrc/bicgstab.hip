@@ -39,10 +39,12 @@ struct BcgParts {
     __device__ double *ss() const { return base + (size_t)7 * G; }
 };
 
-__device__ inline double total(const BcgParts &P, const double *p) {
-    double v[1];
-    krylov_sums<kT>(P.slices, [&](int) { return p; }, P.G, v);
-    return v[0];
+// The sums of several partial arrays in one pass and one block reduction (one
+// at a time, each costs its own two barriers and chain of loads, ~1 us: six of
+// them were half of the direction kernel's 8 us).
+template <int N>
+__device__ inline void totals(const BcgParts &P, const double *const (&p)[N], double (&v)[N]) {
+    krylov_sums<kT>(P.slices, [&](int i) { return p[i]; }, P.G, v);
 }
 __device__ inline int my_slice() { return (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6); }
 
@@ -80,7 +82,9 @@ __global__ __launch_bounds__(kT) void bcg_init_zero_kernel(int32_t n, int k0, co
 
 __global__ __launch_bounds__(kT) void bcg_start_kernel(BcgParts P, PcgState *st, double rtol, int k0,
                                                        int *host_done) {
-    const double rr = total(P, P.rr(k0 - 1));
+    double v[1];
+    totals(P, {P.rr(k0 - 1)}, v);
+    const double rr = v[0];
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         if (k0 == 0) st->bnorm2 = rr;
         st->tol2 = rtol * rtol * rr;
@@ -97,8 +101,10 @@ __global__ __launch_bounds__(kT) void bcg_direction_kernel(int32_t n, int k, int
                                                            double *__restrict__ p, const double *__restrict__ v,
                                                            BcgParts P, PcgState *st, int update) {
     if (st->done) return;
-    const double rr = total(P, P.rr(k - 1));
-    const double rho = total(P, P.rho(k - 1));
+    // those of the last iteration are read (and not used) before there is one
+    double w[6];
+    totals(P, {P.rr(k - 1), P.rho(k - 1), P.rho(k - 2), P.rv(), P.ts(), P.tt()}, w);
+    const double rr = w[0], rho = w[1];
     const bool conv = rr <= st->tol2;
     if (conv || rho == 0.0 || !(rr == rr)) {  // converged, breakdown (rhat orthogonal to r) or NaN
         if (blockIdx.x == 0 && threadIdx.x == 0) krylov_done(st, conv ? 1 : 0, rr);
@@ -112,9 +118,9 @@ __global__ __launch_bounds__(kT) void bcg_direction_kernel(int32_t n, int k, int
         GSB(i, n) p[i] = r[i];
         return;
     }
-    const double rho_prev = total(P, P.rho(k - 2));
-    const double alpha = rho_prev / total(P, P.rv());
-    const double omega = total(P, P.ts()) / total(P, P.tt());
+    const double rho_prev = w[2];
+    const double alpha = rho_prev / w[3];
+    const double omega = w[4] / w[5];
     const double beta = (rho / rho_prev) * (alpha / omega);
     GSB(i, n) p[i] = r[i] + beta * (p[i] - omega * v[i]);
 }
@@ -142,12 +148,14 @@ __global__ __launch_bounds__(SPLIT ? kSplitThreads : kT) void bcg_spmv_dot_kerne
     }
 }
 
-// s = r - alpha v; if |s| already meets the tolerance, x += alpha phat and stop
+// s = r - alpha v and the partials of s.s
 __global__ __launch_bounds__(kT) void bcg_s_kernel(int32_t n, int k, const double *__restrict__ r,
                                                    const double *__restrict__ v, double *__restrict__ s, BcgParts P,
                                                    const PcgState *st) {
     if (st->done) return;
-    const double alpha = total(P, P.rho(k - 1)) / total(P, P.rv());
+    double c[2];
+    totals(P, {P.rho(k - 1), P.rv()}, c);
+    const double alpha = c[0] / c[1];
     double w[1] = {0.0};
     GSB(i, n) {
         const double si = r[i] - alpha * v[i];
@@ -157,34 +165,27 @@ __global__ __launch_bounds__(kT) void bcg_s_kernel(int32_t n, int k, const doubl
     krylov_put<kT, 1>(P.slices, [&](int) { return P.ss(); }, my_slice(), w);
 }
 
-// the half step: when |s|^2 <= tol2, x += alpha phat and the solve is done
-__global__ __launch_bounds__(kT) void bcg_half_kernel(int32_t n, int k, const double *__restrict__ phat,
-                                                      double *__restrict__ x, BcgParts P, PcgState *st) {
-    if (st->done) return;
-    const double ss = total(P, P.ss());
-    if (!(ss <= st->tol2)) return;
-    const double alpha = total(P, P.rho(k - 1)) / total(P, P.rv());
-    GSB(i, n) x[i] += alpha * phat[i];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->iter = k + 1;
-        krylov_done(st, 1, ss);
-    }
-}
-
-// x += alpha phat + omega shat, r = s - omega t; partials r.r and rhat.r
+// x += alpha phat + omega shat, r = s - omega t; partials r.r and rhat.r.
+// When |s|^2 already meets the tolerance, x += alpha phat and r = s: the next
+// direction kernel finds the solve converged.  Asked here, behind the second
+// product, because a kernel of its own for the question took 3 us of every
+// iteration.
 __global__ __launch_bounds__(kT) void bcg_update_kernel(int32_t n, int k, const double *__restrict__ phat,
                                                         const double *__restrict__ shat,
                                                         const double *__restrict__ s, const double *__restrict__ t,
                                                         const double *__restrict__ rhat, double *__restrict__ x,
                                                         double *__restrict__ r, BcgParts P, PcgState *st) {
     if (st->done) return;
-    const double alpha = total(P, P.rho(k - 1)) / total(P, P.rv());
-    const double tt = total(P, P.tt());
-    const double omega = tt > 0.0 ? total(P, P.ts()) / tt : 0.0;
+    double c[5];
+    totals(P, {P.rho(k - 1), P.rv(), P.tt(), P.ts(), P.ss()}, c);
+    const double alpha = c[0] / c[1], tt = c[2];
+    const bool half = c[4] <= st->tol2;
+    const double omega = tt > 0.0 ? c[3] / tt : 0.0;
     double v[2] = {0.0, 0.0};
     GSB(i, n) {
-        x[i] += alpha * phat[i] + omega * shat[i];
-        const double ri = s[i] - omega * t[i];
+        const double xi = x[i], step = fma(alpha, phat[i], omega * shat[i]);
+        x[i] = half ? fma(alpha, phat[i], xi) : xi + step;
+        const double ri = half ? s[i] : s[i] - omega * t[i];
         r[i] = ri;
         v[0] += ri * ri;
         v[1] += rhat[i] * ri;
@@ -230,11 +231,10 @@ void launch_bcg_spmv_v(hipStream_t s, Sell<double> A, const double *phat, double
     const BcgParts P = bcg_parts(parts, A.n);
     BROWS(A.n, bcg_spmv_dot_kernel, A, phat, v, rhat, P, parts + (size_t)2 * P.G, (double *)nullptr, st);
 }
-void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, const double *phat, double *sv,
-                  double *x, double *parts, PcgState *st) {
+void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, double *sv, double *parts,
+                  const PcgState *st) {
     const BcgParts P = bcg_parts(parts, n);
     BLAUNCH(n, bcg_s_kernel, n, k, r, v, sv, P, st);
-    BLAUNCH(n, bcg_half_kernel, n, k, phat, x, P, st);
 }
 void launch_bcg_spmv_t(hipStream_t s, Sell<double> A, const double *shat, double *t, const double *sv, double *parts,
                        const PcgState *st) {

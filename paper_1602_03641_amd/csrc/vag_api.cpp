@@ -583,7 +583,7 @@ void run_bicgstab(vag_handle *h) {
                 launch_bcg_direction(s, n, k, k0, h->r.p, h->p.p, h->q.p, parts, st, true);
                 precond_apply(h, h->p.p, h->z.p, st);
                 launch_bcg_spmv_v(s, A, h->z.p, h->q.p, h->bcg_rhat.p, parts, st);
-                launch_bcg_s(s, n, k, h->r.p, h->q.p, h->z.p, h->bcg_s.p, h->x.p, parts, st);
+                launch_bcg_s(s, n, k, h->r.p, h->q.p, h->bcg_s.p, parts, st);
                 precond_apply(h, h->bcg_s.p, h->bcg_shat.p, st);
                 launch_bcg_spmv_t(s, A, h->bcg_shat.p, h->bcg_t.p, h->bcg_s.p, parts, st);
                 launch_bcg_update(s, n, k, h->z.p, h->bcg_shat.p, h->bcg_s.p, h->bcg_t.p, h->bcg_rhat.p, h->x.p,

@@ -427,8 +427,8 @@ void launch_bcg_direction(hipStream_t s, int32_t n, int k, int k0, const double 
                           double *parts, PcgState *st, bool update);
 void launch_bcg_spmv_v(hipStream_t s, Sell<double> A, const double *phat, double *v, const double *rhat,
                        double *parts, const PcgState *st);
-void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, const double *phat, double *sv,
-                  double *x, double *parts, PcgState *st);
+void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, double *sv, double *parts,
+                  const PcgState *st);
 void launch_bcg_spmv_t(hipStream_t s, Sell<double> A, const double *shat, double *t, const double *sv, double *parts,
                        const PcgState *st);
 void launch_bcg_update(hipStream_t s, int32_t n, int k, const double *phat, const double *shat, const double *sv,
