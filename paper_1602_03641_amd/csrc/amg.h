@@ -24,6 +24,12 @@ struct CoarsenInit {
     int32_t *cnt, *cursor;
     int nundecided = kMisRounds * kCntSlots * kCntStride;
 };
+// Until the device says in pinned memory that it has begun round `least`, or
+// that there are no more (a value past `last`), or nothing runs any more.
+inline void poll_rounds(hipStream_t s, volatile int *started, int least, int last) {
+    for (int spin = 0; *started < least && *started <= last; ++spin)
+        if ((spin & 1023) == 1023 && hipStreamQuery(s) != hipErrorNotReady) break;
+}
 // roots of the coarsening (flag); scol: a stored-size scratch array; progress:
 // pinned host memory
 void amg_launch_mis(hipStream_t s, Sell<double> A, const double *diag, double theta, int rounds, int hops,
@@ -121,12 +127,13 @@ void launch_to_double(hipStream_t s, int64_t n, const float *a, double *b);
 // slots per row; rows are processed in chunks of kClChunk
 constexpr int32_t kClCapMax = 16384;
 constexpr int32_t kClChunk = 65536;
+// counts: kMisRounds ints, cleared
 void cl_launch_strength(hipStream_t s, Sell<double> A, double theta, double *m, uint8_t *sf, uint64_t *key,
-                        int8_t *state);
-// one PMIS round (tmp: n bytes); *cnt += blocks that still hold undecided points
-void cl_launch_pmis_round(hipStream_t s, Sell<double> A, const uint8_t *sf, const uint64_t *key, int8_t *st,
-                          int8_t *tmp, int *cnt);
-void cl_launch_pmis_close(hipStream_t s, int32_t n, int8_t *st);
+                        int8_t *state, int *counts);
+// PMIS from the states st, in place.  counts: the kMisRounds zeros that
+// cl_launch_strength left, progress: pinned host memory
+void cl_launch_pmis(hipStream_t s, Sell<double> A, const uint8_t *sf, const uint64_t *key, int8_t *st, int *counts,
+                    int *progress);
 void cl_launch_interp_count(hipStream_t s, Sell<double> A, const uint8_t *sf, const int8_t *st, int32_t *plen,
                             int32_t *cflag);
 void cl_launch_interp_fill(hipStream_t s, Sell<double> A, const uint8_t *sf, const int8_t *st, const int32_t *cidx,
@@ -252,7 +259,7 @@ class Amg {
     DBuf<double> cm_, chval_, capval_;
     DBuf<uint8_t> csf_;
     DBuf<uint64_t> ckey_;
-    DBuf<int8_t> cst_, cst2_;
+    DBuf<int8_t> cst_;
     DBuf<int32_t> cplen_, cflag_, ccidx_, ccfine_, crlen_, ccap_, choff_, chkey_, captr_, capcol_;
     DBuf<int64_t> captr64_, csums_, ctmp64_;
     void setup_classical(hipStream_t s, Tracker &tr, int64_t stored0);

@@ -56,23 +56,6 @@ __device__ inline uint32_t perm30(uint32_t x) {
 // row's priority below
 __device__ inline int rank_of(uint32_t t) { return (int)(t >> 30); }
 
-// The slots of row i of a sliced-ELL array, kSlots at a time: load(j, q) for
-// the batch (a slot past the row repeats its first, whose lines are there
-// already), so that a row waits for one chain of loads a batch and not one a
-// slot, then use(j, q) in slot order for those that exist.
-constexpr int kSlots = 8;
-template <class Load, class Use>
-__device__ inline void row_slots(const int64_t *__restrict__ ptr, int64_t i, Load load, Use use) {
-    const int64_t b1 = ptr[(i >> 6) + 1];
-    for (int64_t q0 = ptr[i >> 6] + (i & 63); q0 < b1; q0 += 64 * kSlots) {
-#pragma unroll
-        for (int j = 0; j < kSlots; ++j) load(j, q0 + 64 * j < b1 ? q0 + 64 * j : q0);
-#pragma unroll
-        for (int j = 0; j < kSlots; ++j)
-            if (q0 + 64 * j < b1) use(j, q0 + 64 * j);
-    }
-}
-
 // diag and l1-Jacobi inverse
 __global__ __launch_bounds__(kAT) void amg_diag_kernel(Sell<double> A, double *__restrict__ diag,
                                                        double *__restrict__ dinv) {
@@ -1651,8 +1634,7 @@ void amg_launch_mis(hipStream_t s, Sell<double> A, const double *diag, double th
         // pinned memory which round it has begun; the host stays at most three
         // rounds ahead of it, so the device never waits for the host's look as
         // it did for a copy and a synchronisation every fourth round.
-        for (int spin = 0; *started < r - 2 && *started <= kMisRounds; ++spin)
-            if ((spin & 1023) == 1023 && hipStreamQuery(s) != hipErrorNotReady) break;  // nothing runs any more
+        poll_rounds(s, started, r - 2, kMisRounds);
         if (*started > kMisRounds) break;
     }
     ALAUNCH(mis_flag_kernel, gridv(A.n), kAT, A.n, I.T, flag);

@@ -26,13 +26,15 @@
 
 #include "amg.h"
 #include "reduce.h"
+#include "sell.h"
 
 namespace vag {
 
 namespace {
 
 constexpr int kCT = 256;
-constexpr int8_t kU = 0, kC = 1, kF = 2;
+// undecided, coarse, fine; kN: coarse since this round's selection
+constexpr int8_t kU = 0, kC = 1, kF = 2, kN = 3;
 
 #define CL_GS(i, n) \
     for (int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); i < (n); i += (int32_t)(gridDim.x * blockDim.x))
@@ -54,80 +56,105 @@ __device__ inline uint32_t mix32(uint32_t x) {
 
 }  // namespace
 
+// (The kernels over matrix rows read eight slots ahead, row_slots: on the four
+// levels of a 64^3 mesh the row maxima took 151 us and the strengths 135 one
+// slot's chain of loads at a time, now 35 and 89.)
 // m_i = max over off-diagonal entries of -a_ij (0 when none is negative)
 __global__ __launch_bounds__(kCT) void cl_negmax_kernel(Sell<double> A, double *m) {
     CL_GS(i, A.n) {
-        const int64_t b = sell_at(A.ptr, i);
-        const int w = sell_w(A.ptr, i);
-        double mx = 0.0;
-        for (int j = 0; j < w; ++j) {
-            const int64_t p = b + (int64_t)j * 64;
-            if (A.col[p] != i) mx = fmax(mx, -A.val[p]);
-        }
+        double mx = 0.0, v[kSlots];
+        int32_t c[kSlots];
+        row_slots(
+            A.ptr, i,
+            [&](int j, int64_t p) {
+                c[j] = A.col[p];
+                v[j] = A.val[p];
+            },
+            [&](int j, int64_t) {
+                if (c[j] != i) mx = fmax(mx, -v[j]);
+            });
         m[i] = mx;
     }
 }
 
 // per stored entry: bit 0 = i depends strongly on j, bit 1 = j depends
-// strongly on i; keys and initial states
+// strongly on i; keys and initial states; the rounds' counts cleared
 __global__ __launch_bounds__(kCT) void cl_strength_kernel(Sell<double> A, const double *m, double theta, uint8_t *sf,
-                                                          uint64_t *key, int8_t *state) {
+                                                          uint64_t *key, int8_t *state, int *counts) {
+    CL_GS(k, kMisRounds) counts[k] = 0;
     CL_GS(i, A.n) {
-        const int64_t b = sell_at(A.ptr, i);
-        const int w = sell_w(A.ptr, i);
         const double mi = m[i];
         uint32_t lam = 0;
-        for (int j = 0; j < w; ++j) {
-            const int64_t p = b + (int64_t)j * 64;
-            const int32_t c = A.col[p];
-            const double v = -A.val[p];
-            uint8_t f = 0;
-            if (c != i && v > 0.0) {
-                if (v >= theta * mi) f |= 1;
-                if (v >= theta * m[c]) f |= 2;
-            }
-            sf[p] = f;
-            lam += f >> 1;
-        }
+        double v[kSlots], mj[kSlots];
+        int32_t c[kSlots];
+        row_slots(
+            A.ptr, i,
+            [&](int j, int64_t p) {
+                c[j] = A.col[p];
+                v[j] = -A.val[p];
+                mj[j] = m[c[j]];
+            },
+            [&](int j, int64_t p) {
+                uint8_t f = 0;
+                if (c[j] != i && v[j] > 0.0) {
+                    if (v[j] >= theta * mi) f |= 1;
+                    if (v[j] >= theta * mj[j]) f |= 2;
+                }
+                sf[p] = f;
+                lam += f >> 1;
+            });
         key[i] = ((uint64_t)lam << 32) | mix32((uint32_t)i);
         state[i] = lam == 0 ? kF : kU;
     }
 }
 
-// undecided points whose key beats every undecided strong neighbour become coarse
+// Undecided points whose key beats every strong neighbour undecided at the
+// round's start (kU or by now kN) become coarse.  progress (pinned): the round
+// begun, or past kMisRounds when the last one (its count `last`, null in round
+// 0) left nothing undecided; rounds from there on return at once.
 __global__ __launch_bounds__(kCT) void cl_pmis_select_kernel(Sell<double> A, const uint8_t *sf, const uint64_t *key,
-                                                             const int8_t *in, int8_t *out) {
+                                                             int8_t *st, int round, const int *last, int *progress) {
+    const bool over = last && *last == 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) host_put(progress, over ? kMisRounds + 1 : round + 1);
+    if (over) return;
     CL_GS(i, A.n) {
-        int8_t s = in[i];
-        if (s == kU) {
-            const int64_t b = sell_at(A.ptr, i);
-            const int w = sell_w(A.ptr, i);
-            const uint64_t ki = key[i];
-            bool top = true;
-            for (int j = 0; j < w && top; ++j) {
-                const int64_t p = b + (int64_t)j * 64;
-                const int32_t c = A.col[p];
-                if (sf[p] && in[c] == kU && key[c] > ki) top = false;
-            }
-            if (top) s = kC;
-        }
-        out[i] = s;
+        if (st[i] != kU) continue;
+        const uint64_t ki = key[i];
+        bool top = true;
+        int32_t c[kSlots];
+        uint8_t f[kSlots];
+        int8_t u[kSlots];
+        uint64_t k[kSlots];
+        row_slots(
+            A.ptr, i,
+            [&](int j, int64_t p) {
+                c[j] = A.col[p];
+                f[j] = sf[p];
+                u[j] = st[c[j]];
+                k[j] = key[c[j]];
+            },
+            [&](int j, int64_t) { top = top && !(f[j] && (u[j] == kU || u[j] == kN) && k[j] > ki); });
+        if (top) st[i] = kN;
     }
 }
 
 // undecided points that depend strongly on a coarse point become fine; the
 // remaining undecided points are counted (one atomic per block)
-__global__ __launch_bounds__(kCT) void cl_pmis_fine_kernel(Sell<double> A, const uint8_t *sf, int8_t *st, int *cnt) {
+__global__ __launch_bounds__(kCT) void cl_pmis_fine_kernel(Sell<double> A, const uint8_t *sf, int8_t *st, int *cnt,
+                                                           const int *last) {
+    if (last && *last == 0) return;
     int mine = 0;
     CL_GS(i, A.n) {
+        if (st[i] == kN) st[i] = kC;
         if (st[i] != kU) continue;
-        const int64_t b = sell_at(A.ptr, i);
-        const int w = sell_w(A.ptr, i);
-        bool fine = false;
-        for (int j = 0; j < w && !fine; ++j) {
-            const int64_t p = b + (int64_t)j * 64;
-            if ((sf[p] & 1) && st[A.col[p]] == kC) fine = true;
-        }
+        bool fine = false, f[kSlots];
+        row_slots(
+            A.ptr, i,
+            [&](int j, int64_t p) {
+                const int8_t u = st[A.col[p]];
+                f[j] = (sf[p] & 1) && (u == kC || u == kN);
+            },
+            [&](int j, int64_t) { fine = fine || f[j]; });
         if (fine)
             st[i] = kF;
         else
@@ -152,13 +179,11 @@ __global__ __launch_bounds__(kCT) void cl_interp_count_kernel(Sell<double> A, co
             continue;
         }
         cflag[i] = 0;
-        const int64_t b = sell_at(A.ptr, i);
-        const int w = sell_w(A.ptr, i);
         int32_t c = 0;
-        for (int j = 0; j < w; ++j) {
-            const int64_t p = b + (int64_t)j * 64;
-            c += (sf[p] & 1) && st[A.col[p]] == kC;
-        }
+        bool f[kSlots];
+        row_slots(
+            A.ptr, i, [&](int j, int64_t p) { f[j] = (sf[p] & 1) && st[A.col[p]] == kC; },
+            [&](int j, int64_t) { c += f[j]; });
         plen[i] = c;
     }
 }
@@ -175,31 +200,31 @@ __global__ __launch_bounds__(kCT) void cl_interp_fill_kernel(Sell<double> A, con
             continue;
         }
         if (pptr[i + 1] == q) continue;
-        const int64_t b = sell_at(A.ptr, i);
-        const int w = sell_w(A.ptr, i);
-        double aii = 0.0, neg = 0.0, pos = 0.0, negc = 0.0;
-        for (int j = 0; j < w; ++j) {
-            const int64_t p = b + (int64_t)j * 64;
-            const int32_t c = A.col[p];
-            const double v = A.val[p];
-            if (c == i) {
-                aii += v;  // padding entries hold 0
+        double aii = 0.0, neg = 0.0, pos = 0.0, negc = 0.0, v[kSlots];
+        int32_t c[kSlots];
+        bool f[kSlots];
+        auto load = [&](int j, int64_t p) {
+            c[j] = A.col[p];
+            v[j] = A.val[p];
+            f[j] = (sf[p] & 1) && st[c[j]] == kC;
+        };
+        row_slots(A.ptr, i, load, [&](int j, int64_t) {
+            if (c[j] == i) {
+                aii += v[j];  // padding entries hold 0
             } else {
-                neg += fmin(v, 0.0);
-                pos += fmax(v, 0.0);
-                if ((sf[p] & 1) && st[c] == kC) negc += v;
+                neg += fmin(v[j], 0.0);
+                pos += fmax(v[j], 0.0);
+                if (f[j]) negc += v[j];
             }
-        }
+        });
         const double scale = -(neg / negc) / (aii + pos);
-        for (int j = 0; j < w; ++j) {
-            const int64_t p = b + (int64_t)j * 64;
-            const int32_t c = A.col[p];
-            if (c != i && (sf[p] & 1) && st[c] == kC) {
-                pcol[q] = cidx[c];
-                pval[q] = scale * A.val[p];
+        row_slots(A.ptr, i, load, [&](int j, int64_t) {
+            if (c[j] != i && f[j]) {
+                pcol[q] = cidx[c[j]];
+                pval[q] = scale * v[j];
                 ++q;
             }
-        }
+        });
     }
 }
 
@@ -676,20 +701,24 @@ __global__ __launch_bounds__(kCT) void cl_prolong_kernel(int32_t n, const int32_
     } while (0)
 
 void cl_launch_strength(hipStream_t s, Sell<double> A, double theta, double *m, uint8_t *sf, uint64_t *key,
-                        int8_t *state) {
+                        int8_t *state, int *counts) {
     if (A.n <= 0) return;
     CLAUNCH(cl_negmax_kernel, cgrid(A.n), A, m);
-    CLAUNCH(cl_strength_kernel, cgrid(A.n), A, m, theta, sf, key, state);
+    CLAUNCH(cl_strength_kernel, cgrid(A.n), A, m, theta, sf, key, state, counts);
 }
-void cl_launch_pmis_round(hipStream_t s, Sell<double> A, const uint8_t *sf, const uint64_t *key, int8_t *st,
-                          int8_t *tmp, int *cnt) {
+void cl_launch_pmis(hipStream_t s, Sell<double> A, const uint8_t *sf, const uint64_t *key, int8_t *st, int *counts,
+                    int *progress) {
     if (A.n <= 0) return;
-    CLAUNCH(cl_pmis_select_kernel, cgrid(A.n), A, sf, key, st, tmp);
-    CLAUNCH(cl_pmis_fine_kernel, cgrid(A.n), A, sf, tmp, cnt);
-    VAG_HIP(hipMemcpyAsync(st, tmp, (size_t)A.n, hipMemcpyDeviceToDevice, s));
-}
-void cl_launch_pmis_close(hipStream_t s, int32_t n, int8_t *st) {
-    if (n > 0) CLAUNCH(cl_pmis_close_kernel, cgrid(n), n, st);
+    volatile int *started = progress;
+    *started = 0;
+    for (int r = 0; r < kMisRounds; ++r) {
+        const int *last = r ? counts + r - 1 : nullptr;
+        CLAUNCH(cl_pmis_select_kernel, cgrid(A.n), A, sf, key, st, r, last, progress);
+        CLAUNCH(cl_pmis_fine_kernel, cgrid(A.n), A, sf, st, counts + r, last);
+        poll_rounds(s, started, r - 2, kMisRounds);
+        if (*started > kMisRounds) return;
+    }
+    CLAUNCH(cl_pmis_close_kernel, cgrid(A.n), A.n, st);
 }
 void cl_launch_interp_count(hipStream_t s, Sell<double> A, const uint8_t *sf, const int8_t *st, int32_t *plen,
                             int32_t *cflag) {

@@ -189,9 +189,6 @@ void Amg::setup_classical(hipStream_t s, Tracker &tr, int64_t stored0) {
     VAG_HIP(hipMemsetAsync(level_nnz.p, 0, level_nnz.n * sizeof(unsigned long long), s));
     int64_t stored_total = stored0;
     int l = 0;
-    auto read32 = [&](const int32_t *d, int k) {
-        VAG_HIP(hipMemcpyAsync(h_ + k, d, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    };
     for (;; ++l) {
         AmgLevel &lv = *L[l];
         const int32_t n = lv.n;
@@ -204,28 +201,16 @@ void Amg::setup_classical(hipStream_t s, Tracker &tr, int64_t stored0) {
         ensure(csf_, (size_t)lv.stored, tr);
         ensure(ckey_, n, tr);
         ensure(cst_, n, tr);
-        ensure(cst2_, n, tr);
-        cl_launch_strength(s, lv.A, o_.strong_theta, cm_.p, csf_.p, ckey_.p, cst_.p);
-        VAG_HIP(hipMemsetAsync(mis_cnt_.p, 0, (size_t)kMisRounds * sizeof(int), s));
-        bool done = false;
-        for (int r = 0; r < kMisRounds && !done;) {
-            const int r1 = std::min(r + 4, kMisRounds);
-            for (; r < r1; ++r) cl_launch_pmis_round(s, lv.A, csf_.p, ckey_.p, cst_.p, cst2_.p, mis_cnt_.p + r);
-            read32(mis_cnt_.p + r - 1, 0);
-            VAG_HIP(hipStreamSynchronize(s));
-            done = h_[0] == 0;
-        }
-        if (!done) cl_launch_pmis_close(s, n, cst_.p);
+        cl_launch_strength(s, lv.A, o_.strong_theta, cm_.p, csf_.p, ckey_.p, cst_.p, mis_cnt_.p);
+        cl_launch_pmis(s, lv.A, csf_.p, ckey_.p, cst_.p, mis_cnt_.p, h_ + 16);
         // interpolation
         ensure(cplen_, (size_t)n + 1, tr);
         ensure(cflag_, (size_t)n + 1, tr);
         ensure(ccidx_, (size_t)n + 1, tr);
         ensure(lv.pptr, (size_t)n + 1, tr);
         cl_launch_interp_count(s, lv.A, csf_.p, cst_.p, cplen_.p, cflag_.p);
-        amg_launch_scan(s, n, cflag_.p, ccidx_.p, stmp_.p);
-        amg_launch_scan(s, n, cplen_.p, lv.pptr.p, stmp_.p);
-        read32(ccidx_.p + n, 0);
-        read32(lv.pptr.p + n, 1);
+        amg_launch_scan(s, n, cflag_.p, ccidx_.p, stmp_.p, h_);
+        amg_launch_scan(s, n, cplen_.p, lv.pptr.p, stmp_.p, h_ + 1);
         VAG_HIP(hipStreamSynchronize(s));
         const int32_t nc = h_[0], pnnz = h_[1];
         if (nc <= 0 || nc > (int64_t)n * 9 / 10) break;  // coarsening stalled: this level is the coarsest
@@ -238,8 +223,7 @@ void Amg::setup_classical(hipStream_t s, Tracker &tr, int64_t stored0) {
         ensure(lv.rptr, (size_t)nc + 1, tr);
         cl_launch_transpose(s, lv.A, nc, ccfine_.p, cst_.p, lv.pptr.p, lv.pcol.p, lv.pval.p, crlen_.p, nullptr,
                             nullptr, nullptr);
-        amg_launch_scan(s, nc, crlen_.p, lv.rptr.p, stmp_.p);
-        read32(lv.rptr.p + nc, 0);
+        amg_launch_scan(s, nc, crlen_.p, lv.rptr.p, stmp_.p, h_);
         VAG_HIP(hipStreamSynchronize(s));
         const int32_t rnnz = h_[0];
         ensure(lv.rcol, (size_t)rnnz, tr);

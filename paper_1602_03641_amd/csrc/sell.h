@@ -216,4 +216,21 @@ __device__ inline void split_rows(int32_t n, int G, int32_t i, Acc s, Row row, P
         VAG_HIP(hipGetLastError());             \
     } while (0)
 
+// The slots of row i of a sliced-ELL array, kSlots at a time: load(j, q) for
+// the batch (a slot past the row repeats its first, whose lines are there
+// already), so that a row waits for one chain of loads a batch and not one a
+// slot, then use(j, q) in slot order for those that exist.
+constexpr int kSlots = 8;
+template <class Load, class Use>
+__device__ inline void row_slots(const int64_t *__restrict__ ptr, int64_t i, Load load, Use use) {
+    const int64_t b1 = ptr[(i >> 6) + 1];
+    for (int64_t q0 = ptr[i >> 6] + (i & 63); q0 < b1; q0 += 64 * kSlots) {
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) load(j, q0 + 64 * j < b1 ? q0 + 64 * j : q0);
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j)
+            if (q0 + 64 * j < b1) use(j, q0 + 64 * j);
+    }
+}
+
 }  // namespace vag
