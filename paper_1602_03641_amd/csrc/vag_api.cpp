@@ -177,7 +177,8 @@ struct vag_handle {
     // results
     DBuf<double> u_node, u_cell, u_frac, F_cell, F_cell_frac, F_frac, phi_cell, phi_frac, phi_node;
     // transport
-    DBuf<int32_t> slice_width, slice_nnz, tcol, tbase;
+    DBuf<int32_t> slice_width, slice_nnz, tcol;
+    DBuf<int4> tbase;
     DBuf<uint16_t> tcol16;
     DBuf<uint16_t> tmeta;
     DBuf<int64_t> slice_ptr;
@@ -1656,7 +1657,8 @@ namespace {
 // 209 / 191 for 16.
 int64_t noalloc_op_steps(int64_t nrow) { return nrow >= (1 << 18) ? 4 : 12; }
 struct NoallocOp {
-    int32_t *width, *nnz, *col, *base;
+    int32_t *width, *nnz, *col;
+    int4 *base;
     int64_t *ptr, *scan;
     uint16_t *meta, *col16;
     double *val, *diag;
@@ -2138,7 +2140,7 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
     b += 88 * Nc + 56 * Nf + 16 * Nn;                               // pressures, fluxes, porous volumes
     if (o.alpha_rule == 1) b += 8 * Nn;                             // largest permeability per node
     const double nrow = Nn + Nc + Nf, tst = 2.0 * (8 * Nc + 6 * Nf) + 64.0 * 16;
-    b += 24 * nrow + 12 * tst + 12 * nrow / 64;                     // transport
+    b += 24 * nrow + 12 * tst + 28 * nrow / 64;                     // transport
     if (o.precond == VAG_PC_AMG) {
         double amg = 104 * Nx + 17 * S + 0.15 * (12 * S + 104 * Nx);
         if (o.precision == VAG_MIXED) amg += 4.6 * S + 50 * Nx;

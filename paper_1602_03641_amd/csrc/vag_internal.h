@@ -540,8 +540,9 @@ void launch_upwind_fill(hipStream_t s, int32_t nc, int32_t nf, int32_t nn, const
                         double *tval, double *tdiag);
 // Upwind operator: 64-row slices (rows sorted longest first, meta = source
 // lane << 8 | entry count per slot), entries packed by level (jagged
-// diagonals) from slice_ptr[slice]; 16-bit columns from tbase[slice] where
-// tbase >= 0, else the 32-bit tcol.
+// diagonals) from slice_ptr[slice]; 16-bit columns by tbase[slice] = {b0, b1,
+// split} (column = code + (code < split ? b0 : b1)) where split >= 0, else the
+// 32-bit tcol.
 // The sweep splits the slices into two segments, A = [0, sa) (cells and
 // fracture faces) and B = [sa, nslice) (nodes), and gives XCD x of the 8 the
 // slices [xlo[x], xlo[x+1]) of A and [ylo[x], ylo[x+1]) of B, runs of equal
@@ -557,12 +558,12 @@ struct UpwindOp {
     const uint16_t *meta;
     const int32_t *tcol;
     const uint16_t *tcol16;
-    const int32_t *tbase;
+    const int4 *tbase;
     const double *tval, *tdiag;
     int32_t xlo[9], ylo[9];
 };
 // tcol16 and tbase from tcol (after launch_upwind_fill)
-void launch_upwind_pack(hipStream_t s, const UpwindOp &T, uint16_t *tcol16, int32_t *tbase);
+void launch_upwind_pack(hipStream_t s, const UpwindOp &T, uint16_t *tcol16, int4 *tbase);
 // xlo[0..8] and ylo[0..8] (at xlo + 9) from slice_ptr (after the slice scan)
 void launch_xcd_split(hipStream_t s, int32_t nslice, int32_t sa, const int64_t *slice_ptr, int32_t *xlo);
 // backward: sweep each XCD's slices in reverse order (alternate steps)

@@ -329,3 +329,24 @@ def test_ilu_sub_blocks(dims, B):
     print("distance", np.abs(z - zr).max() / np.abs(zr).max())
     assert np.abs(z - zr).max() <= 1e-11 * np.abs(zr).max()
     h.close()
+
+
+@pytest.mark.parametrize("dims,patches", [((12, 11, 10), 6), ((43, 44, 45), 0), ((43, 44, 45), 40), ((300, 9, 16), 12)])
+def test_transport_column_codes(dims, patches):
+    """Operators whose columns lie in one cluster, in two (fracture faces more
+    than 65536 away from the cells' nodes) and, at wells, in neither form: two
+    steps of a random state against the same steps without the operator, within
+    the 1e-12 of the order of additions."""
+    from paper_1602_03641_amd import vag
+    p = synth.random_problem(dims, 41, n_patches=patches, n_steps=0, ratios=(1e1, 1e4))
+    if patches:
+        synth.add_wells(p, 4, n_inj=1, n_prod=1)
+    h, _ = _handle(p, rtol=1e-8, precond=vag.VAG_PC_AMG)
+    rng = np.random.default_rng(42)
+    c0 = {k: rng.uniform(0, 1, n) for k, n in (("c_cell", p.n_cells), ("c_frac", p.n_frac), ("c_node", p.n_nodes))}
+    h.transport(n_steps=2, c0=c0)
+    ref = vag.to_numpy(h.concentration())
+    got = vag.to_numpy(h.transport_noalloc(n_steps=2, c0=c0)[0])
+    for k in ref:
+        assert np.abs(got[k] - ref[k]).max(initial=0.0) <= 1e-12, k
+    h.close()
