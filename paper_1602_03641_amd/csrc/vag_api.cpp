@@ -1595,58 +1595,6 @@ void transport_report(vag_handle *h, const TransportPlan &P, vag_transport_info 
     info->t_nnz = h->h_cnt[0];
     info->t_stored = P.total;
 }
-
-// The powers of the operator for a call of many steps on a small mesh, built
-// for the call and released with it.  A step alone takes 3.6 to 4 us, by fours
-// 0.9 (12.6 k rows of a 64 x 64 x 1 mesh) to 1.7 (12.8 k rows of 18^3), by twos
-// 1.8 (17 k rows of 20^3); building them and looking at the result 80 us (2.4 k
-// rows) to 120 (12.8 k), even at 40 to 60 steps.  Up to kPowerRows4 rows T^4 is read from the L2s in the
-// time of a launch; T^2 up to kPowerRows (46 k rows: 2.9 against 3.9 us in the
-// long run, but 200 steps are needed to see it; 90 k rows: 4.6 against 4.1).
-constexpr int64_t kPowerRows = 32768, kPowerRows4 = 16384;
-constexpr int64_t power_steps(int64_t nrow) { return 40 + nrow / 512; }
-struct TransportPower {
-    int steps = 1;  // of one application: 1 (none), 2 or 4
-    PowerRows R{};
-    Tracker tr;  // the call's own: not part of what the handle holds
-    DBuf<int32_t> ints;
-    DBuf<double> vals;
-};
-void transport_power(vag_handle *h, int64_t steps, TransportPower &Q) {
-    const UpwindOp T = h->upwind();
-    if (steps < power_steps(T.nrow) || T.nrow > kPowerRows) return;
-    hipStream_t s = h->stream;
-    const int32_t n = T.nrow + 1;
-    constexpr int W[3] = {16, 48, 112};
-    const int K = T.nrow <= kPowerRows4 ? 3 : 2;  // powers 1, 2 (and 4)
-    size_t w = 0;
-    for (int k = 0; k < K; ++k) w += W[k];
-    Q.tr.stream = s;
-    try {
-        Q.vals.alloc(n * w, Q.tr);
-        Q.ints.alloc(n * (w + K) + 3, Q.tr);
-    } catch (const Error &) {
-        return;  // no memory for it: step by step
-    }
-    PowerRows R[3];
-    int32_t *p = Q.ints.p;
-    double *v = Q.vals.p;
-    for (int k = 0; k < K; ++k) {
-        R[k] = PowerRows{W[k], p, p + (size_t)n * W[k], v};
-        p += (size_t)n * (W[k] + 1);
-        v += (size_t)n * W[k];
-    }
-    int32_t *over = p, out[3] = {0, 0, 0};
-    VAG_HIP(hipMemsetAsync(over, 0, 3 * sizeof(int32_t), s));
-    launch_power_base(s, T, R[0], over);
-    for (int k = 1; k < K; ++k) launch_power_square(s, n, R[k - 1], R[k], over + k);
-    VAG_HIP(hipMemcpyAsync(out, over, K * sizeof(int), hipMemcpyDeviceToHost, s));
-    VAG_HIP(hipStreamSynchronize(s));
-    if (out[0] || out[1]) return;
-    const bool four = K == 3 && !out[2];
-    Q.steps = four ? 4 : 2;
-    Q.R = R[four ? 2 : 1];
-}
 }  // namespace
 
 vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const double *c0_cell,
@@ -1657,15 +1605,7 @@ vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const d
         const TransportPlan P = transport_prepare(h, n_steps, t_final, c0_cell, c0_frac, c0_node, mem);
         ph.next("vag.transport_steps");
         hipStream_t s = h->stream;
-        TransportPower Q;
-        transport_power(h, P.N, Q);
-        int64_t k = 0;
-        // whole steps (not the last one, which may be shortened)
-        for (; Q.steps > 1 && k + Q.steps < P.N; k += Q.steps) {
-            launch_power_step(s, (int32_t)h->upwind().nrow, Q.R, h->c_cur(), h->c_next());
-            h->cur ^= 1;
-        }
-        for (; k < P.N; ++k) {
+        for (int64_t k = 0; k < P.N; ++k) {
             const double th = (k == P.N - 1) ? P.theta_last : 1.0;
             launch_transport_step(s, h->upwind(), h->c_cur(), h->c_next(), th, (k & 1) != 0);
             h->cur ^= 1;

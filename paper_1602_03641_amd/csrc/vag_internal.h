@@ -571,15 +571,6 @@ void launch_transport_step(hipStream_t s, const UpwindOp &T, const double *c_in,
                            bool backward);
 // blocks of one step's launch over T (a multiple of 8)
 int32_t transport_step_blocks(const UpwindOp &T);
-// Powers of the operator (transport_power.hip): row i's len[i] entries at i * W.
-struct PowerRows {
-    int W;
-    int32_t *col, *len;
-    double *val;
-};
-void launch_power_base(hipStream_t s, const UpwindOp &T, const PowerRows &R, int *over);
-void launch_power_square(hipStream_t s, int32_t n, const PowerRows &A, const PowerRows &C, int *over);  // C = A A
-void launch_power_step(hipStream_t s, int32_t n, const PowerRows &R, const double *c_in, double *c_out);
 // One step of up to kBatchJobs operators in one launch (served jobs): each
 // operator's rows get exactly the arithmetic of launch_transport_step.
 constexpr int kBatchJobs = 8;
