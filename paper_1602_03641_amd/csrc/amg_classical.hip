@@ -335,7 +335,7 @@ __global__ __launch_bounds__(kCT) void cl_chunk_sum_kernel(int32_t n, const int3
 
 // Products, one wavefront per output row (their rows are short: ~20 columns in
 // A P, ~50 in R A P).  The distinct columns are found with an LDS hash set and
-// ranked; the sums run in the order of X's entries, each over its row of Y, so
+// put in the order of cl_product_kernel's table; the sums run in the order of X's entries, each over its row of Y, so
 // the values do not depend on timing.  A row that outgrows the kernel's LDS is
 // marked in big (and counted) and left to cl_product_kernel.  One thread per
 // row with its table in global memory, as there, waits on a chain of dependent
@@ -348,6 +348,49 @@ __device__ inline bool cl_insert(int32_t *keys, int mask, int32_t J, uint32_t &h
         if (prev == -1) return true;
         if (prev == J) return false;
         h = (h + 1) & (uint32_t)mask;
+    }
+}
+
+// The order of a row's columns is that of cl_product_kernel's table, which takes
+// them by first contribution: cols[0 .. nd) in that order to a table of C slots
+// (two 16-bit indices of cols per word of T, 0xffff an empty slot).  In linear
+// probing the earlier column keeps a slot, so a column passes slots of earlier
+// ones and sends later ones on from where they sit: any order of the lanes'
+// steps ends in the same table.  C >= 2 nd, so every chain ends.
+constexpr int kClTable = 4096;
+__device__ inline void cl_place(uint32_t *T, int32_t C, const int32_t *cols, int nd, int lane) {
+    for (int k = lane; k < C / 2; k += 64) T[k] = 0xffffffffu;
+    __syncthreads();
+    const int lg = 31 - __builtin_clz((unsigned)C);
+    for (int k = lane; k < nd; k += 64) {
+        uint32_t cur = (uint32_t)k, h = mix32((uint32_t)cols[k]) >> (32 - lg);
+        for (;;) {
+            const int sh = (int)(h & 1) * 16;
+            uint32_t w = T[h >> 1], old;
+            for (;;) {
+                old = (w >> sh) & 0xffffu;
+                if (old < cur) break;
+                const uint32_t prev = atomicCAS(&T[h >> 1], w, (w & ~(0xffffu << sh)) | cur << sh);
+                if (prev == w) break;
+                w = prev;
+            }
+            if (old == 0xffffu) break;
+            cur = max(cur, old);
+            h = (h + 1) & (uint32_t)(C - 1);
+        }
+    }
+    __syncthreads();
+}
+// f(position, index of cols) for the columns in the order of the slots
+template <class F>
+__device__ inline void cl_placed(const uint32_t *T, int32_t C, int lane, F f) {
+    int n = 0;
+    for (int k0 = 0; k0 < C; k0 += 64) {
+        const int k = k0 + lane;
+        const uint32_t v = k < C ? (T[k >> 1] >> (k & 1) * 16) & 0xffffu : 0xffffu;
+        const uint64_t mask = __ballot(v != 0xffffu);
+        if (v != 0xffffu) f(n + __popcll(mask & ((1ull << lane) - 1)), (int)v);
+        n += __popcll(mask);
     }
 }
 
@@ -365,11 +408,17 @@ __global__ __launch_bounds__(64) void cl_ap_wave_kernel(Sell<double> A, const in
                                                         double *__restrict__ oval) {
     __shared__ int32_t cj[kApCand], keys[kApHash], cols[kApCols], sorted[kApCols];
     __shared__ double cv[FILL ? kApCand : 1], xs[64];
+    __shared__ int first[FILL ? kApHash : 1];  // contribution to each key
+    __shared__ uint8_t hs[FILL ? kApCand : 1];
+    __shared__ uint32_t T[FILL ? kApCand : 1];
     __shared__ int32_t off[65], y0[64];
     const int32_t i = blockIdx.x;
     const int lane = threadIdx.x;
     if (FILL && big[i]) return;
-    for (int k = lane; k < kApHash; k += 64) keys[k] = -1;
+    for (int k = lane; k < kApHash; k += 64) {
+        keys[k] = -1;
+        if (FILL) first[k] = kApCand;
+    }
     const int64_t b = sell_at(A.ptr, i);
     const int w = sell_w(A.ptr, i);
     int m = 0, nd = 0;
@@ -414,6 +463,10 @@ __global__ __launch_bounds__(64) void cl_ap_wave_kernel(Sell<double> A, const in
                 if (FILL) cv[m + e] = xs[lo] * pval[q];
                 uint32_t h;
                 fresh = cl_insert(keys, kApHash - 1, J, h);
+                if (FILL) {
+                    hs[m + e] = (uint8_t)h;
+                    atomicMin(&first[h], m + e);
+                }
             }
             nd += __popcll(__ballot(fresh));
             over = over || nd > kApCols;
@@ -431,34 +484,26 @@ __global__ __launch_bounds__(64) void cl_ap_wave_kernel(Sell<double> A, const in
     }
     __syncthreads();
     int nc = 0;
-    for (int k0 = 0; k0 < kApHash; k0 += 64) {
-        const int32_t J = keys[k0 + lane];
-        const uint64_t mask = __ballot(J >= 0);
-        if (J >= 0) cols[nc + __popcll(mask & ((1ull << lane) - 1))] = J;
+    for (int e0 = 0; e0 < m; e0 += 64) {
+        const int e = e0 + lane;
+        const bool is = e < m && first[hs[e]] == e;
+        const uint64_t mask = __ballot(is);
+        if (is) cols[nc + __popcll(mask & ((1ull << lane) - 1))] = cj[e];
         nc += __popcll(mask);
     }
     __syncthreads();
-    for (int k = lane; k < nd; k += 64) {
-        const int32_t J = cols[k];
-        int rank = 0;
-        for (int u = 0; u < nd; ++u) rank += cols[u] < J;
-        sorted[rank] = J;
-    }
+    const int32_t C = cl_cap(m);  // at most 2 kApCand
+    cl_place(T, C, cols, nd, lane);
+    cl_placed(T, C, lane, [&](int k, int v) { sorted[k] = cols[v]; });
     __syncthreads();
     const int64_t o = optr[i];
-    // few columns: 4 or 2 lanes per column, each over its share of the contributions
-    const int parts = nd <= 16 ? 4 : nd <= 32 ? 2 : 1, per = 64 / parts;
-    for (int k0 = 0; k0 < nd; k0 += per) {
-        const int k = k0 + lane % per;
-        const int32_t J = k < nd ? sorted[k] : -1;
+    for (int k = lane; k < nd; k += 64) {
+        const int32_t J = sorted[k];
         double s = 0.0;
-#pragma unroll 4
-        for (int e = lane / per; e < m; e += parts) s += cj[e] == J ? cv[e] : 0.0;
-        for (int d = per; d < 64; d <<= 1) s += __shfl_xor(s, d, 64);
-        if (k < nd && lane < per) {
-            ocol[o + k] = J;
-            oval[o + k] = s;
-        }
+#pragma unroll 8
+        for (int e = 0; e < m; ++e) s += cj[e] == J ? cv[e] : 0.0;
+        ocol[o + k] = J;
+        oval[o + k] = s;
     }
 }
 
@@ -477,7 +522,9 @@ __global__ __launch_bounds__(64) void cl_rap_wave_kernel(const int32_t *__restri
                                                          int *__restrict__ nbig, int32_t *__restrict__ rowlen,
                                                          const int64_t *__restrict__ optr, int32_t *__restrict__ ocol,
                                                          double *__restrict__ oval) {
-    __shared__ int32_t keys[kRapHash], cols[FILL ? kRapCols : 1];
+    __shared__ uint32_t T[FILL ? kClTable / 2 : kRapHash];  // of cl_place; before that the keys
+    int32_t *keys = reinterpret_cast<int32_t *>(T);
+    __shared__ int32_t cols[FILL ? kRapCols : 1];
     __shared__ double sums[FILL ? kRapHash : 1], xs[64];
     __shared__ uint16_t slot[FILL ? kRapCols : 1];
     __shared__ int32_t lo[64], hi[64];
@@ -488,7 +535,7 @@ __global__ __launch_bounds__(64) void cl_rap_wave_kernel(const int32_t *__restri
         keys[k] = -1;
         if (FILL) sums[k] = 0.0;
     }
-    int nd = 0;
+    int nd = 0, m = 0;
     bool over = false;
     const int32_t a1 = xptr[c + 1];
     for (int32_t a0 = xptr[c]; a0 < a1 && !over; a0 += 64) {
@@ -498,6 +545,7 @@ __global__ __launch_bounds__(64) void cl_rap_wave_kernel(const int32_t *__restri
             lo[lane] = yptr[t];
             hi[lane] = yptr[t + 1];
             if (FILL) xs[lane] = xval[a0 + lane];
+            m += hi[lane] - lo[lane];
         }
         __syncthreads();
         const int na = min(64, (int)(a1 - a0));
@@ -514,12 +562,22 @@ __global__ __launch_bounds__(64) void cl_rap_wave_kernel(const int32_t *__restri
             }
             for (int32_t q = lo[k] + lane;;) {
                 bool fresh = false;
+                uint32_t h = 0;
                 if (J >= 0) {
-                    uint32_t h;
                     fresh = cl_insert(keys, kRapHash - 1, J, h);
-                    if (FILL) sums[h] += x * v;
+                    if (FILL) {
+#pragma clang fp contract(off)  // as cl_product_kernel's sums
+                        const double t = x * v;
+                        sums[h] = sums[h] + t;
+                    }
                 }
-                nd += __popcll(__ballot(fresh));
+                const uint64_t mask = __ballot(fresh);
+                if (FILL && fresh) {  // by first contribution; nd <= kRapCols as counted
+                    const int at = nd + __popcll(mask & ((1ull << lane) - 1));
+                    cols[at] = J;
+                    slot[at] = (uint16_t)h;
+                }
+                nd += __popcll(mask);
                 over = over || nd > kRapCols;
                 q += 64;
                 if (over || __ballot(q < e) == 0) break;
@@ -531,6 +589,10 @@ __global__ __launch_bounds__(64) void cl_rap_wave_kernel(const int32_t *__restri
             v = vn;
         }
     }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) m += __shfl_xor(m, d, 64);
+    const int32_t C = cl_cap(m);
+    over = over || C > kClTable;
     if (!FILL) {
         if (lane == 0) {
             rowlen[c] = over ? 0 : nd;
@@ -540,26 +602,12 @@ __global__ __launch_bounds__(64) void cl_rap_wave_kernel(const int32_t *__restri
         return;
     }
     __syncthreads();
-    int nc = 0;
-    for (int k0 = 0; k0 < kRapHash; k0 += 64) {
-        const int32_t J = keys[k0 + lane];
-        const uint64_t mask = __ballot(J >= 0);
-        if (J >= 0) {
-            const int at = nc + __popcll(mask & ((1ull << lane) - 1));
-            cols[at] = J;
-            slot[at] = (uint16_t)(k0 + lane);
-        }
-        nc += __popcll(mask);
-    }
-    __syncthreads();
+    cl_place(T, C, cols, nd, lane);
     const int64_t o = optr[c >> 6] + (c & 63);
-    for (int k = lane; k < nd; k += 64) {
-        const int32_t J = cols[k];
-        int rank = 0;
-        for (int u = 0; u < nd; ++u) rank += cols[u] < J;
-        ocol[o + (int64_t)rank * 64] = J;
-        oval[o + (int64_t)rank * 64] = sums[slot[k]];
-    }
+    cl_placed(T, C, lane, [&](int k, int v) {
+        ocol[o + (int64_t)k * 64] = cols[v];
+        oval[o + (int64_t)k * 64] = sums[slot[v]];
+    });
     const int w = sell_w(optr, c);  // padding of the slice: the row itself with value 0
     for (int k = nd + lane; k < w; k += 64) {
         ocol[o + (int64_t)k * 64] = c;
@@ -653,8 +701,9 @@ __global__ __launch_bounds__(kCT) void cl_product_kernel(int32_t r0, int32_t r1,
 }
 
 // cycle: bc = R r (and xc = D_c^-1 bc); y = x + P e.  R's rows hold 5 to 20
-// entries: kRLanes lanes per row, combined by a fixed shuffle tree (one lane per
-// row waited on its chain of gathers: 10 us per visit at 57 k rows, 4 us so)
+// entries: kRLanes lanes load and gather, and the row's sum runs over them in the
+// order of the entries (one lane per row waited on its chain of gathers: 10 us
+// per visit at 57 k rows)
 constexpr int kRLanes = 8;
 template <class X>
 __global__ __launch_bounds__(kCT) void cl_restrict_kernel(int32_t nc, const int32_t *rptr, const int32_t *rcol,
@@ -667,11 +716,17 @@ __global__ __launch_bounds__(kCT) void cl_restrict_kernel(int32_t nc, const int3
     // every lane of a wavefront runs the same number of passes (the shuffles need them all)
     for (int64_t cb = t0 / kRLanes - g; cb < nc; cb += step) {
         const int64_t c = cb + g;
+        const int32_t q1 = c < nc ? rptr[c + 1] : 0;
         double s = 0.0;
-        if (c < nc)
-            for (int32_t q = rptr[c] + sub; q < rptr[c + 1]; q += kRLanes) s += rval[q] * (double)r[rcol[q]];
+        for (int32_t q = c < nc ? rptr[c] : 0; __ballot(q < q1); q += kRLanes) {
+            const bool on = q + sub < q1;
+            const double v = on ? rval[q + sub] : 0.0, x = on ? (double)r[rcol[q + sub]] : 0.0;
 #pragma unroll
-        for (int o = kRLanes / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+            for (int k = 0; k < kRLanes; ++k) {
+                const double t = fma(__shfl(v, k, kRLanes), __shfl(x, k, kRLanes), s);
+                s = q + k < q1 ? t : s;
+            }
+        }
         if (sub == 0 && c < nc) {
             bc[c] = (X)s;
             if (xc) xc[c] = dinv_c[c] * (X)s;
