@@ -1595,6 +1595,51 @@ void transport_report(vag_handle *h, const TransportPlan &P, vag_transport_info 
     info->t_nnz = h->h_cnt[0];
     info->t_stored = P.total;
 }
+
+// The parts of a call of many steps on a small hexahedral mesh, built for the
+// call and released with it.  At most one part per CU (a block of 1024 threads
+// each: 62.7 k rows 2.1 us a step in 256 parts, 3.5 in 510), and none below 64
+// rows.  us a step, alone / in parts: 3.6 / 1.1 at 2.3 k rows (10^3 cells),
+// 3.7 / 0.9 at 12.6 k (64 x 64 x 1), 3.7 / 1.4 at 12.7 k (18^3), 3.7 / 1.5 at
+// 17 k, 3.7 / 1.9 at 46 k (28^3), 3.7 / 2.1 at 63 k, past which a part's map
+// does not fit in LDS.  Building them and looking at the result takes 80 us
+// (2.3 k rows) to 120 (63 k), even at 32 to 75 steps.
+constexpr int64_t halo_steps(int64_t nrow) { return 32 + nrow / 1024; }
+struct TransportHalo {
+    int steps = 1;  // of a launch (1: step by step)
+    HaloParts H{};
+    Tracker tr;  // the call's own: not part of what the handle holds
+    DBuf<int32_t> ints;
+    DBuf<uint16_t> words;
+    DBuf<double> vals;
+};
+void transport_halo(vag_handle *h, int64_t steps, TransportHalo &Q) {
+    const UpwindOp T = h->upwind();
+    if (h->general || T.nrow > kHaloMaxRows || steps < halo_steps(T.nrow)) return;
+    hipStream_t s = h->stream;
+    const Symbolic &S = h->S;
+    const int64_t n = T.nrow, np = std::min<int64_t>(256, (n + 63) / 64);
+    Q.tr.stream = s;
+    try {
+        Q.vals.alloc((size_t)(n * kHaloWidth + np * kHaloRows * (kHaloWidth + 1)), Q.tr);
+        Q.ints.alloc((size_t)(n * (kHaloWidth + 1) + np * (kHaloRows + kHaloSteps + 1) + 1), Q.tr);
+        Q.words.alloc((size_t)(np * kHaloRows * (kHaloWidth + 1)), Q.tr);
+    } catch (const Error &) {
+        return;  // no memory for it: step by step
+    }
+    int32_t *p = Q.ints.p;
+    const HaloRows R{p, p + n * kHaloWidth, Q.vals.p};
+    p += n * (kHaloWidth + 1);
+    double *v = Q.vals.p + n * kHaloWidth;
+    Q.H = HaloParts{(int32_t)np, p, p + np * kHaloRows, Q.words.p, Q.words.p + np * kHaloRows,
+                    v + np * kHaloRows, v};
+    int *cut = p + np * (kHaloRows + kHaloSteps + 1), out = 0;
+    VAG_HIP(hipMemsetAsync(cut, 0, sizeof(int), s));
+    launch_halo_build(s, T, S.nc, S.nf, S.nn, h->frac_cell.p, h->node_cell_ptr.p, h->node_cell.p, R, Q.H, cut);
+    VAG_HIP(hipMemcpyAsync(&out, cut, sizeof(int), hipMemcpyDeviceToHost, s));
+    VAG_HIP(hipStreamSynchronize(s));
+    if (kHaloSteps - out >= 2) Q.steps = kHaloSteps - out;
+}
 }  // namespace
 
 vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const double *c0_cell,
@@ -1605,7 +1650,15 @@ vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const d
         const TransportPlan P = transport_prepare(h, n_steps, t_final, c0_cell, c0_frac, c0_node, mem);
         ph.next("vag.transport_steps");
         hipStream_t s = h->stream;
-        for (int64_t k = 0; k < P.N; ++k) {
+        TransportHalo Q;
+        transport_halo(h, P.N, Q);
+        int64_t k = 0;
+        // whole steps (not the last one, which may be shortened)
+        for (; Q.steps > 1 && k + Q.steps < P.N; k += Q.steps) {
+            launch_transport_halo(s, h->upwind().nrow, Q.steps, Q.H, h->c_cur(), h->c_next());
+            h->cur ^= 1;
+        }
+        for (; k < P.N; ++k) {
             const double th = (k == P.N - 1) ? P.theta_last : 1.0;
             launch_transport_step(s, h->upwind(), h->c_cur(), h->c_next(), th, (k & 1) != 0);
             h->cur ^= 1;

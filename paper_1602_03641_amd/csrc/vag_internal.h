@@ -571,6 +571,28 @@ void launch_transport_step(hipStream_t s, const UpwindOp &T, const double *c_in,
                            bool backward);
 // blocks of one step's launch over T (a multiple of 8)
 int32_t transport_step_blocks(const UpwindOp &T);
+// Several steps per launch on parts of a small hexahedral mesh (transport_halo.hip).
+constexpr int kHaloMaxRows = 65536;  // of the mesh
+constexpr int kHaloRows = 2048;      // of a part with its halo
+constexpr int kHaloWidth = 12;       // entries of a row
+constexpr int kHaloSteps = 8;        // of a launch
+struct HaloRows {
+    int32_t *col, *len;  // [nrow][kHaloWidth], [nrow]
+    double *val;
+};
+struct HaloParts {
+    int32_t nparts;
+    int32_t *list;   // [part][kHaloRows] rows, by level
+    int32_t *level;  // [part][kHaloSteps + 1] rows up to each level
+    uint16_t *len;   // [part][kHaloRows]
+    uint16_t *col;   // [part][kHaloWidth][kHaloRows] local columns (kHaloRows: the constant control volume)
+    double *val, *diag;
+};
+// cut[0] is 0 before; after it the steps of a launch are kHaloSteps - cut[0]
+void launch_halo_build(hipStream_t s, const UpwindOp &T, int32_t nc, int32_t nf, int32_t nn, const int32_t *frac_cell,
+                       const int32_t *ncp, const int32_t *ncl, const HaloRows &R, const HaloParts &H, int *cut);
+void launch_transport_halo(hipStream_t s, int32_t nrow, int steps, const HaloParts &H, const double *c_in,
+                           double *c_out);
 // One step of up to kBatchJobs operators in one launch (served jobs): each
 // operator's rows get exactly the arithmetic of launch_transport_step.
 constexpr int kBatchJobs = 8;

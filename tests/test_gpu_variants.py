@@ -350,3 +350,44 @@ def test_transport_column_codes(dims, patches):
     for k in ref:
         assert np.abs(got[k] - ref[k]).max(initial=0.0) <= 1e-12, k
     h.close()
+
+
+@pytest.mark.parametrize("mesh,patches", [((4, 1, 1), 0), ((64, 1, 1), 0), ((24, 20, 2), 3), ((9, 8, 7), 5), ((18, 18, 18), 6),
+                                          ((27, 26, 25), 8), ((31, 31, 31), 9), ((32, 32, 31), 5), ("star", 0)])
+def test_transport_many_steps(mesh, patches):
+    """Calls of many steps on small meshes, several steps per launch on parts of
+    the mesh: one part, parts whose halos allow eight steps or fewer, rows wider
+    than a part holds (step by step), meshes on both sides of the size limit,
+    wells, step counts around where it starts and whole and shortened last
+    steps: the bits of the same steps in calls of one."""
+    from paper_1602_03641_amd import vag
+    if mesh == "star":
+        p = _star(13, 4, False)
+    else:
+        p = synth.random_problem(mesh, 43, n_patches=patches, n_steps=0, ratios=(1e1, 1e4))
+    if patches:
+        synth.add_wells(p, 4, n_inj=1, n_prod=1)
+    h, _ = _handle(p, rtol=1e-8, precond=vag.VAG_PC_JACOBI)
+    rng = np.random.default_rng(44)
+    c0 = {k: rng.uniform(0, 1, n) for k, n in (("c_cell", p.n_cells), ("c_frac", p.n_frac), ("c_node", p.n_nodes))}
+    for steps in (31, 33, 101, 104):
+        h.transport(n_steps=1, c0=c0)
+        for k in range(1, steps):
+            t = h.transport(n_steps=1)
+        ref = vag.to_numpy(h.concentration())
+        info = h.transport(n_steps=steps, c0=c0)
+        got = vag.to_numpy(h.concentration())
+        assert info["n_steps"] == steps
+        for k in ref:
+            assert np.array_equal(got[k], ref[k]), (steps, k)
+    # to a final time: 120 steps, the last one shortened
+    end = 119.25 * t["dt"]
+    h.transport(n_steps=119, c0=c0)
+    h.transport(t_final=end - 119 * t["dt"])
+    ref = vag.to_numpy(h.concentration())
+    info = h.transport(t_final=end, c0=c0)
+    got = vag.to_numpy(h.concentration())
+    assert info["n_steps"] == 120
+    for k in ref:
+        assert np.abs(got[k] - ref[k]).max(initial=0.0) <= 1e-12, k
+    h.close()
