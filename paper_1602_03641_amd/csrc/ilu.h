@@ -44,27 +44,6 @@ struct IluLds {
     bool fits() const { return rows > 0 && ents <= 65535 && bytes() <= 160 * 1024; }
 };
 
-// The solve by sub-blocks of kIluSub consecutive rows: a sub-block's couplings
-// to the others of its block are sparse, those inside it are applied as the
-// inverses of its two triangles, so a substitution is rows / kIluSub steps
-// long instead of one per level.
-constexpr int kIluSub = 16;
-struct IluSub {
-    int32_t rows = 0, ents = 0;  // rows (a multiple of kIluSub) and factor entries of a block
-    // [n] of natural row o, relative to its block's first entry: {first entry,
-    // first at or past the sub-block, first past it, end}
-    const ushort4 *ptr = nullptr;
-    // kIluSub^2 per sub-block: below the diagonal L^-1 (unit diagonal implied),
-    // from it U^-1; entry (i, j) at 16 i + 4 (j % 4) + j / 4
-    double *inv = nullptr;
-    size_t bytes() const { return 8 * (size_t)rows * (2 + kIluSub) + 10 * (size_t)ents; }
-    bool fits() const { return ents <= 65535 && bytes() <= 160 * 1024; }
-};
-// doubles of inverses that a block of B rows has (none: the block is not solved so)
-inline int64_t ilu_sub_inverses(int B) {
-    return B < kIluSub ? 0 : (int64_t)((B + kIluSub - 1) / kIluSub) * kIluSub * kIluSub;
-}
-
 class Ilu {
 public:
     // Host symbolic phase from the device matrix's pattern (once per handle
@@ -86,12 +65,10 @@ private:
     int64_t nent_ = 0;
     IluArgs a_{};
     IluLds lds_;
-    IluSub sub_;  // sub_.inv null: by levels
     DBuf<int32_t> fptr_, fsrc_, fdiag_, rdev_, lvb_f_, lptr_f_, rows_f_, lvb_b_, lptr_b_, rows_b_;
     DBuf<int4> slot_f_, slot_b_;
     DBuf<uint16_t> fcol_;
-    DBuf<ushort4> sptr_;
-    DBuf<double> fval_, sinv_;
+    DBuf<double> fval_;
 };
 
 }  // namespace vag

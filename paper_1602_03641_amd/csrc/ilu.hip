@@ -64,8 +64,6 @@ void block_levels(const std::vector<int32_t> &fptr, const std::vector<uint16_t> 
 
 __global__ void ilu_solve_lds_kernel(IluArgs g, IluLds L, const double *__restrict__ r, double *__restrict__ z,
                                      const PcgState *st);
-__global__ void ilu_solve_sub_kernel(IluArgs g, IluSub L, const double *__restrict__ r, double *__restrict__ z,
-                                     const PcgState *st);
 
 void Ilu::build(hipStream_t s, Tracker &tr, const Symbolic &S, int B) {
     const int32_t n = S.nunk;
@@ -163,26 +161,6 @@ void Ilu::build(hipStream_t s, Tracker &tr, const Symbolic &S, int B) {
     if (lds_.fits())
         VAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(ilu_solve_lds_kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_.bytes()));
-    // sub-blocks, where their inverses fit in LDS too
-    sub_ = IluSub{};
-    sub_.rows = (B + kIluSub - 1) / kIluSub * kIluSub;
-    sub_.ents = lds_.ents;
-    std::vector<ushort4> sptr;
-    if (n > 0 && ilu_sub_inverses(B) && sub_.fits()) {
-        sptr.resize(n);
-        for (int32_t o = 0; o < n; ++o) {
-            const int32_t b0 = o / B * B, s0 = (o - b0) / kIluSub * kIluSub, e0 = fptr[b0];
-            const auto c0 = fcol.begin() + fptr[o], c1 = fcol.begin() + fptr[o + 1];
-            auto at = [&](int32_t c) { return (uint16_t)(std::lower_bound(c0, c1, c) - fcol.begin() - e0); };
-            sptr[o] = make_ushort4((uint16_t)(fptr[o] - e0), at(s0), at(s0 + kIluSub), (uint16_t)(fptr[o + 1] - e0));
-        }
-        put(s, tr, sptr_, sptr);
-        sinv_.alloc((size_t)nblk * ilu_sub_inverses(B), tr);
-        sub_.ptr = sptr_.p;
-        sub_.inv = sinv_.p;
-        VAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(ilu_solve_sub_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)sub_.bytes()));
-    }
     VAG_HIP(hipStreamSynchronize(s));  // the host vectors go out of scope
     nent_ = nent;
     B_ = B;
@@ -223,68 +201,92 @@ __global__ __launch_bounds__(kIluThreads) void ilu_factor_kernel(IluArgs g, cons
     }
 }
 
-// a + the value of another lane of the same 8 (DPP: quad_perm and row_half_mirror)
-template <int CTRL>
-__device__ inline double dpp_sum(double a) {
-    const uint64_t u = __double_as_longlong(a);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-    return a + __longlong_as_double(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-
-// One substitution over a block staged in LDS: level by level, kIluLanes lanes
-// per row, lane q taking entries q, q + kIluLanes, ... of the row.  A level
-// holds few rows (2 or 3 for blocks of 128 unknowns), so its time is the chain
-// slot -> entries -> y -> sum -> y: the slots of the level after next and the
-// first entries of the next level, which do not depend on y, are read ahead.
-// Rows past the wavefront's kIluRows of a level take the same steps unhurried.
-constexpr int kIluLanes = 8, kIluRows = kIluThreads / kIluLanes;
+// One substitution over a block staged in LDS: level by level, one lane per row,
+// the row's entries in their order.  A level holds few rows (2 or 3 for blocks
+// of 128 unknowns), so its time is the chain y -> sum -> y: the slots of the
+// level after next and the first kIluAhead entries of the next level, which do
+// not depend on y, are read ahead.  Rows past the wavefront's 64 of a level take
+// the same steps unhurried.  (Eight lanes per row with their sums combined by a
+// tree took 30 us, inverted triangles of 16 rows 14, but a BiCGStab solve to
+// 1e-12 carries their other rounding to 1e-9 of a face flux: the sums keep the
+// order of ilu_solve_kernel, and the quotient is the correctly rounded one, by
+// Markstein's theorem from the correctly rounded reciprocal, with one more
+// correction so that the second starts within an ulp.)
+constexpr int kIluAhead = 8;
+struct IluRow {
+    ushort4 m;  // local row, its entries [y, z); w = 0: no row
+    double v[kIluAhead], d, di;
+    uint16_t c[kIluAhead];
+};
 template <bool BACK>
 __device__ inline void ilu_sweep(int nlev, const uint16_t *__restrict__ lp, const ushort4 *__restrict__ slot,
                                  const double *__restrict__ val, const uint16_t *__restrict__ col,
                                  const double *__restrict__ dinv, double *y) {
-    const int q = threadIdx.x % kIluLanes, g = threadIdx.x / kIluLanes;
-    const ushort4 none = make_ushort4(0, 0, 0, 0);  // no entries; w = 0: no row
+    const int lane = threadIdx.x;
+    const ushort4 none = make_ushort4(0, 0, 0, 0);
     auto get = [&](int t, int t1) { return t < t1 ? slot[t] : none; };
-    auto row = [&](const ushort4 &m, double v, uint16_t c) {
-        const double y0 = y[m.x];
-        double s = m.y + q < m.z ? v * y[c] : 0.0;
-        for (int p = m.y + q + kIluLanes; p < m.z; p += kIluLanes) s += val[p] * y[col[p]];
-        s = dpp_sum<0xB1>(s);
-        s = dpp_sum<0x4E>(s);
-        s = dpp_sum<0x141>(s);
-        if (m.w && q == 0) y[m.x] = BACK ? (y0 - s) * dinv[m.x] : y0 - s;
+    auto load = [&](IluRow &R, const ushort4 &m) {
+        R.m = m;
+#pragma unroll
+        for (int k = 0; k < kIluAhead; ++k) {  // past the row: 0 times its own y
+            const bool on = m.y + k < m.z;
+            const int p = on ? m.y + k : 0;
+            const double v = val[p];
+            const uint16_t c = col[p];
+            R.v[k] = on ? v : 0.0;
+            R.c[k] = on ? c : m.x;
+        }
+        R.d = BACK && m.w ? val[m.y - 1] : 1.0;
+        R.di = BACK ? dinv[m.x] : 1.0;
+    };
+    auto run = [&](const IluRow &R) {
+        double s = y[R.m.x];
+        double x[kIluAhead];
+        const bool wide = __any(R.m.y + kIluAhead / 2 < R.m.z);
+#pragma unroll
+        for (int k = 0; k < kIluAhead / 2; ++k) x[k] = y[R.c[k]];
+        if (wide)
+#pragma unroll
+            for (int k = kIluAhead / 2; k < kIluAhead; ++k) x[k] = y[R.c[k]];
+#pragma unroll
+        for (int k = 0; k < kIluAhead / 2; ++k) s = fma(-R.v[k], x[k], s);
+        if (wide) {
+#pragma unroll
+            for (int k = kIluAhead / 2; k < kIluAhead; ++k) s = fma(-R.v[k], x[k], s);
+            for (int p = R.m.y + kIluAhead; p < R.m.z; ++p) s = fma(-val[p], y[col[p]], s);
+        }
+        if (BACK) {
+            double q = s * R.di;
+            q = fma(fma(-R.d, q, s), R.di, q);
+            s = fma(fma(-R.d, q, s), R.di, q);
+        }
+        if (R.m.w) y[R.m.x] = s;
     };
     int t0 = lp[0], t1 = lp[1], t2 = lp[2];  // lp is padded by two copies of its end
-    ushort4 m0 = get(t0 + g, t1), m1 = get(t1 + g, t2);
-    int p0 = m0.y + q < m0.z ? m0.y + q : 0;
-    double v0 = val[p0];
-    uint16_t c0 = col[p0];
+    ushort4 m1 = get(t1 + lane, t2);
+    IluRow R0;
+    load(R0, get(t0 + lane, t1));
     for (int l = 0; l < nlev; ++l) {
         const int t3 = lp[l + 3 <= nlev + 1 ? l + 3 : nlev + 1];
-        const ushort4 m2 = get(t2 + g, t3);
-        const int p1 = m1.y + q < m1.z ? m1.y + q : 0;
-        const double v1 = val[p1];
-        const uint16_t c1 = col[p1];
-        row(m0, v0, c0);
-        for (int t = t0 + kIluRows; t < t1; t += kIluRows) {  // the same trip count in every lane
-            const ushort4 m = get(t + g, t1);
-            const int p = m.y + q < m.z ? m.y + q : 0;
-            row(m, val[p], col[p]);
+        const ushort4 m2 = get(t2 + lane, t3);
+        IluRow R1;
+        load(R1, m1);
+        run(R0);
+        for (int t = t0 + kIluThreads; t < t1; t += kIluThreads) {  // the same trip count in every lane
+            IluRow R;
+            load(R, get(t + lane, t1));
+            run(R);
         }
         __syncthreads();
         t0 = t1;
         t1 = t2;
         t2 = t3;
-        m0 = m1;
+        R0 = R1;
         m1 = m2;
-        v0 = v1;
-        c0 = c1;
     }
 }
 
-// z = (L U)^-1 r of a block by levels, one wavefront: blocks too large for
-// their sub-blocks' inverses in LDS.  The block's values, columns,
+// z = (L U)^-1 r of a block, one wavefront.  The block's values, columns,
 // schedules and vector are staged in LDS by coalesced loads, all in flight
 // together; the substitutions then touch LDS only.  (Reading slots and entries
 // from global memory level by level cost two dependent round trips per level,
@@ -321,132 +323,6 @@ __global__ __launch_bounds__(kIluThreads) void ilu_solve_lds_kernel(IluArgs g, I
     ilu_sweep<false>(nf, lpf, slf, val, col, nullptr, y);  // L y = r (unit diagonal), in place
     ilu_sweep<true>(nb, lpb, slb, val, col, dinv, y);      // U z = y, in place
     for (int i = tid; i < nr; i += kIluThreads) z[g.rdev[r0 + i]] = y[i];
-}
-
-// The inverses of the sub-blocks' triangles, one wavefront per sub-block: lane
-// j < 16 column j of L^-1, lane 16 + j column j of U^-1.  Rows past the block's
-// end count as the identity.
-__global__ __launch_bounds__(64) void ilu_inverse_kernel(IluArgs g, IluSub L) {
-    __shared__ double M[kIluSub][kIluSub + 1], X[2][kIluSub][kIluSub + 1];
-    const int nsub = L.rows / kIluSub, b = blockIdx.x / nsub, s0 = (blockIdx.x - b * nsub) * kIluSub;
-    const int32_t r0 = b * g.B, nr = min(g.n, r0 + g.B) - r0;
-    const int lane = threadIdx.x;
-    for (int e = lane; e < kIluSub * kIluSub; e += 64) M[e / kIluSub][e % kIluSub] = e / kIluSub == e % kIluSub;
-    __syncthreads();
-    if (lane < kIluSub && s0 + lane < nr) {
-        const ushort4 m = L.ptr[r0 + s0 + lane];
-        const int32_t e0 = g.fptr[r0];
-        for (int p = m.y; p < m.z; ++p) M[lane][g.fcol[e0 + p] - s0] = g.fval[e0 + p];
-    }
-    __syncthreads();
-    const int j = lane & (kIluSub - 1);
-    if (lane < kIluSub) {
-        for (int i = 0; i < kIluSub; ++i) {
-            double v = i == j;
-            for (int k = j; k < i; ++k) v -= M[i][k] * X[0][k][j];
-            X[0][i][j] = i < j ? 0.0 : v;
-        }
-    } else if (lane < 2 * kIluSub) {
-        for (int i = kIluSub - 1; i >= 0; --i) {
-            double v = i == j;
-            for (int k = i + 1; k <= j; ++k) v -= M[i][k] * X[1][k][j];
-            X[1][i][j] = i > j ? 0.0 : v / M[i][i];
-        }
-    }
-    __syncthreads();
-    double *out = L.inv + (int64_t)blockIdx.x * kIluSub * kIluSub;
-    for (int e = lane; e < kIluSub * kIluSub; e += 64) {
-        const int i = e / kIluSub, c = e % kIluSub, col = (c & 3) * 4 + (c >> 2);
-        out[e] = X[col < i ? 0 : 1][i][col];
-    }
-}
-
-// One substitution by sub-blocks, by the block's first wavefront: lane 4 i + q
-// takes every fourth of row i's entries outside the sub-block, then columns q,
-// q + 4, ... of the inverse.  Two exchanges through LDS per 16 rows; what does
-// not depend on y is read a sub-block ahead.
-template <bool BACK>
-__device__ inline void ilu_sub_sweep(int ns, const ushort4 *__restrict__ ptr, const double *__restrict__ val,
-                                     const uint16_t *__restrict__ col, const double *__restrict__ inv, double *y) {
-    const int lane = threadIdx.x, i = lane >> 2, q = lane & 3;
-    struct Ahead {
-        int p, p1;  // the lane's next entry past the two read ahead, and the end
-        double v0, v1;
-        int c0, c1;
-        double m[4];
-    };
-    auto ahead = [&](int s) {
-        Ahead a;
-        const ushort4 w = ptr[s * kIluSub + i];
-        const int p = (BACK ? w.z : w.x) + q;
-        a.p1 = BACK ? w.w : w.y;
-        a.v0 = p < a.p1 ? val[p] : 0.0;
-        a.c0 = p < a.p1 ? col[p] : s * kIluSub;
-        a.v1 = p + 4 < a.p1 ? val[p + 4] : 0.0;
-        a.c1 = p + 4 < a.p1 ? col[p + 4] : s * kIluSub;
-        a.p = p + 8;
-        const double2 *m = reinterpret_cast<const double2 *>(inv + (s * kIluSub + i) * kIluSub + 4 * q);
-        const double2 m0 = m[0], m1 = m[1];
-        const double mm[4] = {m0.x, m0.y, m1.x, m1.y};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) a.m[k] = (q + 4 * k >= i) == BACK ? mm[k] : 0.0;
-        return a;
-    };
-    Ahead a = ahead(BACK ? ns - 1 : 0);
-    for (int u = 0; u < ns; ++u) {
-        const int s = BACK ? ns - 1 - u : u, n1 = BACK ? max(s - 1, 0) : min(s + 1, ns - 1);
-        const double y0 = y[s * kIluSub + i];
-        double t = a.v0 * y[a.c0] + a.v1 * y[a.c1];
-        for (int p = a.p; p < a.p1; p += 4) t += val[p] * y[col[p]];
-        const Ahead next = ahead(n1);
-        t = dpp_sum<0xB1>(t);
-        t = y0 - dpp_sum<0x4E>(t);
-        double x = 0.0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) x += a.m[k] * __shfl(t, 4 * (q + 4 * k), 64);
-        x = dpp_sum<0xB1>(x);
-        x = dpp_sum<0x4E>(x);
-        if (q == 0) y[s * kIluSub + i] = BACK ? x : t + x;
-        // the stores before the next sub-block's loads (one wavefront: LDS in order)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        a = next;
-    }
-}
-
-// z = (L U)^-1 r of a block by sub-blocks, everything staged in LDS by four
-// wavefronts; the first then does the substitutions.  At 113 k unknowns in
-// blocks of 128 an application by levels (~100 of them, one exchange through
-// LDS each) takes 35 us, this 14.
-constexpr int kIluStage = 256;
-__global__ __launch_bounds__(kIluStage) void ilu_solve_sub_kernel(IluArgs g, IluSub L, const double *__restrict__ r,
-                                                                  double *__restrict__ z, const PcgState *st) {
-    if (st && st->done) return;
-    extern __shared__ double lds[];
-    double *inv = lds, *y = inv + L.rows * kIluSub, *val = y + L.rows;
-    ushort4 *ptr = reinterpret_cast<ushort4 *>(val + L.ents);
-    uint16_t *col = reinterpret_cast<uint16_t *>(ptr + L.rows);
-    const int32_t b = blockIdx.x, r0 = b * g.B, nr = min(g.n, r0 + g.B) - r0;
-    const int32_t e0 = g.fptr[r0], ne = g.fptr[r0 + nr] - e0;
-    const int ns = (nr + kIluSub - 1) / kIluSub, tid = threadIdx.x;
-    for (int i = tid; i < ns * kIluSub; i += kIluStage) {
-        y[i] = i < nr ? r[g.rdev[r0 + i]] : 0.0;
-        ptr[i] = i < nr ? L.ptr[r0 + i] : make_ushort4(0, 0, 0, 0);
-    }
-    const double2 *src = reinterpret_cast<const double2 *>(L.inv + (int64_t)b * L.rows * kIluSub);
-#pragma unroll 4
-    for (int e = tid; e < ns * kIluSub * kIluSub / 2; e += kIluStage) reinterpret_cast<double2 *>(inv)[e] = src[e];
-#pragma unroll 4
-    for (int e = tid; e < ne; e += kIluStage) {
-        val[e] = g.fval[e0 + e];
-        col[e] = g.fcol[e0 + e];
-    }
-    __syncthreads();
-    if (tid >= 64) return;
-    ilu_sub_sweep<false>(ns, ptr, val, col, inv, y);  // L y = r (unit diagonal), in place
-    ilu_sub_sweep<true>(ns, ptr, val, col, inv, y);   // U z = y, in place
-    for (int i = tid; i < nr; i += 64) z[g.rdev[r0 + i]] = y[i];
 }
 
 // The same from global memory, for blocks whose factor does not fit in LDS
@@ -489,19 +365,10 @@ void Ilu::factor(hipStream_t s, const double *A, int *bad) {
     if (a_.nblk == 0) return;
     hipLaunchKernelGGL(ilu_factor_kernel, dim3(a_.nblk), dim3(kIluThreads), 0, s, a_, A, bad);
     VAG_HIP(hipGetLastError());
-    if (sub_.inv) {
-        hipLaunchKernelGGL(ilu_inverse_kernel, dim3(a_.nblk * (sub_.rows / kIluSub)), dim3(64), 0, s, a_, sub_);
-        VAG_HIP(hipGetLastError());
-    }
 }
 
 void Ilu::apply(hipStream_t s, const double *r, double *z, const PcgState *st) const {
     if (a_.nblk == 0) return;
-    if (sub_.inv) {
-        hipLaunchKernelGGL(ilu_solve_sub_kernel, dim3(a_.nblk), dim3(kIluStage), sub_.bytes(), s, a_, sub_, r, z, st);
-        VAG_HIP(hipGetLastError());
-        return;
-    }
     if (lds_.fits()) {
         hipLaunchKernelGGL(ilu_solve_lds_kernel, dim3(a_.nblk), dim3(kIluThreads), lds_.bytes(), s, a_, lds_, r, z, st);
         VAG_HIP(hipGetLastError());

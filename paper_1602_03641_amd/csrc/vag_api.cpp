@@ -2206,10 +2206,7 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
         const double d = std::min(Nx, std::min(cs, 1024.0));
         b += 1.125 * amg + 20.0 * d * d + 65536.0 + 0.5 * 1024 * 1024;
     }
-    if (o.precond == VAG_PC_BJILU0) {  // factor entries, rows, schedules, sub-block inverses
-        const int B = o.ilu_block_rows > 0 ? std::min(o.ilu_block_rows, kIluMaxBlock) : kIluDefaultBlock;
-        b += 14 * nnz + 36 * Nx + 8.0 * ilu_sub_inverses(B) * (Nx / B + 1);
-    }
+    if (o.precond == VAG_PC_BJILU0) b += 14 * nnz + 28 * Nx;        // factor entries, rows, schedules
     if (o.krylov == VAG_GMRES) {  // flexible GMRES: m + 1 basis vectors, m preconditioned ones, a work vector
         const double m = o.gmres_restart > 0 ? o.gmres_restart : 100;
         b += (2 * m + 2) * Nx * (o.precision == VAG_MIXED_IR ? 4.0 : 8.0) + 8 * (m + 1) * Nx / 256;

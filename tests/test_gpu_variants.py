@@ -313,10 +313,9 @@ def test_dense_inverse(dims, n):
 
 @pytest.mark.parametrize("dims,B", [((9, 7, 6), 15), ((9, 7, 6), 16), ((9, 7, 6), 17), ((3, 2, 2), 128),
                                     ((12, 11, 9), 33), ((12, 11, 9), 128), ((12, 11, 9), 400), ((12, 11, 9), 1600)])
-def test_ilu_sub_blocks(dims, B):
-    """Blocks below, of and just past a sub-block of 16 rows, of fewer rows than
-    asked for, of ragged last sub-blocks, and on both sides of where a block's
-    inverses fit in LDS: as test_ilu_substitutions."""
+def test_ilu_block_sizes(dims, B):
+    """Blocks of more sizes, of fewer rows than asked for, ragged last ones, and
+    on both sides of what fits in LDS: as test_ilu_substitutions."""
     from paper_1602_03641_amd import vag
     from oracle import ilu
     p = synth.random_problem(dims, 39, n_patches=4, n_steps=0, ratios=(1e2, 1e4))
