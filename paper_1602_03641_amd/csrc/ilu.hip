@@ -217,6 +217,7 @@ struct IluRow {
     ushort4 m;  // local row, its entries [y, z); w = 0: no row
     double v[kIluAhead], d, di;
     uint16_t c[kIluAhead];
+    bool wide;  // of the wavefront's rows: more than kIluAhead / 2 entries
 };
 template <bool BACK>
 __device__ inline void ilu_sweep(int nlev, const uint16_t *__restrict__ lp, const ushort4 *__restrict__ slot,
@@ -225,34 +226,40 @@ __device__ inline void ilu_sweep(int nlev, const uint16_t *__restrict__ lp, cons
     const int lane = threadIdx.x;
     const ushort4 none = make_ushort4(0, 0, 0, 0);
     auto get = [&](int t, int t1) { return t < t1 ? slot[t] : none; };
+    constexpr int H = kIluAhead / 2;  // rows of more entries take a second turn of loads
     auto load = [&](IluRow &R, const ushort4 &m) {
         R.m = m;
-#pragma unroll
-        for (int k = 0; k < kIluAhead; ++k) {  // past the row: 0 times its own y
+        auto entry = [&](int k) {  // past the row: 0 times its own y
             const bool on = m.y + k < m.z;
             const int p = on ? m.y + k : 0;
             const double v = val[p];
             const uint16_t c = col[p];
             R.v[k] = on ? v : 0.0;
             R.c[k] = on ? c : m.x;
-        }
+        };
+#pragma unroll
+        for (int k = 0; k < H; ++k) entry(k);
+        R.wide = __any(m.y + H < m.z);
+        if (R.wide)
+#pragma unroll
+            for (int k = H; k < kIluAhead; ++k) entry(k);
         R.d = BACK && m.w ? val[m.y - 1] : 1.0;
         R.di = BACK ? dinv[m.x] : 1.0;
     };
-    auto run = [&](const IluRow &R) {
-        double s = y[R.m.x];
-        double x[kIluAhead];
-        const bool wide = __any(R.m.y + kIluAhead / 2 < R.m.z);
+    // the row's sum and store; between its reads of y and their use the loads of `next`
+    auto run = [&](const IluRow &R, IluRow *next, const ushort4 &mn) {
+        double s = y[R.m.x], x[kIluAhead];
 #pragma unroll
-        for (int k = 0; k < kIluAhead / 2; ++k) x[k] = y[R.c[k]];
-        if (wide)
+        for (int k = 0; k < H; ++k) x[k] = y[R.c[k]];
+        if (R.wide)
 #pragma unroll
-            for (int k = kIluAhead / 2; k < kIluAhead; ++k) x[k] = y[R.c[k]];
+            for (int k = H; k < kIluAhead; ++k) x[k] = y[R.c[k]];
+        if (next) load(*next, mn);
 #pragma unroll
-        for (int k = 0; k < kIluAhead / 2; ++k) s = fma(-R.v[k], x[k], s);
-        if (wide) {
+        for (int k = 0; k < H; ++k) s = fma(-R.v[k], x[k], s);
+        if (R.wide) {
 #pragma unroll
-            for (int k = kIluAhead / 2; k < kIluAhead; ++k) s = fma(-R.v[k], x[k], s);
+            for (int k = H; k < kIluAhead; ++k) s = fma(-R.v[k], x[k], s);
             for (int p = R.m.y + kIluAhead; p < R.m.z; ++p) s = fma(-val[p], y[col[p]], s);
         }
         if (BACK) {
@@ -262,36 +269,43 @@ __device__ inline void ilu_sweep(int nlev, const uint16_t *__restrict__ lp, cons
         }
         if (R.m.w) y[R.m.x] = s;
     };
-    int t0 = lp[0], t1 = lp[1], t2 = lp[2];  // lp is padded by two copies of its end
+    auto at = [&](int l) { return (int)lp[min(l, nlev + 1)]; };  // lp is padded by copies of its end
+    int t0 = lp[0], t1 = lp[1], t2 = at(2), t3 = at(3);
     ushort4 m1 = get(t1 + lane, t2);
     IluRow R0;
     load(R0, get(t0 + lane, t1));
     for (int l = 0; l < nlev; ++l) {
-        const int t3 = lp[l + 3 <= nlev + 1 ? l + 3 : nlev + 1];
+        const int t4 = at(l + 4);
         const ushort4 m2 = get(t2 + lane, t3);
         IluRow R1;
-        load(R1, m1);
-        run(R0);
+        run(R0, &R1, m1);
         for (int t = t0 + kIluThreads; t < t1; t += kIluThreads) {  // the same trip count in every lane
             IluRow R;
             load(R, get(t + lane, t1));
-            run(R);
+            run(R, nullptr, none);
         }
-        __syncthreads();
+        // one wavefront, whose LDS accesses are in order: nothing to wait for
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         t0 = t1;
         t1 = t2;
         t2 = t3;
+        t3 = t4;
         R0 = R1;
         m1 = m2;
     }
+    __syncthreads();
 }
+static_assert(kIluThreads == 64, "a substitution is one wavefront's");
 
 // z = (L U)^-1 r of a block, one wavefront.  The block's values, columns,
 // schedules and vector are staged in LDS by coalesced loads, all in flight
 // together; the substitutions then touch LDS only.  (Reading slots and entries
 // from global memory level by level cost two dependent round trips per level,
-// ~0.57 us: 80 us per application at 113 k unknowns in blocks of 128, 30 us
-// staged.  What bounds it is still the chain of levels, ~0.1 us each.)
+// ~0.57 us: 80 us per application at 113 k unknowns in blocks of 128, 47 us
+// staged.  What bounds it is still the chain of levels, ~0.3 us each: reads of
+// slots, entries and y in turn; a third stage of the pipeline did not shorten
+// it, 50 us.)
 __global__ __launch_bounds__(kIluThreads) void ilu_solve_lds_kernel(IluArgs g, IluLds L, const double *__restrict__ r,
                                                                     double *__restrict__ z, const PcgState *st) {
     if (st && st->done) return;
