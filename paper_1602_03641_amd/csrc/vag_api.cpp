@@ -1625,6 +1625,7 @@ void transport_halo(vag_handle *h, int64_t steps, TransportHalo &Q) {
         Q.ints.alloc((size_t)(n * (kHaloWidth + 1) + np * (kHaloRows + kHaloSteps + 1) + 1), Q.tr);
         Q.words.alloc((size_t)(np * kHaloRows * (kHaloWidth + 1)), Q.tr);
     } catch (const Error &) {
+        (void)hipGetLastError();
         return;  // no memory for it: step by step
     }
     int32_t *p = Q.ints.p;
