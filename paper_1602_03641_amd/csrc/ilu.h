@@ -40,8 +40,9 @@ struct IluLds {
     int32_t rows = 0, ents = 0, levs = 0;  // rows, factor entries and levels (of either sweep) of a block
     size_t slots_f() const { return 8 * (size_t)(2 * rows + ents); }  // after y, 1 / diag and the values
     size_t bytes() const { return slots_f() + 16 * (size_t)rows + 2 * (2 * (size_t)(levs + 3) + ents); }
+    static constexpr size_t kMax = 160 * 1024;  // of a CU
     // entry and slot indices inside a block are 16-bit there
-    bool fits() const { return rows > 0 && ents <= 65535 && bytes() <= 160 * 1024; }
+    bool fits() const { return rows > 0 && ents <= 65535 && bytes() <= kMax; }
 };
 
 class Ilu {

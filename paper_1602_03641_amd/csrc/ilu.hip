@@ -158,9 +158,9 @@ void Ilu::build(hipStream_t s, Tracker &tr, const Symbolic &S, int B) {
     put(s, tr, slot_f_, slot_f);
     put(s, tr, slot_b_, slot_b);
     fval_.alloc(std::max<int64_t>(nent, 1), tr);
-    if (lds_.fits())
+    if (lds_.fits())  // the kernel's limit is the process's, so the most that any handle asks for
         VAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(ilu_solve_lds_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_.bytes()));
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)IluLds::kMax));
     VAG_HIP(hipStreamSynchronize(s));  // the host vectors go out of scope
     nent_ = nent;
     B_ = B;

@@ -390,3 +390,21 @@ def test_transport_many_steps(mesh, patches):
     for k in ref:
         assert np.abs(got[k] - ref[k]).max(initial=0.0) <= 1e-12, k
     h.close()
+
+
+@pytest.mark.parametrize("later", [128, 16, 2])
+def test_ilu_handles_of_different_blocks(later):
+    """A handle whose blocks take most of a CU's LDS, used again after another
+    one with smaller blocks was built: the same bits as before."""
+    from paper_1602_03641_amd import vag
+    kw = dict(rtol=1e-8, precond=vag.VAG_PC_BJILU0, krylov=vag.VAG_BICGSTAB, eliminate_frac_faces=0)
+    p = synth.random_problem((24, 23, 22), 45, n_patches=4, n_steps=0, ratios=(1e2, 1e4))
+    h, info = _handle(p, ilu_block_rows=768, **kw)  # 136 KB
+    r = np.random.default_rng(46).standard_normal(info["n_unknowns"])
+    z = h.apply_preconditioner(r)
+    q = synth.random_problem((6, 5, 4), 47, n_patches=2, n_steps=0, ratios=(1e2,))
+    h2, _ = _handle(q, ilu_block_rows=later, **kw)
+    assert np.array_equal(h.apply_preconditioner(r), z)
+    assert h.solve_pressure()["status"] == 0
+    h2.close()
+    h.close()
