@@ -38,7 +38,7 @@ struct IluArgs {
 // layout for every block, sized for the largest counts of any block.
 struct IluLds {
     int32_t rows = 0, ents = 0, levs = 0;  // rows, factor entries and levels (of either sweep) of a block
-    size_t slots_f() const { return 8 * (size_t)(2 * rows + ents); }  // after y, 1 / diag and the values
+    size_t slots_f() const { return 8 * (size_t)(2 * rows + 1 + ents); }  // after y, 0, 1 / diag and the values
     size_t bytes() const { return slots_f() + 16 * (size_t)rows + 2 * (2 * (size_t)(levs + 3) + ents); }
     static constexpr size_t kMax = 160 * 1024;  // of a CU
     // entry and slot indices inside a block are 16-bit there

@@ -201,6 +201,46 @@ __global__ __launch_bounds__(kIluThreads) void ilu_factor_kernel(IluArgs g, cons
     }
 }
 
+// z = (L U)^-1 r of a block, with its factor and schedules in global memory and
+// only its vector y in LDS
+__device__ inline void ilu_solve_block(const IluArgs &g, int32_t b, const double *__restrict__ r,
+                                       double *__restrict__ z, double *y) {
+    const int32_t r0 = b * g.B, r1 = min(g.n, r0 + g.B);
+    const int tid = threadIdx.x;
+    const double *__restrict__ v = g.fval;
+    const uint16_t *__restrict__ col = g.fcol;
+    // the block's right-hand side into LDS, all loads in flight at once
+    for (int32_t i = tid; i < r1 - r0; i += kIluThreads) y[i] = r[g.rdev[r0 + i]];
+    __syncthreads();
+    // L y = r (unit diagonal), in place
+    for (int32_t l = g.lvb_f[b]; l < g.lvb_f[b + 1]; ++l) {
+        for (int32_t t = g.lptr_f[l] + tid; t < g.lptr_f[l + 1]; t += kIluThreads) {
+            const int4 m = g.slot_f[t];
+            double s = y[m.x];
+            for (int32_t p = m.y; p < m.z; ++p) s -= v[p] * y[col[p]];
+            y[m.x] = s;
+        }
+        __syncthreads();
+    }
+    // U z = y, in place
+    for (int32_t l = g.lvb_b[b]; l < g.lvb_b[b + 1]; ++l) {
+        for (int32_t t = g.lptr_b[l] + tid; t < g.lptr_b[l + 1]; t += kIluThreads) {
+            const int4 m = g.slot_b[t];
+            double s = y[m.x];
+            for (int32_t p = m.y + 1; p < m.z; ++p) s -= v[p] * y[col[p]];
+            y[m.x] = s / v[m.y];
+        }
+        __syncthreads();
+    }
+    for (int32_t i = tid; i < r1 - r0; i += kIluThreads) z[g.rdev[r0 + i]] = y[i];
+}
+__global__ __launch_bounds__(kIluThreads) void ilu_solve_kernel(IluArgs g, const double *__restrict__ r,
+                                                                double *__restrict__ z, const PcgState *st) {
+    if (st && st->done) return;
+    extern __shared__ double lds[];
+    ilu_solve_block(g, blockIdx.x, r, z, lds);
+}
+
 // One substitution over a block staged in LDS: level by level, one lane per row,
 // the row's entries in their order.  A level holds few rows (2 or 3 for blocks
 // of 128 unknowns), so its time is the chain y -> sum -> y: the slots of the
@@ -211,31 +251,41 @@ __global__ __launch_bounds__(kIluThreads) void ilu_factor_kernel(IluArgs g, cons
 // 1e-12 carries their other rounding to 1e-9 of a face flux: the sums keep the
 // order of ilu_solve_kernel, and the quotient is the correctly rounded one, by
 // Markstein's theorem from the correctly rounded reciprocal, with one more
-// correction so that the second starts within an ulp.)
+// correction so that the second starts within an ulp.  The theorem wants a
+// reciprocal, a quotient and a remainder that neither overflow nor lose bits
+// below the smallest normal number: numerators and pivots from 2^-500 to 2^500,
+// and zero numerators.  A block with another one is solved again with divisions:
+// asked row by row the question took 5 of 43 us.)
 constexpr int kIluAhead = 8;
+__device__ inline bool ilu_middle(double a) {  // 2^-500 <= |a| < 2^501
+    return ((uint32_t)((uint64_t)__double_as_longlong(a) >> 52) & 0x7ffu) - 523u <= 1000u;
+}
 struct IluRow {
     ushort4 m;  // local row, its entries [y, z); w = 0: no row
     double v[kIluAhead], d, di;
     uint16_t c[kIluAhead];
     bool wide;  // of the wavefront's rows: more than kIluAhead / 2 entries
 };
+// zero: the place of a 0 in y.  True where a lane met a numerator that the
+// quotients are not made for.
 template <bool BACK>
-__device__ inline void ilu_sweep(int nlev, const uint16_t *__restrict__ lp, const ushort4 *__restrict__ slot,
+__device__ inline bool ilu_sweep(int nlev, const uint16_t *__restrict__ lp, const ushort4 *__restrict__ slot,
                                  const double *__restrict__ val, const uint16_t *__restrict__ col,
-                                 const double *__restrict__ dinv, double *y) {
+                                 const double *__restrict__ dinv, double *y, uint16_t zero) {
     const int lane = threadIdx.x;
+    bool off = false;
     const ushort4 none = make_ushort4(0, 0, 0, 0);
     auto get = [&](int t, int t1) { return t < t1 ? slot[t] : none; };
     constexpr int H = kIluAhead / 2;  // rows of more entries take a second turn of loads
     auto load = [&](IluRow &R, const ushort4 &m) {
         R.m = m;
-        auto entry = [&](int k) {  // past the row: 0 times its own y
+        auto entry = [&](int k) {  // past the row: 0 times 0
             const bool on = m.y + k < m.z;
             const int p = on ? m.y + k : 0;
             const double v = val[p];
             const uint16_t c = col[p];
             R.v[k] = on ? v : 0.0;
-            R.c[k] = on ? c : m.x;
+            R.c[k] = on ? c : zero;
         };
 #pragma unroll
         for (int k = 0; k < H; ++k) entry(k);
@@ -265,6 +315,7 @@ __device__ inline void ilu_sweep(int nlev, const uint16_t *__restrict__ lp, cons
         if (BACK) {
             double q = s * R.di;
             q = fma(fma(-R.d, q, s), R.di, q);
+            off |= R.m.w && !(ilu_middle(s) || __double_as_longlong(s) == 0);
             s = fma(fma(-R.d, q, s), R.di, q);
         }
         if (R.m.w) y[R.m.x] = s;
@@ -295,6 +346,7 @@ __device__ inline void ilu_sweep(int nlev, const uint16_t *__restrict__ lp, cons
         m1 = m2;
     }
     __syncthreads();
+    return off;
 }
 static_assert(kIluThreads == 64, "a substitution is one wavefront's");
 
@@ -310,13 +362,14 @@ __global__ __launch_bounds__(kIluThreads) void ilu_solve_lds_kernel(IluArgs g, I
                                                                     double *__restrict__ z, const PcgState *st) {
     if (st && st->done) return;
     extern __shared__ double lds[];
-    double *y = lds, *dinv = y + L.rows, *val = dinv + L.rows;
+    double *y = lds, *dinv = y + L.rows + 1, *val = dinv + L.rows;
     ushort4 *slf = reinterpret_cast<ushort4 *>(val + L.ents), *slb = slf + L.rows;
     uint16_t *lpf = reinterpret_cast<uint16_t *>(slb + L.rows), *lpb = lpf + L.levs + 3, *col = lpb + L.levs + 3;
     const int32_t b = blockIdx.x, r0 = b * g.B, nr = min(g.n, r0 + g.B) - r0;
     const int32_t e0 = g.fptr[r0], ne = g.fptr[r0 + nr] - e0;
     const int32_t f0 = g.lvb_f[b], nf = g.lvb_f[b + 1] - f0, b0 = g.lvb_b[b], nb = g.lvb_b[b + 1] - b0;
     const int tid = threadIdx.x;
+    bool off = false;
 #pragma unroll 4
     for (int e = tid; e < ne; e += kIluThreads) {
         val[e] = g.fval[e0 + e];
@@ -325,54 +378,26 @@ __global__ __launch_bounds__(kIluThreads) void ilu_solve_lds_kernel(IluArgs g, I
 #pragma unroll 2
     for (int i = tid; i < nr; i += kIluThreads) {
         y[i] = r[g.rdev[r0 + i]];
-        dinv[i] = 1.0 / g.fval[g.fdiag[r0 + i]];
+        const double d = g.fval[g.fdiag[r0 + i]];
+        dinv[i] = 1.0 / d;
+        off |= !ilu_middle(d);
         const int4 mf = g.slot_f[r0 + i], mb = g.slot_b[r0 + i];
         slf[i] = make_ushort4((uint16_t)mf.x, (uint16_t)(mf.y - e0), (uint16_t)(mf.z - e0), 1);
         slb[i] = make_ushort4((uint16_t)mb.x, (uint16_t)(mb.y + 1 - e0), (uint16_t)(mb.z - e0), 1);
     }
-    // level pointers, the end repeated (the sweeps read two levels ahead)
+    if (tid == 0) y[L.rows] = 0.0;
+    // level pointers, the end repeated (the sweeps look up to four levels ahead, at most at entry nlev + 1)
     for (int l = tid; l < nf + 3; l += kIluThreads) lpf[l] = (uint16_t)((l < nf ? g.lptr_f[f0 + l] : r0 + nr) - r0);
     for (int l = tid; l < nb + 3; l += kIluThreads) lpb[l] = (uint16_t)((l < nb ? g.lptr_b[b0 + l] : r0 + nr) - r0);
     __syncthreads();
-    ilu_sweep<false>(nf, lpf, slf, val, col, nullptr, y);  // L y = r (unit diagonal), in place
-    ilu_sweep<true>(nb, lpb, slb, val, col, dinv, y);      // U z = y, in place
+    const uint16_t zero = (uint16_t)L.rows;
+    ilu_sweep<false>(nf, lpf, slf, val, col, nullptr, y, zero);  // L y = r (unit diagonal), in place
+    off |= ilu_sweep<true>(nb, lpb, slb, val, col, dinv, y, zero);  // U z = y, in place
+    if (__any(off)) {
+        ilu_solve_block(g, b, r, z, y);
+        return;
+    }
     for (int i = tid; i < nr; i += kIluThreads) z[g.rdev[r0 + i]] = y[i];
-}
-
-// The same from global memory, for blocks whose factor does not fit in LDS
-// (only the block's vector is kept there).
-__global__ __launch_bounds__(kIluThreads) void ilu_solve_kernel(IluArgs g, const double *__restrict__ r,
-                                                                double *__restrict__ z, const PcgState *st) {
-    if (st && st->done) return;
-    extern __shared__ double y[];
-    const int32_t b = blockIdx.x, r0 = b * g.B, r1 = min(g.n, r0 + g.B);
-    const int tid = threadIdx.x;
-    const double *__restrict__ v = g.fval;
-    const uint16_t *__restrict__ col = g.fcol;
-    // the block's right-hand side into LDS, all loads in flight at once
-    for (int32_t i = tid; i < r1 - r0; i += kIluThreads) y[i] = r[g.rdev[r0 + i]];
-    __syncthreads();
-    // L y = r (unit diagonal), in place
-    for (int32_t l = g.lvb_f[b]; l < g.lvb_f[b + 1]; ++l) {
-        for (int32_t t = g.lptr_f[l] + tid; t < g.lptr_f[l + 1]; t += kIluThreads) {
-            const int4 m = g.slot_f[t];
-            double s = y[m.x];
-            for (int32_t p = m.y; p < m.z; ++p) s -= v[p] * y[col[p]];
-            y[m.x] = s;
-        }
-        __syncthreads();
-    }
-    // U z = y, in place
-    for (int32_t l = g.lvb_b[b]; l < g.lvb_b[b + 1]; ++l) {
-        for (int32_t t = g.lptr_b[l] + tid; t < g.lptr_b[l + 1]; t += kIluThreads) {
-            const int4 m = g.slot_b[t];
-            double s = y[m.x];
-            for (int32_t p = m.y + 1; p < m.z; ++p) s -= v[p] * y[col[p]];
-            y[m.x] = s / v[m.y];
-        }
-        __syncthreads();
-    }
-    for (int32_t i = tid; i < r1 - r0; i += kIluThreads) z[g.rdev[r0 + i]] = y[i];
 }
 
 void Ilu::factor(hipStream_t s, const double *A, int *bad) {

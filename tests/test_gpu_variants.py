@@ -408,3 +408,53 @@ def test_ilu_handles_of_different_blocks(later):
     assert h.solve_pressure()["status"] == 0
     h2.close()
     h.close()
+
+
+@pytest.mark.parametrize("B", [16, 128, 200])
+@pytest.mark.parametrize("scale", [0, 505, -505])
+def test_ilu_quotients_of_any_size(B, scale):
+    """Nodes numbered by the parities of their place: a block of unknowns of one
+    class has no couplings, so its z is r / diagonal, to the bit, whatever the
+    sizes: right-hand sides from the least subnormal number to the largest and
+    infinities, pivots about 2^scale.  Then with couplings: where the oracle's z
+    is finite, infinite or neither."""
+    from paper_1602_03641_amd import vag
+    from oracle import ilu
+    import scipy.sparse as sp
+    dims = (16, 15, 14)
+    p = synth.random_problem(dims, 49, n_patches=0, n_steps=0, ratios=(1e2,))
+    i, j, k = (a.ravel(order="F") for a in np.meshgrid(*(np.arange(n + 1) for n in dims), indexing="ij"))
+    old = np.lexsort((np.arange(len(i)), i % 2 + 2 * (j % 2) + 4 * (k % 2)))
+    new = np.empty(len(old), np.int32)
+    new[old] = np.arange(len(old))
+    p.hex8, p.xyz, p.dirichlet, p.p_bar, p.c_bar = (new[p.hex8], p.xyz[old], p.dirichlet[old], p.p_bar[old],
+                                                    p.c_bar[old])
+    p.mu = 2.0 ** -scale
+    kw = dict(rtol=1e-2, max_iter=3, eliminate_frac_faces=0)
+    g, _ = _handle(p, precond=vag.VAG_PC_AMG, **kw)
+    d = g.amg_level(0)["A"]
+    g.close()
+    A = sp.csr_matrix((d[2], d[1], d[0]))
+    n = A.shape[0]
+    h, info = _handle(p, precond=vag.VAG_PC_BJILU0, krylov=vag.VAG_BICGSTAB, ilu_block_rows=B, **kw)
+    assert info["n_unknowns"] == n
+    c = A.tocoo()
+    alone = np.ones((n + B - 1) // B, bool)
+    alone[(c.row // B)[(c.row // B == c.col // B) & (c.row != c.col)]] = False
+    own = np.repeat(alone, B)[:n]
+    assert own.sum() > n // 4
+    rng = np.random.default_rng(50)
+    r = np.ldexp(rng.uniform(1.0, 2.0, n), rng.integers(-1074, 1024, n)) * rng.choice([-1.0, 1.0], n)
+    r[rng.choice(n, n // 20)] = rng.choice([np.inf, -np.inf, 0.0, -0.0], n // 20)
+    z = h.apply_preconditioner(r)
+    with np.errstate(all="ignore"):
+        q = r / A.diagonal()
+    assert np.array_equal(z[own].view(np.int64), q[own].view(np.int64))
+    # the entry that a block's other rows take last, and nothing else in r
+    r = np.zeros(n)
+    r[np.arange(B - 1, n, 3 * B)] = np.inf
+    z = h.apply_preconditioner(r)
+    with np.errstate(all="ignore"):
+        zr = ilu.bj_ilu0_apply(ilu.bj_ilu0(A, B), r)
+    assert np.array_equal(np.isnan(z), np.isnan(zr)) and np.array_equal(np.isinf(z), np.isinf(zr))
+    h.close()
