@@ -8,6 +8,8 @@
 // device matrix.
 #pragma once
 
+#include <algorithm>
+
 #include "vag_internal.h"
 
 namespace vag {
@@ -43,6 +45,23 @@ struct IluLds {
     static constexpr size_t kMax = 160 * 1024;  // of a CU
     // entry and slot indices inside a block are 16-bit there
     bool fits() const { return rows > 0 && ents <= 65535 && bytes() <= kMax; }
+    // Whether nblk such blocks are solved faster there.  Not where a level is a
+    // row (blocks of at most a line of the mesh): the chain is as long, and there
+    // is nothing to share the staging (an application in LDS / in global memory,
+    // us: 48^3 cells, blocks of 64 rows in 47 levels, 44 / 49; of 48 in 47, 48 /
+    // 41; 128^3, 64 in 64, 517 / 447; 200 x 200 x 1, 192 in 192, 301 / 138).  And
+    // not where the blocks take turns because few fit on a CU, while the other
+    // kernel, whose blocks need 8 bytes of LDS per row, has up to 32 there at once
+    // (80^3, blocks of 512, 2 on a CU, 2.0 turns, 159 / 218; 96^3, 3.4 turns, 343 /
+    // 305; 128^3, 8 turns, 983 / 512; with 10 on a CU, blocks of 192: 112^3, 3.2
+    // turns, 372 / 359; 128^3, 4.3 turns, where the other kernel takes turns too,
+    // 570 / 641).
+    bool pays(int64_t nblk) const {
+        if (!fits() || 4 * rows < 5 * levs) return false;
+        constexpr int64_t cus = 256, most = 32;
+        const int64_t per = std::min<int64_t>(most, kMax / bytes());  // on a CU
+        return nblk <= 3 * cus * per || (per >= 6 && nblk > cus * most);
+    }
 };
 
 class Ilu {
@@ -66,6 +85,7 @@ private:
     int64_t nent_ = 0;
     IluArgs a_{};
     IluLds lds_;
+    bool in_lds_ = false;  // lds_.pays
     DBuf<int32_t> fptr_, fsrc_, fdiag_, rdev_, lvb_f_, lptr_f_, rows_f_, lvb_b_, lptr_b_, rows_b_;
     DBuf<int4> slot_f_, slot_b_;
     DBuf<uint16_t> fcol_;

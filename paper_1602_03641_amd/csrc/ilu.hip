@@ -158,7 +158,8 @@ void Ilu::build(hipStream_t s, Tracker &tr, const Symbolic &S, int B) {
     put(s, tr, slot_f_, slot_f);
     put(s, tr, slot_b_, slot_b);
     fval_.alloc(std::max<int64_t>(nent, 1), tr);
-    if (lds_.fits())  // the kernel's limit is the process's, so the most that any handle asks for
+    in_lds_ = lds_.pays(nblk);
+    if (in_lds_)  // the kernel's limit is the process's, so the most that any handle asks for
         VAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(ilu_solve_lds_kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)IluLds::kMax));
     VAG_HIP(hipStreamSynchronize(s));  // the host vectors go out of scope
@@ -408,7 +409,7 @@ void Ilu::factor(hipStream_t s, const double *A, int *bad) {
 
 void Ilu::apply(hipStream_t s, const double *r, double *z, const PcgState *st) const {
     if (a_.nblk == 0) return;
-    if (lds_.fits()) {
+    if (in_lds_) {
         hipLaunchKernelGGL(ilu_solve_lds_kernel, dim3(a_.nblk), dim3(kIluThreads), lds_.bytes(), s, a_, lds_, r, z, st);
         VAG_HIP(hipGetLastError());
         return;

@@ -1,7 +1,11 @@
-"""Limits that the library sets for a kernel belong to the process."""
+"""Limits and choices of kernels, as the host code states them."""
 import glob
 import os
 import re
+import shutil
+import subprocess
+
+import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1602_03641_amd", "csrc")
 
@@ -20,3 +24,31 @@ def test_lds_limits_are_constants():
             found += 1
             assert re.fullmatch(r"[\s\w:*+]+", value), (os.path.basename(f), value)
     assert found >= 2
+
+
+def test_ilu_solve_choice(tmp_path):
+    """The ILU solve stages its blocks in LDS only where that was measured to be
+    the faster one: (rows, entries and levels of a block, blocks, us an
+    application in LDS and in global memory)."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("no compiler")
+    measured = [
+        (16, 36, 16, 7053, 42.9, 22.2), (64, 190, 64, 14000, 232.8, 204.2), (48, 142, 47, 2351, 48.1, 40.5),
+        (64, 346, 47, 1764, 44.1, 49.4), (128, 1004, 50, 882, 43.0, 67.2), (128, 656, 95, 6984, 220.2, 226.5),
+        (128, 382, 127, 16511, 476.6, 438.4), (192, 574, 192, 417, 301.1, 137.8), (192, 1086, 111, 7383, 372.4, 359.5),
+        (192, 1000, 127, 11008, 570.2, 640.9), (256, 1700, 97, 3492, 243.3, 307.2), (384, 3006, 101, 2328, 316.0, 301.2),
+        (512, 4100, 72, 221, 61.7, 103.5), (512, 4040, 94, 1013, 159.2, 218.2), (512, 3850, 133, 4128, 983.1, 511.8),
+        (768, 6400, 109, 1164, 444.8, 306.7), (1024, 8800, 103, 260, 160.2, 185.6), (1024, 8500, 145, 2064, 1114.7, 518.4),
+    ]
+    src, exe = tmp_path / "choice.cpp", str(tmp_path / "choice")
+    rows = ",".join("{%d,%d,%d,%d}" % m[:4] for m in measured)
+    src.write_text('#include <cstdio>\n#include "ilu.h"\nint main() {\n  const int m[][4] = {' + rows + '};\n'
+                   '  for (auto &r : m) { vag::IluLds L; L.rows = r[0]; L.ents = r[1]; L.levs = r[2];'
+                   ' std::printf("%d", (int)L.pays(r[3])); }\n}\n')
+    inc = ["-I" + CSRC, "-I" + os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include")]
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-std=c++17", "-O0", "-w", *inc, str(src), "-o", exe],
+                   check=True, capture_output=True)
+    got = subprocess.run([exe], capture_output=True, text=True, check=True).stdout
+    for m, g in zip(measured, got, strict=True):
+        assert (g == "1") == (m[4] < m[5]), m
