@@ -60,7 +60,7 @@ void amg_launch_slices(hipStream_t s, int32_t n, const int32_t *rowlen, int32_t 
                        unsigned long long *nnz, int64_t *host = nullptr, const int *flag = nullptr,
                        int *host_flag = nullptr);
 void amg_launch_slice_tail(hipStream_t s, int32_t n, const int64_t *ptr, int32_t *col, double *val);
-// D = A^-1 (dense, row-major, at most 1024 rows); work holds A.n^2 + 8192 doubles
+// D = A^-1 (dense, row-major, at most 1024 rows); work holds 256 * A.n + 8192 doubles
 void amg_launch_dense_inverse(hipStream_t s, Sell<double> A, double *D, double *work);
 template <class V, class X>
 void amg_launch_pre(hipStream_t s, Sell<V> A, const X *dinv, const X *b, X *x, X *r, const PcgState *st);

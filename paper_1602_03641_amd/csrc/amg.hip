@@ -899,10 +899,17 @@ __global__ __launch_bounds__(64) void slice_tail_kernel(int32_t n, const int64_t
 // ---------------------------------------------------------------------------
 // coarsest level: dense inverse
 // ---------------------------------------------------------------------------
-// D = A, dense row-major, one wavefront per row.  A row's entries have distinct
-// columns (padding entries are zero).
+// What a block step of the inversion reads beside its own tile: the pivot rows
+// R (kGJ x n) and the pivot columns U (n x kGJ) of M, apart from M, which the
+// step writes in place.
+struct GjPanels {
+    double *U, *R;
+};
+// D = A, dense row-major, one wavefront per row, and the first panels.  A row's
+// entries have distinct columns (padding entries are zero).
 constexpr int kDenseMax = 1024;
-__global__ __launch_bounds__(64) void dense_from_sell_kernel(Sell<double> A, double *__restrict__ D) {
+constexpr int kGJ = 64;
+__global__ __launch_bounds__(64) void dense_from_sell_kernel(Sell<double> A, double *__restrict__ D, GjPanels P) {
     __shared__ double row[kDenseMax];
     const int32_t n = A.n, i = blockIdx.x;
     const int lane = threadIdx.x;
@@ -914,20 +921,25 @@ __global__ __launch_bounds__(64) void dense_from_sell_kernel(Sell<double> A, dou
         if (v != 0.0) row[A.col[b0 + 64 * k]] = v;
     }
     __syncthreads();
-    for (int j = lane; j < n; j += 64) D[(int64_t)i * n + j] = row[j];
+    for (int j = lane; j < n; j += 64) {
+        D[(int64_t)i * n + j] = row[j];
+        if (i < kGJ) P.R[(int64_t)i * n + j] = row[j];
+    }
+    if (lane < n) P.U[(int64_t)i * kGJ + lane] = row[lane];
 }
 // Blocked Gauss-Jordan inversion of an SPD matrix (no pivoting needed: every
 // pivot block is a Schur complement of an SPD matrix, hence SPD).  With P the
 // next kGJ indices, R the others and B = M[P,P]^-1 the block step is
 //   V = B M[P,R],  W = M[R,P] B,
 //   M[R,R] = M[R,R] - M[R,P] V,  M[P,R] = V,  M[R,P] = -W,  M[P,P] = B,
-// one launch, one workgroup per 64 x 64 tile, from one copy of M to another:
-// each tile of M[R,R] forms its own tile of V, and the workgroup of the next
-// pivot block inverts it before it ends.  That inversion is the chain that the
+// one launch, one workgroup per 64 x 64 tile: each tile of M[R,R] forms its own
+// tile of V, and the workgroup of the next pivot block inverts it before it
+// ends.  A workgroup reads its own tile of M and otherwise the panels, of which
+// it also writes its share for the next step (from one copy of M to another the
+// same bits took as long and 8 MB more at 1000 rows).  That inversion is the chain that the
 // steps wait for (~20 us); the products, loads and launches around it were 33
 // us of a step as four kernels (pivot, panels, update, write-back in place: 62
 // us a step, now 27; 430 rows 434 -> 218 us).
-constexpr int kGJ = 64;
 constexpr int kGJLd = kGJ + 2;  // of a tile in LDS: rows 16 bytes aligned, their banks shifted
 constexpr int kQ = 4;  // pivots eliminated together inside the diagonal block
 
@@ -1067,10 +1079,10 @@ __device__ inline void gj_product(const double (&A)[kGJ][kGJLd], const double (&
             }
     }
 }
-// One block step with pivots [p0, p0 + k): Mout from Min and B = Min[P,P]^-1;
-// next = the inverse of the following pivot block.
+// One block step with pivots [p0, p0 + k) on M, given its panels and B =
+// M[P,P]^-1; the panels and next = the inverse of the following pivot block.
 __global__ __launch_bounds__(256) void gj_step_kernel(int32_t n, int32_t p0, int32_t k,
-                                                      const double *__restrict__ Min, double *__restrict__ Mout,
+                                                      double *__restrict__ M, GjPanels P, GjPanels Pnext,
                                                       const double *__restrict__ B, double *__restrict__ next) {
     __shared__ __align__(16) double S[kGJ][kGJLd], T[kGJ][kGJLd];
     const int32_t i0 = blockIdx.y * kGJ, j0 = blockIdx.x * kGJ;
@@ -1087,8 +1099,8 @@ __global__ __launch_bounds__(256) void gj_step_kernel(int32_t n, int32_t p0, int
         const int e = threadIdx.x + it * 256, r = e >> 6, c = e & 63;
         const bool iu = i0 + r < n && c < k, iv = r < k && j0 + c < n;
         const double b = B[e];
-        const double x = Min[(int64_t)(iu ? i0 + r : p0) * n + p0 + (iu ? c : 0)];
-        const double y = Min[(int64_t)(p0 + (iv ? r : 0)) * n + (iv ? j0 + c : p0)];
+        const double x = P.U[(int64_t)(iu ? i0 + r : 0) * kGJ + (iu ? c : 0)];
+        const double y = P.R[(int64_t)(iv ? r : 0) * n + (iv ? j0 + c : 0)];
         u[it] = iu ? x : 0.0;
         v[it] = iv ? y : 0.0;
         S[r][c] = rj && !ri ? u[it] : b;
@@ -1121,7 +1133,7 @@ __global__ __launch_bounds__(256) void gj_step_kernel(int32_t n, int32_t p0, int
                 for (int c = 0; c < 4; ++c) {
                     const int i = i0 + ty * 4 + a, j = j0 + tx * 4 + c;
                     const bool in = i < n && j < n;
-                    out[a][c] = Min[in ? (int64_t)i * n + j : 0];
+                    out[a][c] = M[in ? (int64_t)i * n + j : (int64_t)i0 * n + j0];  // of its own tile
                 }
             __syncthreads();
 #pragma unroll
@@ -1159,7 +1171,11 @@ __global__ __launch_bounds__(256) void gj_step_kernel(int32_t n, int32_t p0, int
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int i = i0 + ty * 4 + a, j = j0 + tx * 4 + c;
-            if (i < n && j < n) Mout[(int64_t)i * n + j] = out[a][c];
+            if (i < n && j < n) {
+                M[(int64_t)i * n + j] = out[a][c];
+                if (j0 == p0 + kGJ) Pnext.U[(int64_t)i * kGJ + j - j0] = out[a][c];
+                if (i0 == p0 + kGJ) Pnext.R[(int64_t)(i - i0) * n + j] = out[a][c];
+            }
         }
 }
 
@@ -1700,13 +1716,16 @@ void amg_launch_dense_inverse(hipStream_t s, Sell<double> A, double *D, double *
     if (n > kDenseMax) throw Error(VAG_ERR_ARG, "internal: dense inverse of too many rows");
     const int nt = (n + kGJ - 1) / kGJ;
     double *B[2] = {work, work + kGJ * kGJ};
-    double *M[2] = {D, work + 2 * kGJ * kGJ};  // the steps alternate and end in D
-    int m = nt & 1;
-    ALAUNCH(dense_from_sell_kernel, n, 64, A, M[m]);
-    ALAUNCH(gj_first_kernel, 1, 256, n, M[m], B[0]);
-    for (int p = 0; p < nt; ++p, m ^= 1) {
-        hipLaunchKernelGGL(gj_step_kernel, dim3(nt, nt), dim3(256), 0, s, n, p * kGJ, std::min(kGJ, n - p * kGJ), M[m],
-                           M[m ^ 1], B[p & 1], B[(p & 1) ^ 1]);
+    GjPanels P[2];
+    for (int h = 0; h < 2; ++h) {
+        P[h].U = work + 2 * kGJ * kGJ + (int64_t)h * 2 * kGJ * n;
+        P[h].R = P[h].U + (int64_t)kGJ * n;
+    }
+    ALAUNCH(dense_from_sell_kernel, n, 64, A, D, P[0]);
+    ALAUNCH(gj_first_kernel, 1, 256, n, D, B[0]);
+    for (int p = 0; p < nt; ++p) {
+        hipLaunchKernelGGL(gj_step_kernel, dim3(nt, nt), dim3(256), 0, s, n, p * kGJ, std::min(kGJ, n - p * kGJ), D,
+                           P[p & 1], P[(p & 1) ^ 1], B[p & 1], B[(p & 1) ^ 1]);
         VAG_HIP(hipGetLastError());
     }
 }

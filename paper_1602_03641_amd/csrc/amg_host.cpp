@@ -122,7 +122,7 @@ void Amg::finish_setup(hipStream_t s, Tracker &tr, int l, int64_t stored_total, 
     }
     if (cl.n <= o_.dense_max && cl.n > 0) {
         ensure(Ainv, (size_t)cl.n * cl.n, tr);
-        ensure(gj_work, (size_t)cl.n * cl.n + 8192, tr);
+        ensure(gj_work, (size_t)256 * cl.n + 8192, tr);
         amg_launch_dense_inverse(s, cl.A, Ainv.p, gj_work.p);
         dense = true;
     }

@@ -2179,6 +2179,11 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
     if (opt) o = *opt; else vag_default_options(&o);
     if (nn <= 0 || nc <= 0 || nf < 0) return 0;
     const double Nn = (double)nn, Nc = (double)nc, Nf = (double)nf, Nx = Nn + Nf;
+    // A job whose estimate exceeds the server's budget is refused, so the terms
+    // are not raised for small buffers that the slack below covers: second
+    // copies of two CG vectors (16 bytes per unknown up to 131072), slots of the
+    // fracture blocks (64 per face), transport bases (4 bytes per row), the second
+    // half of the elimination workspace (1 MB at most).
     // system entries: at most 27 per node row plus the couplings of the
     // fracture faces (face rows, their columns and the group fill); sliced
     // ELL padding
@@ -2186,15 +2191,15 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
     const double S = 1.4 * nnz + 4096.0;
     double b = 0.0;
     b += 24 * Nn + 97 * Nc + 72 * Nf + 14 * Nn + 12.0 * S / 64;    // topology, adjacency
-    b += 4 * S + 4 * (64 * Nc + 74 * Nf) + 8 * Nc;                 // pattern, slot maps
+    b += 4 * S + 4 * (64 * Nc + 58 * Nf) + 8 * Nc;                 // pattern, slot maps
     b += 3000.0 * Nf;                                               // fracture-face groups
     b += 56 * Nc + 24 * Nf + 16 * Nn;                               // rock, fracture, boundary data
     b += 376 * Nc + 304 * Nf + 8 * S + 16 * Nx;                     // local matrices, system
-    b += 42 * Nx + 16 * std::min(Nx, 131072.0) + 64.0 * 1024;       // Krylov vectors and partials
+    b += 40 * Nx + 64.0 * 1024;                                     // Krylov vectors and partials
     b += 88 * Nc + 56 * Nf + 16 * Nn;                               // pressures, fluxes, porous volumes
     if (o.alpha_rule == 1) b += 8 * Nn;                             // largest permeability per node
     const double nrow = Nn + Nc + Nf, tst = 2.0 * (8 * Nc + 6 * Nf) + 64.0 * 16;
-    b += 24 * nrow + 12 * tst + 28 * nrow / 64;                     // transport
+    b += 24 * nrow + 12 * tst + 12 * nrow / 64;                     // transport
     if (o.precond == VAG_PC_AMG) {
         double amg = 104 * Nx + 17 * S + 0.15 * (12 * S + 104 * Nx);
         if (o.precision == VAG_MIXED) amg += 4.6 * S + 50 * Nx;
@@ -2205,7 +2210,7 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
         // modes) and its elimination workspace: at most coarse_size rows
         const double cs = o.amg_coarse_size > 0 ? o.amg_coarse_size : 1000.0;
         const double d = std::min(Nx, std::min(cs, 1024.0));
-        b += 1.125 * amg + 20.0 * d * d + 65536.0 + 0.5 * 1024 * 1024;
+        b += 1.125 * amg + 12.0 * d * d + 1024.0 * d + 0.5 * 1024 * 1024;
     }
     if (o.precond == VAG_PC_BJILU0) b += 14 * nnz + 28 * Nx;        // factor entries, rows, schedules
     if (o.krylov == VAG_GMRES) {  // flexible GMRES: m + 1 basis vectors, m preconditioned ones, a work vector

@@ -458,3 +458,22 @@ def test_ilu_quotients_of_any_size(B, scale):
         zr = ilu.bj_ilu0_apply(ilu.bj_ilu0(A, B), r)
     assert np.array_equal(np.isnan(z), np.isnan(zr)) and np.array_equal(np.isinf(z), np.isinf(zr))
     h.close()
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 9), (9, 9, 9), (10, 9, 10), (4, 15, 16)])
+@pytest.mark.parametrize("opt", ["fp64", "mixed", "mixed_ir", "gmres"])
+def test_footprint_of_small_handles(dims, opt):
+    """About a thousand unknowns, where the dense inverse and its workspace are
+    most of a handle: within the estimate that a server admits it by."""
+    from paper_1602_03641_amd import vag
+    kw = {"fp64": {}, "mixed": dict(precision=vag.VAG_MIXED), "mixed_ir": dict(precision=vag.VAG_MIXED_IR),
+          "gmres": dict(precision=vag.VAG_MIXED, krylov=vag.VAG_GMRES)}[opt]
+    kw.update(precond=vag.VAG_PC_AMG, rtol=1e-8)
+    p = synth.random_problem(dims, 51, n_patches=6, n_steps=0, ratios=(1e2, 1e4))
+    h, info = _handle(p, **kw)
+    assert info["amg_levels"] == 1
+    h.transport(n_steps=2)
+    used, est = vag.load().vag_footprint_bytes(h.h), vag.estimate_footprint(p, **kw)
+    print(used, est)
+    assert used <= est
+    h.close()

@@ -52,3 +52,22 @@ def test_ilu_solve_choice(tmp_path):
     got = subprocess.run([exe], capture_output=True, text=True, check=True).stdout
     for m, g in zip(measured, got, strict=True):
         assert (g == "1") == (m[4] < m[5]), m
+
+
+def test_estimates_admit_known_jobs():
+    """A server refuses a job whose estimate exceeds its budget, so the estimates
+    do not grow: bytes that admitted these jobs (cells a side, options, fracture
+    faces) admit them."""
+    import ctypes as C
+    from paper_1602_03641_amd import vag
+    amg, gmres, bicgstab = dict(precond=vag.VAG_PC_AMG), dict(krylov=vag.VAG_GMRES), dict(krylov=vag.VAG_BICGSTAB)
+    mixed, ir = dict(precision=vag.VAG_MIXED), dict(precision=vag.VAG_MIXED_IR)
+    for n, kw, nf, most in [(10, amg, 100, 21310981), (10, amg | mixed, 100, 21780666), (16, amg | mixed, 256, 34443621),
+                            (16, amg, 0, 30772409), (24, amg | ir, 576, 72134810), (32, amg | mixed, 1024, 141396484),
+                            (48, amg, 2304, 384072173), (48, amg | mixed | gmres, 2304, 644010186),
+                            (64, amg | dict(amg_kind=1), 4096, 2575207893),
+                            (48, bicgstab | dict(precond=vag.VAG_PC_BJILU0), 2304, 294023467),
+                            (32, dict(precond=vag.VAG_PC_JACOBI), 1024, 73679915)]:
+        o = vag.default_options(**kw)
+        got = vag.load().vag_estimate_footprint((n + 1) ** 3, n ** 3, nf, C.byref(o))
+        assert 0 < got <= most, (n, kw, got)
