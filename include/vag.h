@@ -307,8 +307,9 @@ vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const d
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * transport of vag_transport (time step dt = cfl * CFL bound, then n_steps
  * explicit upwind steps, or t_final as there) without memory of its own.  A
- * call of a few steps gathers the upwind fluxes of every control volume from
- * the handle's resident Darcy fluxes in each step; a longer one first builds
+ * call of a few steps, or on a mesh with a node of more than 255 cells and
+ * fracture faces, gathers the upwind fluxes of every control volume from
+ * the handle's resident Darcy fluxes in each step; any other first builds
  * the upwind operator of vag_transport in the handle's array of local matrices
  * (which the next solve computes again).
  * The call allocates nothing: the CFL reduction's partial minima and the time

@@ -180,6 +180,7 @@ struct vag_handle {
     DBuf<int32_t> slice_width, slice_nnz, tcol;
     DBuf<int4> tbase;
     DBuf<uint16_t> tcol16;
+    int max_degree = 0;  // hexahedra: the most fluxes of a node
     DBuf<uint16_t> tmeta;
     DBuf<int64_t> slice_ptr;
     DBuf<int32_t> xsplit;  // [18] the XCDs' runs of slices of the upwind operator (xlo, then ylo)
@@ -1161,8 +1162,11 @@ vag_status vag_create(const vag_mesh *mesh, const vag_fractures *frac, const vag
         launch_node_pos(h->stream, asm_args(h), h->node_pos.p);
         h->frac_pos.alloc(std::max<size_t>(32 * (size_t)nf, 1), h->tr);  // 8 slots per node_frac entry
         launch_frac_pos(h->stream, asm_args(h), S.nf, h->frac_pos.p);
+        VAG_HIP(hipMemsetAsync(h->coef_bad.p, 0, sizeof(int), h->stream));
+        launch_node_degree(h->stream, S.nn, h->node_cell_ptr.p, h->node_frac_ptr.p, h->coef_bad.p);
         int bad = 0;
         VAG_HIP(hipMemcpyAsync(&bad, h->bad.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+        VAG_HIP(hipMemcpyAsync(&h->max_degree, h->coef_bad.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
         VAG_HIP(hipStreamSynchronize(h->stream));
         if (bad != 0x7f7f7f7f) throw Error(VAG_ERR_ARG, "internal: a group's node pair is missing from the pattern");
     });
@@ -1708,7 +1712,8 @@ namespace {
 // gather / operator, whole call: 64^3 134 / 215 us for 1 step, 304 / 238 for 4,
 // 3158 / 742 for 64; 160^3 3162 / 2116 for 4; below 2^18 control volumes a
 // step is a launch either way (7 / 4 us): 16^3 130 / 148 us for 4 steps,
-// 209 / 191 for 16.
+// 209 / 191 for 16.  A mesh with nodes of more fluxes than a row of the
+// operator holds entries is gathered at any step count.
 int64_t noalloc_op_steps(int64_t nrow) { return nrow >= (1 << 18) ? 4 : 12; }
 struct NoallocOp {
     int32_t *width, *nnz, *col;
@@ -1814,7 +1819,7 @@ vag_status vag_transport_noalloc(vag_handle *h, int64_t n_steps, double t_final,
             theta_last = last_dt / dt;
         }
         const NoallocOp o = noalloc_operator(h);
-        const bool op = o.fits && N >= noalloc_op_steps(nrow);
+        const bool op = o.fits && h->max_degree <= kUpwindEntries && N >= noalloc_op_steps(nrow);
         if (op) {
             launch_upwind_count(s, S.nc, S.nf, S.nn, h->fmask.p, h->cell_frac.p, h->frac_cell.p, h->dirichlet.p,
                                 h->node_cell_ptr.p, h->node_cell.p, h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p,

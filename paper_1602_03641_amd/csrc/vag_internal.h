@@ -380,6 +380,8 @@ struct PatArgs {
     const uint8_t *fmask;
     const int32_t *node_grp_ptr, *node_grp, *grp_nptr, *grp_node;
 };
+// *most (0 before) = the most fluxes of a node of a hexahedral mesh
+void launch_node_degree(hipStream_t s, int32_t nn, const int32_t *ncp, const int32_t *nfp, int *most);
 // node_cell_ptr (nn + 1) and node_cell (8 nc: K * 8 + a, ascending per node)
 // of a hexahedral mesh; work: nn + 2 (nn / 1024 + 2) ints
 void launch_node_cell(hipStream_t s, int32_t nn, int64_t nc, const int32_t *hex8, int32_t *ptr, int32_t *cells,
@@ -542,7 +544,7 @@ void launch_upwind_fill(hipStream_t s, int32_t nc, int32_t nf, int32_t nn, const
 // lane << 8 | entry count per slot), entries packed by level (jagged
 // diagonals) from slice_ptr[slice]; 16-bit columns by tbase[slice] = {b0, b1,
 // split} (column = code + (code < split ? b0 : b1)) where split >= 0, else the
-// 32-bit tcol.
+// 32-bit tcol.  The counts of meta have 8 bits: kUpwindEntries entries a row.
 // The sweep splits the slices into two segments, A = [0, sa) (cells and
 // fracture faces) and B = [sa, nslice) (nodes), and gives XCD x of the 8 the
 // slices [xlo[x], xlo[x+1]) of A and [ylo[x], ylo[x+1]) of B, runs of equal
@@ -552,6 +554,7 @@ void launch_upwind_fill(hipStream_t s, int32_t nc, int32_t nf, int32_t nn, const
 // hit the lines the other has brought into that XCD's L2; the cost balance
 // keeps every XCD equally busy when rows differ in length along the
 // numbering (cells of 4 nodes, nodes of 24 cells).
+constexpr int kUpwindEntries = 255;
 struct UpwindOp {
     int32_t nrow;
     const int64_t *slice_ptr;

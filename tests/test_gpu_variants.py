@@ -477,3 +477,27 @@ def test_footprint_of_small_handles(dims, opt):
     print(used, est)
     assert used <= est
     h.close()
+
+
+@pytest.mark.parametrize("sectors", [120, 200, 300])
+def test_noalloc_at_wide_nodes(sectors):
+    """An axis node of 246, 406 and 606 fluxes, of which about half flow in: past
+    the 255 entries that a row of the upwind operator counts, the allocation-free
+    transport gathers at any step count.  Against the oracle's steps on the
+    library's fluxes, within the 1e-10 that its other tests take."""
+    from paper_1602_03641_amd import vag
+    p = _star(sectors, 2, False)
+    h, _ = _handle(p, rtol=1e-10, precond=vag.VAG_PC_JACOBI)
+    flux, phi = vag.to_numpy(h.fluxes()), vag.to_numpy(h.porous_volumes())
+    into = np.bincount(p.hex8.ravel(), weights=(flux["F_cell"].ravel() > 0).astype(float), minlength=p.n_nodes)
+    assert (into[p.dirichlet == 0].max() > 255) == (sectors == 300)
+    rng = np.random.default_rng(52)
+    c0 = {k: rng.uniform(0, 1, n) for k, n in (("c_cell", p.n_cells), ("c_frac", p.n_frac), ("c_node", p.n_nodes))}
+    c0o = dict(c0, c_node=np.where(p.dirichlet == 1, p.c_bar, c0["c_node"]))
+    for n in (11, 13, 40):
+        print("sectors", sectors, "steps", n, flush=True)
+        got, info = h.transport_noalloc(n_steps=n, c0=c0)
+        ref = oracle.transport(p, flux, phi, info["dt"], n, c0=c0o)
+        for k, v in vag.to_numpy(got).items():
+            assert np.abs(v - ref[k]).max(initial=0.0) <= 1e-10, (n, k)
+    h.close()
