@@ -439,7 +439,8 @@ vag_server::Outcome vag_server::run(Job *j, int w, vag_handle *h) {
         return {};
     }
     j->solve_status = st;
-    if ((j->n_steps > 0 || j->t_final > 0) && j->nc + j->nf + j->nn >= kBatchRows) {
+    if ((j->n_steps > 0 || j->t_final > 0) &&
+        (j->nc + j->nf + j->nn >= kBatchRows || !vag_serving_batches(h))) {
         st = vag_transport(h, j->n_steps, j->t_final, nullptr, nullptr, nullptr, VAG_MEM_HOST, &r.transport);
         if (failed(st)) {
             vag_destroy(h);

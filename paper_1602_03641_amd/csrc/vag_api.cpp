@@ -139,6 +139,7 @@ void pinned_put(void *p, size_t bytes) {
 struct TransportPlan {
     int64_t N = 0, total = 0;
     double dt = 0, last_dt = 0, theta_last = 1.0, dtb[3] = {};
+    bool gather = false;  // without the upwind operator: a row has more entries than it holds
 };
 
 }  // namespace vag
@@ -1494,6 +1495,38 @@ vag_status vag_solve_pressure(vag_handle *h, vag_solve_info *info) {
 }
 
 namespace {
+// the upwind operator of `total` entries, after their counts and offsets
+void upwind_fill(vag_handle *h, int64_t total, int32_t nslice) {
+    const Symbolic &S = h->S;
+    hipStream_t s = h->stream;
+    if ((size_t)total > h->tcol.n) {
+        h->tcol.alloc((size_t)total + (size_t)total / 8, h->tr);
+        h->tcol16.alloc((size_t)total + (size_t)total / 8, h->tr);
+        h->tval.alloc((size_t)total + (size_t)total / 8, h->tr);
+    }
+    ensure(h->tbase, (size_t)std::max<int64_t>(nslice, 1), h->tr);
+    if (h->general)
+        launch_gen_upwind_fill(s, h->ginc(), h->Fall.p, h->well_src(), h->well_out(), h->phi_cell.p,
+                               h->phi_frac.p, h->phi_node.p, h->dt4.p, h->slice_ptr.p, h->tmeta.p, h->tcol.p,
+                               h->tval.p, h->tdiag.p);
+    else
+        launch_upwind_fill(s, S.nc, S.nf, S.nn, h->hex8.p, h->fmask.p, h->cell_frac.p, h->frac_cell.p,
+                           h->frac_nodes.p, h->dirichlet.p, h->node_cell_ptr.p, h->node_cell.p,
+                           h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p, h->F_cell_frac.p, h->F_frac.p,
+                           h->well_src(), h->well_out(), h->phi_cell.p, h->phi_frac.p, h->phi_node.p, h->dt4.p,
+                           h->slice_ptr.p, h->tmeta.p, h->tcol.p, h->tval.p, h->tdiag.p);
+    launch_upwind_pack(s, h->upwind(), h->tcol16.p, h->tbase.p);
+}
+// a step without the operator, dt from dt4[3]
+void gather_step(vag_handle *h, const double *dt4, double theta) {
+    const Symbolic &S = h->S;
+    launch_transport_gather(h->stream, S.nc, S.nf, S.nn, h->hex8.p, h->fmask.p, h->cell_frac.p, h->frac_cell.p,
+                            h->frac_nodes.p, h->dirichlet.p, h->node_cell_ptr.p, h->node_cell.p,
+                            h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p, h->F_cell_frac.p, h->F_frac.p,
+                            h->well_src(), h->well_out(), h->phi_cell.p, h->phi_frac.p, h->phi_node.p, dt4, theta,
+                            h->c_cur(), h->c_next());
+}
+
 // vag_transport up to its steps: CFL time step, the upwind operator, the
 // initial state (ev[5] .. ev[6] on the handle's stream)
 TransportPlan transport_prepare(vag_handle *h, int64_t n_steps, double t_final, const double *c0_cell,
@@ -1534,24 +1567,15 @@ TransportPlan transport_prepare(vag_handle *h, int64_t n_steps, double t_final, 
     const double dt = h->h_scal[3];
     double dtb[3] = {h->h_scal[0], h->h_scal[1], h->h_scal[2]};
     if (!(dt < INFINITY)) throw Error(VAG_ERR_ARG, "no control volume has an outflow: CFL bound is infinite");
-    if ((size_t)total > h->tcol.n) {
-        h->tcol.alloc((size_t)total + (size_t)total / 8, h->tr);
-        h->tcol16.alloc((size_t)total + (size_t)total / 8, h->tr);
-        h->tval.alloc((size_t)total + (size_t)total / 8, h->tr);
+    TransportPlan P;
+    if (h->max_degree > kUpwindEntries) {  // rare: the rows' counts decide
+        std::vector<int32_t> width((size_t)nslice);
+        VAG_HIP(hipMemcpyAsync(width.data(), h->slice_width.p, (size_t)nslice * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        VAG_HIP(hipStreamSynchronize(s));
+        P.gather = *std::max_element(width.begin(), width.end()) > kUpwindEntries;
     }
-    ensure(h->tbase, (size_t)std::max<int64_t>(nslice, 1), h->tr);
-    if (h->general)
-        launch_gen_upwind_fill(s, h->ginc(), h->Fall.p, h->well_src(), h->well_out(), h->phi_cell.p,
-                               h->phi_frac.p, h->phi_node.p, h->dt4.p, h->slice_ptr.p, h->tmeta.p, h->tcol.p,
-                               h->tval.p, h->tdiag.p);
-    else
-        launch_upwind_fill(s, S.nc, S.nf, S.nn, h->hex8.p, h->fmask.p, h->cell_frac.p, h->frac_cell.p,
-                           h->frac_nodes.p, h->dirichlet.p, h->node_cell_ptr.p, h->node_cell.p,
-                           h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p, h->F_cell_frac.p, h->F_frac.p,
-                           h->well_src(), h->well_out(), h->phi_cell.p, h->phi_frac.p, h->phi_node.p, h->dt4.p,
-                           h->slice_ptr.p, h->tmeta.p, h->tcol.p, h->tval.p, h->tdiag.p);
-    launch_upwind_pack(s, h->upwind(), h->tcol16.p, h->tbase.p);
-    h->have_op = true;
+    if (!P.gather) upwind_fill(h, total, nslice);
+    h->have_op = !P.gather;
     // initial state
     if (c0_cell || c0_frac || c0_node) {
         if (!c0_cell || !c0_node || (S.nf && !c0_frac))
@@ -1570,7 +1594,6 @@ TransportPlan transport_prepare(vag_handle *h, int64_t n_steps, double t_final, 
     launch_fill(s, 1, 1.0, h->cbuf0.p + nrow);  // the constant control volume
     launch_fill(s, 1, 1.0, h->cbuf1.p + nrow);
     h->have_c = true;
-    TransportPlan P;
     P.N = n_steps;
     P.dt = P.last_dt = dt;
     P.total = total;
@@ -1656,7 +1679,7 @@ vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const d
         ph.next("vag.transport_steps");
         hipStream_t s = h->stream;
         TransportHalo Q;
-        transport_halo(h, P.N, Q);
+        if (!P.gather) transport_halo(h, P.N, Q);
         int64_t k = 0;
         // whole steps (not the last one, which may be shortened)
         for (; Q.steps > 1 && k + Q.steps < P.N; k += Q.steps) {
@@ -1665,7 +1688,10 @@ vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const d
         }
         for (; k < P.N; ++k) {
             const double th = (k == P.N - 1) ? P.theta_last : 1.0;
-            launch_transport_step(s, h->upwind(), h->c_cur(), h->c_next(), th, (k & 1) != 0);
+            if (P.gather)
+                gather_step(h, h->dt4.p, th);
+            else
+                launch_transport_step(s, h->upwind(), h->c_cur(), h->c_next(), th, (k & 1) != 0);
             h->cur ^= 1;
         }
         VAG_HIP(hipEventRecord(h->ev[7], s));
@@ -1676,6 +1702,7 @@ vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const d
 
 // Served jobs: the steps of a job's transport run in launches shared with
 // other jobs (launch_transport_batch), driven by the server.
+bool vag_serving_batches(const vag_handle *h) { return h->max_degree <= kUpwindEntries; }
 vag_status vag_serving_transport_begin(vag_handle *h, int64_t n_steps, double t_final, int64_t *N) {
     if (!h || !N) return VAG_ERR_ARG;
     return guard(h, [&] {
@@ -1840,11 +1867,7 @@ vag_status vag_transport_noalloc(vag_handle *h, int64_t n_steps, double t_final,
             if (op)
                 launch_transport_step(s, o.T, h->c_cur(), h->c_next(), th, (k & 1) != 0);
             else
-                launch_transport_gather(s, S.nc, S.nf, S.nn, h->hex8.p, h->fmask.p, h->cell_frac.p, h->frac_cell.p,
-                                        h->frac_nodes.p, h->dirichlet.p, h->node_cell_ptr.p, h->node_cell.p,
-                                        h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p, h->F_cell_frac.p,
-                                        h->F_frac.p, h->well_src(), h->well_out(), h->phi_cell.p, h->phi_frac.p,
-                                        h->phi_node.p, dt4, th, h->c_cur(), h->c_next());
+                gather_step(h, dt4, th);
             h->cur ^= 1;
         }
         const double *c = h->c_cur();

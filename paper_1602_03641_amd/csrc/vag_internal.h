@@ -623,6 +623,8 @@ void launch_transport_batch(hipStream_t s, TransportBatch &B);
 // first step and event 7 after its last, on the stream it launches on; end
 // waits for event 7 and reports.
 extern "C" {
+// whether the handle's steps can share launches (its rows fit in the operator)
+bool vag_serving_batches(const vag_handle *h);
 vag_status vag_serving_transport_begin(vag_handle *h, int64_t n_steps, double t_final, int64_t *N);
 void vag_serving_transport_job(vag_handle *h, int64_t k, vag::TransportJob *J);
 hipEvent_t vag_serving_event(vag_handle *h, int i);

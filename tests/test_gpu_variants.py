@@ -501,3 +501,36 @@ def test_noalloc_at_wide_nodes(sectors):
         for k, v in vag.to_numpy(got).items():
             assert np.abs(v - ref[k]).max(initial=0.0) <= 1e-10, (n, k)
     h.close()
+
+
+@pytest.mark.parametrize("sectors", [200, 300])
+def test_transport_at_wide_nodes(sectors):
+    """The same nodes in vag_transport and through the serving loop: rows of more
+    than 255 entries are gathered; calls of many steps, a last step shortened."""
+    from paper_1602_03641_amd import vag
+    p = _star(sectors, 2, False)
+    opt = dict(rtol=1e-10, precond=vag.VAG_PC_JACOBI, max_iter=20000, cfl=p.cfl)
+    h, _ = _handle(p, **opt)
+    flux, phi = vag.to_numpy(h.fluxes()), vag.to_numpy(h.porous_volumes())
+    rng = np.random.default_rng(53)
+    c0 = {k: rng.uniform(0, 1, n) for k, n in (("c_cell", p.n_cells), ("c_frac", p.n_frac), ("c_node", p.n_nodes))}
+    c0o = dict(c0, c_node=np.where(p.dirichlet == 1, p.c_bar, c0["c_node"]))
+    for n, part in ((1, 0.0), (50, 0.0), (50, 0.25)):
+        print("sectors", sectors, "steps", n, part, flush=True)
+        dt = h.transport(n_steps=1, c0=c0)["dt"]
+        info = h.transport(n_steps=n, c0=c0) if not part else h.transport(t_final=(n - 1 + part) * dt, c0=c0)
+        assert info["n_steps"] == n
+        ref = oracle.transport(p, flux, phi, info["dt"], n, last_dt=info["last_dt"] if part else 0.0, c0=c0o)
+        for k, v in vag.to_numpy(h.concentration()).items():
+            assert np.abs(v - ref[k]).max(initial=0.0) <= 1e-10, (n, k)
+    # a job starts from zero
+    h.solve_pressure()
+    h.transport(n_steps=20)
+    lone = vag.to_numpy(h.concentration())
+    h.close()
+    srv = vag.Server(n_workers=1)
+    res = srv.wait(srv.submit(p, n_steps=20, **opt))
+    srv.close()
+    assert res["status"] == 0
+    for k, v in lone.items():
+        assert np.array_equal(res[k], v), k
