@@ -182,6 +182,7 @@ struct vag_handle {
     DBuf<int4> tbase;
     DBuf<uint16_t> tcol16;
     int max_degree = 0;  // hexahedra: the most fluxes of a node
+    HaloTries halo_tries;
     DBuf<uint16_t> tmeta;
     DBuf<int64_t> slice_ptr;
     DBuf<int32_t> xsplit;  // [18] the XCDs' runs of slices of the upwind operator (xlo, then ylo)
@@ -1642,7 +1643,8 @@ struct TransportHalo {
 };
 void transport_halo(vag_handle *h, int64_t steps, TransportHalo &Q) {
     const UpwindOp T = h->upwind();
-    if (h->general || T.nrow > kHaloMaxRows || steps < halo_steps(T.nrow)) return;
+    if (h->general || T.nrow > kHaloMaxRows || steps < halo_steps(T.nrow) || !h->halo_tries.due()) return;
+    h->halo_tries.ended(false);  // until it has fitted
     hipStream_t s = h->stream;
     const Symbolic &S = h->S;
     const int64_t n = T.nrow, np = std::min<int64_t>(256, (n + 63) / 64);
@@ -1666,7 +1668,9 @@ void transport_halo(vag_handle *h, int64_t steps, TransportHalo &Q) {
     launch_halo_build(s, T, S.nc, S.nf, S.nn, h->frac_cell.p, h->node_cell_ptr.p, h->node_cell.p, R, Q.H, cut);
     VAG_HIP(hipMemcpyAsync(&out, cut, sizeof(int), hipMemcpyDeviceToHost, s));
     VAG_HIP(hipStreamSynchronize(s));
-    if (kHaloSteps - out >= 2) Q.steps = kHaloSteps - out;
+    if (kHaloSteps - out < 2) return;
+    Q.steps = kHaloSteps - out;
+    h->halo_tries.ended(true);
 }
 }  // namespace
 

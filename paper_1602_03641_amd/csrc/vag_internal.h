@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <memory>
 #include <stdexcept>
@@ -590,6 +591,18 @@ struct HaloParts {
     uint16_t *len;   // [part][kHaloRows]
     uint16_t *col;   // [part][kHaloWidth][kHaloRows] local columns (kHaloRows: the constant control volume)
     double *val, *diag;
+};
+// Which calls of a handle try the parts.  A mesh whose parts do not fit (cells
+// numbered without order, whose parts reach everywhere; rows wider than
+// kHaloWidth; no memory) pays for the attempt, about what 30 steps take, and goes
+// step by step: after an attempt that failed the next 1, 3, 7, ... kMost calls do
+// without one, so that such a handle loses under 1 % in the long run and one
+// whose fluxes come to fit is found again.
+struct HaloTries {
+    static constexpr int kMost = 255;
+    int gap = 0, skip = 0;
+    bool due() { return skip == 0 || (--skip, false); }
+    void ended(bool fits) { skip = gap = fits ? 0 : std::min(2 * gap + 1, kMost); }
 };
 // cut[0] is 0 before; after it the steps of a launch are kHaloSteps - cut[0]
 void launch_halo_build(hipStream_t s, const UpwindOp &T, int32_t nc, int32_t nf, int32_t nn, const int32_t *frac_cell,

@@ -71,3 +71,42 @@ def test_estimates_admit_known_jobs():
         o = vag.default_options(**kw)
         got = vag.load().vag_estimate_footprint((n + 1) ** 3, n ** 3, nf, C.byref(o))
         assert 0 < got <= most, (n, kw, got)
+
+
+def _host_program(tmp_path, text, *args):
+    """Compiles text against the library's headers (host code only) and returns
+    what it prints."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("no compiler")
+    src, exe = tmp_path / "program.cpp", str(tmp_path / "program")
+    src.write_text(text)
+    inc = ["-I" + CSRC, "-I" + os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include")]
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-std=c++17", "-O0", "-w", *inc, str(src), *args, "-o",
+                    exe], check=True, capture_output=True)
+    return subprocess.run([exe], capture_output=True, text=True, check=True).stdout
+
+
+def test_parts_are_not_tried_in_vain(tmp_path):
+    """Calls that try to take their steps in parts of the mesh: every call of a
+    handle whose parts fit; of one whose parts never fit, fewer and fewer, though
+    never none; and every call again once they fit."""
+    out = _host_program(tmp_path, """
+#include <cstdio>
+#include "vag_internal.h"
+int main() {
+    vag::HaloTries t;
+    auto calls = [&](int n, bool fits) {
+        int tried = 0;
+        for (int k = 0; k < n; ++k)
+            if (t.due()) ++tried, t.ended(false), fits ? t.ended(true) : void();
+        return tried;
+    };
+    const int a = calls(50, true), b = calls(2, false), c = calls(998, false), d = calls(9000, false);
+    std::printf("%d %d %d %d %d\\n", a, b, c, d, calls(256 + 100, true));
+}
+""")
+    always, first, thousand, more, again = map(int, out.split())
+    assert always == 50 and first == 1 and thousand <= 10
+    assert 9000 // 256 <= more <= 9000 // 256 + 1
+    assert again >= 100
