@@ -400,7 +400,7 @@ __device__ inline void cl_placed(const uint32_t *T, int32_t C, int lane, F f) {
 // it owns over all contributions in order.
 constexpr int kApCand = 256, kApHash = 256, kApCols = 128;
 template <bool FILL>
-__global__ __launch_bounds__(64) void cl_ap_wave_kernel(Sell<double> A, const int32_t *__restrict__ pptr,
+__global__ __launch_bounds__(64) void cl_ap_wave_kernel(int32_t r0, Sell<double> A, const int32_t *__restrict__ pptr,
                                                         const int32_t *__restrict__ pcol,
                                                         const double *__restrict__ pval, int32_t *__restrict__ big,
                                                         int *__restrict__ nbig, int32_t *__restrict__ rowlen,
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64) void cl_ap_wave_kernel(Sell<double> A, const in
     __shared__ uint8_t hs[FILL ? kApCand : 1];
     __shared__ uint32_t T[FILL ? kApCand : 1];
     __shared__ int32_t off[65], y0[64];
-    const int32_t i = blockIdx.x;
+    const int32_t i = r0 + (int32_t)blockIdx.x;
     const int lane = threadIdx.x;
     if (FILL && big[i]) return;
     for (int k = lane; k < kApHash; k += 64) {
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(64) void cl_ap_wave_kernel(Sell<double> A, const in
 // distinct columns (at most 93 on those meshes).
 constexpr int kRapHash = 512, kRapCols = 256;
 template <bool FILL>
-__global__ __launch_bounds__(64) void cl_rap_wave_kernel(const int32_t *__restrict__ xptr,
+__global__ __launch_bounds__(64) void cl_rap_wave_kernel(int32_t r0, const int32_t *__restrict__ xptr,
                                                          const int32_t *__restrict__ xcol,
                                                          const double *__restrict__ xval,
                                                          const int32_t *__restrict__ yptr,
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(64) void cl_rap_wave_kernel(const int32_t *__restri
     __shared__ double sums[FILL ? kRapHash : 1], xs[64];
     __shared__ uint16_t slot[FILL ? kRapCols : 1];
     __shared__ int32_t lo[64], hi[64];
-    const int32_t c = blockIdx.x;
+    const int32_t c = r0 + (int32_t)blockIdx.x;
     const int lane = threadIdx.x;
     if (FILL && big[c]) return;
     for (int k = lane; k < kRapHash; k += 64) {
@@ -824,15 +824,20 @@ void cl_launch_product_rows(hipStream_t s, int32_t n, const Sell<double> *AX, co
                             const double *yval, int32_t *big, int *nbig, bool fill, int32_t *rowlen,
                             const int64_t *optr, int32_t *ocol, double *oval) {
     if (n <= 0) return;
+    // a launch has fewer than 2^32 threads
+    constexpr int32_t kRows = 1 << 25;
 #define CL_ROWS(kern, ...)                                                                                   \
     do {                                                                                                     \
-        if (fill)                                                                                            \
-            hipLaunchKernelGGL((kern<true>), dim3(n), dim3(64), 0, s, __VA_ARGS__, yptr, ycol, yval, big, nbig, \
-                               rowlen, optr, ocol, oval);                                                    \
-        else                                                                                                 \
-            hipLaunchKernelGGL((kern<false>), dim3(n), dim3(64), 0, s, __VA_ARGS__, yptr, ycol, yval, big, nbig, \
-                               rowlen, optr, ocol, oval);                                                    \
-        VAG_HIP(hipGetLastError());                                                                          \
+        for (int32_t r0 = 0; r0 < n; r0 += std::min(kRows, n - r0)) {                                        \
+            const dim3 grid((unsigned)std::min(kRows, n - r0));                                              \
+            if (fill)                                                                                        \
+                hipLaunchKernelGGL((kern<true>), grid, dim3(64), 0, s, r0, __VA_ARGS__, yptr, ycol, yval, big, \
+                                   nbig, rowlen, optr, ocol, oval);                                          \
+            else                                                                                             \
+                hipLaunchKernelGGL((kern<false>), grid, dim3(64), 0, s, r0, __VA_ARGS__, yptr, ycol, yval, big, \
+                                   nbig, rowlen, optr, ocol, oval);                                          \
+            VAG_HIP(hipGetLastError());                                                                      \
+        }                                                                                                    \
     } while (0)
     if (AX)
         CL_ROWS(cl_ap_wave_kernel, *AX);

@@ -110,3 +110,50 @@ int main() {
     assert always == 50 and first == 1 and thousand <= 10
     assert 9000 // 256 <= more <= 9000 // 256 + 1
     assert again >= 100
+
+
+def test_launches_of_many_rows(tmp_path):
+    """The classical products take a wavefront per row.  A launch has fewer than
+    2^32 threads, so rows from 2^26 on need several: every row once, none beyond
+    (the library's launcher, with the runtime's launch replaced by a count)."""
+    lib = os.path.join(os.path.dirname(CSRC), "libvag.so")
+    if not os.path.exists(lib):
+        pytest.skip("the library is not built")
+    out = _host_program(tmp_path, """
+#include <cstdio>
+#include <cstdint>
+#include "amg.h"
+static dim3 grid, block;
+static long long rows, next_row, bad;
+extern "C" hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t, hipStream_t) {
+    grid = g;
+    block = b;
+    return hipSuccess;
+}
+extern "C" hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *l, hipStream_t *s) {
+    *g = grid;
+    *b = block;
+    *l = 0;
+    *s = nullptr;
+    return hipSuccess;
+}
+extern "C" hipError_t hipLaunchKernel(const void *, dim3 g, dim3 b, void **args, size_t, hipStream_t) {
+    bad += (unsigned long long)g.x * b.x >= 1ull << 32 || *(int32_t *)args[0] != next_row;
+    next_row += g.x;
+    rows += (long long)g.x * g.y * g.z;
+    return hipSuccess;
+}
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+int main() {
+    vag::Sell<double> A{};
+    for (int n : {1, 1 << 20, (1 << 25) + 1, 1 << 26, (1 << 30) - 1})
+        for (int k = 0; k < 4; ++k) {
+            rows = next_row = 0;
+            vag::cl_launch_product_rows(nullptr, n, k & 1 ? &A : nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                        nullptr, nullptr, nullptr, k & 2, nullptr, nullptr, nullptr, nullptr);
+            bad += rows != n;
+        }
+    std::printf("%lld\\n", bad);
+}
+""", "-rdynamic", "-x", "none", lib, "-Wl,-rpath," + os.path.dirname(lib))
+    assert int(out) == 0
