@@ -2,6 +2,7 @@
 #pragma once
 
 #include <memory>
+#include <thread>
 #include <vector>
 
 #include "vag_internal.h"
@@ -25,10 +26,15 @@ struct CoarsenInit {
     int nundecided = kMisRounds * kCntSlots * kCntStride;
 };
 // Until the device says in pinned memory that it has begun round `least`, or
-// that there are no more (a value past `last`), or nothing runs any more.
+// that there are no more (a value past `last`), or nothing runs any more.  The
+// core goes to any thread that wants it (the other workers of a server have
+// meshes to sort on it) about every microsecond.
 inline void poll_rounds(hipStream_t s, volatile int *started, int least, int last) {
     for (int spin = 0; *started < least && *started <= last; ++spin)
-        if ((spin & 1023) == 1023 && hipStreamQuery(s) != hipErrorNotReady) break;
+        if ((spin & 1023) == 1023) {
+            if (hipStreamQuery(s) != hipErrorNotReady) break;
+            std::this_thread::yield();
+        }
 }
 // roots of the coarsening (flag); scol: a stored-size scratch array; progress:
 // pinned host memory

@@ -157,3 +157,28 @@ int main() {
 }
 """, "-rdynamic", "-x", "none", lib, "-Wl,-rpath," + os.path.dirname(lib))
     assert int(out) == 0
+
+
+def test_polls_give_the_core_away(tmp_path):
+    """A worker that waits for the device's rounds lets other threads have its
+    core, and ends when the device has got there, or has nothing more to run."""
+    out = _host_program(tmp_path, """
+#include <cstdio>
+#include "amg.h"
+static int yields, queries, ends;
+static volatile int started;
+extern "C" int sched_yield() { return ++yields, 0; }
+extern "C" hipError_t hipStreamQuery(hipStream_t) {
+    if (++queries == 100) ends ? (void)0 : (void)(started = 5);
+    return ends && queries > 100 ? hipSuccess : hipErrorNotReady;
+}
+int main() {
+    for (ends = 0; ends < 2; ++ends) {
+        yields = queries = started = 0;
+        vag::poll_rounds(nullptr, &started, 3, 48);
+        std::printf("%d %d %d\\n", yields, queries, started);
+    }
+}
+""", "-rdynamic")
+    begun, over = (tuple(map(int, line.split())) for line in out.splitlines())
+    assert begun == (100, 100, 5) and over == (100, 101, 0)
