@@ -1246,7 +1246,7 @@ __global__ __launch_bounds__(kAT) void vc_sweep_kernel(Sell<V> A, const X *__res
         out[i] = y[i] + dinv[i] * (b[i] - s);
     }
 }
-// (levels of more than kSmallRows rows)
+// (levels of more than kSplitMaxRows rows)
 template <class V, class X>
 __global__ __launch_bounds__(kKrylovThreads) void vc_sweep_rz_kernel(Sell<V> A, const X *__restrict__ dinv,
                                                                      const X *__restrict__ b, const X *__restrict__ y,
@@ -1499,7 +1499,7 @@ __global__ __launch_bounds__(kAT) void kc_combine_kernel(int32_t n, KcE<X> E, X 
 }
 
 // ---------------------------------------------------------------------------
-// CG around a finest level of at most kSmallRows rows: fewer launches.
+// CG around a finest level of at most kSplitMaxRows rows: fewer launches.
 // There an iteration is bound by its launches and by each kernel's one chain of
 // loads.  Five kernels and 26 us of them per two-level iteration at 1089 rows
 // (product, residual and sweep alone were 10 us each); a time step on 10^3

@@ -376,7 +376,7 @@ void Amg::cycle(hipStream_t s, int l, const X *b, X *out, const PcgState *st, bo
         amg_launch_restrict<X>(s, cv.n, lv.mptr.p, lv.mrows.p, r, bc, coarse_x ? dinv_c : nullptr,
                                coarse_x ? xc : nullptr, st);
         if constexpr (sizeof(X) == 8) {
-            if (rz && lv.n <= kSmallRows) {
+            if (rz && lv.n <= kSplitMaxRows) {
                 const bool two = coarse<V, X>(s, l + 1, bc, ec, st, coarse_x, true);
                 amg_launch_post_rz<V, X>(s, A, dinv, b, xa, lv.agg.p, two ? cv.kc_c.p : ec, two ? cv.kc_d.p : nullptr,
                                          cv.kc_parts.p, cv.n, out, rz, zq_, zq_ ? qv_ : nullptr, st);

@@ -196,19 +196,20 @@ __global__ __launch_bounds__(kT) void bcg_update_kernel(int32_t n, int k, const 
 
 }  // namespace
 
-int bcg_grid(int64_t n) { return krylov_shape(n).G; }
+static KrylovShape bcg_shape(int64_t n) { return krylov_shape(n, kSplitMaxBcg); }
+int bcg_grid(int64_t n) { return bcg_shape(n).G; }
 static BcgParts bcg_parts(double *base, int64_t n) {
-    const KrylovShape k = krylov_shape(n);
+    const KrylovShape k = bcg_shape(n);
     return BcgParts{base, k.G, k.split};
 }
 
 #define BLAUNCH(n, kern, ...)                                                                                \
     do {                                                                                                     \
-        hipLaunchKernelGGL(kern, dim3(krylov_shape(n).vec_blocks), dim3(kT), 0, s, __VA_ARGS__);             \
+        hipLaunchKernelGGL(kern, dim3(bcg_shape(n).vec_blocks), dim3(kT), 0, s, __VA_ARGS__);                \
         VAG_HIP(hipGetLastError());                                                                          \
     } while (0)
 #define BROWS(n, kern, ...) \
-    VAG_ROWS_LAUNCH(n, hipLaunchKernelGGL(kern<SPLIT>, dim3(ks.row_blocks), dim3(threads), 0, s, __VA_ARGS__))
+    VAG_ROWS_LAUNCH(bcg_shape(n), hipLaunchKernelGGL(kern<SPLIT>, dim3(ks.row_blocks), dim3(threads), 0, s, __VA_ARGS__))
 
 void launch_bcg_init(hipStream_t s, Sell<double> A, bool zero_x, int k0, const double *b, double *x, double *r,
                      double *rhat, double *parts) {

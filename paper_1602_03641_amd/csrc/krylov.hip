@@ -23,9 +23,9 @@ namespace vag {
 
 constexpr int kThreads = kKrylovThreads;  // of the kernels without partials
 
-KrylovShape krylov_shape(int64_t n) {
+KrylovShape krylov_shape(int64_t n, int64_t split_rows) {
     const int b = (int)reduce_grid(n, kThreads);
-    return n <= kSplitMaxRows ? KrylovShape{16 * b, true, 16 * b, b} : KrylovShape{b, false, b, b};
+    return n <= split_rows ? KrylovShape{16 * b, true, 16 * b, b} : KrylovShape{b, false, b, b};
 }
 int pcg_grid(int64_t n) { return krylov_shape(n).G; }
 PcgParts pcg_parts(double *base, int64_t n) {
@@ -357,7 +357,7 @@ void launch_pcg_direction_spmv(hipStream_t s, Sell<double> A, int k, int k0, con
 }
 template <class V, class T>
 void launch_pcg_spmv(hipStream_t s, Sell<V> A, int k, const T *p, T *q, PcgParts P, const PcgState *st) {
-    VAG_ROWS_LAUNCH(A.n, hipLaunchKernelGGL((pcg_spmv_kernel<SPLIT, V, T>), dim3(ks.row_blocks), dim3(threads), 0, s, A,
+    VAG_ROWS_LAUNCH(krylov_shape(A.n), hipLaunchKernelGGL((pcg_spmv_kernel<SPLIT, V, T>), dim3(ks.row_blocks), dim3(threads), 0, s, A,
                                             k, p, q, P, st));
 }
 void launch_pcg_update(hipStream_t s, int32_t n, int k, double *x, double *r, double *z, const double *p,

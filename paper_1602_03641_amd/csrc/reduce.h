@@ -123,9 +123,10 @@ __device__ inline unsigned xcd_unblock(unsigned b, unsigned nb) {
 // Totals of NV arrays of G slice sums (see KrylovShape), in every thread: the
 // 16 slices of 1024 rows one after the other, then the shuffle tree and the
 // wavefront totals as block_reduce and sum_parts combine blocks of 1024 rows.
+static_assert(kSplitMaxRows <= kSplitMaxBcg, "the most slices that slice_sums adds up");
 template <int NT, int NV, class P>
 __device__ inline void slice_sums(P p, int G, double (&v)[NV]) {
-    __shared__ double lds[NV][(kSplitMaxRows / kSliceRows + 1023) / 1024];
+    __shared__ double lds[NV][(kSplitMaxBcg / kSliceRows + 1023) / 1024];
     const int lane = threadIdx.x & 63, nc = (G + 1023) / 1024;
     for (int c = threadIdx.x >> 6; c < nc; c += NT / 64) {
         const int at = (c * 64 + lane) * 16;

@@ -200,10 +200,10 @@ __device__ inline void split_rows(int32_t n, int G, int32_t i, Acc s, Row row, P
 }
 
 // Evaluates call (a launch of some kern<SPLIT, ...> over matrix rows, blocks of
-// `threads`) in the shape ks of n rows
-#define VAG_ROWS_LAUNCH(n, call)                \
+// `threads`) in the given shape
+#define VAG_ROWS_LAUNCH(shape, call)            \
     do {                                        \
-        const KrylovShape ks = krylov_shape(n); \
+        const KrylovShape ks = shape;           \
         if (ks.split) {                         \
             constexpr bool SPLIT = true;        \
             constexpr int threads = kSplitThreads; \

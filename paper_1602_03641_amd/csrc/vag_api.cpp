@@ -2213,7 +2213,7 @@ size_t vag_estimate_footprint(int64_t nn, int64_t nc, int64_t nf, const vag_opti
     const double Nn = (double)nn, Nc = (double)nc, Nf = (double)nf, Nx = Nn + Nf;
     // A job whose estimate exceeds the server's budget is refused, so the terms
     // are not raised for small buffers that the slack below covers: second
-    // copies of two CG vectors (16 bytes per unknown up to 131072), slots of the
+    // copies of two CG vectors (16 bytes per unknown up to 81920), slots of the
     // fracture blocks (64 per face), transport bases (4 bytes per row), the second
     // half of the elimination workspace (1 MB at most).
     // system entries: at most 27 per node row plus the couplings of the

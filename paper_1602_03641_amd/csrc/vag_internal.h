@@ -104,9 +104,14 @@ constexpr int kKrylovThreads = 1024;
 // The line: below it one lane per row leaves most of the 256 CUs without a
 // block and every kernel waits for one row's chain of loads (product 10 us at
 // 1089 and at 45 k rows; 6.3 and 10.3 us with 4 lanes, the direction included);
-// from 262 k rows the product runs at the last-level cache's 5 TB/s either way,
-// and fusing would gather two vectors instead of one.
-constexpr int64_t kSplitMaxRows = 131072;
+// above, the vectors that the fused kernels gather, two or three instead of one,
+// cost more than the launches they save.  Whole solves, ms with 4 lanes and
+// the fused kernels / with one: Jacobi CG 65 k rows 6.14 / 6.22, 81 k 7.20 /
+// 6.71, 99 k 9.08 / 7.36, 120 k 14.9 / 10.7; CG with the aggregation hierarchy
+// 3.83 / 3.96, 4.02 / 4.03, 4.46 / 4.21, 4.64 / 4.23.  BiCGStab's kernels are not
+// fused, only their lanes change (Jacobi 83 k 19.1 / 20.7, 93 k 17.8 / 17.9, 99 k
+// 18.9 / 18.8, 120 k 25.4 / 24.0): their line is kSplitMaxBcg.
+constexpr int64_t kSplitMaxRows = 81920, kSplitMaxBcg = 98304;
 constexpr int kSplitThreads = 256;
 
 struct KrylovShape {
@@ -115,7 +120,7 @@ struct KrylovShape {
     int row_blocks;  // in the kernels over matrix rows
     int vec_blocks;  // of kKrylovThreads, in the kernels over vectors
 };
-KrylovShape krylov_shape(int64_t n);
+KrylovShape krylov_shape(int64_t n, int64_t split_rows = kSplitMaxRows);
 
 // ---------------------------------------------------------------------------
 // device buffer

@@ -534,3 +534,12 @@ def test_transport_at_wide_nodes(sectors):
     assert res["status"] == 0
     for k, v in lone.items():
         assert np.array_equal(res[k], v), k
+
+
+@pytest.mark.parametrize("dims", [(43, 43, 43), (43, 44, 43)])
+@pytest.mark.parametrize("opt", ["cg", "cg mixed", "cg V", "jacobi", "bicgstab"])
+def test_krylov_rows_at_the_line(dims, opt):
+    """Systems on both sides of 81920 unknowns: the fused kernels with four lanes
+    per row, and one lane per row around a finest level whose coarse levels keep
+    theirs.  Tolerance and bits as in test_krylov_rows_per_block."""
+    test_krylov_rows_per_block(dims, opt)

@@ -182,3 +182,21 @@ int main() {
 """, "-rdynamic")
     begun, over = (tuple(map(int, line.split())) for line in out.splitlines())
     assert begun == (100, 100, 5) and over == (100, 101, 0)
+
+
+def test_krylov_shape_choice(tmp_path):
+    """Where the Krylov kernels go from four lanes per row to one: (unknowns, us
+    of a solve with four, with one) of Jacobi CG and of CG with the aggregation
+    hierarchy, the sizes at which both agree."""
+    lib = os.path.join(os.path.dirname(CSRC), "libvag.so")
+    if not os.path.exists(lib):
+        pytest.skip("the library is not built")
+    measured = [(22707, 3396, 5274), (22707, 1911, 2380), (47915, 5789, 7585), (47915, 3386, 3815), (65559, 6137, 6219),
+                (65559, 3831, 3960), (99405, 9083, 7358), (99405, 4460, 4211), (120000, 14878, 10668), (120000, 4635, 4229)]
+    out = _host_program(tmp_path, """
+#include <cstdio>
+#include "vag_internal.h"
+int main() { for (int n : {%s}) std::printf("%%d ", (int)vag::krylov_shape(n).split); }
+""" % ",".join(str(m[0]) for m in measured), "-x", "none", lib, "-Wl,-rpath," + os.path.dirname(lib))
+    for m, g in zip(measured, out.split(), strict=True):
+        assert (g == "1") == (m[1] < m[2]), m
