@@ -267,6 +267,8 @@ __global__ __launch_bounds__(128) void node_pos_kernel(AsmArgs g, uint16_t *__re
     const int32_t s = g.unk_node[r];
     const int64_t base = g.sell_ptr[r >> 6] + (r & 63);
     const int32_t len = g.row_len[r];
+    if (g.node_cell_ptr[s + 1] - g.node_cell_ptr[s] + g.node_frac_ptr[s + 1] - g.node_frac_ptr[s] > kUpwindEntries)
+        atomicMin(g.bad, kWideNode);
     const bool regs = len <= kPosRegs;
     int32_t a[kPosRegs];
 #pragma unroll

@@ -264,16 +264,6 @@ __global__ __launch_bounds__(kPT) void scan64_apply_kernel(int32_t n, int32_t nb
     if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = sums[nb];
 }
 
-// *most = the most fluxes of a node (its cells and fracture faces), 0 before
-__global__ __launch_bounds__(kPT) void node_degree_kernel(int32_t nn, const int32_t *__restrict__ ncp,
-                                                          const int32_t *__restrict__ nfp, int *most) {
-    const int32_t i = blockIdx.x * kPT + threadIdx.x;
-    int d = i < nn ? ncp[i + 1] - ncp[i] + nfp[i + 1] - nfp[i] : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) d = max(d, __shfl_xor(d, o, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(most, d);
-}
-
 // node -> (cell, slot) lists: counts, their scan, the entries K * 8 + a put
 // in place by atomic cursors, then every list sorted (ascending, as a pass
 // over the cells in order would give)
@@ -312,11 +302,6 @@ __global__ __launch_bounds__(kPT) void node_cell_sort_kernel(int32_t nn, const i
     }
 }
 
-void launch_node_degree(hipStream_t s, int32_t nn, const int32_t *ncp, const int32_t *nfp, int *most) {
-    if (nn <= 0) return;
-    hipLaunchKernelGGL(node_degree_kernel, dim3((unsigned)((nn + kPT - 1) / kPT)), dim3(kPT), 0, s, nn, ncp, nfp, most);
-    VAG_HIP(hipGetLastError());
-}
 void launch_node_cell(hipStream_t s, int32_t nn, int64_t nc, const int32_t *hex8, int32_t *ptr, int32_t *cells,
                       int32_t *work) {
     const int64_t n8 = 8 * nc;

@@ -181,7 +181,7 @@ struct vag_handle {
     DBuf<int32_t> slice_width, slice_nnz, tcol;
     DBuf<int4> tbase;
     DBuf<uint16_t> tcol16;
-    int max_degree = 0;  // hexahedra: the most fluxes of a node
+    bool wide_nodes = false;  // hexahedra: a node of more fluxes than a row of the upwind operator has entries
     HaloTries halo_tries;
     DBuf<uint16_t> tmeta;
     DBuf<int64_t> slice_ptr;
@@ -1164,13 +1164,12 @@ vag_status vag_create(const vag_mesh *mesh, const vag_fractures *frac, const vag
         launch_node_pos(h->stream, asm_args(h), h->node_pos.p);
         h->frac_pos.alloc(std::max<size_t>(32 * (size_t)nf, 1), h->tr);  // 8 slots per node_frac entry
         launch_frac_pos(h->stream, asm_args(h), S.nf, h->frac_pos.p);
-        VAG_HIP(hipMemsetAsync(h->coef_bad.p, 0, sizeof(int), h->stream));
-        launch_node_degree(h->stream, S.nn, h->node_cell_ptr.p, h->node_frac_ptr.p, h->coef_bad.p);
         int bad = 0;
         VAG_HIP(hipMemcpyAsync(&bad, h->bad.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-        VAG_HIP(hipMemcpyAsync(&h->max_degree, h->coef_bad.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
         VAG_HIP(hipStreamSynchronize(h->stream));
-        if (bad != 0x7f7f7f7f) throw Error(VAG_ERR_ARG, "internal: a group's node pair is missing from the pattern");
+        h->wide_nodes = bad == kWideNode;
+        if (bad != 0x7f7f7f7f && !h->wide_nodes)
+            throw Error(VAG_ERR_ARG, "internal: a group's node pair is missing from the pattern");
     });
     if (st != VAG_OK) {
         g_create_error = h->err;
@@ -1569,7 +1568,7 @@ TransportPlan transport_prepare(vag_handle *h, int64_t n_steps, double t_final, 
     double dtb[3] = {h->h_scal[0], h->h_scal[1], h->h_scal[2]};
     if (!(dt < INFINITY)) throw Error(VAG_ERR_ARG, "no control volume has an outflow: CFL bound is infinite");
     TransportPlan P;
-    if (h->max_degree > kUpwindEntries) {  // rare: the rows' counts decide
+    if (h->wide_nodes) {  // rare: the rows' counts decide
         std::vector<int32_t> width((size_t)nslice);
         VAG_HIP(hipMemcpyAsync(width.data(), h->slice_width.p, (size_t)nslice * sizeof(int32_t), hipMemcpyDeviceToHost, s));
         VAG_HIP(hipStreamSynchronize(s));
@@ -1706,7 +1705,7 @@ vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const d
 
 // Served jobs: the steps of a job's transport run in launches shared with
 // other jobs (launch_transport_batch), driven by the server.
-bool vag_serving_batches(const vag_handle *h) { return h->max_degree <= kUpwindEntries; }
+bool vag_serving_batches(const vag_handle *h) { return !h->wide_nodes; }
 vag_status vag_serving_transport_begin(vag_handle *h, int64_t n_steps, double t_final, int64_t *N) {
     if (!h || !N) return VAG_ERR_ARG;
     return guard(h, [&] {
@@ -1850,7 +1849,7 @@ vag_status vag_transport_noalloc(vag_handle *h, int64_t n_steps, double t_final,
             theta_last = last_dt / dt;
         }
         const NoallocOp o = noalloc_operator(h);
-        const bool op = o.fits && h->max_degree <= kUpwindEntries && N >= noalloc_op_steps(nrow);
+        const bool op = o.fits && !h->wide_nodes && N >= noalloc_op_steps(nrow);
         if (op) {
             launch_upwind_count(s, S.nc, S.nf, S.nn, h->fmask.p, h->cell_frac.p, h->frac_cell.p, h->dirichlet.p,
                                 h->node_cell_ptr.p, h->node_cell.p, h->node_frac_ptr.p, h->node_frac.p, h->F_cell.p,

@@ -386,8 +386,6 @@ struct PatArgs {
     const uint8_t *fmask;
     const int32_t *node_grp_ptr, *node_grp, *grp_nptr, *grp_node;
 };
-// *most (0 before) = the most fluxes of a node of a hexahedral mesh
-void launch_node_degree(hipStream_t s, int32_t nn, const int32_t *ncp, const int32_t *nfp, int *most);
 // node_cell_ptr (nn + 1) and node_cell (8 nc: K * 8 + a, ascending per node)
 // of a hexahedral mesh; work: nn + 2 (nn / 1024 + 2) ints
 void launch_node_cell(hipStream_t s, int32_t nn, int64_t nc, const int32_t *hex8, int32_t *ptr, int32_t *cells,
@@ -408,7 +406,10 @@ void launch_sell_fill(hipStream_t s, int32_t n, int64_t nslice, const int32_t *r
 // (both left as they were where none fails)
 void launch_check_coef(hipStream_t s, int32_t nc, const double *perm, int32_t nf, const double *fwidth,
                        const double *fperm, int *bad);
-// node_pos (see AsmArgs) for the rows of the free nodes, once per handle.
+// node_pos (see AsmArgs) for the rows of the free nodes, once per handle; *bad
+// is at most kWideNode where a free node has more fluxes than a row of the
+// upwind operator has entries.
+constexpr int kWideNode = 1;
 void launch_node_pos(hipStream_t s, const AsmArgs &g, uint16_t *node_pos);
 void launch_frac_pos(hipStream_t s, const AsmArgs &g, int32_t nf, uint16_t *frac_pos);
 // System positions of the node pairs of each eliminated group.
