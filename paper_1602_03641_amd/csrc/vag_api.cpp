@@ -1738,13 +1738,8 @@ namespace {
 // of local matrices: the next solve (or vag_set_fluxes) computes those again,
 // and nothing reads them in between.  Every flux pair gives one entry and a
 // well's injection one more, so the bounds of the sizes need no device read.
-// Building the operator pays from this many steps on.  Measured with wells,
-// gather / operator, whole call: 64^3 134 / 215 us for 1 step, 304 / 238 for 4,
-// 3158 / 742 for 64; 160^3 3162 / 2116 for 4; below 2^18 control volumes a
-// step is a launch either way (7 / 4 us): 16^3 130 / 148 us for 4 steps,
-// 209 / 191 for 16.  A mesh with nodes of more fluxes than a row of the
-// operator holds entries is gathered at any step count.
-int64_t noalloc_op_steps(int64_t nrow) { return nrow >= (1 << 18) ? 4 : 12; }
+// Building it pays from noalloc_op_steps on; a mesh with nodes of more fluxes
+// than its rows have entries is gathered at any step count.
 struct NoallocOp {
     int32_t *width, *nnz, *col;
     int4 *base;

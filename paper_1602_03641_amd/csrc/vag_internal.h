@@ -547,6 +547,15 @@ void launch_upwind_fill(hipStream_t s, int32_t nc, int32_t nf, int32_t nn, const
                         const double *phi_node,
                         const double *dt, const int64_t *slice_ptr, const uint16_t *meta, int32_t *tcol,
                         double *tval, double *tdiag);
+// From this many steps on a call of vag_transport_noalloc builds the operator.
+// Whole calls, us, gather / operator: 10^3 cells (2.3 k rows) 12 steps 134 / 134,
+// 14 147 / 141, 16 160 / 144; 16^3 (9 k) 12 123 / 136, 14 136 / 143, 16 150 / 147;
+// 24^3 (29 k) 12 128 / 132, 16 155 / 145; 32^3 (69 k) 8 105 / 118, 12 135 / 127; 40^3
+// (133 k) 4 87 / 107, 8 123 / 122, 10 140 / 132; 50^3 (258 k) 5 122 / 124, 6 137 /
+// 128; 54^3 (324 k) 4 120 / 133, 5 136 / 141, 6 152 / 145; 64^3 (537 k) 4 221 / 182; 128^3 (4.2 M) 4 1620 / 1023.
+constexpr int64_t noalloc_op_steps(int64_t nrow) {
+    return nrow < (1 << 16) ? 16 : nrow < (1 << 17) ? 12 : nrow < (3 << 16) ? 8 : nrow < (1 << 19) ? 6 : 4;
+}
 // Upwind operator: 64-row slices (rows sorted longest first, meta = source
 // lane << 8 | entry count per slot), entries packed by level (jagged
 // diagonals) from slice_ptr[slice]; 16-bit columns by tbase[slice] = {b0, b1,

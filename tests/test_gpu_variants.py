@@ -543,3 +543,26 @@ def test_krylov_rows_at_the_line(dims, opt):
     per row, and one lane per row around a finest level whose coarse levels keep
     theirs.  Tolerance and bits as in test_krylov_rows_per_block."""
     test_krylov_rows_per_block(dims, opt)
+
+
+@pytest.mark.parametrize("dims,steps", [((17, 16, 15), (15, 16, 17)), ((33, 32, 32), (11, 12)),
+                                        ((40, 41, 40), (7, 8)), ((66, 50, 48), (5, 6)), ((64, 65, 64), (3, 4))])
+def test_noalloc_where_the_operator_starts(dims, steps):
+    """The step counts from which the allocation-free transport builds the
+    operator, in each range of sizes: against the oracle's steps on the library's
+    fluxes, within the 1e-10 that its other tests take."""
+    from paper_1602_03641_amd import vag
+    p = synth.random_problem(dims, 54, n_patches=4, n_steps=0, ratios=(1e2, 1e3))
+    synth.add_wells(p, 4, n_inj=1, n_prod=1)
+    h, _ = _handle(p, rtol=1e-8, precond=vag.VAG_PC_AMG)
+    flux, phi = vag.to_numpy(h.fluxes()), vag.to_numpy(h.porous_volumes())
+    flux["well_rate"] = h.well_rates()
+    rng = np.random.default_rng(55)
+    c0 = {k: rng.uniform(0, 1, n) for k, n in (("c_cell", p.n_cells), ("c_frac", p.n_frac), ("c_node", p.n_nodes))}
+    c0o = dict(c0, c_node=np.where(p.dirichlet == 1, p.c_bar, c0["c_node"]))
+    for n in steps:
+        got, info = h.transport_noalloc(n_steps=n, c0=c0)
+        ref = oracle.transport(p, flux, phi, info["dt"], n, c0=c0o)
+        for k, v in vag.to_numpy(got).items():
+            assert np.abs(v - ref[k]).max(initial=0.0) <= 1e-10, (n, k)
+    h.close()

@@ -200,3 +200,27 @@ int main() { for (int n : {%s}) std::printf("%%d ", (int)vag::krylov_shape(n).sp
 """ % ",".join(str(m[0]) for m in measured), "-x", "none", lib, "-Wl,-rpath," + os.path.dirname(lib))
     for m, g in zip(measured, out.split(), strict=True):
         assert (g == "1") == (m[1] < m[2]), m
+
+
+def test_noalloc_operator_choice(tmp_path):
+    """The allocation-free transport builds the upwind operator where that was
+    measured to be faster: (cells a side, steps, us of a call with gathered
+    steps, with the operator), where they differ by over 2 %."""
+    measured = [(3, 10, 126, 130), (10, 8, 104, 123), (10, 16, 160, 144), (16, 8, 99, 121), (16, 12, 122, 137),
+                (16, 18, 163, 152), (24, 10, 115, 123), (24, 12, 128, 131.9), (24, 16, 155, 143), (32, 8, 106, 117),
+                (32, 12, 136, 127), (40, 4, 87, 107), (40, 10, 140, 132), (40, 12, 156, 141), (50, 4, 106, 118), (50, 6, 136, 130),
+                (54, 4, 119, 134), (54, 5, 136, 141), (54, 6, 151, 146), (64, 2, 141, 166), (64, 4, 220, 182),
+                (90, 4, 578, 385), (128, 4, 1623, 1030), (128, 8, 3030, 1225)]
+    out = _host_program(tmp_path, """
+#include <cstdio>
+#include "vag_internal.h"
+int main() {
+    const int m[][2] = {%s};
+    for (auto &r : m) {
+        const long n = r[0];
+        std::printf("%%d ", r[1] >= vag::noalloc_op_steps(n * n * n + (n + 1) * (n + 1) * (n + 1)));
+    }
+}
+""" % ",".join("{%d,%d}" % m[:2] for m in measured))
+    for m, g in zip(measured, out.split(), strict=True):
+        assert abs(m[2] - m[3]) > 0.02 * m[2] and (g == "1") == (m[3] < m[2]), m
