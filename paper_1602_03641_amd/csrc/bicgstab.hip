@@ -32,9 +32,9 @@ struct BcgParts {
     int G;
     bool slices;
     __device__ double *rho(int k) const { return base + (size_t)(k & 1) * G; }
-    __device__ double *rv() const { return base + (size_t)2 * G; }
-    __device__ double *ts() const { return base + (size_t)3 * G; }
-    __device__ double *tt() const { return base + (size_t)4 * G; }
+    __host__ __device__ double *rv() const { return base + (size_t)2 * G; }
+    __host__ __device__ double *ts() const { return base + (size_t)3 * G; }
+    __host__ __device__ double *tt() const { return base + (size_t)4 * G; }
     __device__ double *rr(int k) const { return base + (size_t)(5 + (k & 1)) * G; }
     __device__ double *ss() const { return base + (size_t)7 * G; }
 };
@@ -125,8 +125,10 @@ __global__ __launch_bounds__(kT) void bcg_direction_kernel(int32_t n, int k, int
     GSB(i, n) p[i] = r[i] + beta * (p[i] - omega * v[i]);
 }
 
-// y = A x with the partials of w . y into parts (and of y . y into parts2)
-template <bool SPLIT>
+// y = A x with the partials of w . y into parts (and of y . y into parts2).
+// LOCAL: each XCD takes a run of the rows; the partials go to the places of their
+// slices either way.
+template <bool SPLIT, bool LOCAL>
 __global__ __launch_bounds__(SPLIT ? kSplitThreads : kT) void bcg_spmv_dot_kernel(Sell<double> A, const double *__restrict__ x,
                                                           double *__restrict__ y, const double *__restrict__ w,
                                                           BcgParts P, double *__restrict__ parts,
@@ -140,9 +142,9 @@ __global__ __launch_bounds__(SPLIT ? kSplitThreads : kT) void bcg_spmv_dot_kerne
     };
     auto put = [&](int i) { return i ? parts2 : parts; };
     if constexpr (SPLIT) {
-        const int32_t i = split_row<kSplitThreads, false>();
+        const int32_t i = split_row<kSplitThreads, LOCAL>();
         const double s = lane_row(A, i, f).template sum<double, 1>([](double t) { return t; });
-        split_rows<kSplitThreads, 2, false>(A.n, P.G, i, s, row, put);
+        split_rows<kSplitThreads, 2, LOCAL, false>(A.n, P.G, i, s, row, put);
     } else {
         krylov_rows<kT, 2, false, double, double>(A, false, P.G, f, row, put);
     }
@@ -196,56 +198,52 @@ __global__ __launch_bounds__(kT) void bcg_update_kernel(int32_t n, int k, const 
 
 }  // namespace
 
-static KrylovShape bcg_shape(int64_t n) { return krylov_shape(n, kSplitMaxBcg); }
-int bcg_grid(int64_t n) { return bcg_shape(n).G; }
-static BcgParts bcg_parts(double *base, int64_t n) {
-    const KrylovShape k = bcg_shape(n);
-    return BcgParts{base, k.G, k.split};
-}
+static BcgParts bcg_parts(const BcgWork &W) { return BcgParts{W.parts, W.shape.G, W.shape.split}; }
 
-#define BLAUNCH(n, kern, ...)                                                                                \
+#define BLAUNCH(blocks, kern, ...)                                                                           \
     do {                                                                                                     \
-        hipLaunchKernelGGL(kern, dim3(bcg_shape(n).vec_blocks), dim3(kT), 0, s, __VA_ARGS__);                \
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kT), 0, s, __VA_ARGS__);                                 \
         VAG_HIP(hipGetLastError());                                                                          \
     } while (0)
-#define BROWS(n, kern, ...) \
-    VAG_ROWS_LAUNCH(bcg_shape(n), hipLaunchKernelGGL(kern<SPLIT>, dim3(ks.row_blocks), dim3(threads), 0, s, __VA_ARGS__))
+#define BROWS(kern, ...)                                                                                      \
+    VAG_ROWS_LAUNCH(W.shape, hipLaunchKernelGGL((W.local ? kern<SPLIT, SPLIT> : kern<SPLIT, false>),          \
+                                                dim3(ks.row_blocks), dim3(threads), 0, s, __VA_ARGS__))
 
 void launch_bcg_init(hipStream_t s, Sell<double> A, bool zero_x, int k0, const double *b, double *x, double *r,
-                     double *rhat, double *parts) {
-    const BcgParts P = bcg_parts(parts, A.n);
+                     double *rhat, const BcgWork &W) {
+    const BcgParts P = bcg_parts(W);
     if (zero_x)
-        BLAUNCH(A.n, bcg_init_zero_kernel, A.n, k0, b, x, r, rhat, P);
+        BLAUNCH(W.shape.vec_blocks, bcg_init_zero_kernel, A.n, k0, b, x, r, rhat, P);
     else
-        BLAUNCH(A.n, bcg_init_kernel, A, k0, b, x, r, rhat, P);
+        BLAUNCH(W.shape.vec_blocks, bcg_init_kernel, A, k0, b, x, r, rhat, P);
 }
-void launch_bcg_start(hipStream_t s, int32_t n, double *parts, PcgState *st, double rtol, int k0, int *host_done) {
-    BLAUNCH(1, bcg_start_kernel, bcg_parts(parts, n), st, rtol, k0, host_done);
+void launch_bcg_start(hipStream_t s, int32_t n, const BcgWork &W, PcgState *st, double rtol, int k0, int *host_done) {
+    BLAUNCH(1, bcg_start_kernel, bcg_parts(W), st, rtol, k0, host_done);
 }
 void launch_bcg_direction(hipStream_t s, int32_t n, int k, int k0, const double *r, double *p, const double *v,
-                          double *parts, PcgState *st, bool update) {
-    const BcgParts P = bcg_parts(parts, n);
-    BLAUNCH(n, bcg_direction_kernel, n, k, k0, r, p, v, P, st, update ? 1 : 0);
+                          const BcgWork &W, PcgState *st, bool update) {
+    const BcgParts P = bcg_parts(W);
+    BLAUNCH(W.shape.vec_blocks, bcg_direction_kernel, n, k, k0, r, p, v, P, st, update ? 1 : 0);
 }
 void launch_bcg_spmv_v(hipStream_t s, Sell<double> A, const double *phat, double *v, const double *rhat,
-                       double *parts, const PcgState *st) {
-    const BcgParts P = bcg_parts(parts, A.n);
-    BROWS(A.n, bcg_spmv_dot_kernel, A, phat, v, rhat, P, parts + (size_t)2 * P.G, (double *)nullptr, st);
+                       const BcgWork &W, const PcgState *st) {
+    const BcgParts P = bcg_parts(W);
+    BROWS(bcg_spmv_dot_kernel, A, phat, v, rhat, P, P.rv(), (double *)nullptr, st);
 }
-void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, double *sv, double *parts,
+void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, double *sv, const BcgWork &W,
                   const PcgState *st) {
-    const BcgParts P = bcg_parts(parts, n);
-    BLAUNCH(n, bcg_s_kernel, n, k, r, v, sv, P, st);
+    const BcgParts P = bcg_parts(W);
+    BLAUNCH(W.shape.vec_blocks, bcg_s_kernel, n, k, r, v, sv, P, st);
 }
-void launch_bcg_spmv_t(hipStream_t s, Sell<double> A, const double *shat, double *t, const double *sv, double *parts,
+void launch_bcg_spmv_t(hipStream_t s, Sell<double> A, const double *shat, double *t, const double *sv, const BcgWork &W,
                        const PcgState *st) {
-    const BcgParts P = bcg_parts(parts, A.n);
-    BROWS(A.n, bcg_spmv_dot_kernel, A, shat, t, sv, P, parts + (size_t)3 * P.G, parts + (size_t)4 * P.G, st);
+    const BcgParts P = bcg_parts(W);
+    BROWS(bcg_spmv_dot_kernel, A, shat, t, sv, P, P.ts(), P.tt(), st);
 }
 void launch_bcg_update(hipStream_t s, int32_t n, int k, const double *phat, const double *shat, const double *sv,
-                       const double *t, const double *rhat, double *x, double *r, double *parts, PcgState *st) {
-    const BcgParts P = bcg_parts(parts, n);
-    BLAUNCH(n, bcg_update_kernel, n, k, phat, shat, sv, t, rhat, x, r, P, st);
+                       const double *t, const double *rhat, double *x, double *r, const BcgWork &W, PcgState *st) {
+    const BcgParts P = bcg_parts(W);
+    BLAUNCH(W.shape.vec_blocks, bcg_update_kernel, n, k, phat, shat, sv, t, rhat, x, r, P, st);
 }
 
 }  // namespace vag

@@ -78,6 +78,7 @@ public:
     // st && st->done.
     void apply(hipStream_t s, const double *r, double *z, const PcgState *st) const;
     int levels() const { return nlev_; }
+    bool in_lds() const { return in_lds_; }  // the solve stages its blocks in LDS
     int64_t entries() const { return nent_; }
 
 private:

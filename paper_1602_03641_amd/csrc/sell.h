@@ -178,7 +178,7 @@ __device__ inline int32_t split_row() {
     const int64_t blk = XCD ? xcd_block() : blockIdx.x;
     return (int32_t)(blk * (NT / kChains) + (threadIdx.x >> 6) * kSplitRows + (threadIdx.x & 63) % kSplitRows);
 }
-template <int NT, int NV, bool XCD, class Acc, class Row, class P>
+template <int NT, int NV, bool XCD, bool PLACE = XCD, class Acc, class Row, class P>
 __device__ inline void split_rows(int32_t n, int G, int32_t i, Acc s, Row row, P p) {
     __shared__ double share[NV][NT / kChains];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -195,7 +195,7 @@ __device__ inline void split_rows(int32_t n, int G, int32_t i, Acc s, Row row, P
 #pragma unroll
         for (int k = 0; k < NV; ++k) v[k] = share[k][threadIdx.x];
         const int64_t blk = XCD ? xcd_block() : blockIdx.x;
-        krylov_put<NT, NV>(true, p, slice_place<XCD>((int)(blk * (NT / kChains / 64) + wave), G), v);
+        krylov_put<NT, NV>(true, p, slice_place<PLACE>((int)(blk * (NT / kChains / 64) + wave), G), v);
     }
 }
 

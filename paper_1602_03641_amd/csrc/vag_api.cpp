@@ -570,31 +570,33 @@ void run_bicgstab(vag_handle *h) {
     const int32_t n = h->S.nunk;
     const size_t nv = (size_t)std::max(n, 1);
     for (auto *v : {&h->bcg_rhat, &h->bcg_s, &h->bcg_shat, &h->bcg_t}) ensure(*v, nv, h->tr);
-    ensure(h->bcg_parts, 8 * (size_t)bcg_grid(n), h->tr);
-    double *parts = h->bcg_parts.p;
+    const bool global_ilu = h->opt.precond == VAG_PC_BJILU0 && !h->ilu.in_lds();
+    const KrylovShape shape = krylov_shape(n, global_ilu ? kSplitMaxIlu : kSplitMaxBcg);
+    ensure(h->bcg_parts, 8 * (size_t)shape.G, h->tr);
+    const BcgWork W{h->bcg_parts.p, shape, global_ilu};
     PcgState *st = h->pcg.p;
     const Sell<double> A = h->Asell();
     const int max_iter = h->opt.max_iter;
     int k = 0, k0 = 0;
     double rtol = h->opt.rtol, bb = -1.0;
     for (int restart = 0;; ++restart) {
-        launch_bcg_init(s, A, restart == 0, k0, h->b.p, h->x.p, h->r.p, h->bcg_rhat.p, parts);
+        launch_bcg_init(s, A, restart == 0, k0, h->b.p, h->x.p, h->r.p, h->bcg_rhat.p, W);
         *h->h_done() = 0;
-        launch_bcg_start(s, n, parts, st, rtol, k0, h->h_done());
+        launch_bcg_start(s, n, W, st, rtol, k0, h->h_done());
         for (;;) {
             const int kend = std::min(k + h->opt.check_every, max_iter);
             for (; k < kend && !h->krylov_ended(); ++k) {
-                launch_bcg_direction(s, n, k, k0, h->r.p, h->p.p, h->q.p, parts, st, true);
+                launch_bcg_direction(s, n, k, k0, h->r.p, h->p.p, h->q.p, W, st, true);
                 precond_apply(h, h->p.p, h->z.p, st);
-                launch_bcg_spmv_v(s, A, h->z.p, h->q.p, h->bcg_rhat.p, parts, st);
-                launch_bcg_s(s, n, k, h->r.p, h->q.p, h->bcg_s.p, parts, st);
+                launch_bcg_spmv_v(s, A, h->z.p, h->q.p, h->bcg_rhat.p, W, st);
+                launch_bcg_s(s, n, k, h->r.p, h->q.p, h->bcg_s.p, W, st);
                 precond_apply(h, h->bcg_s.p, h->bcg_shat.p, st);
-                launch_bcg_spmv_t(s, A, h->bcg_shat.p, h->bcg_t.p, h->bcg_s.p, parts, st);
+                launch_bcg_spmv_t(s, A, h->bcg_shat.p, h->bcg_t.p, h->bcg_s.p, W, st);
                 launch_bcg_update(s, n, k, h->z.p, h->bcg_shat.p, h->bcg_s.p, h->bcg_t.p, h->bcg_rhat.p, h->x.p,
-                                  h->r.p, parts, st);
+                                  h->r.p, W, st);
             }
             // convergence test of the last residual without a new direction
-            launch_bcg_direction(s, n, k, k0, h->r.p, h->p.p, h->q.p, parts, st, false);
+            launch_bcg_direction(s, n, k, k0, h->r.p, h->p.p, h->q.p, W, st, false);
             VAG_HIP(hipMemcpyAsync(h->h_pcg, st, sizeof(PcgState), hipMemcpyDeviceToHost, s));
             VAG_HIP(hipStreamSynchronize(s));
             if (h->h_pcg->done || k >= max_iter) break;

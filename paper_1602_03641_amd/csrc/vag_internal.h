@@ -109,9 +109,15 @@ constexpr int kKrylovThreads = 1024;
 // the fused kernels / with one: Jacobi CG 65 k rows 6.14 / 6.22, 81 k 7.20 /
 // 6.71, 99 k 9.08 / 7.36, 120 k 14.9 / 10.7; CG with the aggregation hierarchy
 // 3.83 / 3.96, 4.02 / 4.03, 4.46 / 4.21, 4.64 / 4.23.  BiCGStab's kernels are not
-// fused, only their lanes change (Jacobi 83 k 19.1 / 20.7, 93 k 17.8 / 17.9, 99 k
-// 18.9 / 18.8, 120 k 25.4 / 24.0): their line is kSplitMaxBcg.
-constexpr int64_t kSplitMaxRows = 81920, kSplitMaxBcg = 98304;
+// fused, only their lanes change (Jacobi 83 k 19.1 / 20.7, 99 k 18.9 / 18.8, 120 k
+// 25.4 / 24.0; ILU in blocks of 128, 113 k 36.8 / 37.1): their line is kSplitMaxBcg.
+// With an ILU that is solved from global memory it is kSplitMaxIlu, and the
+// products' rows go in runs to the XCDs: rows spread over all of them leave less
+// of the factor in their L2s (100 iterations, ms, blocks of 1500 rows, spread / in
+// runs / one lane per row: 40 k 77.1 / 70.7 / 71.7, 57 k 60.9 / 57.7 / 56.0, 72 k
+// 59.8 / 60.1 / 55.7; of 4096: 40 k 136 / 121 / 121, 48 k 153 / 150 / 141; of 32: 48 k
+// 9.5 / 9.1 / 9.7, 66 k 10.2 / 11.0 / 10.5).
+constexpr int64_t kSplitMaxRows = 81920, kSplitMaxBcg = 114688, kSplitMaxIlu = 45056;
 constexpr int kSplitThreads = 256;
 
 struct KrylovShape {
@@ -427,21 +433,25 @@ void launch_group_back(hipStream_t s, int32_t ngroup, int max_g, int max_m, cons
                        const int64_t *grp_off, const int32_t *frac_unk, const double *Gb, const double *b, double *x);
 void launch_diag_inv(hipStream_t s, int32_t n, const int32_t *diag_pos, const double *A, double *dinv);
 
-// BiCGStab (bicgstab.hip): parts holds 8 * bcg_grid(n) doubles
-int bcg_grid(int64_t n);
+// BiCGStab (bicgstab.hip): parts holds 8 * shape.G doubles
+struct BcgWork {
+    double *parts;
+    KrylovShape shape;
+    bool local;  // the products' rows in runs per XCD
+};
 void launch_bcg_init(hipStream_t s, Sell<double> A, bool zero_x, int k0, const double *b, double *x, double *r,
-                     double *rhat, double *parts);
-void launch_bcg_start(hipStream_t s, int32_t n, double *parts, PcgState *st, double rtol, int k0, int *host_done);
+                     double *rhat, const BcgWork &W);
+void launch_bcg_start(hipStream_t s, int32_t n, const BcgWork &W, PcgState *st, double rtol, int k0, int *host_done);
 void launch_bcg_direction(hipStream_t s, int32_t n, int k, int k0, const double *r, double *p, const double *v,
-                          double *parts, PcgState *st, bool update);
+                          const BcgWork &W, PcgState *st, bool update);
 void launch_bcg_spmv_v(hipStream_t s, Sell<double> A, const double *phat, double *v, const double *rhat,
-                       double *parts, const PcgState *st);
-void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, double *sv, double *parts,
+                       const BcgWork &W, const PcgState *st);
+void launch_bcg_s(hipStream_t s, int32_t n, int k, const double *r, const double *v, double *sv, const BcgWork &W,
                   const PcgState *st);
-void launch_bcg_spmv_t(hipStream_t s, Sell<double> A, const double *shat, double *t, const double *sv, double *parts,
+void launch_bcg_spmv_t(hipStream_t s, Sell<double> A, const double *shat, double *t, const double *sv, const BcgWork &W,
                        const PcgState *st);
 void launch_bcg_update(hipStream_t s, int32_t n, int k, const double *phat, const double *shat, const double *sv,
-                       const double *t, const double *rhat, double *x, double *r, double *parts, PcgState *st);
+                       const double *t, const double *rhat, double *x, double *r, const BcgWork &W, PcgState *st);
 
 // Krylov
 int pcg_grid(int64_t n);

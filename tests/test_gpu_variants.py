@@ -566,3 +566,24 @@ def test_noalloc_where_the_operator_starts(dims, steps):
         for k, v in vag.to_numpy(got).items():
             assert np.abs(v - ref[k]).max(initial=0.0) <= 1e-10, (n, k)
     h.close()
+
+
+@pytest.mark.parametrize("dims,rows", [((35, 35, 35), 1500), ((35, 36, 36), 1500), ((48, 48, 48), 128), ((48, 49, 49), 128)])
+def test_bicgstab_rows_at_its_lines(dims, rows):
+    """BiCGStab on both sides of 45056 unknowns, its line with an ILU that is
+    solved from global memory, and of 114688, its line otherwise: the oracle's
+    pressures as in test_krylov_rows_per_block, and the same bits twice."""
+    from paper_1602_03641_amd import vag
+    p = synth.random_problem(dims, 56, n_patches=5, n_steps=0, ratios=(1e2, 1e3))
+    od = oracle.solve_darcy(p, rtol=1e-13)
+    h, info = _handle(p, rtol=1e-12, precond=vag.VAG_PC_BJILU0, krylov=vag.VAG_BICGSTAB, ilu_block_rows=rows,
+                      eliminate_frac_faces=0)
+    print(dims, info["n_unknowns"], flush=True)
+    assert info["status"] == 0
+    u = vag.to_numpy(h.pressure())
+    for k in ("u_node", "u_frac"):
+        assert np.abs(u[k] - od[k]).max(initial=0.0) <= 1e-6 * np.abs(od["u_node"]).max(), k
+    h.solve_pressure()
+    for k, v in vag.to_numpy(h.pressure()).items():
+        assert np.array_equal(v, u[k]), k
+    h.close()

@@ -187,19 +187,27 @@ int main() {
 def test_krylov_shape_choice(tmp_path):
     """Where the Krylov kernels go from four lanes per row to one: (unknowns, us
     of a solve with four, with one) of Jacobi CG and of CG with the aggregation
-    hierarchy, the sizes at which both agree."""
+    hierarchy, the sizes at which both agree, and of BiCGStab."""
     lib = os.path.join(os.path.dirname(CSRC), "libvag.so")
     if not os.path.exists(lib):
         pytest.skip("the library is not built")
-    measured = [(22707, 3396, 5274), (22707, 1911, 2380), (47915, 5789, 7585), (47915, 3386, 3815), (65559, 6137, 6219),
-                (65559, 3831, 3960), (99405, 9083, 7358), (99405, 4460, 4211), (120000, 14878, 10668), (120000, 4635, 4229)]
+    cg = [(22707, 3396, 5274), (22707, 1911, 2380), (47915, 5789, 7585), (47915, 3386, 3815), (65559, 6137, 6219),
+          (65559, 3831, 3960), (99405, 9083, 7358), (99405, 4460, 4211), (120000, 14878, 10668), (120000, 4635, 4229)]
+    bcg = [(47915, 14258, 17321), (83160, 19100, 20700), (112847, 36756, 37143), (120000, 25400, 24000)]  # BiCGStab, Jacobi
+    ilu = [(40425, 70700, 71700), (48159, 150400, 140800), (56700, 57700, 56000), (72000, 60100, 55700)]  # and ILU from global memory
+    measured = [(m, line) for ms, line in ((cg, "kSplitMaxRows"), (bcg, "kSplitMaxBcg"), (ilu, "kSplitMaxIlu")) for m in ms]
     out = _host_program(tmp_path, """
 #include <cstdio>
 #include "vag_internal.h"
-int main() { for (int n : {%s}) std::printf("%%d ", (int)vag::krylov_shape(n).split); }
-""" % ",".join(str(m[0]) for m in measured), "-x", "none", lib, "-Wl,-rpath," + os.path.dirname(lib))
-    for m, g in zip(measured, out.split(), strict=True):
-        assert (g == "1") == (m[1] < m[2]), m
+int main() {
+    using namespace vag;
+    const int64_t m[][2] = {%s};
+    for (auto &r : m) std::printf("%%d ", (int)krylov_shape(r[0], r[1]).split);
+}
+""" % ",".join("{%d,%s}" % (m[0], line) for m, line in measured), "-x", "none", lib,
+                        "-Wl,-rpath," + os.path.dirname(lib))
+    for (m, line), g in zip(measured, out.split(), strict=True):
+        assert (g == "1") == (m[1] < m[2]), (m, line)
 
 
 def test_noalloc_operator_choice(tmp_path):
