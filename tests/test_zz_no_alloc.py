@@ -94,3 +94,44 @@ def test_noalloc_final_time_and_no_sync():
     for k in ("c_cell", "c_frac", "c_node"):
         assert np.abs(got[k] - ref[k]).max(initial=0.0) <= 1e-12, k
     h.close()
+
+
+@pytest.mark.parametrize("n_steps", [3, 20])
+def test_noalloc_in_a_graph(n_steps):
+    """Gathered steps and steps with the operator captured into a graph: every
+    replay gives the eager call's bits, between eager calls of other lengths,
+    solves (which use the operator's memory) and new fluxes."""
+    torch = _torch()
+    from paper_1602_03641_amd import vag
+    p = synth.random_problem((9, 8, 7), 24, n_patches=4, n_steps=0, ratios=(1e2,))
+    synth.add_wells(p, 3, n_inj=1, n_prod=1)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        h = vag.Handle(p, rtol=1e-10, max_iter=20000, cfl=p.cfl)
+        h.solve_pressure()
+        rng = np.random.default_rng(25)
+        c0 = {k: torch.tensor(rng.uniform(0, 1, n), device="cuda")
+              for k, n in (("c_cell", p.n_cells), ("c_frac", p.n_frac), ("c_node", p.n_nodes))}
+        eager = lambda: _host(h.transport_noalloc(n_steps=n_steps, c0=c0, info=False)[0])  # noqa: E731
+        ref = eager()
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            out, _ = h.transport_noalloc(n_steps=n_steps, c0=c0, info=False)
+        flux = {k: v.clone() for k, v in h.fluxes().items()}
+        for replay in range(4):
+            print("steps", n_steps, "replay", replay, flush=True)
+            if replay == 1:
+                h.transport_noalloc(n_steps=23 - n_steps, info=False)
+            if replay == 2:
+                h.solve_pressure()
+            if replay == 3:
+                h.set_fluxes({k: 0.5 * v.cpu().numpy() for k, v in flux.items()})
+                ref = eager()
+            for v in out.values():
+                v.zero_()
+            graph.replay()
+            stream.synchronize()
+            for k, v in _host(out).items():
+                assert np.array_equal(v, ref[k]), (replay, k)
+        h.close()
