@@ -223,7 +223,9 @@ typedef struct {
 
 /* Kernels that vag_benchmark_kernel can time. */
 typedef enum {
-    VAG_KERNEL_SPMV = 0,            /* y = A x with the assembled system (Krylov operator) */
+    VAG_KERNEL_SPMV = 0,            /* y = A x with the assembled system, with the partial sums of a
+                                       Krylov loop; CG itself runs this kernel above 81920 unknowns
+                                       and one that also forms its direction below */
     VAG_KERNEL_TRANSPORT_STEP = 1,  /* one explicit upwind step */
     VAG_KERNEL_LOCAL = 2,           /* per-cell local VAG matrices */
     VAG_KERNEL_PRECOND = 3          /* one application of the preconditioner */
@@ -297,6 +299,11 @@ vag_status vag_solve_pressure(vag_handle *h, vag_solve_info *info);
  * otherwise n_steps steps of dt.  The initial state is c0 (cell, fracture-face,
  * node arrays; NULL = continue from the current state, which is 0 after a
  * solve); Dirichlet nodes are held at c_bar.
+ * A call of 32 steps or more on a hexahedral mesh of at most 65536 control
+ * volumes may take 10 to 80 MB of device memory while it runs, beyond
+ * vag_footprint_bytes: cached blocks where there are any, returned to the cache
+ * at its end, and the call does without where there is no memory.  Served jobs
+ * of that size do not (their steps are batched).
  */
 vag_status vag_transport(vag_handle *h, int64_t n_steps, double t_final, const double *c0_cell,
                          const double *c0_frac, const double *c0_node, vag_mem mem,

@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kCT) void cl_chunk_sum_kernel(int32_t n, const int3
 // marked in big (and counted) and left to cl_product_kernel.  One thread per
 // row with its table in global memory, as there, waits on a chain of dependent
 // loads per contribution: 17 ms for the four levels of a 64^3 hierarchy,
-// against 1.5 ms here.
+// against 1.1 ms here, both passes of both products.
 __device__ inline bool cl_insert(int32_t *keys, int mask, int32_t J, uint32_t &h) {
     h = mix32((uint32_t)J) & (uint32_t)mask;
     for (;;) {

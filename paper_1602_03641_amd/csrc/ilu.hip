@@ -355,10 +355,10 @@ static_assert(kIluThreads == 64, "a substitution is one wavefront's");
 // schedules and vector are staged in LDS by coalesced loads, all in flight
 // together; the substitutions then touch LDS only.  (Reading slots and entries
 // from global memory level by level cost two dependent round trips per level,
-// ~0.57 us: 80 us per application at 113 k unknowns in blocks of 128, 47 us
+// ~0.57 us: 67 us per application at 113 k unknowns in blocks of 128, 43 us
 // staged.  What bounds it is still the chain of levels, ~0.3 us each: reads of
 // slots, entries and y in turn; a third stage of the pipeline did not shorten
-// it, 50 us.)
+// it.)
 __global__ __launch_bounds__(kIluThreads) void ilu_solve_lds_kernel(IluArgs g, IluLds L, const double *__restrict__ r,
                                                                     double *__restrict__ z, const PcgState *st) {
     if (st && st->done) return;

@@ -1630,9 +1630,12 @@ void transport_report(vag_handle *h, const TransportPlan &P, vag_transport_info 
 // each: 62.7 k rows 2.1 us a step in 256 parts, 3.5 in 510), and none below 64
 // rows.  us a step, alone / in parts: 3.6 / 1.1 at 2.3 k rows (10^3 cells),
 // 3.7 / 0.9 at 12.6 k (64 x 64 x 1), 3.7 / 1.4 at 12.7 k (18^3), 3.7 / 1.5 at
-// 17 k, 3.7 / 1.9 at 46 k (28^3), 3.7 / 2.1 at 63 k, past which a part's map
-// does not fit in LDS.  Building them and looking at the result takes 80 us
-// (2.3 k rows) to 120 (63 k), even at 32 to 75 steps.
+// 17 k, 3.7 / 1.9 at 46 k (28^3), 3.7 / 2.1 at 63 k: the gain shrinks as the halos
+// grow, and above kHaloMaxRows was not tried (a part's map of the rows, 2 bytes
+// each, would fit in LDS up to 81920).  Building them and looking at the result
+// takes 80 us (2.3 k rows) to 120 (63 k), even at 32 to 75 steps.  The memory, 10
+// MB (2.3 k rows) to 80 (from 16 k on), comes from the device's block cache and
+// goes back to it when the call ends; it is not part of the handle's footprint.
 constexpr int64_t halo_steps(int64_t nrow) { return 32 + nrow / 1024; }
 struct TransportHalo {
     int steps = 1;  // of a launch (1: step by step)
@@ -2010,7 +2013,8 @@ vag_status vag_benchmark_kernel(vag_handle *h, int kernel, int reps, double *ms)
         auto once = [&] {
             ++rep;
             switch (kernel) {
-                case VAG_KERNEL_SPMV:  // the Krylov loop's SpMV (with its dot-product partials)
+                case VAG_KERNEL_SPMV:  // the product with its dot-product partials, by itself (CG on
+                    // systems below kSplitMaxRows forms its direction in the same kernel)
                     if (h->opt.precision == VAG_MIXED_IR && h->amg.have32)
                         launch_pcg_spmv<float, float>(s, h->amg.L[0]->A32, 0, h->x32.p, h->q32.p,
                                                       pcg_parts(h->parts.p, S.nunk), h->pcg.p + 1);

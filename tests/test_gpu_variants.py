@@ -587,3 +587,27 @@ def test_bicgstab_rows_at_its_lines(dims, rows):
     for k, v in vag.to_numpy(h.pressure()).items():
         assert np.array_equal(v, u[k]), k
     h.close()
+
+
+def test_fan_has_the_wide_rows():
+    """What test_classical_products and test_aggregation_products mean by wide:
+    the fan's rows outgrow the limits of the kernels that most rows take."""
+    import os
+    import re
+    from paper_1602_03641_amd import vag
+    import scipy.sparse as sp
+    csrc = os.path.join(os.path.dirname(vag.__file__), "csrc")
+    limit = {}
+    for f in ("amg.hip", "amg_classical.hip"):
+        with open(os.path.join(csrc, f)) as src:
+            limit.update({k: int(v) for k, v in re.findall(r"\b(k\w+) = (\d+)[,;]", src.read())})
+    for kind, names in ((1, ("kApCand", "kRapCols")), (0, ("kSet", "kGalDistinct"))):
+        h, _ = _handle(_fan(120, 14), rtol=1e-8, precond=vag.VAG_PC_AMG, amg_kind=kind, amg_coarse_size=12,
+                       amg_aggregate_hops=1, amg_theta=0.3)
+        a, b = h.amg_level(0), h.amg_level(1)
+        A = sp.csr_matrix((np.ones(len(a["A"][2])), a["A"][1], a["A"][0]))
+        P = sp.csr_matrix((np.ones(len(a["P"][2])), a["P"][1], a["P"][0]), shape=(A.shape[0], a["n_coarse"]))
+        # contributions to a row of A P (classical), its columns (aggregation); columns of a coarse row
+        most = int((A @ P.getnnz(axis=1)).max()) if kind else int((A @ P).getnnz(axis=1).max())
+        assert most > limit[names[0]] and np.diff(b["A"][0]).max() > limit[names[1]], (kind, most, limit)
+        h.close()
